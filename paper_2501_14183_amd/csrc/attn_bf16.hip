@@ -1167,31 +1167,6 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
   }
 }
 
-// column sums of up to four bf16 [rows][d] matrices (bias gradients)
-struct ColSumBf16 {
-  const bf16_t* src[4];
-  float* dst[4];
-  long long rows;
-  int d;
-  const int32_t* n_dev;           // device-side token count: rows = n_mul * n
-  int n_max, n_mul;
-};
-__global__ __launch_bounds__(256) void colsum_bf16_kernel(ColSumBf16 a) {
-  const bf16_t* src = a.src[blockIdx.y];
-  float* dst = a.dst[blockIdx.y];
-  if (!dst) return;
-  if (a.n_dev) {
-    int n;
-    if (!vd_count(a.n_dev, a.n_max, n)) return;
-    a.rows = (long long)a.n_mul * n;
-  }
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= a.d) return;
-  float s = 0.f;
-  for (long long r = 0; r < a.rows; ++r) s += bf2f(src[r * a.d + c]);
-  dst[c] = s;
-}
-
 // Launches of the kernels for long selections.  A workgroup of four wavefronts takes 128 queries (or keys)
 // when that still gives the chip two workgroups per compute unit, else two wavefronts take 64.  (Two query
 // groups per wavefront, QG = 2, halve the LDS reads per matrix instruction; measured, the kernels are not
@@ -1402,13 +1377,9 @@ int vd_attn_bwd_bf16(vardrop_ctx* ctx, const void* dy, const void* xs, int B, in
     if (gw.splitk > 1 && (rc = vd_gemm_bf16_sum_slices(ctx, part, dW, (long long)d * d, gw.splitk, s, 4, dn.dev ? &gw : nullptr))) return rc;
   }
   if (db[0] || db[1] || db[2] || db[3]) {
-    ColSumBf16 c = {};
-    c.src[0] = dq; c.src[1] = dk; c.src[2] = dv; c.src[3] = (const bf16_t*)dy;
-    for (int z = 0; z < 4; ++z) c.dst[z] = db[z];
-    c.rows = M; c.d = d;
-    c.n_dev = dn.dev; c.n_max = n; c.n_mul = B;
-    hipLaunchKernelGGL(colsum_bf16_kernel, dim3(vd_ceil_div(d, 256), 4), dim3(256), 0, s, c);
-    VD_LAUNCH_CHECK(ctx);
+    // (the dO rows of the workspace have served their purpose)
+    const void* src[4] = {dq, dk, dv, dy};
+    return vd_colsum(ctx, VARDROP_BF16, src, db, M, d, dO, s, dn, n, B);
   }
   return VARDROP_OK;
 }

@@ -285,31 +285,6 @@ __global__ __launch_bounds__(64) void sdpa_bwd_dkv_f32(const float* __restrict__
   }
 }
 
-// column sums of up to four [rows][d] matrices (bias gradients)
-struct ColSumF32 {
-  const float* src[4];
-  float* dst[4];
-  long long rows;
-  int d;
-  const int32_t* n_dev;           // device-side token count: rows = n_mul * n
-  int n_max, n_mul;
-};
-__global__ __launch_bounds__(256) void colsum_f32_kernel(ColSumF32 a) {
-  const float* src = a.src[blockIdx.y];
-  float* dst = a.dst[blockIdx.y];
-  if (!dst) return;
-  if (a.n_dev) {
-    int n;
-    if (!vd_count(a.n_dev, a.n_max, n)) return;
-    a.rows = (long long)a.n_mul * n;
-  }
-  const int c = blockIdx.x * 256 + threadIdx.x;
-  if (c >= a.d) return;
-  float s = 0.f;
-  for (long long r = 0; r < a.rows; ++r) s += src[r * a.d + c];
-  dst[c] = s;
-}
-
 template <int DH>
 int run_fwd_core(vardrop_ctx* ctx, const float* q, const float* k, const float* v, float* o, float* lse,
                  int B, int n, int d, int H, hipStream_t s, const int32_t* n_dev) {
@@ -446,13 +421,9 @@ int vd_attn_bwd_f32(vardrop_ctx* ctx, const float* dy, const float* xs, int B, i
     if ((rc = launch_gemm(ctx, VARDROP_K_GEMM_DXS, g, 1, s))) return rc;
   }
   if (db[0] || db[1] || db[2] || db[3]) {
-    ColSumF32 c = {};
-    c.src[0] = dq; c.src[1] = dk; c.src[2] = dv; c.src[3] = dy;
-    for (int z = 0; z < 4; ++z) c.dst[z] = db[z];
-    c.rows = M; c.d = d;
-    c.n_dev = dn.dev; c.n_max = n; c.n_mul = B;
-    hipLaunchKernelGGL(colsum_f32_kernel, dim3(vd_ceil_div(d, 256), 4), dim3(256), 0, s, c);
-    VD_LAUNCH_CHECK(ctx);
+    // (the dO rows of the workspace have served their purpose)
+    const void* src[4] = {dq, dk, dv, dy};
+    return vd_colsum(ctx, VARDROP_F32, src, db, M, d, dO, s, dn, n, B);
   }
   return VARDROP_OK;
 }

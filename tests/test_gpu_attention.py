@@ -123,6 +123,17 @@ def test_fp32_head_sizes_and_biases(vd, ctx, B, n, d, H):
     compare(got, want, "fp32", ("y",) + GRADS + ("dbq", "dbk", "dbv", "dbo"))
 
 
+@pytest.mark.parametrize("B,n,d,H,dtype", [(1, 127, 64, 1, "bf16"), (1, 128, 64, 1, "bf16"), (3, 43, 576, 9, "bf16"),
+                                           (33, 129, 128, 2, "bf16"), (1, 129, 272, 17, "fp32"), (65, 64, 32, 2, "fp32")])
+def test_bias_gradients_over_row_slices(vd, ctx, B, n, d, H, dtype):
+    """Column sums of 127 rows (one slice), 128 and 129 (two, the second one row short or not), more columns than a
+    workgroup takes at once, and the largest number of slices."""
+    xs, W, dy, b = random_case(B + n, B, n, d, dtype, bias=True)
+    want = oracle_attention(xs, W, H, dy, tuple(b))
+    got = run_gpu(vd, ctx, xs, W, H, dy, dtype, biases=b)
+    compare(got, want, dtype, ("dbq", "dbk", "dbv", "dbo"))
+
+
 def test_dense_mode_equals_identity_selection(vd, ctx):
     """Inference path of the paper: no variate dropped, all N tokens attend."""
     w = wl.WORKLOADS["electricity"]
