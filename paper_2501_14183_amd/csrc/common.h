@@ -134,10 +134,7 @@ size_t vd_attn_bf16_ws_bytes(int B, int n, int d, int H);
 // device address of the static scratch array (sample.hip) on the current device; 0 or the hipError_t
 int vd_static_scratch_address(void** out);
 
-// strided fp32 GEMM of the fp32 back end (attn_f32.hip)
-int vd_gemm_f32(vardrop_ctx*, int kid, const float* A, long long sam, long long sak,
-                const float* B, long long sbk, long long sbn, float* C, int ldc, const float* bias,
-                int M, int N, int K, hipStream_t s);
+size_t vd_attn_f32_ws_bytes(int B, int n, int d);
 
 // attention back ends (attn_f32.hip, attn_bf16.hip); argument checks are done by the caller
 // K slices of the embedding's weight gradient dWe = z^T dxs (K = B * n_sel rows; tiles of 64 x 128): enough of them

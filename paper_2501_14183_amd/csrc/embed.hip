@@ -11,9 +11,10 @@
 // fixed order, and writes the standardised window in the operand type: bf16 rows padded with zeros to a
 // multiple of 64 samples, or fp32 rows.  The caller keeps that buffer for the backward pass.  (2) The
 // products run on the GEMM kernels of the attention back end: bf16 on the matrix cores (the padding
-// lets the 64-deep K slices run past L), fp32 on the plain multiply-add kernel.
+// lets the 64-deep K slices run past L), fp32 on the fp32 matrix instruction.
 #include "bf16_mfma.h"
 #include "gemm_bf16.h"
+#include "gemm_f32.h"
 
 namespace {
 
@@ -330,8 +331,11 @@ extern "C" size_t vardrop_embed_saved_bytes(int B, int n_sel, int L, int dtype) 
 
 extern "C" size_t vardrop_embed_workspace_bytes(int B, int n_sel, int L, int d, int dtype) {
   if (check(B, n_sel, L, d, dtype) != VARDROP_OK) return 0;
-  // partial column sums of dxs (bias gradient), then, for bf16, room for the largest slice count of dWe
-  return embed_colsum_bytes(d) + (dtype == VARDROP_BF16 ? vd_align_up((size_t)16 * (L + 8) * d * sizeof(float), 256) : 0);
+  // partial column sums of dxs (bias gradient), then room for the K slices of dWe: bf16 for the largest number of them,
+  // fp32 for this one (it grows with the token count)
+  const int slices = vd_f32_splitk(L, d, 1, (long long)B * n_sel);
+  return embed_colsum_bytes(d) + (dtype == VARDROP_BF16 ? vd_align_up((size_t)16 * (L + 8) * d * sizeof(float), 256)
+                                                        : vd_align_up((size_t)slices * L * d * sizeof(float), 256));
 }
 
 namespace {
@@ -398,8 +402,11 @@ int embed_fwd(vardrop_ctx* ctx, const float* x, int B, int N, int L, int64_t sb,
     g.a_kpad = 1;
     return vd_gemm_bf16(ctx, VARDROP_K_GEMM_EMBED, g, 1, false, s);
   }
-  return vd_gemm_f32(ctx, VARDROP_K_GEMM_EMBED, (const float*)saved, L, 1, (const float*)We, d, 1,
-                     (float*)xs, d, (const float*)be, (int)M, d, L, s);
+  GemmF32 g = {};
+  g.set(0, (const float*)saved, (const float*)We, (float*)xs, (const float*)be);
+  g.lda = L; g.ldb = d; g.ldc = d;
+  g.M = (int)M; g.N = d; g.K = L; g.nz = 1; g.nseg = 1;
+  return vd_gemm_f32(ctx, VARDROP_K_GEMM_EMBED, g, false, s);
 }
 
 int embed_bwd(vardrop_ctx* ctx, const void* dxs, int B, int n_sel, int L, int d, int dtype,
@@ -462,9 +469,12 @@ int embed_bwd(vardrop_ctx* ctx, const void* dxs, int B, int n_sel, int L, int d,
     return VARDROP_OK;
   }
   // fp32: dWe(t, c) = sum_r z[r][t] dxs[r][c]
-  if ((rc = vd_gemm_f32(ctx, VARDROP_K_GEMM_DWE, (const float*)saved, 1, L, (const float*)dxs, d, 1, dWe, d, nullptr,
-                        L, d, (int)M, s)))
-    return rc;
+  GemmF32 g = {};
+  g.set(0, (const float*)saved, (const float*)dxs, dWe, nullptr);
+  g.lda = L; g.ldb = d; g.ldc = d;
+  g.M = L; g.N = d; g.K = (int)M; g.nz = 1; g.nseg = 1;
+  g.part = slices;
+  if ((rc = vd_gemm_f32_wgrad(ctx, VARDROP_K_GEMM_DWE, g, s))) return rc;
   if (dbe) return embed_colsum(ctx, (const float*)dxs, colpart, dbe, M, d, s);
   return VARDROP_OK;
 }

@@ -1,0 +1,275 @@
+// fp32 GEMMs on v_mfma_f32_32x32x2_f32 (fp32 operands, fp32 accumulation).
+//
+// Bound by the fp32 matrix rate (157 TFLOP/s: one 32 x 32 x 2 instruction per 64 clocks and SIMD).  At 16 operand bytes
+// per clock and compute unit a 64 x 64 tile asks far less of L2 and LDS than they give, so the tile is small for the sake of many
+// workgroups (a selection of a few thousand token rows is 400 tiles), four wavefronts of one 32 x 32 block each.
+// Global memory goes through registers into two LDS buffers of 32 k each: edges and unaligned rows are handled there
+// with zeros, so the inner loop has no masks; loads are issued two slices ahead, one barrier per slice (1024 matrix clocks).
+// The plain multiply-add kernel this replaced ran at 4-8 TFLOP/s (K = 3328, 512 x 512: 394 us a matrix).
+#include "bf16_mfma.h"
+#include "gemm_f32.h"
+
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int kT = 64, kK = 32;              // tile edge, k per LDS buffer
+constexpr int kOperand = kT * kK * 4;        // bytes of one operand in one buffer
+
+template <typename T>
+__device__ inline T pick(int z, T p0, T p1, T p2, T p3) { return z == 0 ? p0 : (z == 1 ? p1 : (z == 2 ? p2 : p3)); }
+
+struct DimsF32 {
+  int M, K, splitk, kchunk;
+};
+
+// The product's dimensions with a device-side count resolved; false: nothing to do.
+__device__ inline bool resolve_f32(const GemmF32& g, DimsF32& dm, bool wgrad) {
+  dm.M = g.M;
+  dm.K = g.K;
+  if (g.n_dev) {
+    int n;
+    if (!vd_count(g.n_dev, g.n_max, n, g.status)) return false;
+    if (g.n_role == 0) dm.M = g.n_mul * n;
+    else dm.K = g.n_mul * n;
+  }
+  dm.splitk = wgrad ? vd_f32_splitk(g.M, g.N, g.nz, dm.K) : 1;
+  dm.kchunk = wgrad ? (int)vd_align_up((size_t)vd_ceil_div(dm.K, dm.splitk), kK) : dm.K;
+  return true;
+}
+
+// One operand's slice of 32 k travels as two 16-byte units per thread.
+//   KC (rows contiguous in k): LDS [64 rows][32 k], 16-byte chunk position XORed with (row / 2) % 8 (a read takes one
+//      chunk of 16 consecutive rows; two rows share 256 bytes);
+//   otherwise (rows contiguous in m or n): LDS [32 k][64], chunk position XORed with 8 on k rows 4..7 of every 8 (a read
+//      takes 32 consecutive columns of rows k and k + 4).
+// VEC: rows are 16-byte aligned and their extent along the contiguous index is a multiple of 4.
+template <bool KC, bool VEC>
+__device__ inline void fetch(f32x4 (&v)[2], const float* __restrict__ P, int ld, int r0, int rows, int k0, int kend) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int i = u * 256 + threadIdx.x;
+    const int row = KC ? r0 + (i >> 3) : k0 + (i >> 4);                // index of the strided dimension
+    const int c = KC ? k0 + 4 * (i & 7) : r0 + 4 * (i & 15);           // first index of the contiguous one
+    const int row_end = KC ? rows : kend, c_end = KC ? kend : rows;
+    const bool ok = row < row_end;
+    const float* p = P + (long long)(ok ? row : 0) * ld;
+    if constexpr (VEC) {
+      const bool in = ok && c < c_end;
+      const f32x4 w = *reinterpret_cast<const f32x4*>(p + (in ? c : 0));
+      v[u] = in ? w : f32x4{0.f, 0.f, 0.f, 0.f};
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool in = ok && c + e < c_end;
+        const float w = p[in ? c + e : 0];
+        v[u][e] = in ? w : 0.f;
+      }
+    }
+  }
+}
+template <bool KC>
+__device__ inline void put(unsigned char* lds, const f32x4 (&v)[2]) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int i = u * 256 + threadIdx.x;
+    const int addr = KC ? (i >> 3) * 128 + (((i & 7) ^ ((i >> 4) & 7)) * 16)
+                        : (i >> 4) * 256 + (((i & 15) ^ ((((i >> 4) >> 2) & 1) << 3)) * 16);
+    *reinterpret_cast<f32x4*>(lds + addr) = v[u];
+  }
+}
+// k = 8 g + 4 half + e of row / column `mn` of the tile, e = 0..3: both halves of a wavefront and both operands agree on
+// this order of k, which is all the contraction needs
+template <bool KC>
+__device__ inline f32x4 frag(const unsigned char* lds, int mn, int g, int half) {
+  if constexpr (KC) {
+    return *reinterpret_cast<const f32x4*>(lds + mn * 128 + (((2 * g + half) ^ ((mn >> 1) & 7)) * 16));
+  } else {
+    f32x4 v;
+    const unsigned char* p = lds + (8 * g + 4 * half) * 256 + (((mn >> 2) ^ (half << 3)) * 16) + (mn & 3) * 4;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = *reinterpret_cast<const float*>(p + e * 256);
+    return v;
+  }
+}
+
+template <bool AKC, bool BKC, bool VEC>
+__device__ __forceinline__ void gemm_f32_tile(const GemmF32& g, const DimsF32& dm, int bx, int by, int bz, unsigned char* smem) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = wave >> 1, wn = wave & 1, col = lane & 31, half = lane >> 5;
+  const int z = bz / dm.splitk, slice = bz - z * dm.splitk;
+  const int m0 = by * kT, n0 = bx * kT;
+  const int kbeg = slice * dm.kchunk, kend = min(dm.K, kbeg + dm.kchunk);
+  const int nk = kend > kbeg ? (kend - kbeg + kK - 1) / kK : 0;
+  const int total = nk * (g.nseg > 1 ? g.nseg : 1);
+  // (values, not references into the argument block: selecting among addresses would put a copy of it into private memory)
+  const float *A1 = g.A1, *A2 = g.A2, *B1 = g.B1, *B2 = g.B2;
+  const float* A0 = pick(z, g.A0, A1, A2, g.A3);
+  const float* B0 = pick(z, g.B0, B1, B2, g.B3);
+  const int lda = g.lda, ldb = g.ldb, M = dm.M, N = g.N;
+  floatx16 acc = zero16();
+  f32x4 ra[2][2], rb[2][2];
+  int fk = kbeg, fseg = 0;                     // fetch cursor
+  const float *Ap = A0, *Bp = B0;
+  auto load = [&](f32x4 (&a)[2], f32x4 (&b)[2]) {
+    fetch<AKC, VEC>(a, Ap, lda, m0, M, fk, kend);
+    fetch<BKC, VEC>(b, Bp, ldb, n0, N, fk, kend);
+    fk += kK;
+    if (fk >= kend) {
+      fk = kbeg;
+      ++fseg;
+      Ap = fseg == 1 ? A1 : A2;
+      Bp = fseg == 1 ? B1 : B2;
+    }
+  };
+  auto store = [&](int buf, const f32x4 (&a)[2], const f32x4 (&b)[2]) {
+    put<AKC>(smem + buf * 2 * kOperand, a);
+    put<BKC>(smem + buf * 2 * kOperand + kOperand, b);
+  };
+  auto compute = [&](int buf) {
+    const unsigned char* la = smem + buf * 2 * kOperand;
+    const unsigned char* lb = la + kOperand;
+#pragma unroll
+    for (int q = 0; q < kK / 8; ++q) {
+      const f32x4 a = frag<AKC>(la, wm * 32 + col, q, half), b = frag<BKC>(lb, wn * 32 + col, q, half);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc, 0, 0, 0);
+    }
+  };
+  if (total > 0) load(ra[0], rb[0]);
+  if (total > 1) load(ra[1], rb[1]);
+  if (total > 0) store(0, ra[0], rb[0]);
+  for (int t = 0; t < total; t += 2) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      if (t + s < total) {
+        __syncthreads();                       // slice t + s is in; everyone is done with slice t + s - 1
+        if (t + s + 2 < total) load(ra[s], rb[s]);
+        compute(s);
+        if (t + s + 1 < total) store(1 - s, ra[1 - s], rb[1 - s]);
+      }
+    }
+  }
+  const float* bias = pick(z, g.bias0, g.bias1, g.bias2, g.bias3);
+  float* C = pick(z, g.C0, g.C1, g.C2, g.C3);
+  int ldc = g.ldc;
+  if (dm.splitk > 1) {
+    C = g.part + (long long)bz * dm.M * g.N;
+    ldc = g.N;
+  }
+  const int n = n0 + wn * 32 + col;
+  if (n < g.N) {
+    const float bv = bias ? bias[n] : 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = m0 + wm * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+      if (m < dm.M) C[(long long)m * ldc + n] = acc[r] + bv;
+    }
+  }
+}
+
+template <bool AKC, bool BKC, bool VEC>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * kOperand];
+  DimsF32 dm;
+  if (!resolve_f32(g, dm, !AKC)) return;
+  const int gx = (g.N + kT - 1) / kT, gy = (dm.M + kT - 1) / kT;
+  const int total = gx * gy * g.nz * dm.splitk;
+  if ((int)blockIdx.x >= total) return;        // (a grid sized for the bound of a device-side count)
+  const int t = xcd_contiguous(blockIdx.x, total);
+  gemm_f32_tile<AKC, BKC, VEC>(g, dm, t % gx, (t / gx) % gy, t / (gx * gy), smem);
+}
+
+// Input gradient and weight gradients of one layer depend on the same dQ, dK, dV and on nothing of each other: one
+// launch, the weight-gradient tiles (K = all tokens: the longer chains) first.
+__global__ __launch_bounds__(256) void gemm_f32_bwd_pair_kernel(GemmF32 gx, GemmF32 gw) {
+  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * kOperand];
+  DimsF32 dx, dw;
+  if (!resolve_f32(gx, dx, false) || !resolve_f32(gw, dw, true)) return;
+  const int wn = (gw.N + kT - 1) / kT, wm = (dw.M + kT - 1) / kT, nw = wn * wm * gw.nz * dw.splitk;
+  const int xn = (gx.N + kT - 1) / kT, xm = (dx.M + kT - 1) / kT, nx = xn * xm;
+  if ((int)blockIdx.x < nw) {
+    const int t = xcd_contiguous(blockIdx.x, nw);
+    gemm_f32_tile<false, false, true>(gw, dw, t % wn, (t / wn) % wm, t / (wn * wm), smem);
+  } else if ((int)blockIdx.x < nw + nx) {
+    const int t = xcd_contiguous(blockIdx.x - nw, nx);
+    gemm_f32_tile<true, true, true>(gx, dx, t % xn, t / xn, 0, smem);
+  }
+}
+
+// C[z][i] = sum over the slices, in order (a single slice was written as the result itself)
+__global__ __launch_bounds__(256) void sum_slices_f32_kernel(GemmF32 g) {
+  DimsF32 dm;
+  if (!resolve_f32(g, dm, true) || dm.splitk <= 1) return;
+  const int z = blockIdx.y;
+  const long long count = (long long)g.M * g.N;
+  const float* p = g.part + z * dm.splitk * count;
+  float* C = pick(z, g.C0, g.C1, g.C2, g.C3);
+  for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < count; i += (long long)gridDim.x * 256) {
+    float s = 0.f;
+    int k = 0;
+    for (; k + 8 <= dm.splitk; k += 8) {       // eight loads in flight, added in slice order
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = p[(k + e) * count + i];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s += v[e];
+    }
+    for (; k < dm.splitk; ++k) s += p[k * count + i];
+    C[(i / g.N) * g.ldc + i % g.N] = s;
+  }
+}
+
+bool aligned4(const GemmF32& g, bool a_kc, bool b_kc) {
+  bool ok = g.lda % 4 == 0 && g.ldb % 4 == 0 && (a_kc ? g.K : g.M) % 4 == 0 && (b_kc ? g.K : g.N) % 4 == 0;
+  const void* p[8] = {g.A0, g.A1, g.A2, g.A3, g.B0, g.B1, g.B2, g.B3};
+  for (const void* q : p) ok = ok && vd_aligned(q, 16);
+  return ok;
+}
+
+int sum_slices(vardrop_ctx* ctx, const GemmF32& g, int bound, hipStream_t s) {
+  if (bound <= 1) return VARDROP_OK;
+  const long long blocks = ((long long)g.M * g.N + 255) / 256;
+  VdTimer timer(ctx, VARDROP_K_REDUCE_DW, s);
+  VD_KERNEL(ctx, sum_slices_f32_kernel, dim3((unsigned)(blocks > 1024 ? 1024 : blocks), g.nz), dim3(256), 0, s, g);
+  VD_LAUNCH_CHECK(ctx);
+  return VARDROP_OK;
+}
+
+template <bool AKC, bool BKC>
+int launch_f32(vardrop_ctx* ctx, int kid, const GemmF32& g, int slices, hipStream_t s) {
+  const long long grid = (long long)vd_ceil_div(g.N, kT) * vd_ceil_div(g.M, kT) * g.nz * slices;
+  if (grid >= (1ll << 31)) return VARDROP_EUNSUPPORTED;
+  VdTimer timer(ctx, kid, s);
+  if (aligned4(g, AKC, BKC)) VD_KERNEL(ctx, (gemm_f32_kernel<AKC, BKC, true>), dim3((unsigned)grid), dim3(256), 0, s, g);
+  else VD_KERNEL(ctx, (gemm_f32_kernel<AKC, BKC, false>), dim3((unsigned)grid), dim3(256), 0, s, g);
+  VD_LAUNCH_CHECK(ctx);
+  return VARDROP_OK;
+}
+
+}  // namespace
+
+int vd_gemm_f32(vardrop_ctx* ctx, int kid, const GemmF32& g, bool b_kc, hipStream_t s) {
+  if (g.M == 0 || g.N == 0) return VARDROP_OK;
+  return b_kc ? launch_f32<true, true>(ctx, kid, g, 1, s) : launch_f32<true, false>(ctx, kid, g, 1, s);
+}
+
+int vd_gemm_f32_wgrad(vardrop_ctx* ctx, int kid, const GemmF32& g, hipStream_t s) {
+  const int slices = vd_f32_splitk(g.M, g.N, g.nz, g.K);
+  const int rc = launch_f32<false, false>(ctx, kid, g, slices, s);
+  return rc ? rc : sum_slices(ctx, g, slices, s);
+}
+
+int vd_gemm_f32_bwd_pair(vardrop_ctx* ctx, const GemmF32& gx, const GemmF32& gw, hipStream_t s) {
+  if (!aligned4(gx, true, true) || !aligned4(gw, false, false)) return VARDROP_EUNSUPPORTED;
+  const int slices = vd_f32_splitk(gw.M, gw.N, gw.nz, gw.K);
+  const long long grid = (long long)vd_ceil_div(gx.N, kT) * vd_ceil_div(gx.M, kT) +
+                         (long long)vd_ceil_div(gw.N, kT) * vd_ceil_div(gw.M, kT) * gw.nz * slices;
+  if (grid >= (1ll << 31)) return VARDROP_EUNSUPPORTED;
+  {
+    VdTimer timer(ctx, VARDROP_K_GEMM_DW_DXS, s);
+    VD_KERNEL(ctx, gemm_f32_bwd_pair_kernel, dim3((unsigned)grid), dim3(256), 0, s, gx, gw);
+  }
+  VD_LAUNCH_CHECK(ctx);
+  return sum_slices(ctx, gw, slices, s);
+}

@@ -73,6 +73,14 @@ def test_ragged_shapes_raw_and_standardised(vd, ctx, dtype, B, N, L, d, n_sel):
     check(vd, ctx, x, sel, d, dtype, standardise=False, bias=False, seed=2)
 
 
+@pytest.mark.parametrize("B,N,L,d,n_sel", [(1, 3, 2, 1, 3), (4, 160, 97, 30, 150), (2, 40, 65, 63, 31), (3, 200, 128, 66, 171)])
+def test_fp32_rows_off_the_16_byte_grid(vd, ctx, B, N, L, d, n_sel):
+    """Windows and widths whose rows are not 16-byte aligned, alone and with several K slices of the weight gradient."""
+    rng = np.random.default_rng([B, N, L, d])
+    x = rng.standard_normal((B, N, L)).astype(np.float32)
+    check(vd, ctx, x, np.sort(rng.choice(N, n_sel, replace=False)), d, "fp32", standardise=L > 2, bias=True, seed=5)
+
+
 def test_kept_only_equals_gather_of_the_full_embedding(vd, ctx):
     """Rows of the kept-only embedding are bit-identical to the same rows of the all-variate embedding."""
     rng = np.random.default_rng(3)
