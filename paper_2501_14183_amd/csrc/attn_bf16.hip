@@ -10,6 +10,7 @@
 //     whole head in LDS: projection + attention forward, and dO + the whole attention backward;
 //   * the projections and their gradients are the GEMMs of gemm_bf16.hip.
 #include <algorithm>
+#include <type_traits>
 #include "bf16_mfma.h"
 #include "gemm_bf16.h"
 
@@ -43,8 +44,8 @@ struct SdpaArgs {
   const bf16_t *q, *k, *v, *o, *dout;
   const bf16_t *dy, *wo;          // short selections: dO is formed inside the kernel from dy and Wo
   bf16_t *out, *dq, *dk, *dv;
-  float *lse, *Dsum;
-  float* nlse2;                   // long selections: -log2(e) * lse, for the dK/dV part
+  float* lse;
+  float *Dsum, *nlse2;            // long selections: -rowsum(dO * O), and -log2(e) * lse for the dK/dV part
   int n, d, H;
   float scale;
   const int32_t* n_dev;           // device-side token count (then n is its bound, see vd_count)
@@ -63,20 +64,45 @@ constexpr int kRingTile = 64 * kDh * 2;
 constexpr int kRingStage = 2 * kRingTile + 512;
 constexpr int kRingStages = 3;
 constexpr int kRingLds = kRingStages * kRingStage;
-constexpr float kSlack = 8.f;                   // log2 of the largest unnormalised probability (see the forward kernel)
+constexpr float kSlack = 8.f;                   // log2 of the largest unnormalised probability that is let pass, and
+constexpr float kSumMax = 8192.f;               // the sum of 32 of them (see the forward kernel)
 
-// copies rows [j0, j0 + 64) of two head slices into a stage; a wavefront-wide copy fills 8 token rows and
-// rows past n repeat row n-1
+// Copies rows [j0, j0 + 64) of two head slices into a stage; a wavefront-wide copy fills 8 token rows and rows past n
+// repeat row n-1.  `off` holds this lane's byte offsets of its share of a whole block, so that a copy costs no vector
+// instruction but itself (the address is a scalar base plus the offset); only the last block computes clamped ones.
 template <int NW>
-__device__ inline void ring_issue(const bf16_t* p0, const bf16_t* p1, long long ld, int j0, int n,
-                                  unsigned char* stage, int wave, int lane) {
+struct RingSrc {
+  uint32_t off[8 / NW];
+};
+template <int NW>
+__device__ inline RingSrc<NW> ring_src(long long ld, int wave, int lane) {
+  RingSrc<NW> r;
 #pragma unroll
   for (int u = 0; u < 8 / NW; ++u) {
-    const int rb = u * NW + wave;
-    const int row = rb * 8 + (lane >> 3);
-    const long long off = (long long)min(j0 + row, n - 1) * ld + (((lane & 7) ^ tile_swz(row)) * 8);
-    dma16(p0 + off, stage + rb * 1024);
-    dma16(p1 + off, stage + kRingTile + rb * 1024);
+    const int row = (u * NW + wave) * 8 + (lane >> 3);
+    r.off[u] = (uint32_t)(row * (int)ld + ((lane & 7) ^ tile_swz(row)) * 8) * 2u;
+  }
+  return r;
+}
+template <int NW>
+__device__ inline void ring_issue(const bf16_t* p0, const bf16_t* p1, const RingSrc<NW>& src, long long ld, int j0, int n,
+                                  unsigned char* stage, int wave, int lane) {
+  if (j0 + 64 <= n) {
+    const bf16_t* s0 = p0 + (long long)j0 * ld;
+    const bf16_t* s1 = p1 + (long long)j0 * ld;
+#pragma unroll
+    for (int u = 0; u < 8 / NW; ++u) {
+      dma16_at(s0, src.off[u], stage + (u * NW + wave) * 1024);
+      dma16_at(s1, src.off[u], stage + kRingTile + (u * NW + wave) * 1024);
+    }
+  } else {
+#pragma unroll
+    for (int u = 0; u < 8 / NW; ++u) {
+      const int row = (u * NW + wave) * 8 + (lane >> 3);
+      const uint32_t off = (uint32_t)(min(j0 + row, n - 1) * (int)ld + ((lane & 7) ^ tile_swz(row)) * 8) * 2u;
+      dma16_at(p0, off, stage + (u * NW + wave) * 1024);
+      dma16_at(p1, off, stage + kRingTile + (u * NW + wave) * 1024);
+    }
   }
 }
 // Per-lane LDS addresses (relative to a stage's first tile) of the two fragment kinds:
@@ -119,168 +145,187 @@ __device__ inline bool ring_block(SdpaArgs& a, int rows, int parts, int& xb, int
   return true;
 }
 
-// four row-major fragments (k steps 0..3) of sub-tile KT of tile TILE
-#define VD_ROW4(F, TILE, KT, SO)                                                        \
-  lds_read16_at<(TILE) * kRingTile + (KT) * 4096>(F[0].q, ra.row[0] + (SO));            \
-  lds_read16_at<(TILE) * kRingTile + (KT) * 4096>(F[1].q, ra.row[1] + (SO));            \
-  lds_read16_at<(TILE) * kRingTile + (KT) * 4096>(F[2].q, ra.row[2] + (SO));            \
-  lds_read16_at<(TILE) * kRingTile + (KT) * 4096>(F[3].q, ra.row[3] + (SO));
+// four row-major fragments (k steps 0..3) of sub-tile KT of tile TILE in the stage at byte offset SO (a constant: the
+// loops over the ring are unrolled over its stages, so that a read's whole offset is an immediate)
+#define VD_ROW1(F, S, TILE, KT, SO) lds_read16_at<(SO) + (TILE) * kRingTile + (KT) * 4096>(F[S].q, ra.row[S]);
+#define VD_ROW4(F, TILE, KT, SO) VD_ROW1(F, 0, TILE, KT, SO) VD_ROW1(F, 1, TILE, KT, SO) VD_ROW1(F, 2, TILE, KT, SO) VD_ROW1(F, 3, TILE, KT, SO)
 // four transposed fragments of the 32 token rows KT of tile TILE: F[2 * s2 + dt] = rows 16 s2 .., dimensions 32 dt ..
-#define VD_TR4(F, TILE, KT, SO)                                                                              \
-  lds_read8_tr<(TILE) * kRingTile + ((KT) * 32) * 128>(F[0].d[0], ra.tr[0] + (SO));                          \
-  lds_read8_tr<(TILE) * kRingTile + ((KT) * 32) * 128>(F[0].d[1], ra.tr8[0] + (SO));                      \
-  lds_read8_tr<(TILE) * kRingTile + ((KT) * 32) * 128>(F[1].d[0], ra.tr[1] + (SO));                          \
-  lds_read8_tr<(TILE) * kRingTile + ((KT) * 32) * 128>(F[1].d[1], ra.tr8[1] + (SO));                      \
-  lds_read8_tr<(TILE) * kRingTile + ((KT) * 32 + 16) * 128>(F[2].d[0], ra.tr[0] + (SO));                     \
-  lds_read8_tr<(TILE) * kRingTile + ((KT) * 32 + 16) * 128>(F[2].d[1], ra.tr8[0] + (SO));                     \
-  lds_read8_tr<(TILE) * kRingTile + ((KT) * 32 + 16) * 128>(F[3].d[0], ra.tr[1] + (SO));                     \
-  lds_read8_tr<(TILE) * kRingTile + ((KT) * 32 + 16) * 128>(F[3].d[1], ra.tr8[1] + (SO));
+#define VD_TR4(F, TILE, KT, SO)                                                                    \
+  lds_read8_tr<(SO) + (TILE) * kRingTile + ((KT) * 32) * 128>(F[0].d[0], ra.tr[0]);                \
+  lds_read8_tr<(SO) + (TILE) * kRingTile + ((KT) * 32) * 128>(F[0].d[1], ra.tr8[0]);               \
+  lds_read8_tr<(SO) + (TILE) * kRingTile + ((KT) * 32) * 128>(F[1].d[0], ra.tr[1]);                \
+  lds_read8_tr<(SO) + (TILE) * kRingTile + ((KT) * 32) * 128>(F[1].d[1], ra.tr8[1]);               \
+  lds_read8_tr<(SO) + (TILE) * kRingTile + ((KT) * 32 + 16) * 128>(F[2].d[0], ra.tr[0]);           \
+  lds_read8_tr<(SO) + (TILE) * kRingTile + ((KT) * 32 + 16) * 128>(F[2].d[1], ra.tr8[0]);          \
+  lds_read8_tr<(SO) + (TILE) * kRingTile + ((KT) * 32 + 16) * 128>(F[3].d[0], ra.tr[1]);           \
+  lds_read8_tr<(SO) + (TILE) * kRingTile + ((KT) * 32 + 16) * 128>(F[3].d[1], ra.tr8[1]);
+// runs STEP(stage constant, j) for j = 0 .. NB-1 with the stage j % 3
+#define VD_RING_LOOP(STEP, NB)                                          \
+  for (int j = 0; j < (NB); j += kRingStages) {                         \
+    STEP(std::integral_constant<int, 0>{}, j);                          \
+    if (j + 1 < (NB)) STEP(std::integral_constant<int, 1>{}, j + 1);    \
+    if (j + 2 < (NB)) STEP(std::integral_constant<int, 2>{}, j + 2);    \
+  }
 
-// ---- forward: a wavefront owns 32 QG queries (lane = query of each group), NW wavefronts share the K / V stages.
+// ---- forward: a wavefront owns 32 queries (lane = query), NW wavefronts share the K / V stages.
 // S^T = K q^T, online softmax on per-lane scalars, O^T = V^T P^T with the probability registers as the
-// right-hand operand; every K or V fragment read from LDS serves all QG query groups.
-template <int NW, int QG>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void sdpa_fwd_bf16(SdpaArgs a) {
-  constexpr int NS = kRingStages;
+// right-hand operand.
+// What bounds it: with d_k = 64 a 32 x 32 tile of scores costs 8 matrix instructions (256 clocks) and, per score, a
+// fused multiply-add, an exponential (two issue slots), an addition and half a conversion on the vector pipe of the
+// same SIMD; the two pipes overlap for 40 % of the matrix time only, so every vector instruction in the loop counts.
+// Without the maximum per block, with scalar copy addresses and immediate read offsets: 143 -> 117 us at 1924 tokens
+// (B = 8, H = 12; 0.84 PFLOP/s), 82 -> 69 us at 862 (B = 32, H = 8).
+__device__ __forceinline__ float other_half(float v) {       // the value of lane ^ 32
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
+}
+template <int NW>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) void sdpa_fwd_bf16(SdpaArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int LPS = 16 / NW;                 // copies per wavefront and stage
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 31, half = lane >> 5;
   int qb, h, b;
-  if (!ring_block(a, NW * 32 * QG, 1, qb, h, b)) return;
+  if (!ring_block(a, NW * 32, 1, qb, h, b)) return;
   const int n = a.n;
   const long long ld = a.d;
   const long long base = (long long)b * n * ld + h * kDh;
   const bf16_t* kp = a.k + base;
   const bf16_t* vp = a.v + base;
-  const int q0 = (qb * NW + wave) * (32 * QG);
+  const int qi = (qb * NW + wave) * 32 + col;
   const int nb = (n + 63) >> 6;
-  ring_issue<NW>(kp, vp, ld, 0, n, smem, wave, lane);
-  if (NS > 2 && nb > 1) ring_issue<NW>(kp, vp, ld, 64, n, smem + kRingStage, wave, lane);
-  Frag qf[QG][4];
-#pragma unroll
-  for (int g = 0; g < QG; ++g) row_frags(qf[g], a.q + base, ld, q0 + 32 * g + col, n, half);
+  const RingSrc<NW> src = ring_src<NW>(ld, wave, lane);
+  ring_issue<NW>(kp, vp, src, ld, 0, n, smem, wave, lane);
+  if (nb > 1) ring_issue<NW>(kp, vp, src, ld, 64, n, smem + kRingStage, wave, lane);
+  Frag qf[4];
+  row_frags(qf, a.q + base, ld, qi, n, half);
   const RingAddr ra = ring_addr(smem, lane);
-  floatx16 acc[QG][2];
-  float m[QG], l[QG];
-#pragma unroll
-  for (int g = 0; g < QG; ++g) {
-    acc[g][0] = zero16();
-    acc[g][1] = zero16();
-    m[g] = -INFINITY;
-    l[g] = 0.f;
-  }
+  floatx16 acc[2] = {zero16(), zero16()};
+  float m = -INFINITY, l = 0.f;
   const float c = a.scale * kLog2e;
-  int buf = 0;
-  for (int j = 0; j < nb; ++j) {
+  auto step = [&](auto stage, int j) __attribute__((always_inline)) {
+    constexpr int ST = decltype(stage)::value, SO = ST * kRingStage;
     // block j has landed once only the copies of block j+1 are in flight; behind the barrier everyone's have,
     // and everyone is done with block j-1, whose stage block j+2 takes
-    if (NS > 2 && j + 1 < nb) wait_vm<LPS>(); else wait_vm<0>();
+    if (j + 1 < nb) wait_vm<LPS>(); else wait_vm<0>();
     __builtin_amdgcn_s_barrier();
-    if (j + NS - 1 < nb) ring_issue<NW>(kp, vp, ld, (j + NS - 1) * 64, n, smem + ((buf + NS - 1) % NS) * kRingStage, wave, lane);
-    const uint32_t so = buf * kRingStage;
-    buf = buf == NS - 1 ? 0 : buf + 1;
-    floatx16 st[QG][2];
+    if (j + 2 < nb) ring_issue<NW>(kp, vp, src, ld, (j + 2) * 64, n, smem + ((ST + 2) % kRingStages) * kRingStage, wave, lane);
+    floatx16 st[2];
     Frag fa[4], fb[4];
-    VD_ROW4(fa, 0, 0, so)
-    VD_ROW4(fb, 0, 1, so)
-#pragma unroll
-    for (int g = 0; g < QG; ++g) {
-      st[g][0] = zero16();
-      st[g][1] = zero16();
-    }
 #define VD_S_STEP(F, KT, S, PENDING)                                                    \
   wait_lds<PENDING>(F[S]);                                                              \
-  _Pragma("unroll") for (int g = 0; g < QG; ++g) st[g][KT] = mfma(F[S], qf[g][S], st[g][KT]);
-    __builtin_amdgcn_s_setprio(1);              // a wavefront feeding the matrix pipeline goes first
-    VD_S_STEP(fa, 0, 0, 7) VD_S_STEP(fa, 0, 1, 6) VD_S_STEP(fa, 0, 2, 5) VD_S_STEP(fa, 0, 3, 4)
-    VD_S_STEP(fb, 1, 0, 3) VD_S_STEP(fb, 1, 1, 2) VD_S_STEP(fb, 1, 2, 1) VD_S_STEP(fb, 1, 3, 0)
-#undef VD_S_STEP
-    __builtin_amdgcn_s_setprio(0);
-    __builtin_amdgcn_sched_barrier(0);
-    VD_TR4(fa, 1, 0, so)                        // V^T fragments of the first 32 keys travel during the softmax
-    // online softmax on the raw scores: exp2(c s - reference) as one fused multiply-add per score.  The
-    // reference of a query is a past maximum of its scaled scores; it moves up (and the running sum and output
-    // are rescaled, for the whole wavefront) only when a new score exceeds it by more than kSlack, so
-    // probabilities stay below 2^kSlack and, after the first blocks, rescaling is rare.  The result is the same
-    // as with the exact running maximum: numerator and denominator share the reference.
-    // Keys past the end exist only in the last block.
-    const bool tail = j * 64 + 64 > n;
-#pragma unroll
-    for (int g = 0; g < QG; ++g) {
-      if (tail) {
-#pragma unroll
-        for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int key = j * 64 + kt * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-            st[g][kt][r] = key < n ? st[g][kt][r] : -INFINITY;
-          }
+  st[KT] = mfma(F[S], qf[S], (S) == 0 ? zero16() : st[KT]);                             \
+  __builtin_amdgcn_sched_barrier(0);
+    // the scores of block j; keys past the end (only in the last block) get -inf
+#define VD_SCORES()                                                                     \
+  VD_ROW4(fa, 0, 0, SO)                                                                 \
+  VD_ROW4(fb, 0, 1, SO)                                                                 \
+  __builtin_amdgcn_s_setprio(1);              /* a wavefront feeding the matrix pipeline goes first */ \
+  VD_S_STEP(fa, 0, 0, 7) VD_S_STEP(fa, 0, 1, 6) VD_S_STEP(fa, 0, 2, 5) VD_S_STEP(fa, 0, 3, 4) \
+  VD_S_STEP(fb, 1, 0, 3) VD_S_STEP(fb, 1, 1, 2) VD_S_STEP(fb, 1, 2, 1) VD_S_STEP(fb, 1, 3, 0) \
+  __builtin_amdgcn_s_setprio(0);
+#define VD_TAIL()                                                                       \
+  if (j * 64 + 64 > n) {                                                                \
+    _Pragma("unroll") for (int kt = 0; kt < 2; ++kt)                                    \
+      _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                  \
+        const int key = j * 64 + kt * 32 + 8 * (r >> 2) + 4 * half + (r & 3);           \
+        st[kt][r] = key < n ? st[kt][r] : -INFINITY;                                    \
+      }                                                                                 \
+  }
+    // exp2(c s - reference) as one fused multiply-add and the exponential, and their sum
+#define VD_EXP_SUM(RS)                                                                  \
+  {                                                                                     \
+    float r0 = 0.f, r1 = 0.f;                                                           \
+    _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                    \
+      st[0][r] = fast_exp2(fmaf(st[0][r], c, -m));                                      \
+      st[1][r] = fast_exp2(fmaf(st[1][r], c, -m));                                      \
+      r0 += st[0][r];                                                                   \
+      r1 += st[1][r];                                                                   \
+    }                                                                                   \
+    RS = r0 + r1;                                                                       \
+  }
+    VD_SCORES()
+    VD_TR4(fa, 1, 0, SO)                        // V^T fragments of the first 32 keys travel during the softmax
+    VD_TAIL()
+    // Online softmax without a maximum per block.  The reference of a query is a past maximum of its scaled scores; a
+    // block is taken with the reference as it stands, and the sum of its probabilities, which is needed anyway, says
+    // whether that was good enough: a score more than kSlack above the reference makes it exceed kSumMax (so does
+    // anything that is not a number).  Only then, and in the first block, the maximum is formed, the reference moved
+    // and the running sum and output rescaled, and the scores are computed once more from the stage.  Numerator and
+    // denominator share the reference, and fp32 and bf16 keep their relative precision at any scale: same result.
+    float rs = 0.f;
+    bool redo = j == 0;
+    if (!redo) {
+      VD_EXP_SUM(rs)
+      redo = __any(!(rs <= kSumMax));
+      if (redo) {
+        wait_lds<0>(fa[0], fa[1], fa[2], fa[3]);
+        VD_SCORES()
+        VD_TR4(fa, 1, 0, SO)
+        VD_TAIL()
       }
+    }
+    if (redo) {
       float mt = -INFINITY;
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mt = fmaxf(mt, st[g][kt][r]);
-      mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
+        for (int r = 0; r < 16; ++r) mt = fmaxf(mt, st[kt][r]);
+      mt = fmaxf(mt, other_half(mt));
       const float mc = mt * c;                        // c > 0: scaling commutes with the maximum
-      const float mn = mc > m[g] + kSlack ? mc : m[g];
-      float rs = 0.f;
-#pragma unroll
-      for (int kt = 0; kt < 2; ++kt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          st[g][kt][r] = fast_exp2(fmaf(st[g][kt][r], c, -mn));
-          rs += st[g][kt][r];
-        }
-      if (__any(mn != m[g])) {
-        const float alpha = fast_exp2(m[g] - mn);
-        l[g] *= alpha;
+      const float mn = mc > m + kSlack ? mc : m;
+      if (__any(mn != m)) {
+        const float alpha = fast_exp2(m - mn);
+        l *= alpha;
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
-          for (int r = 0; r < 16; ++r) acc[g][dt][r] *= alpha;
+          for (int r = 0; r < 16; ++r) acc[dt][r] *= alpha;
       }
-      l[g] += rs;
-      m[g] = mn;
+      m = mn;
+      VD_EXP_SUM(rs)
     }
+    l += rs;
     __builtin_amdgcn_sched_barrier(0);
     wait_lds_count<7>();                        // (the counter holds 15)
-    VD_TR4(fb, 1, 1, so)
+    VD_TR4(fb, 1, 1, SO)
 #define VD_PV_STEP(F, KT, I, PENDING)                                                   \
   wait_lds<PENDING>(F[I]);                                                              \
-  _Pragma("unroll") for (int g = 0; g < QG; ++g)                                        \
-    acc[g][(I) & 1] = mfma(F[I], regs_to_frag(st[g][KT], (I) >> 1), acc[g][(I) & 1]);
+  acc[(I) & 1] = mfma(F[I], regs_to_frag(st[KT], (I) >> 1), acc[(I) & 1]);
     __builtin_amdgcn_s_setprio(1);
     VD_PV_STEP(fa, 0, 0, 8) VD_PV_STEP(fa, 0, 1, 8) VD_PV_STEP(fa, 0, 2, 8) VD_PV_STEP(fa, 0, 3, 8)
+    __builtin_amdgcn_sched_barrier(0);
     VD_PV_STEP(fb, 1, 0, 6) VD_PV_STEP(fb, 1, 1, 4) VD_PV_STEP(fb, 1, 2, 2) VD_PV_STEP(fb, 1, 3, 0)
-#undef VD_PV_STEP
     __builtin_amdgcn_s_setprio(0);
     __builtin_amdgcn_sched_barrier(0);
-  }
-#pragma unroll
-  for (int g = 0; g < QG; ++g) {
-    const int qi = q0 + 32 * g + col;
-    const float lt = l[g] + __shfl_xor(l[g], 32, 64);
-    if (qi < n) {
-      const float inv = 1.f / lt;
-      bf16_t* orow = a.out + base + (long long)qi * ld;
-      store_accT(orow, acc[g][0], 0, half, inv);
-      store_accT(orow, acc[g][1], 1, half, inv);
-      if (half == 0) a.lse[((long long)b * a.H + h) * n + qi] = (m[g] + log2f(lt)) * 0.6931471805599453f;
-    }
+#undef VD_PV_STEP
+#undef VD_EXP_SUM
+#undef VD_TAIL
+#undef VD_SCORES
+#undef VD_S_STEP
+  };
+  VD_RING_LOOP(step, nb)
+  const float lt = l + other_half(l);
+  if (qi < n) {
+    const float inv = 1.f / lt;
+    bf16_t* orow = a.out + base + (long long)qi * ld;
+    store_accT(orow, acc[0], 0, half, inv);
+    store_accT(orow, acc[1], 1, half, inv);
+    if (half == 0) a.lse[((long long)b * a.H + h) * n + qi] = (m + log2f(lt)) * 0.6931471805599453f;
   }
 }
 
-// ---- backward, part 1: dQ (D = rowsum(dO * O) comes with dO from the GEMM before).  A wavefront owns 32 QG queries (lane = query), loop over
-// key blocks: S^T = K q^T and dP^T = V dO^T from row fragments of the K and V tiles, dS^T in registers as the
-// right-hand operand of dQ^T = K^T dS^T, whose left operand is the K tile again, read transposed.
-template <int NW, int QG, bool DLOCAL>
+// ---- backward, part 1: dQ.  A wavefront owns 32 queries (lane = query), loop over key blocks: S^T = K q^T and
+// dP^T = V dO^T from row fragments of the K and V tiles, dS^T in registers as the right-hand operand of
+// dQ^T = K^T dS^T, whose left operand is the K tile again, read transposed.  D = rowsum(dO * O) is formed here (DLOCAL)
+// or comes with dO from the GEMM before; Dsum holds -D, with which the accumulators of dP start, so that
+// dP - D costs no vector instruction (the vector pipe bounds these loops, as in the forward kernel): 172 -> 151 us at
+// 1924 tokens (B = 8, H = 12), the dK / dV part 224 -> 212 us, both parts in one launch 60 -> 53 us at 321 (B = 32, H = 8).
+template <int NW, bool DLOCAL>
 __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int h, int b) {
-  constexpr int NS = kRingStages;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int LPS = 16 / NW;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 31, half = lane >> 5;
   const int n = a.n;
   const long long ld = a.d;
@@ -288,72 +333,67 @@ __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int 
   const long long srow = ((long long)b * a.H + h) * n;
   const bf16_t* kp = a.k + base;
   const bf16_t* vp = a.v + base;
-  const int q0 = (qb * NW + wave) * (32 * QG);
+  const int qi = (qb * NW + wave) * 32 + col;
   const int nb = (n + 63) >> 6;
-  ring_issue<NW>(kp, vp, ld, 0, n, smem, wave, lane);
-  if (NS > 2 && nb > 1) ring_issue<NW>(kp, vp, ld, 64, n, smem + kRingStage, wave, lane);
-  Frag qf[QG][4], dof[QG][4];
-  float D[QG], nlse2[QG];                      // nlse2 = -log2(e) * log-sum-exp (-inf for a query past the end)
+  const RingSrc<NW> src = ring_src<NW>(ld, wave, lane);
+  ring_issue<NW>(kp, vp, src, ld, 0, n, smem, wave, lane);
+  if (nb > 1) ring_issue<NW>(kp, vp, src, ld, 64, n, smem + kRingStage, wave, lane);
+  Frag qf[4], dof[4];
+  float nD;                                    // -D
+  row_frags(qf, a.q + base, ld, qi, n, half);
+  row_frags(dof, a.dout + base, ld, qi, n, half);
+  if constexpr (DLOCAL) {   // formed here and left for the dK/dV kernel
+    Frag of[4];
+    row_frags(of, a.o + base, ld, qi, n, half);
+    float dsum = 0.f;
 #pragma unroll
-  for (int g = 0; g < QG; ++g) {
-    const int qi = q0 + 32 * g + col;
-    row_frags(qf[g], a.q + base, ld, qi, n, half);
-    row_frags(dof[g], a.dout + base, ld, qi, n, half);
-    if constexpr (DLOCAL) {   // D = rowsum(dO * O) formed here and left for the dK/dV kernel
-      Frag of[4];
-      row_frags(of, a.o + base, ld, qi, n, half);
-      float dsum = 0.f;
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
-      for (int s = 0; s < 4; ++s)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) dsum = fmaf(bf2f(dof[g][s].h[e]), bf2f(of[s].h[e]), dsum);
-      D[g] = dsum + __shfl_xor(dsum, 32, 64);
-    } else {
-      D[g] = a.Dsum[srow + min(qi, n - 1)];
-    }
-    nlse2[g] = qi < n ? -a.lse[srow + qi] * kLog2e : -INFINITY;
+      for (int e = 0; e < 8; ++e) dsum = fmaf(bf2f(dof[s].h[e]), bf2f(of[s].h[e]), dsum);
+    nD = -(dsum + other_half(dsum));
+  } else {
+    nD = a.Dsum[srow + min(qi, n - 1)];
   }
+  const float nlse2 = qi < n ? -a.lse[srow + qi] * kLog2e : -INFINITY;   // (-inf for a query past the end)
+  floatx16 nD16;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) nD16[r] = nD;
   const RingAddr ra = ring_addr(smem, lane);
-  floatx16 acc[QG][2];
-#pragma unroll
-  for (int g = 0; g < QG; ++g) {
-    acc[g][0] = zero16();
-    acc[g][1] = zero16();
-  }
+  floatx16 acc[2] = {zero16(), zero16()};
   const float c = a.scale * kLog2e;
-  int buf = 0;
-  for (int j = 0; j < nb; ++j) {
-    if (NS > 2 && j + 1 < nb) wait_vm<LPS>(); else wait_vm<0>();
+  auto step = [&](auto stage, int j) __attribute__((always_inline)) {
+    constexpr int ST = decltype(stage)::value, SO = ST * kRingStage;
+    if (j + 1 < nb) wait_vm<LPS>(); else wait_vm<0>();
     __builtin_amdgcn_s_barrier();
-    if (j + NS - 1 < nb) ring_issue<NW>(kp, vp, ld, (j + NS - 1) * 64, n, smem + ((buf + NS - 1) % NS) * kRingStage, wave, lane);
-    const uint32_t so = buf * kRingStage;
-    buf = buf == NS - 1 ? 0 : buf + 1;
+    if (j + 2 < nb) ring_issue<NW>(kp, vp, src, ld, (j + 2) * 64, n, smem + ((ST + 2) % kRingStages) * kRingStage, wave, lane);
     const bool tail = j * 64 + 64 > n;
+#define VD_DQ_STEP(ACC, F, RHS, S, INIT, PENDING)                                       \
+  wait_lds<PENDING>(F[S]);                                                              \
+  ACC = mfma(F[S], RHS[S], (S) == 0 ? INIT : ACC);                                      \
+  __builtin_amdgcn_sched_barrier(0);
+#define VD_DQ_ACC(F, I, PENDING)                                                        \
+  wait_lds<PENDING>(F[I]);                                                              \
+  acc[(I) & 1] = mfma(F[I], regs_to_frag(st, (I) >> 1), acc[(I) & 1]);
 #define VD_DQ_HALF(KT)                                                                                   \
   {                                                                                                      \
-    floatx16 st[QG], dp[QG];                                                                             \
+    floatx16 st, dp;                                                                                     \
     Frag fk[4], fv[4], ft[4];                                                                            \
-    VD_ROW4(fk, 0, KT, so)                                                                               \
-    VD_ROW4(fv, 1, KT, so)                                                                               \
-    _Pragma("unroll") for (int g = 0; g < QG; ++g) {                                                     \
-      st[g] = zero16();                                                                                  \
-      dp[g] = zero16();                                                                                  \
-    }                                                                                                    \
+    VD_ROW4(fk, 0, KT, SO)              /* (the V fragments follow one by one: they can take the K fragments' registers) */ \
     __builtin_amdgcn_s_setprio(1);                                                                       \
-    VD_DQ_STEP(st, fk, qf, 0, 7) VD_DQ_STEP(st, fk, qf, 1, 6) VD_DQ_STEP(st, fk, qf, 2, 5) VD_DQ_STEP(st, fk, qf, 3, 4) \
-    VD_DQ_STEP(dp, fv, dof, 0, 3) VD_DQ_STEP(dp, fv, dof, 1, 2) VD_DQ_STEP(dp, fv, dof, 2, 1) VD_DQ_STEP(dp, fv, dof, 3, 0) \
+    VD_DQ_STEP(st, fk, qf, 0, zero16(), 3) VD_ROW1(fv, 0, 1, KT, SO)                                     \
+    VD_DQ_STEP(st, fk, qf, 1, zero16(), 3) VD_ROW1(fv, 1, 1, KT, SO)                                     \
+    VD_DQ_STEP(st, fk, qf, 2, zero16(), 3) VD_ROW1(fv, 2, 1, KT, SO)                                     \
+    VD_DQ_STEP(st, fk, qf, 3, zero16(), 3) VD_ROW1(fv, 3, 1, KT, SO)                                     \
+    VD_DQ_STEP(dp, fv, dof, 0, nD16, 3) VD_DQ_STEP(dp, fv, dof, 1, nD16, 2)                              \
+    VD_DQ_STEP(dp, fv, dof, 2, nD16, 1) VD_DQ_STEP(dp, fv, dof, 3, nD16, 0)                              \
     __builtin_amdgcn_s_setprio(0);                                                                       \
-    __builtin_amdgcn_sched_barrier(0);                                                                   \
-    VD_TR4(ft, 0, KT, so)                                                                                \
-    _Pragma("unroll") for (int g = 0; g < QG; ++g)                                                       \
-      _Pragma("unroll") for (int r = 0; r < 16; ++r)                                                     \
-        st[g][r] = fast_exp2(fmaf(st[g][r], c, nlse2[g])) * (dp[g][r] - D[g]);                           \
+    VD_TR4(ft, 0, KT, SO)                                                                                \
+    _Pragma("unroll") for (int r = 0; r < 16; ++r) st[r] = fast_exp2(fmaf(st[r], c, nlse2)) * dp[r];     \
     if (tail) {                                 /* a key past the end repeats the last one: its dS is dropped */ \
-      _Pragma("unroll") for (int g = 0; g < QG; ++g)                                                     \
-        _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                                 \
-          const int key = j * 64 + (KT) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);                        \
-          st[g][r] = key < n ? st[g][r] : 0.f;                                                           \
-        }                                                                                                \
+      _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                                   \
+        const int key = j * 64 + (KT) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);                          \
+        st[r] = key < n ? st[r] : 0.f;                                                                   \
+      }                                                                                                  \
     }                                                                                                    \
     __builtin_amdgcn_sched_barrier(0);                                                                   \
     __builtin_amdgcn_s_setprio(1);                                                                       \
@@ -361,43 +401,33 @@ __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int 
     __builtin_amdgcn_s_setprio(0);                                                                       \
     __builtin_amdgcn_sched_barrier(0);                                                                   \
   }
-#define VD_DQ_STEP(ACC, F, RHS, S, PENDING)                                             \
-  wait_lds<PENDING>(F[S]);                                                              \
-  _Pragma("unroll") for (int g = 0; g < QG; ++g) ACC[g] = mfma(F[S], RHS[g][S], ACC[g]);
-#define VD_DQ_ACC(F, I, PENDING)                                                        \
-  wait_lds<PENDING>(F[I]);                                                              \
-  _Pragma("unroll") for (int g = 0; g < QG; ++g)                                        \
-    acc[g][(I) & 1] = mfma(F[I], regs_to_frag(st[g], (I) >> 1), acc[g][(I) & 1]);
     VD_DQ_HALF(0)
     VD_DQ_HALF(1)
 #undef VD_DQ_HALF
 #undef VD_DQ_STEP
 #undef VD_DQ_ACC
-  }
-#pragma unroll
-  for (int g = 0; g < QG; ++g) {
-    const int qi = q0 + 32 * g + col;
-    if (qi < n) {
-      bf16_t* row = a.dq + base + (long long)qi * ld;
-      store_accT(row, acc[g][0], 0, half, a.scale);
-      store_accT(row, acc[g][1], 1, half, a.scale);
-      if (DLOCAL && half == 0) {
-        a.Dsum[srow + qi] = D[g];
-        a.nlse2[srow + qi] = nlse2[g];
-      }
+  };
+  VD_RING_LOOP(step, nb)
+  if (qi < n) {
+    bf16_t* row = a.dq + base + (long long)qi * ld;
+    store_accT(row, acc[0], 0, half, a.scale);
+    store_accT(row, acc[1], 1, half, a.scale);
+    if (DLOCAL && half == 0) {
+      a.Dsum[srow + qi] = nD;
+      a.nlse2[srow + qi] = nlse2;
     }
   }
 }
 
 // ---- backward, part 2: dK and dV.  A wavefront owns 32 keys (lane = key), loop over query blocks: a stage holds
-// the Q and dO tiles of 64 queries, their log-sum-exp and their D.  S = Q k^T and dP = dO v^T from row
-// fragments; P and dS in registers are the right-hand operands of dV^T = dO^T P and dK^T = Q^T dS, whose left
+// the Q and dO tiles of 64 queries, their log-sum-exp and their -D, which the accumulators of dP start with.
+// S = Q k^T and dP = dO v^T from row fragments; P and dS in registers are the right-hand operands of dV^T = dO^T P and dK^T = Q^T dS, whose left
 // operands are the same tiles read transposed.
 template <int NW>
 __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int h, int b) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int LPS = 16 / NW + 1;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int col = lane & 31, half = lane >> 5;
   const int n = a.n;
   const long long ld = a.d;
@@ -407,14 +437,15 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
   const bf16_t* op = a.dout + base;
   const int kj = (kb * NW + wave) * 32 + col;
   const int nb = (n + 63) >> 6;
-  // even wavefronts copy the block's -log2(e) * log-sum-exp values, odd ones its D (NW is even); queries past n
+  const RingSrc<NW> src = ring_src<NW>(ld, wave, lane);
+  // even wavefronts copy the block's -log2(e) * log-sum-exp values, odd ones its -D (NW is even); queries past n
   // repeat the last
   const float* stat = (wave & 1) ? a.Dsum + srow : a.nlse2 + srow;
   const int stat_off = 2 * kRingTile + (wave & 1) * 256;
 #define VD_ISSUE_Q(J, BUF)                                                                            \
   {                                                                                                   \
     unsigned char* sp = smem + (BUF) * kRingStage;                                                    \
-    ring_issue<NW>(qp, op, ld, (J) * 64, n, sp, wave, lane);                                          \
+    ring_issue<NW>(qp, op, src, ld, (J) * 64, n, sp, wave, lane);                                     \
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(stat + min((J) * 64 + lane, n - 1)), \
                                      (__attribute__((address_space(3))) void*)(sp + stat_off), 4, 0, 0); \
   }
@@ -427,76 +458,74 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
   const uint32_t stat_addr = ra.lds0 + 2 * kRingTile + 16 * half;   // + 32 per 8 queries
   floatx16 accK[2] = {zero16(), zero16()}, accV[2] = {zero16(), zero16()};
   const float c = a.scale * kLog2e;
-  int buf = 0;
-  for (int i = 0; i < nb; ++i) {
+  auto step = [&](auto stage, int i) __attribute__((always_inline)) {
+    constexpr int ST = decltype(stage)::value, SO = ST * kRingStage;
     if (i + 1 < nb) wait_vm<LPS>(); else wait_vm<0>();
     __builtin_amdgcn_s_barrier();
-    if (i + 2 < nb) VD_ISSUE_Q(i + 2, (buf + 2) % kRingStages)
-    const uint32_t so = buf * kRingStage;
-    buf = buf == kRingStages - 1 ? 0 : buf + 1;
+    if (i + 2 < nb) VD_ISSUE_Q(i + 2, (ST + 2) % kRingStages)
     const bool tail = i * 64 + 64 > n;
 #define VD_DKV_HALF(QT)                                                                                  \
   {                                                                                                      \
-    floatx16 st = zero16(), dp = zero16();                                                               \
-    Frag fq[4], fo[4], ls[4], ds_[4];                                                                    \
-    VD_ROW4(fq, 0, QT, so)                                                                               \
-    VD_ROW4(fo, 1, QT, so)                                                                               \
+    floatx16 st;                                                                                         \
+    Acc16 dp;                                                                                            \
+    Frag fq[4], fo[4], ls[4];                                                                            \
+    /* -D of queries 32 QT + 8 q4 + 4 half + 0..3, the rows of registers 4 q4 .. 4 q4 + 3 */             \
+    lds_read16_at<SO + (QT) * 128 + 256>(dp.q[0], stat_addr);                                            \
+    lds_read16_at<SO + (QT) * 128 + 256 + 32>(dp.q[1], stat_addr);                                       \
+    lds_read16_at<SO + (QT) * 128 + 256 + 64>(dp.q[2], stat_addr);                                       \
+    lds_read16_at<SO + (QT) * 128 + 256 + 96>(dp.q[3], stat_addr);                                       \
+    VD_ROW4(fq, 0, QT, SO)                                                                               \
+    VD_ROW4(fo, 1, QT, SO)              /* (12 reads on the way; the counter holds 15) */                \
     __builtin_amdgcn_s_setprio(1);                                                                       \
-    wait_lds<7>(fq[0]); st = mfma(fq[0], kf[0], st);                                                     \
+    wait_lds<7>(fq[0]); st = mfma(fq[0], kf[0], zero16());                                               \
     wait_lds<6>(fq[1]); st = mfma(fq[1], kf[1], st);                                                     \
     wait_lds<5>(fq[2]); st = mfma(fq[2], kf[2], st);                                                     \
     wait_lds<4>(fq[3]); st = mfma(fq[3], kf[3], st);                                                     \
     __builtin_amdgcn_sched_barrier(0);                                                                   \
-    /* log-sum-exp and D of queries 32 QT + 8 q4 + 4 half + 0..3, the rows of registers 4 q4 .. 4 q4 + 3 */ \
-    lds_read16_at<(QT) * 128>(ls[0].q, stat_addr + so);                                                  \
-    lds_read16_at<(QT) * 128 + 32>(ls[1].q, stat_addr + so);                                             \
-    lds_read16_at<(QT) * 128 + 64>(ls[2].q, stat_addr + so);                                             \
-    lds_read16_at<(QT) * 128 + 96>(ls[3].q, stat_addr + so);                                             \
-    lds_read16_at<(QT) * 128 + 256>(ds_[0].q, stat_addr + so);                                           \
-    lds_read16_at<(QT) * 128 + 256 + 32>(ds_[1].q, stat_addr + so);                                      \
-    lds_read16_at<(QT) * 128 + 256 + 64>(ds_[2].q, stat_addr + so);                                      \
-    lds_read16_at<(QT) * 128 + 256 + 96>(ds_[3].q, stat_addr + so);                                      \
-    wait_lds<11>(fo[0]); dp = mfma(fo[0], vf[0], dp);                                                    \
-    wait_lds<10>(fo[1]); dp = mfma(fo[1], vf[1], dp);                                                    \
-    wait_lds<9>(fo[2]); dp = mfma(fo[2], vf[2], dp);                                                     \
-    wait_lds<8>(fo[3]); dp = mfma(fo[3], vf[3], dp);                                                     \
+    /* log-sum-exp of the same queries */                                                                \
+    lds_read16_at<SO + (QT) * 128>(ls[0].q, stat_addr);                                                  \
+    lds_read16_at<SO + (QT) * 128 + 32>(ls[1].q, stat_addr);                                             \
+    lds_read16_at<SO + (QT) * 128 + 64>(ls[2].q, stat_addr);                                             \
+    lds_read16_at<SO + (QT) * 128 + 96>(ls[3].q, stat_addr);                                             \
+    wait_lds<7>(fo[0]); wait_acc<7>(dp); dp.f = mfma(fo[0], vf[0], dp.f);                                \
+    wait_lds<6>(fo[1]); dp.f = mfma(fo[1], vf[1], dp.f);                                                 \
+    wait_lds<5>(fo[2]); dp.f = mfma(fo[2], vf[2], dp.f);                                                 \
+    wait_lds<4>(fo[3]); dp.f = mfma(fo[3], vf[3], dp.f);                                                 \
     __builtin_amdgcn_s_setprio(0);                                                                       \
     __builtin_amdgcn_sched_barrier(0);                                                                   \
-    wait_lds_count<7>();                        /* (the counter holds 15) */                             \
-    VD_TR4(fo, 1, QT, so)                       /* dO^T */                                               \
+    VD_TR4(fo, 1, QT, SO)                       /* dO^T */                                               \
     wait_lds<8>(ls[0], ls[1], ls[2], ls[3]);                                                             \
-    wait_lds<8>(ds_[0], ds_[1], ds_[2], ds_[3]);                                                         \
     _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                                     \
-      const float p = fast_exp2(fmaf(st[r], c, __uint_as_float(ls[r >> 2].w[r & 3])));                   \
-      st[r] = p;                                                                                         \
-      dp[r] = p * (dp[r] - __uint_as_float(ds_[r >> 2].w[r & 3]));                                       \
+      st[r] = fast_exp2(fmaf(st[r], c, __uint_as_float(ls[r >> 2].w[r & 3])));                           \
+      dp.f[r] *= st[r];                                                                                  \
     }                                                                                                    \
     if (tail) {                                 /* a query past the end repeats the last one: dropped */ \
       _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                                   \
         const int iq = i * 64 + (QT) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);                           \
         st[r] = iq < n ? st[r] : 0.f;                                                                    \
-        dp[r] = iq < n ? dp[r] : 0.f;                                                                    \
+        dp.f[r] = iq < n ? dp.f[r] : 0.f;                                                                \
       }                                                                                                  \
     }                                                                                                    \
     __builtin_amdgcn_sched_barrier(0);                                                                   \
     wait_lds_count<7>();                                                                                 \
-    VD_TR4(fq, 0, QT, so)                       /* Q^T */                                                \
+    VD_TR4(fq, 0, QT, SO)                       /* Q^T */                                                \
     __builtin_amdgcn_s_setprio(1);                                                                       \
     wait_lds<8>(fo[0]); accV[0] = mfma(fo[0], regs_to_frag(st, 0), accV[0]);                             \
     wait_lds<8>(fo[1]); accV[1] = mfma(fo[1], regs_to_frag(st, 0), accV[1]);                             \
     wait_lds<8>(fo[2]); accV[0] = mfma(fo[2], regs_to_frag(st, 1), accV[0]);                             \
     wait_lds<8>(fo[3]); accV[1] = mfma(fo[3], regs_to_frag(st, 1), accV[1]);                             \
-    wait_lds<6>(fq[0]); accK[0] = mfma(fq[0], regs_to_frag(dp, 0), accK[0]);                             \
-    wait_lds<4>(fq[1]); accK[1] = mfma(fq[1], regs_to_frag(dp, 0), accK[1]);                             \
-    wait_lds<2>(fq[2]); accK[0] = mfma(fq[2], regs_to_frag(dp, 1), accK[0]);                             \
-    wait_lds<0>(fq[3]); accK[1] = mfma(fq[3], regs_to_frag(dp, 1), accK[1]);                             \
+    wait_lds<6>(fq[0]); accK[0] = mfma(fq[0], regs_to_frag(dp.f, 0), accK[0]);                           \
+    wait_lds<4>(fq[1]); accK[1] = mfma(fq[1], regs_to_frag(dp.f, 0), accK[1]);                           \
+    wait_lds<2>(fq[2]); accK[0] = mfma(fq[2], regs_to_frag(dp.f, 1), accK[0]);                           \
+    wait_lds<0>(fq[3]); accK[1] = mfma(fq[3], regs_to_frag(dp.f, 1), accK[1]);                           \
     __builtin_amdgcn_s_setprio(0);                                                                       \
     __builtin_amdgcn_sched_barrier(0);                                                                   \
   }
     VD_DKV_HALF(0)
     VD_DKV_HALF(1)
 #undef VD_DKV_HALF
-  }
+  };
+  VD_RING_LOOP(step, nb)
 #undef VD_ISSUE_Q
   if (kj < n) {
     bf16_t* rk = a.dk + base + (long long)kj * ld;
@@ -507,16 +536,18 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
     store_accT(rv, accV[1], 1, half, 1.f);
   }
 }
+#undef VD_RING_LOOP
+#undef VD_ROW1
 #undef VD_ROW4
 #undef VD_TR4
 
-// Many workgroups: two launches, D = rowsum(dO * O) and -log2(e) * lse written by the dQ kernel, whose matrix work
+// Many workgroups: two launches, -D = -rowsum(dO * O) and -log2(e) * lse written by the dQ kernel, whose matrix work
 // hides the read of O.
 template <int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void sdpa_bwd_dq_bf16(SdpaArgs a) {
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) void sdpa_bwd_dq_bf16(SdpaArgs a) {
   int xb, h, b;
   if (!ring_block(a, NW * 32, 1, xb, h, b)) return;
-  sdpa_bwd_dq_body<NW, 1, true>(a, xb, h, b);
+  sdpa_bwd_dq_body<NW, true>(a, xb, h, b);
 }
 template <int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void sdpa_bwd_dkv_bf16(SdpaArgs a) {
@@ -526,13 +557,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 }
 // Few workgroups: one launch, so that the two parts fill the chip's places together.  Of the workgroups of a
 // (batch, head) pair the first half take query blocks (dQ), the second half key blocks (dK, dV); neither part
-// reads what the other writes: D and -log2(e) * lse come with dO from the GEMM before.
+// reads what the other writes: -D and -log2(e) * lse come with dO from the GEMM before.
 template <int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void sdpa_bwd_dqkv_bf16(SdpaArgs a) {
   int xb, h, b;
   if (!ring_block(a, NW * 32, 2, xb, h, b)) return;
   const int nblk = (a.n + NW * 32 - 1) / (NW * 32);
-  if (xb < nblk) sdpa_bwd_dq_body<NW, 1, false>(a, xb, h, b);
+  if (xb < nblk) sdpa_bwd_dq_body<NW, false>(a, xb, h, b);
   else sdpa_bwd_dkv_body<NW>(a, xb - nblk, h, b);
 }
 
@@ -1183,8 +1214,8 @@ int launch_ring(vardrop_ctx* ctx, int kid, K kernel, int rows, int parts, const 
 }
 bool ring_fills(const SdpaArgs& a, int rows) { return (long long)vd_ceil_div(a.n, rows) * a.H * a.B >= 512; }
 int launch_sdpa_fwd(vardrop_ctx* ctx, const SdpaArgs& a, hipStream_t s) {
-  if (ring_fills(a, 128)) return launch_ring(ctx, VARDROP_K_SDPA_FWD, sdpa_fwd_bf16<4, 1>, 128, 1, a, s);
-  return launch_ring(ctx, VARDROP_K_SDPA_FWD, sdpa_fwd_bf16<2, 1>, 64, 1, a, s);
+  if (ring_fills(a, 128)) return launch_ring(ctx, VARDROP_K_SDPA_FWD, sdpa_fwd_bf16<4>, 128, 1, a, s);
+  return launch_ring(ctx, VARDROP_K_SDPA_FWD, sdpa_fwd_bf16<2>, 64, 1, a, s);
 }
 // Fewer than three rounds of the chip's 512 workgroup places per part: both parts in one launch.  Measured per step
 // at B = 32, H = 8: 1.2-1.8 % faster at 173, 205 and 321 tokens, 1.3 % at 422 (1024 workgroups per part), 0.9 % at 543
@@ -1293,7 +1324,7 @@ int vd_attn_fwd_bf16(vardrop_ctx* ctx, const void* xs, int B, int n, int d, int 
   return vd_gemm_bf16(ctx, VARDROP_K_GEMM_OUT, go, 1, false, s);
 }
 
-// ws: dO, dq, dk, dv ([M][d] bf16 each), D and -log2(e) lse, fp32 [B][H][n] each, then the split-K partial products
+// ws: dO, dq, dk, dv ([M][d] bf16 each), -D and -log2(e) lse, fp32 [B][H][n] each, then the split-K partial products
 // (with a device-side count: sub-buffers placed for the bound n, rows packed for the actual count, as in the forward)
 int vd_attn_bwd_bf16(vardrop_ctx* ctx, const void* dy, const void* xs, int B, int n, int d, int H,
                      const void* const W[4], const void* saved, void* dxs,
@@ -1320,8 +1351,8 @@ int vd_attn_bwd_bf16(vardrop_ctx* ctx, const void* dy, const void* xs, int B, in
     g.set(0, dy, W[3], dO, nullptr);
     g.lda = d; g.ldb = d; g.ldc = d;
     g.M = (int)M; g.N = d; g.K = d; g.nseg = 1;
-    if (paired) {     // D = rowsum(dO * O) per head from the same tiles, and -log2(e) * lse beside it
-      g.rs_o = o; g.rs_out = D; g.rs_n = n; g.rs_H = H;
+    if (paired) {     // -D = -rowsum(dO * O) per head from the same tiles, and -log2(e) * lse beside it
+      g.rs_o = o; g.rs_out = D; g.rs_mul = -1.f; g.rs_n = n; g.rs_H = H;
       g.rs_aux_in = lse; g.rs_aux_out = nlse2; g.rs_aux_mul = -kLog2e;
     }
     if (dn.dev) g.count_rows(dn.dev, dn.status, n, B);

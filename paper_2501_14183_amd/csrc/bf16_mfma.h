@@ -63,6 +63,11 @@ __device__ inline void dma16(const bf16_t* gp, unsigned char* lp) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)gp,
                                    (__attribute__((address_space(3))) void*)lp, 16, 0, 0);
 }
+// the same from a uniform base plus a byte offset per lane (the copy's own addressing: no address arithmetic per copy)
+__device__ inline void dma16_at(const bf16_t* base, uint32_t off, unsigned char* lp) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((const char*)base + off),
+                                   (__attribute__((address_space(3))) void*)lp, 16, 0, 0);
+}
 __device__ inline void lds_read16(u32x4& dst, uint32_t addr) {
   asm volatile("ds_read_b128 %0, %1" : "=v"(dst) : "v"(addr) : "memory");
 }
@@ -94,6 +99,15 @@ __device__ inline void wait_lds(Frag& a) {
   asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(a.q) : "n"(N));
 }
 
+// an accumulator whose start values come from LDS, four rows per read
+union Acc16 {
+  floatx16 f;
+  u32x4 q[4];
+};
+template <int N>
+__device__ inline void wait_acc(Acc16& a) {
+  asm volatile("s_waitcnt lgkmcnt(%1)" : "+v"(a.f) : "n"(N));
+}
 // waits until at most N LDS reads are outstanding (nothing tied to it: it only keeps the counter in range)
 template <int N>
 __device__ inline void wait_lds_count() { asm volatile("s_waitcnt lgkmcnt(%0)" ::"n"(N) : "memory"); }

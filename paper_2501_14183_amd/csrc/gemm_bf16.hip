@@ -438,7 +438,7 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
         if (live && (idx & 1) == 0) {
           const int b = m / dm.rs_n;
           const long long i = ((long long)b * g.rs_H + ((n0 + c0) >> 6)) * dm.rs_n + (m - b * dm.rs_n);
-          g.rs_out[i] = p;
+          g.rs_out[i] = g.rs_mul * p;
           if (g.rs_aux_out) g.rs_aux_out[i] = g.rs_aux_mul * g.rs_aux_in[i];
         }
       }

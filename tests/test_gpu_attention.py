@@ -167,6 +167,23 @@ def test_softmax_with_large_logits_stays_finite(vd, ctx):
     assert rel_err(got["y"], want["y"]) <= 5e-2             # near-ties between keys amplify bf16 rounding of Q, K
 
 
+@pytest.mark.parametrize("B,n", [(2, 129), (2, 192), (3, 300), (256, 300)])
+def test_softmax_reference_moves_between_key_blocks(vd, ctx, B, n):
+    """Scores that leave the reference taken in an earlier block of 64 keys behind: by less than what the forward lets
+    pass, by more, by enough to overflow an exponential, and back down (two and four wavefronts per workgroup).
+    Wq = Wk = 1, so Q and K hold the tokens exactly and the usual bounds apply to what follows the scores."""
+    rng = np.random.default_rng(n + B)
+    xs = 0.5 * rng.standard_normal((B, n, 64))
+    top = np.array([1.0, 5.0, 25.0, 150.0, 2.0])[np.arange(n) // 64]
+    xs[:, :, 0] = top * rng.uniform(-1.0, 1.0, (B, n))
+    xs = wl.quantise(xs, "bf16")
+    W = [np.eye(64), np.eye(64)] + [wl.quantise(rng.standard_normal((64, 64)) / 8.0, "bf16") for _ in range(2)]
+    dy = wl.quantise(rng.standard_normal((B, n, 64)), "bf16")
+    want = oracle_attention(xs, W, 1, dy)
+    got = run_gpu(vd, ctx, xs, W, 1, dy, "bf16")
+    compare(got, want, "bf16", ("y", "dWv", "dWo"))
+
+
 def test_determinism(vd, ctx):
     xs, W, dy, _ = random_case(9, 4, 130, 512, "bf16", bias=False)
     a = run_gpu(vd, ctx, xs, W, 8, dy, "bf16")
