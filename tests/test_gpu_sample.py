@@ -89,6 +89,51 @@ def test_counts_reach_pinned_host_memory_and_runs_are_deterministic(vd, ctx):
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
 
 
+@pytest.mark.parametrize("N", [63, 192, 255, 256, 257, 1024, 1025, 2047, 2048, 2049, 4096, 5000])
+@pytest.mark.parametrize("bits", [17, 32, 33, 40, 57, 64])
+def test_counts_at_launch_boundaries_and_hash_widths(vd, ctx, N, bits):
+    """Sizes at which the launch shape changes or a workgroup's share ends early, with hashes of every width class:
+    among the widest, neighbours that agree in the 32 topmost bits in use and differ below, one large group, singletons."""
+    rng = np.random.default_rng(N * 100 + bits)
+    top = rng.integers(0, 2 ** min(bits, 32), size=max(2, N // 40), dtype=np.uint64) << np.uint64(max(0, bits - 32))
+    low = rng.integers(0, 3, size=N, dtype=np.uint64) if bits > 34 else np.zeros(N, dtype=np.uint64)
+    hashes = top[rng.integers(0, len(top), size=N)] + low
+    hashes[rng.random(N) < 0.3] = top[0]
+    hashes[N // 2] = np.uint64(2 ** bits - 1)
+    check(vd, ctx, hashes, 0, 1, 7, seed=bits, step=N)
+    check(vd, ctx, hashes, 4, 1, 1, seed=3, step=2 ** 33)
+
+
+def test_both_launches_of_a_sample_carry_one_signal_and_one_time(vd, ctx):
+    h = torch.arange(1000, device="cuda") % 90
+    kid = {vd.vardrop_kernel_name(k): k for k in range(64) if vd.vardrop_kernel_name(k)}["sample"]
+    want = vd.vardrop_sample(ctx, h, 0, 1, 5, 1, 2)
+    out = tuple(torch.full_like(t, -1) for t in want)
+    copy = torch.empty_like(out[2])
+    main, side = torch.cuda.Stream(), torch.cuda.Stream()
+    ev = torch.cuda.Event()
+    ev.record(main)
+    torch.cuda.synchronize()
+    vd.vardrop_signal_after(ctx, kid, ev.cuda_event)
+    vd.vardrop_sample(ctx, h, 0, 1, 5, 1, 2, out=out, stream=main.cuda_stream)
+    side.wait_event(ev)
+    with torch.cuda.stream(side):
+        copy.copy_(out[2])                      # the counts: what the second launch writes
+    side.synchronize()
+    assert copy.tolist() == want[2].tolist()
+    main.synchronize()
+    n = int(copy[0])
+    assert torch.equal(out[0], want[0]) and torch.equal(out[1][:n], want[1][:n])
+    vd.vardrop_profile_select(ctx, kid)
+    for _ in range(3):
+        vd.vardrop_sample(ctx, h, 0, 1, 5, 1, 2, out=out, stream=main.cuda_stream)
+    main.synchronize()
+    ms, launches = vd.vardrop_profile_read(ctx)
+    vd.vardrop_profile_select(ctx, -1)
+    print("sample: %.2f us" % (1e3 * ms / launches))
+    assert launches == 3 and ms > 0
+
+
 def test_error_codes(vd, ctx):
     h = torch.zeros(10, dtype=torch.int64, device="cuda")
     for args, code in [((0, 2, 1, 0, 0), -1), ((0, 1, 0, 0, 0), -1)]:
