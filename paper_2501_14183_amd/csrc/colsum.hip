@@ -1,4 +1,4 @@
-// Column sums of the bias gradients (dbq, dbk, dbv, dbo = column sums of dQ, dK, dV, dy).
+// Column sums of the bias gradients (dbq, dbk, dbv, dbo = column sums of dQ, dK, dV, dy; dbe = column sums of dxs).
 //
 // Bound by reading the four [rows][d] matrices once.  One thread per column walks all rows serially and leaves the chip
 // empty (2 700 us for four bf16 matrices of 10272 x 512); here the rows are cut into slices, a workgroup sums one slice
@@ -103,27 +103,27 @@ __global__ __launch_bounds__(256) void colsum_finish_kernel(ColSum a) {
 
 }  // namespace
 
-// Column sums of up to four [rows][d] matrices of the given type (d a multiple of 8, rows 16-byte aligned) into dst[z]
-// (fp32, null: skipped).  `scratch`: at least rows * d elements of that type, 16-byte aligned, free to be overwritten.
+// Column sums of the first nz of up to four [rows][d] matrices of the given type (d a multiple of 8, rows 16-byte aligned) into dst[z]
+// (fp32, null: skipped).  `scratch`: nz * min(64, rows / 64) * d floats, 16-byte aligned, free to be overwritten.
 int vd_colsum(vardrop_ctx* ctx, int dtype, const void* const src[4], float* const dst[4], long long rows, int d,
-              void* scratch, hipStream_t s, VdDevCount dn, int n_max, int n_mul) {
+              void* scratch, hipStream_t s, VdDevCount dn, int n_max, int n_mul, int nz) {
   ColSum c = {};
   for (int z = 0; z < 4; ++z) {
     c.src[z] = src[z];
     c.dst[z] = dst[z];
   }
-  c.part = (float*)scratch;      // 16 slices d bytes, at most rows d / 4
+  c.part = (float*)scratch;      // 4 nz slices d bytes (all four matrices: at most rows d / 4)
   c.rows = rows; c.d = d;
   c.n_dev = dn.dev; c.n_max = n_max; c.n_mul = n_mul;
   const long long want = rows / kSliceRows;
   c.slices = want > kMaxSlices ? kMaxSlices : (want < 1 ? 1 : (int)want);
   const int epu = dtype == VARDROP_BF16 ? 8 : 4;
-  const dim3 grid(c.slices, 4, vd_ceil_div(d / epu, 64));
+  const dim3 grid(c.slices, nz, vd_ceil_div(d / epu, 64));
   if (dtype == VARDROP_BF16) hipLaunchKernelGGL(colsum_kernel<8>, grid, dim3(256), 0, s, c);
   else hipLaunchKernelGGL(colsum_kernel<4>, grid, dim3(256), 0, s, c);
   VD_LAUNCH_CHECK(ctx);
   if (c.slices > 1) {
-    hipLaunchKernelGGL(colsum_finish_kernel, dim3(vd_ceil_div(d, 16), 4), dim3(256), 0, s, c);
+    hipLaunchKernelGGL(colsum_finish_kernel, dim3(vd_ceil_div(d, 16), nz), dim3(256), 0, s, c);
     VD_LAUNCH_CHECK(ctx);
   }
   return VARDROP_OK;

@@ -259,8 +259,9 @@ __global__ __launch_bounds__(256, 2) void embed_fwd_fused_kernel(EmbedFused a) {
   }
 }
 
-// Column sums in two steps with a fixed order: part[j][c] = sum of rows [j * per, (j + 1) * per) of column c
-// (a thread per column, rows ascending), then dst[c] = sum_j part[j][c] (j ascending).
+// Bias gradient of the paths whose product does not form it: column sums of dxs (colsum.hip: 16-byte loads of row
+// slices) when rows are whole 16-byte units, else a thread per column and slice, rows ascending, then the slices in order
+// (3008 x 512 bf16: 13.2 + 3.9 us that way, 5.8 + 2.6 with the wide loads).
 constexpr int kColSlices = 64;
 template <typename T>
 __global__ __launch_bounds__(256) void embed_colsum_part_kernel(const T* __restrict__ src, float* __restrict__ part,
@@ -282,10 +283,16 @@ __global__ __launch_bounds__(256) void embed_colsum_final_kernel(const float* __
   for (int j = 0; j < kColSlices; ++j) s += part[(long long)j * d + c];
   dst[c] = s;
 }
-template <typename T>
-int embed_colsum(vardrop_ctx* ctx, const T* src, float* part, float* dst, long long rows, int d, hipStream_t s) {
+int embed_colsum(vardrop_ctx* ctx, const void* src, int dtype, float* part, float* dst, long long rows, int d, hipStream_t s) {
+  if (vd_aligned(src, 16) && d % (dtype == VARDROP_BF16 ? 8 : 4) == 0) {
+    const void* from[4] = {src, nullptr, nullptr, nullptr};
+    float* to[4] = {dst, nullptr, nullptr, nullptr};
+    return vd_colsum(ctx, dtype, from, to, rows, d, part, s, VdDevCount{nullptr, nullptr}, 0, 0, 1);
+  }
   const long long per = (rows + kColSlices - 1) / kColSlices;
-  hipLaunchKernelGGL(embed_colsum_part_kernel<T>, dim3(vd_ceil_div(d, 256), kColSlices), dim3(256), 0, s, src, part, rows, per, d);
+  const dim3 grid(vd_ceil_div(d, 256), kColSlices);
+  if (dtype == VARDROP_BF16) hipLaunchKernelGGL(embed_colsum_part_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)src, part, rows, per, d);
+  else hipLaunchKernelGGL(embed_colsum_part_kernel<float>, grid, dim3(256), 0, s, (const float*)src, part, rows, per, d);
   hipLaunchKernelGGL(embed_colsum_final_kernel, dim3(vd_ceil_div(d, 256)), dim3(256), 0, s, part, dst, d);
   VD_LAUNCH_CHECK(ctx);
   return VARDROP_OK;
@@ -465,7 +472,7 @@ int embed_bwd(vardrop_ctx* ctx, const void* dxs, int B, int n_sel, int L, int d,
     } else if ((rc = vd_gemm_bf16_wgrad_split(ctx, VARDROP_K_GEMM_DWE, g, s))) {
       return rc;
     }
-    if (dbe) return embed_colsum(ctx, (const bf16_t*)dxs, colpart, dbe, M, d, s);
+    if (dbe) return embed_colsum(ctx, dxs, dtype, colpart, dbe, M, d, s);
     return VARDROP_OK;
   }
   // fp32: dWe(t, c) = sum_r z[r][t] dxs[r][c]
@@ -475,7 +482,7 @@ int embed_bwd(vardrop_ctx* ctx, const void* dxs, int B, int n_sel, int L, int d,
   g.M = L; g.N = d; g.K = (int)M; g.nz = 1; g.nseg = 1;
   g.part = slices;
   if ((rc = vd_gemm_f32_wgrad(ctx, VARDROP_K_GEMM_DWE, g, s))) return rc;
-  if (dbe) return embed_colsum(ctx, (const float*)dxs, colpart, dbe, M, d, s);
+  if (dbe) return embed_colsum(ctx, dxs, dtype, colpart, dbe, M, d, s);
   return VARDROP_OK;
 }
 }  // namespace

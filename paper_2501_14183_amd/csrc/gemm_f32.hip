@@ -44,8 +44,11 @@ __device__ inline bool resolve_f32(const GemmF32& g, DimsF32& dm, bool wgrad) {
 //   otherwise (rows contiguous in m or n): LDS [32 k][64], chunk position XORed with 8 on k rows 4..7 of every 8 (a read
 //      takes 32 consecutive columns of rows k and k + 4).
 // VEC: rows are 16-byte aligned and their extent along the contiguous index is a multiple of 4.
+// What lies outside is zeroed on the way into LDS (`in`: one bit per unit, or per element), not here: a use of the loaded
+// values right behind the loads would wait for them in front of the slice's matrix instructions.
 template <bool KC, bool VEC>
-__device__ inline void fetch(f32x4 (&v)[2], const float* __restrict__ P, int ld, int r0, int rows, int k0, int kend) {
+__device__ inline void fetch(f32x4 (&v)[2], uint32_t& in_bits, const float* __restrict__ P, int ld, int r0, int rows, int k0, int kend) {
+  in_bits = 0;
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     const int i = u * 256 + threadIdx.x;
@@ -56,26 +59,29 @@ __device__ inline void fetch(f32x4 (&v)[2], const float* __restrict__ P, int ld,
     const float* p = P + (long long)(ok ? row : 0) * ld;
     if constexpr (VEC) {
       const bool in = ok && c < c_end;
-      const f32x4 w = *reinterpret_cast<const f32x4*>(p + (in ? c : 0));
-      v[u] = in ? w : f32x4{0.f, 0.f, 0.f, 0.f};
+      v[u] = *reinterpret_cast<const f32x4*>(p + (in ? c : 0));
+      in_bits |= in ? 1u << u : 0u;
     } else {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const bool in = ok && c + e < c_end;
-        const float w = p[in ? c + e : 0];
-        v[u][e] = in ? w : 0.f;
+        v[u][e] = p[in ? c + e : 0];
+        in_bits |= in ? 1u << (4 * u + e) : 0u;
       }
     }
   }
 }
-template <bool KC>
-__device__ inline void put(unsigned char* lds, const f32x4 (&v)[2]) {
+template <bool KC, bool VEC>
+__device__ inline void put(unsigned char* lds, const f32x4 (&v)[2], uint32_t in_bits) {
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     const int i = u * 256 + threadIdx.x;
     const int addr = KC ? (i >> 3) * 128 + (((i & 7) ^ ((i >> 4) & 7)) * 16)
                         : (i >> 4) * 256 + (((i & 15) ^ ((((i >> 4) >> 2) & 1) << 3)) * 16);
-    *reinterpret_cast<f32x4*>(lds + addr) = v[u];
+    f32x4 w;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = (in_bits >> (VEC ? u : 4 * u + e)) & 1u ? v[u][e] : 0.f;
+    *reinterpret_cast<f32x4*>(lds + addr) = w;
   }
 }
 // k = 8 g + 4 half + e of row / column `mn` of the tile, e = 0..3: both halves of a wavefront and both operands agree on
@@ -101,7 +107,8 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32& g, const DimsF32& d
   const int m0 = by * kT, n0 = bx * kT;
   const int kbeg = slice * dm.kchunk, kend = min(dm.K, kbeg + dm.kchunk);
   const int nk = kend > kbeg ? (kend - kbeg + kK - 1) / kK : 0;
-  const int total = nk * (g.nseg > 1 ? g.nseg : 1);
+  const int nseg = g.nseg > 1 ? g.nseg : 1;
+  const int total = nk * nseg;
   // (values, not references into the argument block: selecting among addresses would put a copy of it into private memory)
   const float *A1 = g.A1, *A2 = g.A2, *B1 = g.B1, *B2 = g.B2;
   const float* A0 = pick(z, g.A0, A1, A2, g.A3);
@@ -109,22 +116,23 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32& g, const DimsF32& d
   const int lda = g.lda, ldb = g.ldb, M = dm.M, N = g.N;
   floatx16 acc = zero16();
   f32x4 ra[2][2], rb[2][2];
+  uint32_t ia[2], ib[2];
   int fk = kbeg, fseg = 0;                     // fetch cursor
   const float *Ap = A0, *Bp = B0;
-  auto load = [&](f32x4 (&a)[2], f32x4 (&b)[2]) {
-    fetch<AKC, VEC>(a, Ap, lda, m0, M, fk, kend);
-    fetch<BKC, VEC>(b, Bp, ldb, n0, N, fk, kend);
+  auto load = [&](int s) {
+    fetch<AKC, VEC>(ra[s], ia[s], Ap, lda, m0, M, fk, kend);
+    fetch<BKC, VEC>(rb[s], ib[s], Bp, ldb, n0, N, fk, kend);
     fk += kK;
-    if (fk >= kend) {
+    if (fk >= kend && fseg + 1 < nseg) {       // (past the last slice: everything is outside and becomes zeros)
       fk = kbeg;
       ++fseg;
       Ap = fseg == 1 ? A1 : A2;
       Bp = fseg == 1 ? B1 : B2;
     }
   };
-  auto store = [&](int buf, const f32x4 (&a)[2], const f32x4 (&b)[2]) {
-    put<AKC>(smem + buf * 2 * kOperand, a);
-    put<BKC>(smem + buf * 2 * kOperand + kOperand, b);
+  auto store = [&](int s) {
+    put<AKC, VEC>(smem + s * 2 * kOperand, ra[s], ia[s]);
+    put<BKC, VEC>(smem + s * 2 * kOperand + kOperand, rb[s], ib[s]);
   };
   auto compute = [&](int buf) {
     const unsigned char* la = smem + buf * 2 * kOperand;
@@ -136,19 +144,25 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32& g, const DimsF32& d
       for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc, 0, 0, 0);
     }
   };
-  if (total > 0) load(ra[0], rb[0]);
-  if (total > 1) load(ra[1], rb[1]);
-  if (total > 0) store(0, ra[0], rb[0]);
-  for (int t = 0; t < total; t += 2) {
+  // Two slices per round, loads and stores without conditions (a load that some path skips would make the compiler wait
+  // for the newest loads where it needs the ones before): slices past the end are never read.
+  if (total > 0) {
+    load(0);
+    load(1);
+    store(0);
+  }
+  for (int t = 0; t + 2 <= total; t += 2) {
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
-      if (t + s < total) {
-        __syncthreads();                       // slice t + s is in; everyone is done with slice t + s - 1
-        if (t + s + 2 < total) load(ra[s], rb[s]);
-        compute(s);
-        if (t + s + 1 < total) store(1 - s, ra[1 - s], rb[1 - s]);
-      }
+      __syncthreads();                         // slice t + s is in; everyone is done with slice t + s - 1
+      load(s);
+      compute(s);
+      store(1 - s);
     }
+  }
+  if (total & 1) {
+    __syncthreads();
+    compute(0);
   }
   const float* bias = pick(z, g.bias0, g.bias1, g.bias2, g.bias3);
   float* C = pick(z, g.C0, g.C1, g.C2, g.C3);
