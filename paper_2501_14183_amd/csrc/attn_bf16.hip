@@ -1235,11 +1235,10 @@ int launch_sdpa_bwd(vardrop_ctx* ctx, const SdpaArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// largest slice count the rule above gives for any token count
 // largest slice count of any token count up to n_max (the rule is not monotone)
-static int splitk_bound(int d, int B, int n_max) {
+static int splitk_bound(int d, int B, int n_max, bool many) {
   int s = 1;
-  for (int n = 1; n <= n_max; ++n) s = std::max(s, vd_attn_bf16_splitk(d, (long long)B * n, nullptr));
+  for (int n = 1; n <= n_max; ++n) s = std::max(s, vd_attn_bf16_splitk(d, (long long)B * n, many, nullptr));
   return s;
 }
 size_t vd_attn_bf16_partial_offset(int B, int n, int d, int H) {
@@ -1393,7 +1392,8 @@ int vd_attn_bwd_bf16(vardrop_ctx* ctx, const void* dy, const void* xs, int B, in
     gw.lda = d; gw.ldb = d; gw.ldc = d;
     gw.M = d; gw.N = d; gw.K = (int)M; gw.nseg = 1;
     int kchunk = 0;
-    gw.splitk = vd_attn_bf16_splitk(d, M, &kchunk);
+    gw.many = vd_attn_bf16_many_tokens(d, M);
+    gw.splitk = vd_attn_bf16_splitk(d, M, gw.many != 0, &kchunk);
     gw.kchunk = kchunk;
     float* part = (float*)((char*)ws + vd_attn_bf16_partial_offset(B, n, d, H));
     gw.part = part;
@@ -1401,7 +1401,7 @@ int vd_attn_bwd_bf16(vardrop_ctx* ctx, const void* dy, const void* xs, int B, in
       // the kernels derive the slices from the count; the grid is sized for the largest number of them
       gx.count_rows(dn.dev, nullptr, n, B);
       gw.count_k(dn.dev, n, B);
-      gw.splitk = splitk_bound(d, B, n);
+      gw.splitk = splitk_bound(d, B, n, gw.many != 0);
     }
     if ((rc = vd_gemm_bf16_bwd_pair(ctx, gx, gw, 4, s))) return rc;
     // a single slice is written as the result itself

@@ -101,21 +101,27 @@ static inline bool vd_aligned(const void* p, size_t a) { return ((uintptr_t)p % 
 __host__ __device__ static inline int vd_ceil_div(int a, int b) { return (a + b - 1) / b; }
 
 // Number of K slices of the weight-gradient GEMMs (K = M = B*n rows).  They share a launch with the input gradient.
-// Few tokens (fewer than 512 input-gradient tiles of 128 rows): the 64 x 128 weight-gradient tiles walk over K
-// beside 128-row input-gradient tiles, one workgroup per compute unit, in slices of at most 4608 rows: one slice
-// up to there, so that no partial products exist (a second slice makes that launch 3.5 us shorter at the Traffic
-// shape and costs a 5 us launch that sums the slices).  Many tokens: enough slices of 128 x 128 tiles for two
-// workgroups per compute unit (counted as twice as many 64-row tiles), at least 256 rows each.  Slices are a
-// multiple of the 64-row stage.
+// Few tokens: the 64 x 128 weight-gradient tiles walk over K beside 128-row input-gradient tiles, one workgroup per
+// compute unit, in slices of at most 4608 rows: one slice up to there, so that no partial products exist (a second slice
+// makes that launch 3.5 us shorter at the Traffic shape and costs a 5 us launch that sums the slices).  Many tokens:
+// 128 x 128 tiles for both, two workgroups per compute unit, and enough slices for that (counted as twice as many 64-row
+// tiles), at least 256 rows each.  Slices are a multiple of the 64-row stage.
+// Many tokens begin at 512 input-gradient tiles of 128 rows, and already at 148 where that adds no launch (more than
+// 4608 rows have several slices either way, a d of 1024 has one either way) and d gives the weight gradients tiles enough:
+// d = 512 33.2 -> 29.3 us at 4800 rows, 37.8 -> 33.3 at 6080, 44.4 -> 40.4 at 8192; d = 256 33.4 -> 24.6 at 11200;
+// d = 768 80.6 -> 73.2 at 5600; d = 1024 88 -> 73 at 4000.  d = 128: 34.9 -> 43.6 at 32000 (32 weight-gradient workgroups).
+// d = 512 with 3840 rows: 27.3 -> 25.9 + 4.8 for the sum of slices.
 // (Host and device: with a device-side token count the kernels evaluate it themselves.)
+__host__ __device__ static inline int vd_attn_bf16_weight_tiles(int d) { return vd_ceil_div(d, 64) * vd_ceil_div(d, 128) * 4; }
 __host__ __device__ static inline bool vd_attn_bf16_many_tokens(int d, long long M) {
-  return (long long)vd_ceil_div((int)M, 128) * vd_ceil_div(d, 128) >= 512;
+  const long long tiles = (long long)vd_ceil_div((int)M, 128) * vd_ceil_div(d, 128);
+  return tiles >= 512 || (tiles >= 148 && d >= 256 && (M > 4608 || vd_attn_bf16_weight_tiles(d) >= 512));
 }
-__host__ __device__ static inline int vd_attn_bf16_splitk(int d, long long M, int* kchunk) {
+// `many`: which of the two the launch was made for (with a device-side count: by its bound)
+__host__ __device__ static inline int vd_attn_bf16_splitk(int d, long long M, bool many, int* kchunk) {
   int s;
-  if (vd_attn_bf16_many_tokens(d, M)) {
-    const int tiles = vd_ceil_div(d, 64) * vd_ceil_div(d, 128) * 4;
-    s = vd_ceil_div(512, tiles);
+  if (many) {
+    s = vd_ceil_div(512, vd_attn_bf16_weight_tiles(d));
     if (s > 8) s = 8;
     while (s > 1 && M / s < 256) --s;
   } else {

@@ -19,6 +19,7 @@ struct GemmBf16 {
   float* part;        //      (the partial products; with splitk == 1 the result goes to C[z] itself,
   int force_part;     //       unless force_part: then a single slice is a partial product as well)
   int kchunk;         // K elements per slice (multiple of 64)
+  int many;           // weight gradients: tiles and slices for many tokens (vd_attn_bf16_many_tokens; set with n_role 1 or bwd_pair)
   int a_kpad;         // != 0: the rows of a k-contiguous A hold zeros from K up to the next multiple of 64, so K
                       // itself need not be one (B must then be n-contiguous: its last k-row is re-read, times zero)
   // rs_out != nullptr (bf16 output, one matrix, N a multiple of 64): the epilogue also writes, per row m = b * rs_n + q

@@ -13,7 +13,7 @@ struct SplitkReduce {
   int splitk;
   // device-side token count: the slice count is the one the weight-gradient kernel derived from it (d = dn_d)
   const int32_t* n_dev;
-  int n_max, n_mul, dn_d;
+  int n_max, n_mul, dn_d, many;
 };
 // One matrix of `stride` elements per slice, always `splitk` partial products (no direct result): its first count0
 // elements go to out0, the next count1 to out1 (nullable).  With a device-side count the slices follow the
@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(SplitkReduce a) {
   if (a.n_dev) {
     int n;
     if (!vd_count(a.n_dev, a.n_max, n)) return;
-    a.splitk = vd_attn_bf16_splitk(a.dn_d, (long long)a.n_mul * n, nullptr);
+    a.splitk = vd_attn_bf16_splitk(a.dn_d, (long long)a.n_mul * n, a.many != 0, nullptr);
     if (a.splitk <= 1 && n > 0) return;          // a single slice was written as the result itself
     if (n == 0) a.splitk = 0;                    // no tokens: the gradients are zero
   }
@@ -467,7 +467,7 @@ __device__ __forceinline__ bool gemm_resolve(const GemmBf16& g, GemmDims& dm) {
     dm.K = g.n_mul * n;
     int kchunk = 64;
     dm.splitk = g.n_role == 2 ? vd_embed_splitk(g.M, g.N, (long long)dm.K, &kchunk)
-                              : vd_attn_bf16_splitk(g.M, (long long)dm.K, &kchunk);
+                              : vd_attn_bf16_splitk(g.M, (long long)dm.K, g.many != 0, &kchunk);
     dm.kchunk = kchunk;
   }
   // (no tokens: an input gradient has no rows to write; a weight gradient is all zeros, which its tiles write
@@ -583,9 +583,8 @@ int launch_gemm_bwd_pair(vardrop_ctx* ctx, const GemmBf16& gx, const GemmBf16& g
       gw.M % 8 != 0 || gw.N % 8 != 0 || gw.kchunk % 64 != 0 || gw.splitk < 1 ||
       (long long)gw.K * gw.lda >= (1ll << 31) || (long long)gw.K * gw.ldb >= (1ll << 31))
     return VARDROP_EUNSUPPORTED;
-  // (with a device-side count gx.M is the bound: a count in the few-token range under a bound in the other one
-  // still runs correctly on the many-token tiles, with the single slice its own rule gives it)
-  if (vd_attn_bf16_many_tokens(gx.N, gx.M)) return launch_gemm_bwd_pair_cfg<PairLarge>(ctx, gx, gw, nzw, s);
+  // (with a device-side count the choice is made for its bound, tiles and slices alike)
+  if (gw.many) return launch_gemm_bwd_pair_cfg<PairLarge>(ctx, gx, gw, nzw, s);
   return launch_gemm_bwd_pair_cfg<PairSmall>(ctx, gx, gw, nzw, s);
 }
 
@@ -654,6 +653,7 @@ int vd_gemm_bf16_sum_slices(vardrop_ctx* ctx, const float* part, float* const ou
     r.n_max = like->n_max;
     r.n_mul = like->n_mul;
     r.dn_d = like->M;
+    r.many = like->many;
   }
   r.part = part;
   for (int z = 0; z < nz; ++z) r.out[z] = out[z];
