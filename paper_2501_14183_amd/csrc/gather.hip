@@ -32,28 +32,40 @@ __global__ __launch_bounds__(256) void gather_kernel(const T* __restrict__ src, 
   }
 }
 
-// dst[b][n][:] = src[b][i][:] if sel[i] == n for some i (sel ascending), else 0.
+// dst[b][n][:] = src[b][i][:] if sel[i] == n for some i (sel ascending), else 0.  threadIdx.y takes a variate and writes
+// its rows of the batches blockIdx.y * bper ..: a search serves all of them and four rows travel at once.  Bound by the
+// writes (862 variates of 32 batches, 1 KB rows: 8.6 us; a search for every row took 12.6).
 template <typename T>
 __global__ __launch_bounds__(256) void scatter_kernel(const T* __restrict__ src, T* __restrict__ dst,
                                                      const int32_t* __restrict__ sel,
-                                                     int B, int N, int n_sel, int row_units,
+                                                     int B, int N, int n_sel, int row_units, int bper,
                                                      const int32_t* n_dev, int32_t* status) {
   if (!vd_count(n_dev, n_sel, n_sel, status)) return;
-  const int rows = B * N;
-  for (int row = blockIdx.x * blockDim.y + threadIdx.y; row < rows; row += gridDim.x * blockDim.y) {
-    const int b = row / N, n = row - b * N;
-    int lo = 0, hi = n_sel;                       // first position with sel[pos] >= n
-    while (lo < hi) {
-      const int mid = (lo + hi) >> 1;
-      if (sel[mid] < n) lo = mid + 1; else hi = mid;
-    }
-    const bool hit = lo < n_sel && sel[lo] == n;
-    T* q = dst + (long long)row * row_units;
+  const int n = blockIdx.x * blockDim.y + threadIdx.y;
+  if (n >= N) return;
+  const int b0 = blockIdx.y * bper, b1 = min(B, b0 + bper);
+  int lo = 0, hi = n_sel;                         // first position with sel[pos] >= n
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (sel[mid] < n) lo = mid + 1; else hi = mid;
+  }
+  const bool hit = lo < n_sel && sel[lo] == n;
+  const long long ps = (long long)n_sel * row_units, qs = (long long)N * row_units;   // from a batch to the next
+  for (int c = threadIdx.x; c < row_units; c += blockDim.x) {
+    const T* p = src + (long long)lo * row_units + c;
+    T* q = dst + (long long)n * row_units + c;
+    int b = b0;
     if (hit) {
-      const T* p = src + ((long long)b * n_sel + lo) * row_units;
-      for (int c = threadIdx.x; c < row_units; c += blockDim.x) q[c] = p[c];
+      for (; b + 4 <= b1; b += 4) {
+        T v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) v[u] = p[(b + u) * ps];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) q[(b + u) * qs] = v[u];
+      }
+      for (; b < b1; ++b) q[b * qs] = p[b * ps];
     } else {
-      for (int c = threadIdx.x; c < row_units; c += blockDim.x) q[c] = zero_unit<T>();
+      for (; b < b1; ++b) q[b * qs] = zero_unit<T>();
     }
   }
 }
@@ -67,7 +79,7 @@ int launch(vardrop_ctx* ctx, const void* src, void* dst, const int32_t* sel, int
            int d, int dtype, hipStream_t s, VdDevCount dn = {nullptr, nullptr}) {
   const int es = elem_size(dtype);
   const long long row_bytes = (long long)d * es;
-  const long long rows = (long long)B * (kScatter ? N : n_sel);
+  const long long rows = (long long)B * (kScatter ? N : n_sel);       // (rows of the result)
   if (rows == 0) return VARDROP_OK;
   const bool wide = row_bytes % 16 == 0 && vd_aligned(src, 16) && vd_aligned(dst, 16);
   const int unit = wide ? 16 : es;
@@ -79,15 +91,23 @@ int launch(vardrop_ctx* ctx, const void* src, void* dst, const int32_t* sel, int
   long long blocks = (rows + ty - 1) / ty;
   if (blocks > 256 * 64) blocks = 256 * 64;
   dim3 grid((unsigned)blocks), block(tx, ty);
+  int bper = 1;                                   // scatter: batches per workgroup, as many as leave the chip 1024 workgroups
+  if (kScatter) {
+    const int gx = (N + ty - 1) / ty;
+    bper = (int)((long long)B * gx / 1024);
+    bper = bper < 1 ? 1 : (bper > B ? B : bper);
+    if (bper < (B + 65534) / 65535) bper = (B + 65534) / 65535;
+    grid = dim3((unsigned)gx, (unsigned)((B + bper - 1) / bper));
+  }
   VdTimer timer(ctx, kScatter ? VARDROP_K_SCATTER : VARDROP_K_GATHER, s);
   if (wide) {
-    if (kScatter) VD_KERNEL(ctx, scatter_kernel<Chunk16>, grid, block, 0, s, (const Chunk16*)src, (Chunk16*)dst, sel, B, N, n_sel, row_units, dn.dev, dn.status);
+    if (kScatter) VD_KERNEL(ctx, scatter_kernel<Chunk16>, grid, block, 0, s, (const Chunk16*)src, (Chunk16*)dst, sel, B, N, n_sel, row_units, bper, dn.dev, dn.status);
     else VD_KERNEL(ctx, gather_kernel<Chunk16>, grid, block, 0, s, (const Chunk16*)src, (Chunk16*)dst, sel, B, N, n_sel, row_units, dn.dev, dn.status);
   } else if (es == 4) {
-    if (kScatter) VD_KERNEL(ctx, scatter_kernel<uint32_t>, grid, block, 0, s, (const uint32_t*)src, (uint32_t*)dst, sel, B, N, n_sel, row_units, dn.dev, dn.status);
+    if (kScatter) VD_KERNEL(ctx, scatter_kernel<uint32_t>, grid, block, 0, s, (const uint32_t*)src, (uint32_t*)dst, sel, B, N, n_sel, row_units, bper, dn.dev, dn.status);
     else VD_KERNEL(ctx, gather_kernel<uint32_t>, grid, block, 0, s, (const uint32_t*)src, (uint32_t*)dst, sel, B, N, n_sel, row_units, dn.dev, dn.status);
   } else {
-    if (kScatter) VD_KERNEL(ctx, scatter_kernel<uint16_t>, grid, block, 0, s, (const uint16_t*)src, (uint16_t*)dst, sel, B, N, n_sel, row_units, dn.dev, dn.status);
+    if (kScatter) VD_KERNEL(ctx, scatter_kernel<uint16_t>, grid, block, 0, s, (const uint16_t*)src, (uint16_t*)dst, sel, B, N, n_sel, row_units, bper, dn.dev, dn.status);
     else VD_KERNEL(ctx, gather_kernel<uint16_t>, grid, block, 0, s, (const uint16_t*)src, (uint16_t*)dst, sel, B, N, n_sel, row_units, dn.dev, dn.status);
   }
   VD_LAUNCH_CHECK(ctx);
