@@ -222,9 +222,14 @@ __device__ __forceinline__ void bwd_dq_f32(const SdpaF32& a, int qb, int h, int 
       floatx16 st = rows_times<DH>(ks, qf, col, half);
       const floatx16 dp = rows_times<DH>(ks + T::kBytes, df, col, half);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {           // (a key past the end has a row of zeros in K: its dS contributes nothing)
+      for (int r = 0; r < 16; ++r) {
         const float p = expf(fmaf(st[r], a.scale, -lse));
         st[r] = p * (dp[r] - D) * a.scale;
+      }
+      if (j * 32 + 32 > n) {                   // (a key past the end scores 0: its p = exp(-lse) may be infinite, so its zeros
+#pragma unroll                                 //  in K would not drop it)
+        for (int r = 0; r < 16; ++r)
+          st[r] = j * 32 + 8 * (r >> 2) + 4 * half + (r & 3) < n ? st[r] : 0.f;
       }
       cols_times<DH>(acc, ks, st, col, half);
     }

@@ -167,6 +167,32 @@ def test_softmax_with_large_logits_stays_finite(vd, ctx):
     assert rel_err(got["y"], want["y"]) <= 5e-2             # near-ties between keys amplify bf16 rounding of Q, K
 
 
+# (bf16: the kernel of short selections below 129 tokens, those of long ones from there on)
+@pytest.mark.parametrize("sign", [-1.0, 1.0])
+@pytest.mark.parametrize("n,d,H,dtype", [(5, 16, 1, "fp32"), (33, 32, 1, "fp32"), (33, 64, 1, "fp32"), (33, 128, 1, "fp32"), (40, 96, 3, "fp32"),
+                                         (129, 16, 1, "fp32"), (129, 256, 2, "fp32"), (31, 64, 1, "bf16"), (129, 128, 2, "bf16"), (200, 64, 1, "bf16")])
+def test_all_logits_of_every_query_far_from_zero(vd, ctx, n, d, H, dtype, sign):
+    """Every logit lies near -110 (or 110), where exp(-logit) of an absent key's zero score overflows, at token counts
+    that end a block of keys early.  The last dimension of a head is a constant of Q and of K, so the others behave as
+    usual."""
+    B, dk = 2, d // H
+    xs, W, dy, b = random_case(n + d, B, n, d, dtype, bias=True)
+    const = np.arange(d) % dk == dk - 1
+    a = np.ceil(np.sqrt(110.0 * np.sqrt(dk)))                    # a whole number: a bf16 value too
+    W[0][:, const] = W[1][:, const] = 0.0
+    b[0][const], b[1][const] = a, sign * a
+    want = oracle_attention(xs, W, H, dy, tuple(b))
+    got = run_gpu(vd, ctx, xs, W, H, dy, dtype, biases=b)
+    assert all(torch.isfinite(v.float()).all() for v in got.values())
+    for name in ("dWq", "dWk"):                                  # (the constants' columns cancel to rounding)
+        got[name], want[name] = got[name][:, to_dev(~const)], want[name][:, ~const]
+    # A score and a log-sum-exp of magnitude a^2 / sqrt(dk) carry a few roundings of 2^-24 of it into the exponent, so
+    # that much relative error enters every probability, on top of what the tensors have anyway.
+    tol = TOL[dtype] + 8.0 * (a * a / np.sqrt(dk)) * 2.0 ** -24
+    errs = {k: rel_err(got[k], want[k]) for k in ("y",) + GRADS}
+    assert all(e <= tol for e in errs.values()), (tol, errs)
+
+
 @pytest.mark.parametrize("B,n", [(2, 129), (2, 192), (3, 300), (256, 300)])
 def test_softmax_reference_moves_between_key_blocks(vd, ctx, B, n):
     """Scores that leave the reference taken in an earlier block of 64 keys behind: by less than what the forward lets
