@@ -1248,7 +1248,7 @@ size_t vd_attn_bf16_partial_offset(int B, int n, int d, int H) {
 // Room for the largest slice count, so that a workspace sized for n tokens also serves any smaller
 // selection (the slice count is not monotone in the token count).
 size_t vd_attn_bf16_ws_bytes(int B, int n, int d, int H) {
-  return vd_attn_bf16_partial_offset(B, n, d, H) + (size_t)4 * 8 * d * d * sizeof(float);
+  return vd_attn_bf16_partial_offset(B, n, d, H) + (size_t)4 * vd_attn_bf16_max_splitk(d, (long long)B * n) * d * d * sizeof(float);
 }
 
 // saved: q, k, v, o ([M][d] bf16 each, M = B*n) then lse fp32 [B][H][n]

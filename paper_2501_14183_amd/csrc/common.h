@@ -112,6 +112,8 @@ __host__ __device__ static inline int vd_ceil_div(int a, int b) { return (a + b 
 // d = 768 80.6 -> 73.2 at 5600; d = 1024 88 -> 73 at 4000.  d = 128: 34.9 -> 43.6 at 32000 (32 weight-gradient workgroups).
 // d = 512 with 3840 rows: 27.3 -> 25.9 + 4.8 for the sum of slices.
 // (Host and device: with a device-side token count the kernels evaluate it themselves.)
+static const int kFewSliceRows = 4608;      // few tokens: rows of a slice at most
+static const int kManySlices = 8;           // many tokens: slices at most
 __host__ __device__ static inline int vd_attn_bf16_weight_tiles(int d) { return vd_ceil_div(d, 64) * vd_ceil_div(d, 128) * 4; }
 __host__ __device__ static inline bool vd_attn_bf16_many_tokens(int d, long long M) {
   const long long tiles = (long long)vd_ceil_div((int)M, 128) * vd_ceil_div(d, 128);
@@ -122,10 +124,10 @@ __host__ __device__ static inline int vd_attn_bf16_splitk(int d, long long M, bo
   int s;
   if (many) {
     s = vd_ceil_div(512, vd_attn_bf16_weight_tiles(d));
-    if (s > 8) s = 8;
+    if (s > kManySlices) s = kManySlices;
     while (s > 1 && M / s < 256) --s;
   } else {
-    s = vd_ceil_div((int)M, 4608);
+    s = vd_ceil_div((int)M, kFewSliceRows);
   }
   if (s < 1) s = 1;
   int chunk = (int)vd_align_up((size_t)vd_ceil_div((int)M, s), 64);
@@ -133,6 +135,13 @@ __host__ __device__ static inline int vd_attn_bf16_splitk(int d, long long M, bo
   s = M > 0 ? vd_ceil_div((int)M, chunk) : 1;
   if (kchunk) *kchunk = chunk;
   return s;
+}
+// Most slices of any count of up to M rows.  The few-token side has more than kManySlices only while one column of tiles
+// (d <= 128) keeps it going past 36864 rows: 15 at its end, 511 tiles.  Grows with M.
+static inline int vd_attn_bf16_max_splitk(int d, long long M) {
+  const long long few_end = 511ll / vd_ceil_div(d, 128) * 128;
+  const int s = vd_ceil_div((int)(M < few_end ? M : few_end), kFewSliceRows);
+  return s > kManySlices ? s : kManySlices;
 }
 size_t vd_attn_bf16_partial_offset(int B, int n, int d, int H);
 size_t vd_attn_bf16_ws_bytes(int B, int n, int d, int H);

@@ -145,6 +145,31 @@ def test_fp32_matrix_core_tiles(vd, ctx, B, n, d, H):
     compare(got, want, "fp32", ("y",) + GRADS + ("dbq", "dbk", "dbv", "dbo"))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_weight_gradients_of_many_rows_stay_in_their_workspace(vd, ctx, d):
+    """37152 rows of one column of tiles: nine partial products per weight, one more than any wider model has, with a host
+    and a device-side count.  What lies behind the workspace stays as it was."""
+    B, n, H, dtype = 288, 129, d // 64, "bf16"
+    xs, W, dy, _ = random_case(d, B, n, d, dtype, bias=False)
+    want = oracle_attention(xs, W, H, dy)
+    td = torch_dtype(dtype)
+    xs_t, dy_t, W_t = to_dev(xs, td), to_dev(dy, td), [to_dev(w, td) for w in W]
+    need = vd.load_library().vardrop_attn_workspace_bytes(B, n, d, H, vd.BF16)
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    n_dev = torch.full((1,), n, dtype=torch.int32, device="cuda")
+    y, saved = vd.vardrop_attn_fwd(ctx, xs_t, *W_t, H)
+    for device_count in (False, True):
+        buf = torch.full((need + (4 << 20),), 0x5A, dtype=torch.uint8, device="cuda")   # (a partial product more would fit)
+        out = (torch.empty_like(xs_t), *[torch.empty((d, d), device="cuda") for _ in range(4)])
+        if device_count:
+            vd.vardrop_attn_bwd_dev(ctx, dy_t, xs_t, n_dev, n, *W_t, H, saved, buf[:need], out, status=status)
+        else:
+            vd.vardrop_attn_bwd(ctx, dy_t, xs_t, *W_t, H, saved, ws=buf[:need], out=out)
+        torch.cuda.synchronize()
+        assert int(status[0]) == 0 and bool((buf[need:] == 0x5A).all())
+        compare(dict(zip(GRADS, out), y=y), want, dtype, ("y",) + GRADS)
+
+
 def test_dense_mode_equals_identity_selection(vd, ctx):
     """Inference path of the paper: no variate dropped, all N tokens attend."""
     w = wl.WORKLOADS["electricity"]
