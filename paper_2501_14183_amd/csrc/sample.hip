@@ -11,7 +11,7 @@
 //      is left packed in group_id[n].
 //   2. select_kernel, one workgroup: dense group ids (a bitmap of the occupied starts and its prefix sums) and the kept
 //      variates in ascending order.
-// Up to 256 variates one workgroup does both in one launch.
+// Up to 192 variates one workgroup does both in one launch.
 // Measured (both launches; before: one workgroup ordering the variates in LDS): N = 32 3.0 us (8.1), 321 4.3 + 1.8
 // (9.5), 862 6.3 + 2.1 (14.0), 2048 8.9 + 4.7 (25.5), 8192 34 + 5.8 (142).
 #include "common.h"
@@ -19,7 +19,9 @@
 namespace {
 
 constexpr int kMaxN = 8192;
-constexpr int kSmallSample = 256;           // variates one workgroup handles in one launch
+constexpr int kSmallSample = 192;           // variates one workgroup handles in one launch
+                                            // (192: 7.0 us, two launches 6.3 and 1-2 us more for a call alone; 220: 8.8
+                                            // against 6.5, 256: 10.0 against 6.4; 137: 5.7 against 6.1)
 
 __device__ inline void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3,
                                      uint32_t k0, uint32_t k1, uint32_t& r0, uint32_t& r1) {
@@ -288,7 +290,7 @@ __global__ __launch_bounds__(1024) void select_kernel(SampleArgs a) {
   }
   select_phase<E>(a, v, s, blockDim.x);
 }
-// Up to 256 variates: wavefront w counts for the variates of block w % nb of 64 over one of 16 / nb parts of them.
+// Up to 192 variates: wavefront w counts for the variates of block w % nb of 64 over one of 16 / nb parts of them.
 __global__ __launch_bounds__(1024) void sample_small_kernel(SampleArgs a) {
   __shared__ uint64_t hs[kSmallSample], us[kSmallSample];
   __shared__ int cnt[3][kSmallSample];

@@ -89,7 +89,7 @@ def test_counts_reach_pinned_host_memory_and_runs_are_deterministic(vd, ctx):
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1], b[1])
 
 
-@pytest.mark.parametrize("N", [63, 192, 255, 256, 257, 1024, 1025, 2047, 2048, 2049, 4096, 5000])
+@pytest.mark.parametrize("N", [63, 192, 193, 255, 256, 257, 1024, 1025, 2047, 2048, 2049, 4096, 5000])
 @pytest.mark.parametrize("bits", [17, 32, 33, 40, 57, 64])
 def test_counts_at_launch_boundaries_and_hash_widths(vd, ctx, N, bits):
     """Sizes at which the launch shape changes or a workgroup's share ends early, with hashes of every width class:
