@@ -235,6 +235,60 @@ def test_softmax_reference_moves_between_key_blocks(vd, ctx, B, n):
     compare(got, want, "bf16", ("y", "dWv", "dWo"))
 
 
+def placed_logits(seed, B, n, x0):
+    """One head whose logit for key j is x0[j] plus noise of standard deviation 1/4: Q's first dimension is 8, K's is x0,
+    held exactly."""
+    rng = np.random.default_rng(seed)
+    xs = 0.5 * rng.standard_normal((B, n, 64))
+    xs[:, :, 0], xs[:, :, 1] = x0, 8.0
+    Wq, Wk = np.eye(64), np.eye(64)
+    Wq[0] = Wk[1] = Wq[1] = 0.0
+    Wq[1, 0] = 1.0
+    Wv, Wo = (wl.quantise(rng.standard_normal((64, 64)) / 8.0, "bf16") for _ in range(2))
+    Wv[0] = Wv[1] = 0.0
+    return wl.quantise(xs, "bf16"), [Wq, Wk, Wv, Wo], wl.quantise(rng.standard_normal((B, n, 64)), "bf16")
+
+
+def check_placed(got, want, gradients):
+    """All finite, y, dWv and dWo within the usual bounds, and the gradients that go through the probabilities within the
+    RMS bound, the placed dimension apart from the others: it is 16 times as large.  (The worst element has no bound
+    against a tensor's RMS here, since tokens differ by the weight they take, and what belongs to the constant token
+    dimension vanishes identically, a row of dS summing to zero, so that only rounding is left of it.)"""
+    assert all(torch.isfinite(v.float()).all() for v in got.values())
+    compare(got, want, "bf16", ("y", "dWv", "dWo"))
+    if gradients:
+        for k, cut in (("dxs", (np.s_[..., 2:], np.s_[..., 0])), ("dWq", (np.s_[2:, 1:], np.s_[2:, 0])),
+                       ("dWk", (np.s_[2:, 1:], np.s_[2:, 0]))):
+            for at in cut:
+                rms, _ = elem_err(got[k][at], want[k][at], "bf16")
+                assert rms <= 1.0, (k, at, rms)
+
+
+@pytest.mark.parametrize("B", [2, 256])
+@pytest.mark.parametrize("slope", [0.02, 0.05, 0.125, 0.5, 2.0, -0.125])
+def test_logits_that_rise_over_the_keys(vd, ctx, B, slope):
+    """The reference is left behind a little, enough to move, and beyond an exponential's range in every block of 64 keys
+    (and never, when they fall).  Up to 0.5 a key several neighbours share the weight; with 2 the last key has nearly all
+    of it, and what is left of dQ and dK is rounding."""
+    n = 270
+    j = np.arange(n)
+    xs, W, dy = placed_logits(int(1000 * slope) % 977, B, n, slope * (j - (n - 1) if slope > 0 else j))
+    want = oracle_attention(xs, W, 1, dy)
+    check_placed(run_gpu(vd, ctx, xs, W, 1, dy, "bf16"), want, gradients=slope <= 0.5)
+
+
+@pytest.mark.parametrize("at", [64, 130, 199])
+@pytest.mark.parametrize("above", [7.5, 9.0, 11.0, 12.5, 14.0, 20.0, 140.0])
+def test_one_key_above_all_before_it(vd, ctx, above, at):
+    """A single key of a later block `above` (log2) over the others: its probability alone is let pass up to 2^13, moves the
+    reference beyond that, and would overflow.  From 11 on it takes nearly all the weight."""
+    x0 = np.zeros(200)
+    x0[at] = above * np.log(2.0)
+    xs, W, dy = placed_logits(at, 3, 200, x0)
+    want = oracle_attention(xs, W, 1, dy)
+    check_placed(run_gpu(vd, ctx, xs, W, 1, dy, "bf16"), want, gradients=above <= 9.0)
+
+
 def test_determinism(vd, ctx):
     xs, W, dy, _ = random_case(9, 4, 130, 512, "bf16", bias=False)
     a = run_gpu(vd, ctx, xs, W, 8, dy, "bf16")
