@@ -106,19 +106,10 @@ __host__ __device__ static inline int vd_ceil_div(int a, int b) { return (a + b 
 // makes that launch 3.5 us shorter at the Traffic shape and costs a 5 us launch that sums the slices).  Many tokens:
 // 128 x 128 tiles for both, two workgroups per compute unit, and enough slices for that (counted as twice as many 64-row
 // tiles), at least 256 rows each.  Slices are a multiple of the 64-row stage.
-// Many tokens begin at 512 input-gradient tiles of 128 rows, and already at 148 where that adds no launch (more than
-// 4608 rows have several slices either way, a d of 1024 has one either way) and d gives the weight gradients tiles enough:
-// d = 512 33.2 -> 29.3 us at 4800 rows, 37.8 -> 33.3 at 6080, 44.4 -> 40.4 at 8192; d = 256 33.4 -> 24.6 at 11200;
-// d = 768 80.6 -> 73.2 at 5600; d = 1024 88 -> 73 at 4000.  d = 128: 34.9 -> 43.6 at 32000 (32 weight-gradient workgroups).
-// d = 512 with 3840 rows: 27.3 -> 25.9 + 4.8 for the sum of slices.
 // (Host and device: with a device-side token count the kernels evaluate it themselves.)
 static const int kFewSliceRows = 4608;      // few tokens: rows of a slice at most
 static const int kManySlices = 8;           // many tokens: slices at most
 __host__ __device__ static inline int vd_attn_bf16_weight_tiles(int d) { return vd_ceil_div(d, 64) * vd_ceil_div(d, 128) * 4; }
-__host__ __device__ static inline bool vd_attn_bf16_many_tokens(int d, long long M) {
-  const long long tiles = (long long)vd_ceil_div((int)M, 128) * vd_ceil_div(d, 128);
-  return tiles >= 512 || (tiles >= 148 && d >= 256 && (M > 4608 || vd_attn_bf16_weight_tiles(d) >= 512));
-}
 // `many`: which of the two the launch was made for (with a device-side count: by its bound)
 __host__ __device__ static inline int vd_attn_bf16_splitk(int d, long long M, bool many, int* kchunk) {
   int s;
@@ -135,6 +126,30 @@ __host__ __device__ static inline int vd_attn_bf16_splitk(int d, long long M, bo
   s = M > 0 ? vd_ceil_div((int)M, chunk) : 1;
   if (kchunk) *kchunk = chunk;
   return s;
+}
+// Many tokens begin at 512 input-gradient tiles of 128 rows, and earlier, from 148 on, where that adds no launch (more than
+// 4608 rows have several slices either way, a d of 1024 has one either way), d gives the weight gradients tiles enough, and
+// the launch needs fewer rounds of the chip: 512 places for the many-token workgroups, 256 for the others.
+//   One round (few -> many, with the sum of slices): d = 256 34.8 -> 26.5 us at 10425 rows, 45.0 -> 42.1 at 24500, the last
+//     that fit; d = 384 40.4 -> 28.8 at 8680; d = 448 35.8 -> 30.6 at 6116; d = 512 36.0 -> 32.0 at 4692, 43.0 -> 40.2 at
+//     8037; d = 768 66.7 -> 49.8 at 4692; d = 1024 64.1 -> 48.3 at 2397, 73.7 -> 65.3 at 4060.
+//   Two rounds against four or more: d = 512 92.5 -> 77.6 at 13622; d = 704 71.6 -> 66.9 at 5217; d = 832 105 -> 80.5 at
+//     5460; d = 960 128 -> 102 at 5320; d = 1024 123 -> 107 at 4830.
+//   Two against three: d = 320 43.9 -> 43.3 at 14000, d = 384 51.0 -> 45.4 at 12880, d = 448 55.0 -> 48.9 at 9452, d = 512
+//     55.2 -> 54.1 at 8260, d = 576 53.8 -> 52.7 at 5600, d = 640 58.3 -> 58.3 at 6116; but d = 256 45.5 -> 59.2 at 24920 (few
+//     columns, long slices) and d = 704 54.0 -> 64.4 at 4830 (the three rounds are full).
+//   Two against two: d = 320 34.4 -> 36.3 at 9800, d = 384 36.3 -> 40.2 at 9800, d = 448 36.5 -> 40.8 at 6348.
+// d = 128: 34.9 -> 43.6 at 32000 (32 weight-gradient workgroups).  d = 512 with 3840 rows: 27.3 -> 25.9 + 4.8 for the sum.
+// With a device-side count the bound decides.  Counts near it gain as above, counts far below it lose: d = 512, bound 6144
+// rows, 6080 rows 43.2 -> 38.2, 4160 44.8 -> 31.9, 3200 27.4 -> 28.5; bound 6896, 4000 rows 31.8 -> 30.6, 720 20.2 -> 24.8.
+static inline bool vd_attn_bf16_many_tokens(int d, long long M) {
+  const int cols = vd_ceil_div(d, 128), weight_tiles = vd_attn_bf16_weight_tiles(d);
+  const long long tiles = (long long)vd_ceil_div((int)M, 128) * cols;
+  if (tiles >= 512) return true;
+  if (tiles < 148 || d < 256 || (M <= kFewSliceRows && weight_tiles < 512)) return false;
+  const long long many = tiles + 4 * cols * cols * vd_attn_bf16_splitk(d, M, true, nullptr);
+  const long long few = tiles + weight_tiles * vd_attn_bf16_splitk(d, M, false, nullptr);
+  return many <= 512 || few > 768 || (few > 512 && d >= 320 && d <= 640);
 }
 // Most slices of any count of up to M rows.  The few-token side has more than kManySlices only while one column of tiles
 // (d <= 128) keeps it going past 36864 rows: 15 at its end, 511 tiles.  Grows with M.

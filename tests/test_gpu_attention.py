@@ -170,6 +170,16 @@ def test_weight_gradients_of_many_rows_stay_in_their_workspace(vd, ctx, d):
         compare(dict(zip(GRADS, out), y=y), want, dtype, ("y",) + GRADS)
 
 
+@pytest.mark.parametrize("B,d", [(73, 384), (76, 384), (190, 256), (192, 256), (36, 704), (37, 704)])
+def test_gradient_launch_on_both_sides_of_its_rounds(vd, ctx, B, d):
+    """129 tokens a window: the last row counts whose many-token workgroups fit the chip in one round and the first that
+    take the few-token tiles instead (in three, six and two slices)."""
+    xs, W, dy, _ = random_case(B + d, B, 129, d, "bf16", bias=False)
+    want = oracle_attention(xs, W, d // 64, dy)
+    got = run_gpu(vd, ctx, xs, W, d // 64, dy, "bf16")
+    compare(got, want, "bf16", ("y",) + GRADS)
+
+
 def test_dense_mode_equals_identity_selection(vd, ctx):
     """Inference path of the paper: no variate dropped, all N tokens attend."""
     w = wl.WORKLOADS["electricity"]
