@@ -84,14 +84,14 @@ enum {
   VARDROP_K_SDPA_FWD,        /* softmax(Q K^T / sqrt(d_k)) V                                */
   VARDROP_K_GEMM_OUT,        /* y = O Wo                                                    */
   VARDROP_K_GEMM_DO,         /* dO = dy Wo^T                                                */
-  VARDROP_K_SDPA_BWD_DQ,     /* dQ and rowsum(dO * O)                                       */
-  VARDROP_K_SDPA_BWD_DKV,    /* dK, dV                                                      */
-  VARDROP_K_GEMM_DW,         /* dWq, dWk, dWv, dWo (K slices)                               */
+  VARDROP_K_SDPA_BWD_DQ,     /* bf16, n > 128, many workgroups: dQ and rowsum(dO * O)       */
+  VARDROP_K_SDPA_BWD_DKV,    /* bf16, n > 128, many workgroups: dK, dV                      */
+  VARDROP_K_GEMM_DW,         /* (no path launches weight gradients alone: see GEMM_DW_DXS)  */
   VARDROP_K_REDUCE_DW,       /* sum of the K slices                                         */
-  VARDROP_K_GEMM_DXS,        /* dxs = dQ Wq^T + dK Wk^T + dV Wv^T                           */
+  VARDROP_K_GEMM_DXS,        /* (no path launches dxs alone: see GEMM_DW_DXS)               */
   VARDROP_K_SCATTER,         /* adjoint of the gather                                       */
   VARDROP_K_GEMM_DW_DXS,     /* weight gradients (K slices) and dxs in one launch           */
-  VARDROP_K_SDPA_BWD,        /* dQ, dK, dV of a short selection (n <= 128) in one launch    */
+  VARDROP_K_SDPA_BWD,        /* dQ, dK, dV in one launch: bf16 short selections (n <= 128), fp32 always */
   VARDROP_K_QKV_SDPA_FWD,    /* Q, K, V projection and attention of a short selection       */
   VARDROP_K_EMBED_ROWS,      /* kept windows: gather from the raw batch, standardise, convert */
   VARDROP_K_GEMM_EMBED,      /* xs = z We + be                                              */
@@ -205,9 +205,9 @@ int vardrop_sample_dev(vardrop_ctx* ctx, const uint64_t* hash, int N,
  *
  *   abar   fp32 [N][F], F = number of candidate bins
  *   ws     vardrop_sample_nearest_workspace_bytes(N, F), 256-byte aligned
- * Other arguments, outputs and limits as vardrop_sample.  Cost: the grouping pass runs twice and the
- * group means take O(G N F) operations; meant for the selection of fixed representatives, not tuned
- * like the random sampler.
+ * Other arguments, outputs and limits as vardrop_sample.  Cost: one launch in front of the sampling pass, O(N F)
+ * sums in it, a group's by one workgroup: 18 us at N = 2048, F = 85 and 61 groups, but 90 us with a single group of
+ * all variates (0.5 ms at N = 8192, F = 128).  Meant for the selection of fixed representatives.
  */
 size_t vardrop_sample_nearest_workspace_bytes(int N, int F);
 int vardrop_sample_nearest(vardrop_ctx* ctx, const uint64_t* hash, const float* abar, int N, int F,
@@ -270,7 +270,7 @@ int vardrop_scatter_dev(vardrop_ctx* ctx, const void* dxs, int B, int N, int d, 
  *   dWe    fp32 [L][d], overwritten;  dbe fp32 [d], overwritten, NULL = skip
  *   ws     bwd only: vardrop_embed_workspace_bytes (partial sums of the gradients), 256-byte aligned
  * VARDROP_BF16 rounds z to bf16 and multiplies on the matrix cores with fp32 accumulation; it requires
- * d % 8 == 0, L % 8 == 0 and B*n_sel*max(d, L+63) < 2^31.  VARDROP_F32 is plain fp32.  2 <= L <= 1024.
+ * d % 8 == 0, L % 8 == 0 and B*n_sel*max(d, L+63) < 2^31.  VARDROP_F32 multiplies and sums in fp32.  2 <= L <= 1024.
  * n_sel == 0 is a no-op for fwd; bwd then zero-fills the gradients.
  * VARDROP_BF16 windows of at most 383 samples take one kernel forward (gather through sel, standardisation and
  * the product: the standardised window is formed inside the product's operand load and written to `saved` on
@@ -308,7 +308,7 @@ int vardrop_embed_bwd_dev(vardrop_ctx* ctx, const void* dxs, int B, const int32_
  *                    in fp32; written by fwd, read by bwd
  *   dWq..dWo         fp32 [d][d], overwritten;  dbq..dbo fp32 [d], overwritten, NULL = skip
  * VARDROP_BF16 multiplies bf16 operands on the matrix cores with fp32 accumulation and
- * fp32 softmax, and requires d_k == 64 and d % 64 == 0; VARDROP_F32 is plain fp32 and
+ * fp32 softmax, and requires d_k == 64 and d % 64 == 0; VARDROP_F32 multiplies and sums in fp32 and
  * requires d_k in {16, 32, 64, 128}.  n == 0 is a no-op (weight gradients zero-filled).
  * The backward recomputes the attention probabilities from Q, K and the saved
  * log-sum-exp; it does not store them.  VARDROP_BF16 also requires B*n*d < 2^31
@@ -346,9 +346,10 @@ int vardrop_attn_bwd(vardrop_ctx* ctx, const void* dy, const void* xs,
  * selection vardrop_sample writes has N).  xs, y, dy, dxs are [B][N'][d] packed in buffers of at least B * n_max * d
  * elements; `saved` and `ws` are sized by vardrop_attn_saved_bytes / vardrop_attn_workspace_bytes for n_max, and
  * the backward call must be given the same n_max as the forward call that wrote `saved`.  The kernels are chosen
- * for n_max (VARDROP_BF16: the single-kernel path of short selections when n_max <= 128), results are those of
- * the host-count entry points called with N'.  N' == 0 leaves y, xs, dxs untouched and zero-fills the weight
- * gradients.  *status as in the general rules (forward and backward may share one). */
+ * for n_max (VARDROP_BF16: the single-kernel path of short selections when n_max <= 128; tiles and slices of the
+ * gradients), so a bound near N' is also the fastest; results are those of the host-count entry points called with
+ * N', but for the order of sums where those would choose other kernels.  N' == 0 leaves y, xs, dxs untouched and
+ * zero-fills the weight gradients.  *status as in the general rules (forward and backward may share one). */
 int vardrop_gather_attn_fwd_dev(vardrop_ctx* ctx, const void* tokens, int B, int N, const int32_t* sel,
                                 const int32_t* n_dev, int n_max, int32_t* status,
                                 int d, int H, int dtype,

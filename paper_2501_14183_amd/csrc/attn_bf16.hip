@@ -1206,10 +1206,9 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
 }
 
 // Launches of the kernels for long selections.  A workgroup of four wavefronts takes 128 queries (or keys)
-// when that still gives the chip two workgroups per compute unit, else two wavefronts take 64.  (Two query
-// groups per wavefront, QG = 2, halve the LDS reads per matrix instruction; measured, the kernels are not
-// bound by those: equal at 1936 tokens, slower at 862.)  With a device-side count a.n is its bound: the grid
-// and the choices below are made for the bound, and the workgroups the actual count does not need return at once.
+// when that still gives the chip two workgroups per compute unit, else two wavefronts take 64.  With a device-side
+// count a.n is its bound: the grid and the choices below are made for the bound, and the workgroups the actual count
+// does not need return at once.
 template <typename K>
 int launch_ring(vardrop_ctx* ctx, int kid, K kernel, int rows, int parts, const SdpaArgs& a, hipStream_t s) {
   const long long grid = (long long)parts * vd_ceil_div(a.n, rows) * a.H * a.B;

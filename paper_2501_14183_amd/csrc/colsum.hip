@@ -103,7 +103,7 @@ __global__ __launch_bounds__(256) void colsum_finish_kernel(ColSum a) {
 
 }  // namespace
 
-// Column sums of the first nz of up to four [rows][d] matrices of the given type (d a multiple of 8, rows 16-byte aligned) into dst[z]
+// Column sums of the first nz of up to four [rows][d] matrices of the given type (rows whole 16-byte units, 16-byte aligned) into dst[z]
 // (fp32, null: skipped).  `scratch`: nz * min(64, rows / 64) * d floats, 16-byte aligned, free to be overwritten.
 int vd_colsum(vardrop_ctx* ctx, int dtype, const void* const src[4], float* const dst[4], long long rows, int d,
               void* scratch, hipStream_t s, VdDevCount dn, int n_max, int n_mul, int nz) {

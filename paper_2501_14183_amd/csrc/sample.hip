@@ -6,7 +6,7 @@
 //   rank(n)  = #{h_m = h_n, (u_m, m) < (u_n, n)}   its place in the random order of the group,
 // with u[n] from Philox4x32-10, counter (n, 0, step_lo, step_hi), key (seed_lo, seed_hi), or a caller's key.  n is kept
 // when rank(n) < n_i(size).  Counting needs no order, no atomics on shared buckets and no exchange between workgroups,
-// so it spreads over the chip, and its time does not depend on how the hashes are distributed:
+// so it spreads over the chip (N = 8192: 28 us with all hashes different, 35 with 1756 groups, 63 with one):
 //   1. rank_kernel: a workgroup owns 16 (above 4096 variates 32) variates; its wavefronts share out the m.  The result
 //      is left packed in group_id[n].
 //   2. select_kernel, one workgroup: dense group ids (a bitmap of the occupied starts and its prefix sums) and the kept
@@ -502,8 +502,8 @@ int run_sample_nearest(vardrop_ctx* ctx, const uint64_t* hash, const float* abar
   return run_sample(ctx, hash, N, gs, ratio_num, ratio_den, 0, 0, keys, group_id, sel, counts, counts_host, stream);
 }
 
-// Scratch of the entry point that allocates nothing: the group means ([G][F] floats, G F <= N F <= kStaticMeanFloats)
-// followed by the distance keys ([N] uint64, N <= kMaxN).  Part of the code object, one copy per device, held until
+// Scratch of the entry point that allocates nothing: [N][F] floats, a group's mean in the row of its first member
+// (N F <= kStaticMeanFloats), followed by the distance keys ([N] uint64, N <= kMaxN).  Part of the code object, one copy per device, held until
 // the process ends; every call on a device uses it, so calls that overlap on one device race.
 constexpr size_t kStaticMeanFloats = (size_t)1 << 20;
 constexpr size_t kStaticScratchBytes = kStaticMeanFloats * sizeof(float) + (size_t)kMaxN * sizeof(uint64_t);
