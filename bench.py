@@ -849,7 +849,9 @@ def main():
     dominant = max(attn, key=lambda k: attn[k]["us_per_step"])
     roof = {"kernel": dominant}
     roof.update({k: roof_all[dominant][k] for k in ("bound", "achieved", "peak", "unit", "frac")})
-    roof["traffic"] = recorded_traffic(w.name, dominant)
+    # (the counters were taken at the workload's own k and keep ratio)
+    own_selection = not (args.dense or args.k or args.gs)
+    roof["traffic"] = recorded_traffic(w.name, dominant) if own_selection else None
     roof["avg_launch_us"] = roof_all[dominant]["avg_launch_us"]
     roof["launches"] = roof_all[dominant]["launches"]
     if dominant == "gemm_dw_dxs" and "reduce_dw" not in roof_all:
