@@ -138,7 +138,7 @@ def test_bias_gradients_over_row_slices(vd, ctx, B, n, d, H, dtype):
                                      (1, 257, 128, 1), (2, 65, 96, 3), (4, 128, 64, 1), (9, 300, 80, 5)])
 def test_fp32_matrix_core_tiles(vd, ctx, B, n, d, H):
     """Token blocks of 32 and 128 ended exactly and one past, all head sizes, widths off the 64-wide product tiles, and
-    weight gradients in one K slice (255 rows at most), two (512) and ten with a short last one (2700)."""
+    weight gradients in one K slice (up to 291 rows), two (512) and ten with a short last one (2700)."""
     xs, W, dy, b = random_case(3 * d + n, B, n, d, "fp32", bias=True)
     want = oracle_attention(xs, W, H, dy, tuple(b))
     got = run_gpu(vd, ctx, xs, W, H, dy, "fp32", biases=b)
