@@ -19,6 +19,10 @@ namespace {
 // ================================================================== attention core (d_k = 64)
 constexpr int kDh = 64;
 constexpr float kLog2e = 1.4426950408889634f;
+constexpr float kLn2 = 0.6931471805599453f;
+// Q is kept as (xs Wq + bq) * log2(e) / sqrt(d_k): the factor goes in before the rounding to bf16, so nothing is rounded
+// twice, and the products with K are exponents of two as they leave the matrix pipe (dK = dS^T Q / sqrt(d_k) then takes
+// ln 2 for a factor).
 
 // a lane's row of a head slice as four right-hand (or left-hand) operands: k = 16*s + 8*half + e
 __device__ inline void row_frags(Frag f[4], const bf16_t* P, long long ld, int row, int n, int half) {
@@ -71,6 +75,12 @@ constexpr float kSumMax = 8192.f;               // a sum of 32 unnormalised prob
 // Copies rows [j0, j0 + 64) of two head slices into a stage; a wavefront-wide copy fills 8 token rows and rows past n
 // repeat row n-1.  `off` holds this lane's byte offsets of its share of a whole block, so that a copy costs no vector
 // instruction but itself (the address is a scalar base plus the offset); only the last block computes clamped ones.
+// the lane, read afresh: what is derived from it is not kept in registers over the loop before
+__device__ __forceinline__ int fresh_lane() {
+  int lane;
+  asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(lane));
+  return lane;
+}
 template <int NW>
 struct RingSrc {
   uint32_t off[8 / NW];
@@ -97,6 +107,7 @@ __device__ inline void ring_issue(const bf16_t* p0, const bf16_t* p1, const Ring
       dma16_at(s1, src.off[u], stage + kRingTile + (u * NW + wave) * 1024);
     }
   } else {
+    lane = fresh_lane();
 #pragma unroll
     for (int u = 0; u < 8 / NW; ++u) {
       const int row = (u * NW + wave) * 8 + (lane >> 3);
@@ -171,17 +182,20 @@ __device__ inline bool ring_block(SdpaArgs& a, int rows, int parts, int& xb, int
 // ---- forward: a wavefront owns 32 queries (lane = query), NW wavefronts share the K / V stages.
 // S^T = K q^T, online softmax on per-lane scalars, O^T = V^T P^T with the probability registers as the
 // right-hand operand.
-// What bounds it: with d_k = 64 a 32 x 32 tile of scores costs 8 matrix instructions (256 clocks) and, per score, a
-// fused multiply-add, an exponential (two issue slots), an addition and half a conversion on the vector pipe of the
-// same SIMD; the two pipes overlap for 40 % of the matrix time only, so every vector instruction in the loop counts.
+// What bounds it: with d_k = 64 a 32 x 32 tile of scores costs 8 matrix instructions (256 clocks) and, per score, an
+// exponential (8 clocks a wavefront), an addition and half a conversion (4 clocks each) on the vector pipe of the same
+// SIMD.  A probe with both kinds on one SIMD shows them overlapping fully between wavefronts; here the three wavefronts
+// of a SIMD overlap them for 40 % of the matrix time only, so every vector instruction in the loop counts.
 // Without the maximum per block, with scalar copy addresses and immediate read offsets: 143 -> 117 us at 1924 tokens
-// (B = 8, H = 12; 0.84 PFLOP/s), 82 -> 69 us at 862 (B = 32, H = 8).
+// (B = 8, H = 12; 0.84 PFLOP/s), 82 -> 69 us at 862 (B = 32, H = 8).  With the scale in Q and the accumulators of the
+// scores starting at minus the reference (no multiply-add per score): 119 -> 113 us and 84 -> 80 us on one box.  Tried:
+// fixed priorities by wavefront slot instead of priority while feeding the matrix pipe 125 us, no priorities 117 us.
 __device__ __forceinline__ float other_half(float v) {       // the value of lane ^ 32
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
 }
 template <int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) void sdpa_fwd_bf16(SdpaArgs a) {
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 3 : 2))) void sdpa_fwd_bf16(SdpaArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   constexpr int LPS = 16 / NW;                 // copies per wavefront and stage
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -193,7 +207,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
   const long long base = (long long)b * n * ld + h * kDh;
   const bf16_t* kp = a.k + base;
   const bf16_t* vp = a.v + base;
-  const int qi = (qb * NW + wave) * 32 + col;
+  int qi = (qb * NW + wave) * 32 + col;
   const int nb = (n + 63) >> 6;
   const RingSrc<NW> src = ring_src<NW>(ld, wave, lane);
   ring_issue<NW>(kp, vp, src, ld, 0, n, smem, wave, lane);
@@ -202,9 +216,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
   row_frags(qf, a.q + base, ld, qi, n, half);
   const RingAddr ra = ring_addr(smem, lane);
   floatx16 acc[2] = {zero16(), zero16()};
-  float m = -INFINITY, l = 0.f;
+  float m = 0.f, l = 0.f;
+  floatx16 nm16 = zero16();                    // -m, what the accumulators of the scores start with
   bool careful = true;                         // form a block's maximum first (the same for the whole wavefront)
-  const float c = a.scale * kLog2e;
   auto step = [&](auto stage, int j) __attribute__((always_inline)) {
     constexpr int ST = decltype(stage)::value, SO = ST * kRingStage;
     // block j has landed once only the copies of block j+1 are in flight; behind the barrier everyone's have,
@@ -216,7 +230,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
     Frag fa[4], fb[4];
 #define VD_S_STEP(F, KT, S, PENDING)                                                    \
   wait_lds<PENDING>(F[S]);                                                              \
-  st[KT] = mfma(F[S], qf[S], (S) == 0 ? zero16() : st[KT]);                             \
+  st[KT] = mfma(F[S], qf[S], (S) == 0 ? nm16 : st[KT]);                                 \
   __builtin_amdgcn_sched_barrier(0);
     // the scores of block j; keys past the end (only in the last block) get -inf
 #define VD_SCORES()                                                                     \
@@ -234,13 +248,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
         st[kt][r] = key < n ? st[kt][r] : -INFINITY;                                    \
       }                                                                                 \
   }
-    // exp2(c s - reference) as one fused multiply-add and the exponential, and their sum
-#define VD_EXP_SUM(RS)                                                                  \
+    // exp2(score - reference) and their sum; the accumulators hold the difference already, up to a MOVE of the reference
+#define VD_EXP_SUM(RS, MOVE)                                                            \
   {                                                                                     \
     float r0 = 0.f, r1 = 0.f;                                                           \
     _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                    \
-      st[0][r] = fast_exp2(fmaf(st[0][r], c, -m));                                      \
-      st[1][r] = fast_exp2(fmaf(st[1][r], c, -m));                                      \
+      st[0][r] = fast_exp2(st[0][r] MOVE);                                              \
+      st[1][r] = fast_exp2(st[1][r] MOVE);                                              \
       r0 += st[0][r];                                                                   \
       r1 += st[1][r];                                                                   \
     }                                                                                   \
@@ -262,7 +276,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
     float rs = 0.f;
     bool redo = careful;
     if (!redo) {
-      VD_EXP_SUM(rs)
+      VD_EXP_SUM(rs, )
       redo = __any(!(rs <= kSumMax));
       if (redo) {
         wait_lds<0>(fa[0], fa[1], fa[2], fa[3]);
@@ -277,19 +291,21 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mt = fmaxf(mt, st[kt][r]);
-      mt = fmaxf(mt, other_half(mt));
-      const float mc = mt * c;                        // c > 0: scaling commutes with the maximum
-      const float mn = mc > m + kSlack ? mc : m;
-      if (__any(mn != m)) {
-        const float alpha = fast_exp2(m - mn);
+      mt = fmaxf(mt, other_half(mt));                 // relative to the reference
+      float move = 0.f;                               // (the first block sets the reference: nothing to rescale yet)
+      if (j == 0 || mt > kSlack) move = (m + mt) - m;
+      if (j > 0 && __any(move != 0.f)) {
+        const float alpha = fast_exp2(-move);
         l *= alpha;
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[dt][r] *= alpha;
       }
-      m = mn;
-      VD_EXP_SUM(rs)
+      m += move;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) nm16[r] = -m;
+      VD_EXP_SUM(rs, - move)
       careful = j > 0 || __any(rs < 1.f / kSumMax);
     }
     l += rs;
@@ -313,12 +329,14 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
   };
   VD_RING_LOOP(step, nb)
   const float lt = l + other_half(l);
+  const int lane2 = fresh_lane(), half2 = lane2 >> 5;
+  qi = (qb * NW + wave) * 32 + (lane2 & 31);
   if (qi < n) {
     const float inv = 1.f / lt;
     bf16_t* orow = a.out + base + (long long)qi * ld;
-    store_accT(orow, acc[0], 0, half, inv);
-    store_accT(orow, acc[1], 1, half, inv);
-    if (half == 0) a.lse[((long long)b * a.H + h) * n + qi] = (m + log2f(lt)) * 0.6931471805599453f;
+    store_accT(orow, acc[0], 0, half2, inv);
+    store_accT(orow, acc[1], 1, half2, inv);
+    if (half2 == 0) a.lse[((long long)b * a.H + h) * n + qi] = (m + log2f(lt)) * 0.6931471805599453f;
   }
 }
 
@@ -328,6 +346,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
 // or comes with dO from the GEMM before; Dsum holds -D, with which the accumulators of dP start, so that
 // dP - D costs no vector instruction (the vector pipe bounds these loops, as in the forward kernel): 172 -> 151 us at
 // 1924 tokens (B = 8, H = 12), the dK / dV part 224 -> 212 us, both parts in one launch 60 -> 53 us at 321 (B = 32, H = 8).
+// With the scale in Q (and, in the dK / dV part, scores that start at -log2(e) lse): 155 -> 151, 216 -> 208 and 58.6 -> 54.6
+// us on another box.
 template <int NW, bool DLOCAL>
 __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int h, int b) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -367,7 +387,6 @@ __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int 
   for (int r = 0; r < 16; ++r) nD16[r] = nD;
   const RingAddr ra = ring_addr(smem, lane);
   floatx16 acc[2] = {zero16(), zero16()};
-  const float c = a.scale * kLog2e;
   auto step = [&](auto stage, int j) __attribute__((always_inline)) {
     constexpr int ST = decltype(stage)::value, SO = ST * kRingStage;
     if (j + 1 < nb) wait_vm<LPS>(); else wait_vm<0>();
@@ -395,7 +414,7 @@ __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int 
     VD_DQ_STEP(dp, fv, dof, 2, nD16, 1) VD_DQ_STEP(dp, fv, dof, 3, nD16, 0)                              \
     __builtin_amdgcn_s_setprio(0);                                                                       \
     VD_TR4(ft, 0, KT, SO)                                                                                \
-    _Pragma("unroll") for (int r = 0; r < 16; ++r) st[r] = fast_exp2(fmaf(st[r], c, nlse2)) * dp[r];     \
+    _Pragma("unroll") for (int r = 0; r < 16; ++r) st[r] = fast_exp2(st[r] + nlse2) * dp[r];             \
     if (tail) {                                 /* a key past the end repeats the last one: its dS is dropped */ \
       _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                                   \
         const int key = j * 64 + (KT) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);                          \
@@ -427,7 +446,7 @@ __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int 
 }
 
 // ---- backward, part 2: dK and dV.  A wavefront owns 32 keys (lane = key), loop over query blocks: a stage holds
-// the Q and dO tiles of 64 queries, their log-sum-exp and their -D, which the accumulators of dP start with.
+// the Q and dO tiles of 64 queries, their -log2(e) lse and their -D, which the accumulators of S and dP start with.
 // S = Q k^T and dP = dO v^T from row fragments; P and dS in registers are the right-hand operands of dV^T = dO^T P and dK^T = Q^T dS, whose left
 // operands are the same tiles read transposed.
 template <int NW>
@@ -464,7 +483,6 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
   const RingAddr ra = ring_addr(smem, lane);
   const uint32_t stat_addr = ra.lds0 + 2 * kRingTile + 16 * half;   // + 32 per 8 queries
   floatx16 accK[2] = {zero16(), zero16()}, accV[2] = {zero16(), zero16()};
-  const float c = a.scale * kLog2e;
   auto step = [&](auto stage, int i) __attribute__((always_inline)) {
     constexpr int ST = decltype(stage)::value, SO = ST * kRingStage;
     if (i + 1 < nb) wait_vm<LPS>(); else wait_vm<0>();
@@ -473,43 +491,39 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
     const bool tail = i * 64 + 64 > n;
 #define VD_DKV_HALF(QT)                                                                                  \
   {                                                                                                      \
-    floatx16 st;                                                                                         \
-    Acc16 dp;                                                                                            \
-    Frag fq[4], fo[4], ls[4];                                                                            \
-    /* -D of queries 32 QT + 8 q4 + 4 half + 0..3, the rows of registers 4 q4 .. 4 q4 + 3 */             \
+    Acc16 st, dp;                                                                                        \
+    Frag fq[4], fo[4];                                                                                   \
+    /* -log2(e) lse, then -D, of queries 32 QT + 8 q4 + 4 half + 0..3, the rows of registers 4 q4 .. 4 q4 + 3 */\
+    lds_read16_at<SO + (QT) * 128>(st.q[0], stat_addr);                                                  \
+    lds_read16_at<SO + (QT) * 128 + 32>(st.q[1], stat_addr);                                             \
+    lds_read16_at<SO + (QT) * 128 + 64>(st.q[2], stat_addr);                                             \
+    lds_read16_at<SO + (QT) * 128 + 96>(st.q[3], stat_addr);                                             \
+    VD_ROW4(fq, 0, QT, SO)                                                                               \
     lds_read16_at<SO + (QT) * 128 + 256>(dp.q[0], stat_addr);                                            \
     lds_read16_at<SO + (QT) * 128 + 256 + 32>(dp.q[1], stat_addr);                                       \
     lds_read16_at<SO + (QT) * 128 + 256 + 64>(dp.q[2], stat_addr);                                       \
     lds_read16_at<SO + (QT) * 128 + 256 + 96>(dp.q[3], stat_addr);                                       \
-    VD_ROW4(fq, 0, QT, SO)                                                                               \
-    VD_ROW4(fo, 1, QT, SO)              /* (12 reads on the way; the counter holds 15) */                \
-    __builtin_amdgcn_s_setprio(1);                                                                       \
-    wait_lds<7>(fq[0]); st = mfma(fq[0], kf[0], zero16());                                               \
-    wait_lds<6>(fq[1]); st = mfma(fq[1], kf[1], st);                                                     \
-    wait_lds<5>(fq[2]); st = mfma(fq[2], kf[2], st);                                                     \
-    wait_lds<4>(fq[3]); st = mfma(fq[3], kf[3], st);                                                     \
+    __builtin_amdgcn_s_setprio(1);              /* (12 reads on the way; the counter holds 15) */        \
+    wait_lds<7>(fq[0]); wait_acc<7>(st); st.f = mfma(fq[0], kf[0], st.f); VD_ROW1(fo, 0, 1, QT, SO)      \
+    wait_lds<7>(fq[1]); st.f = mfma(fq[1], kf[1], st.f); VD_ROW1(fo, 1, 1, QT, SO)                       \
+    wait_lds<7>(fq[2]); st.f = mfma(fq[2], kf[2], st.f); VD_ROW1(fo, 2, 1, QT, SO)                       \
+    wait_lds<7>(fq[3]); st.f = mfma(fq[3], kf[3], st.f); VD_ROW1(fo, 3, 1, QT, SO)                       \
     __builtin_amdgcn_sched_barrier(0);                                                                   \
-    /* log-sum-exp of the same queries */                                                                \
-    lds_read16_at<SO + (QT) * 128>(ls[0].q, stat_addr);                                                  \
-    lds_read16_at<SO + (QT) * 128 + 32>(ls[1].q, stat_addr);                                             \
-    lds_read16_at<SO + (QT) * 128 + 64>(ls[2].q, stat_addr);                                             \
-    lds_read16_at<SO + (QT) * 128 + 96>(ls[3].q, stat_addr);                                             \
-    wait_lds<7>(fo[0]); wait_acc<7>(dp); dp.f = mfma(fo[0], vf[0], dp.f);                                \
-    wait_lds<6>(fo[1]); dp.f = mfma(fo[1], vf[1], dp.f);                                                 \
-    wait_lds<5>(fo[2]); dp.f = mfma(fo[2], vf[2], dp.f);                                                 \
-    wait_lds<4>(fo[3]); dp.f = mfma(fo[3], vf[3], dp.f);                                                 \
+    wait_lds<3>(fo[0]); wait_acc<3>(dp); dp.f = mfma(fo[0], vf[0], dp.f);                                \
+    wait_lds<2>(fo[1]); dp.f = mfma(fo[1], vf[1], dp.f);                                                 \
+    wait_lds<1>(fo[2]); dp.f = mfma(fo[2], vf[2], dp.f);                                                 \
+    wait_lds<0>(fo[3]); dp.f = mfma(fo[3], vf[3], dp.f);                                                 \
     __builtin_amdgcn_s_setprio(0);                                                                       \
     __builtin_amdgcn_sched_barrier(0);                                                                   \
     VD_TR4(fo, 1, QT, SO)                       /* dO^T */                                               \
-    wait_lds<8>(ls[0], ls[1], ls[2], ls[3]);                                                             \
     _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                                     \
-      st[r] = fast_exp2(fmaf(st[r], c, __uint_as_float(ls[r >> 2].w[r & 3])));                           \
-      dp.f[r] *= st[r];                                                                                  \
+      st.f[r] = fast_exp2(st.f[r]);                                                                      \
+      dp.f[r] *= st.f[r];                                                                                \
     }                                                                                                    \
     if (tail) {                                 /* a query past the end repeats the last one: dropped */ \
       _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                                   \
         const int iq = i * 64 + (QT) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);                           \
-        st[r] = iq < n ? st[r] : 0.f;                                                                    \
+        st.f[r] = iq < n ? st.f[r] : 0.f;                                                                \
         dp.f[r] = iq < n ? dp.f[r] : 0.f;                                                                \
       }                                                                                                  \
     }                                                                                                    \
@@ -517,10 +531,10 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
     wait_lds_count<7>();                                                                                 \
     VD_TR4(fq, 0, QT, SO)                       /* Q^T */                                                \
     __builtin_amdgcn_s_setprio(1);                                                                       \
-    wait_lds<8>(fo[0]); accV[0] = mfma(fo[0], regs_to_frag(st, 0), accV[0]);                             \
-    wait_lds<8>(fo[1]); accV[1] = mfma(fo[1], regs_to_frag(st, 0), accV[1]);                             \
-    wait_lds<8>(fo[2]); accV[0] = mfma(fo[2], regs_to_frag(st, 1), accV[0]);                             \
-    wait_lds<8>(fo[3]); accV[1] = mfma(fo[3], regs_to_frag(st, 1), accV[1]);                             \
+    wait_lds<8>(fo[0]); accV[0] = mfma(fo[0], regs_to_frag(st.f, 0), accV[0]);                           \
+    wait_lds<8>(fo[1]); accV[1] = mfma(fo[1], regs_to_frag(st.f, 0), accV[1]);                           \
+    wait_lds<8>(fo[2]); accV[0] = mfma(fo[2], regs_to_frag(st.f, 1), accV[0]);                           \
+    wait_lds<8>(fo[3]); accV[1] = mfma(fo[3], regs_to_frag(st.f, 1), accV[1]);                           \
     wait_lds<6>(fq[0]); accK[0] = mfma(fq[0], regs_to_frag(dp.f, 0), accK[0]);                           \
     wait_lds<4>(fq[1]); accK[1] = mfma(fq[1], regs_to_frag(dp.f, 0), accK[1]);                           \
     wait_lds<2>(fq[2]); accK[0] = mfma(fq[2], regs_to_frag(dp.f, 1), accK[0]);                           \
@@ -537,8 +551,8 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
   if (kj < n) {
     bf16_t* rk = a.dk + base + (long long)kj * ld;
     bf16_t* rv = a.dv + base + (long long)kj * ld;
-    store_accT(rk, accK[0], 0, half, a.scale);
-    store_accT(rk, accK[1], 1, half, a.scale);
+    store_accT(rk, accK[0], 0, half, kLn2);
+    store_accT(rk, accK[1], 1, half, kLn2);
     store_accT(rv, accV[0], 0, half, 1.f);
     store_accT(rv, accV[1], 1, half, 1.f);
   }
@@ -764,7 +778,6 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
   __syncthreads();
 
   // ---- phase 1: lane = key; this wavefront's query tiles are 2*part and 2*part + 1
-  const float c = a.scale * kLog2e;
   const int kj = blk * 32 + col;
   floatx16 accK[2] = {zero16(), zero16()}, accV[2] = {zero16(), zero16()};
   {
@@ -787,7 +800,7 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         const int iq = qt * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-        const float p = kj < n ? fast_exp2(st[r] * c - Ls[iq]) : 0.f;      // Ls = +inf past the last query
+        const float p = kj < n ? fast_exp2(st[r] - Ls[iq]) : 0.f;      // Ls = +inf past the last query
         st[r] = p;
         dp[r] = p * (dp[r] - Ds[iq]);
       }
@@ -840,7 +853,7 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
       }
     if (kj < n) {
       bf16_t* row = (part == 0 ? a.dk : a.dv) + base + (long long)kj * ld;
-      const float mul = part == 0 ? a.scale : 1.f;
+      const float mul = part == 0 ? kLn2 : 1.f;
       store_accT(row, mine[0], 0, half, mul);
       store_accT(row, mine[1], 1, half, mul);
     }
@@ -906,7 +919,7 @@ struct FusedFwdArgs {
   bf16_t *q, *k, *v, *o;
   float* lse;
   int n, d, H;
-  float scale;
+  float q_mul;                    // what Q is multiplied by before it is rounded (kLog2e / sqrt(d_k))
   const int32_t* n_dev;           // device-side token count (then n is its bound, see vd_count)
   int32_t* status;
 };
@@ -1094,9 +1107,10 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
         bv[2] = __uint_as_float(b4.y << 16); bv[3] = __uint_as_float(b4.y & 0xffff0000u);
       }
       const int row = wr * 32 + col;
+      const float mul = z == 0 ? a.q_mul : 1.f;
       u32x2 o;
-      o.x = pack2(acc[j][4 * q4] + bv[0], acc[j][4 * q4 + 1] + bv[1]);
-      o.y = pack2(acc[j][4 * q4 + 2] + bv[2], acc[j][4 * q4 + 3] + bv[3]);
+      o.x = pack2((acc[j][4 * q4] + bv[0]) * mul, (acc[j][4 * q4 + 1] + bv[1]) * mul);
+      o.y = pack2((acc[j][4 * q4 + 2] + bv[2]) * mul, (acc[j][4 * q4 + 3] + bv[3]) * mul);
       *reinterpret_cast<u32x2*>(smem + z * kSmallTile + row * 128 + (((dim >> 3) ^ tile_swz(row)) * 16) + ((dim >> 2) & 1) * 8) = o;
     }
   }
@@ -1127,7 +1141,6 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
   Frag qf[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) qf[s] = small_row_frag(Qs, qi, 2 * s + half);
-  const float c = a.scale * kLog2e;
   floatx16 st[2];
   float m = -INFINITY;
 #pragma unroll
@@ -1141,7 +1154,7 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int j = kt * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-      st[k2][r] = j < n ? st[k2][r] * c : -INFINITY;
+      st[k2][r] = j < n ? st[k2][r] : -INFINITY;
       m = fmaxf(m, st[k2][r]);
     }
   }
@@ -1257,7 +1270,7 @@ size_t vd_attn_bf16_ws_bytes(int B, int n, int d, int H) {
   return vd_attn_bf16_partial_offset(B, n, d, H) + (size_t)4 * vd_attn_bf16_max_splitk(d, (long long)B * n) * d * d * sizeof(float);
 }
 
-// saved: q, k, v, o ([M][d] bf16 each, M = B*n) then lse fp32 [B][H][n]
+// saved: q (times log2(e) / sqrt(d_k)), k, v, o ([M][d] bf16 each, M = B*n) then lse fp32 [B][H][n]
 // With `sel` (device, n ascending rows of [0, N)), `xs` holds the tokens of all N variates and the kept ones are
 // gathered on the way: inside the fused kernel for short selections, by the gather kernel otherwise; either
 // way `xs_out` [B][n][d] receives them.
@@ -1293,7 +1306,7 @@ int vd_attn_fwd_bf16(vardrop_ctx* ctx, const void* xs, int B, int n, int d, int 
     f.Wq = (const bf16_t*)W[0]; f.Wk = (const bf16_t*)W[1]; f.Wv = (const bf16_t*)W[2];
     f.bq = (const bf16_t*)bias[0]; f.bk = (const bf16_t*)bias[1]; f.bv = (const bf16_t*)bias[2];
     f.q = q; f.k = k; f.v = v; f.o = o; f.lse = lse;
-    f.n = n; f.d = d; f.H = H; f.scale = 1.0f / sqrtf((float)kDh);
+    f.n = n; f.d = d; f.H = H; f.q_mul = kLog2e / sqrtf((float)kDh);
     f.n_dev = dn.dev; f.status = dn.status;
     static int configured_device = -1;
     if (configured_device != ctx->device) {
@@ -1311,12 +1324,13 @@ int vd_attn_fwd_bf16(vardrop_ctx* ctx, const void* xs, int B, int n, int d, int 
     for (int z = 0; z < 3; ++z) g.set(z, xs, W[z], qkv[z], bias[z]);
     g.lda = d; g.ldb = d; g.ldc = d;
     g.M = (int)M; g.N = d; g.K = d; g.nseg = 1;
+    g.c0_mul = kLog2e / sqrtf((float)kDh);
     if (dn.dev) g.count_rows(dn.dev, counted ? nullptr : dn.status, n, B);
     rc = vd_gemm_bf16(ctx, VARDROP_K_GEMM_QKV, g, 3, false, s);
     if (rc) return rc;
     SdpaArgs a = {};
     a.q = q; a.k = k; a.v = v; a.out = o; a.lse = lse;
-    a.n = n; a.d = d; a.H = H; a.B = B; a.scale = 1.0f / sqrtf((float)kDh);
+    a.n = n; a.d = d; a.H = H; a.B = B;
     a.n_dev = dn.dev;
     rc = launch_sdpa_fwd(ctx, a, s);
     if (rc) return rc;

@@ -332,6 +332,7 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
   // ---- epilogue.  acc[i][j] register 4*q4 + e is C[wm*MROWS + i*32 + col][wn*64 + j*32 + 8*q4 + 4*half + e]
   // of the tile; it is written to LDS (with the bias), then stored as 16-byte chunks of whole rows.
   const bf16_t* bias = SPLIT ? nullptr : (zsel == 0 ? g.bias0 : (zsel == 1 ? g.bias1 : (zsel == 2 ? g.bias2 : g.bias3)));
+  const float cmul = !SPLIT && zsel == 0 && g.c0_mul != 0.f ? g.c0_mul : 1.f;
   __syncthreads();                        // every wavefront is done reading the last slice
   if constexpr (KH) {
     // the upper K half hands its sums over through LDS; the lower half adds them to its own (lower + upper)
@@ -377,8 +378,8 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
           *reinterpret_cast<float4*>(p) = o;
         } else {
           u32x2 o;
-          o.x = pack2(acc[i][j][4 * q4] + bv[0], acc[i][j][4 * q4 + 1] + bv[1]);
-          o.y = pack2(acc[i][j][4 * q4 + 2] + bv[2], acc[i][j][4 * q4 + 3] + bv[3]);
+          o.x = pack2((acc[i][j][4 * q4] + bv[0]) * cmul, (acc[i][j][4 * q4 + 1] + bv[1]) * cmul);
+          o.y = pack2((acc[i][j][4 * q4 + 2] + bv[2]) * cmul, (acc[i][j][4 * q4 + 3] + bv[3]) * cmul);
           *reinterpret_cast<u32x2*>(p) = o;
         }
       }
