@@ -74,7 +74,7 @@ constexpr float kSumMax = 8192.f;               // a sum of 32 unnormalised prob
 
 // Copies rows [j0, j0 + 64) of two head slices into a stage; a wavefront-wide copy fills 8 token rows and rows past n
 // repeat row n-1.  `off` holds this lane's byte offsets of its share of a whole block, so that a copy costs no vector
-// instruction but itself (the address is a scalar base plus the offset); only the last block computes clamped ones.
+// instruction but itself (the block's offset is a scalar of it); only the last block computes clamped ones.
 // the lane, read afresh: what is derived from it is not kept in registers over the loop before
 __device__ __forceinline__ int fresh_lane() {
   int lane;
@@ -96,15 +96,14 @@ __device__ inline RingSrc<NW> ring_src(long long ld, int wave, int lane) {
   return r;
 }
 template <int NW>
-__device__ inline void ring_issue(const bf16_t* p0, const bf16_t* p1, const RingSrc<NW>& src, long long ld, int j0, int n,
+__device__ inline void ring_issue(copy_src p0, copy_src p1, const RingSrc<NW>& src, long long ld, int j0, int n,
                                   unsigned char* stage, int wave, int lane) {
   if (j0 + 64 <= n) {
-    const bf16_t* s0 = p0 + (long long)j0 * ld;
-    const bf16_t* s1 = p1 + (long long)j0 * ld;
+    const uint32_t at = (uint32_t)(j0 * (int)ld) * 2u;
 #pragma unroll
     for (int u = 0; u < 8 / NW; ++u) {
-      dma16_at(s0, src.off[u], stage + (u * NW + wave) * 1024);
-      dma16_at(s1, src.off[u], stage + kRingTile + (u * NW + wave) * 1024);
+      dma16_buf(p0, src.off[u], at, stage + (u * NW + wave) * 1024);
+      dma16_buf(p1, src.off[u], at, stage + kRingTile + (u * NW + wave) * 1024);
     }
   } else {
     lane = fresh_lane();
@@ -112,8 +111,8 @@ __device__ inline void ring_issue(const bf16_t* p0, const bf16_t* p1, const Ring
     for (int u = 0; u < 8 / NW; ++u) {
       const int row = (u * NW + wave) * 8 + (lane >> 3);
       const uint32_t off = (uint32_t)(min(j0 + row, n - 1) * (int)ld + ((lane & 7) ^ tile_swz(row)) * 8) * 2u;
-      dma16_at(p0, off, stage + (u * NW + wave) * 1024);
-      dma16_at(p1, off, stage + kRingTile + (u * NW + wave) * 1024);
+      dma16_buf(p0, off, 0, stage + (u * NW + wave) * 1024);
+      dma16_buf(p1, off, 0, stage + kRingTile + (u * NW + wave) * 1024);
     }
   }
 }
@@ -205,8 +204,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
   const int n = a.n;
   const long long ld = a.d;
   const long long base = (long long)b * n * ld + h * kDh;
-  const bf16_t* kp = a.k + base;
-  const bf16_t* vp = a.v + base;
+  const copy_src kp = copy_source(a.k + base), vp = copy_source(a.v + base);
   int qi = (qb * NW + wave) * 32 + col;
   const int nb = (n + 63) >> 6;
   const RingSrc<NW> src = ring_src<NW>(ld, wave, lane);
@@ -358,8 +356,7 @@ __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int 
   const long long ld = a.d;
   const long long base = (long long)b * n * ld + h * kDh;
   const long long srow = ((long long)b * a.H + h) * n;
-  const bf16_t* kp = a.k + base;
-  const bf16_t* vp = a.v + base;
+  const copy_src kp = copy_source(a.k + base), vp = copy_source(a.v + base);
   const int qi = (qb * NW + wave) * 32 + col;
   const int nb = (n + 63) >> 6;
   const RingSrc<NW> src = ring_src<NW>(ld, wave, lane);
@@ -459,21 +456,20 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
   const long long ld = a.d;
   const long long base = (long long)b * n * ld + h * kDh;
   const long long srow = ((long long)b * a.H + h) * n;
-  const bf16_t* qp = a.q + base;
-  const bf16_t* op = a.dout + base;
+  const copy_src qp = copy_source(a.q + base), op = copy_source(a.dout + base);
   const int kj = (kb * NW + wave) * 32 + col;
   const int nb = (n + 63) >> 6;
   const RingSrc<NW> src = ring_src<NW>(ld, wave, lane);
   // even wavefronts copy the block's -log2(e) * log-sum-exp values, odd ones its -D (NW is even); queries past n
   // repeat the last
-  const float* stat = (wave & 1) ? a.Dsum + srow : a.nlse2 + srow;
+  const copy_src stat = copy_source((const bf16_t*)((wave & 1) ? a.Dsum + srow : a.nlse2 + srow));
   const int stat_off = 2 * kRingTile + (wave & 1) * 256;
 #define VD_ISSUE_Q(J, BUF)                                                                            \
   {                                                                                                   \
     unsigned char* sp = smem + (BUF) * kRingStage;                                                    \
     ring_issue<NW>(qp, op, src, ld, (J) * 64, n, sp, wave, lane);                                     \
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(stat + min((J) * 64 + lane, n - 1)), \
-                                     (__attribute__((address_space(3))) void*)(sp + stat_off), 4, 0, 0); \
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(stat, (__attribute__((address_space(3))) void*)(sp + stat_off), 4,  \
+                                             min((J) * 64 + lane, n - 1) * 4, 0, 0, 0);               \
   }
   VD_ISSUE_Q(0, 0)
   if (nb > 1) VD_ISSUE_Q(1, 1)
@@ -660,14 +656,15 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
     constexpr int NS = kBwdStages, STAGE = kBwdStage, A_BYTES = kSmallN * 64 * 2, LPS = 3;
     unsigned char* ring = dSt;
     const bf16_t* dy_b = a.dy + (long long)b * n * ld;
-    const bf16_t* srcA[2];
+    const copy_src srcA = copy_source(dy_b), srcB = copy_source(a.wo + (long long)h * kDh * ld);
+    uint32_t offA[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
       const int row = (u * 8 + wave) * 8 + (lane >> 3);
-      srcA[u] = dy_b + (long long)min(row, n - 1) * ld + (((lane & 7) ^ tile_swz(row)) * 8);
+      offA[u] = (uint32_t)(min(row, n - 1) * a.d + (((lane & 7) ^ tile_swz(row)) * 8)) * 2u;
     }
     const int rowB = wave * 8 + (lane >> 3);
-    const bf16_t* srcB = a.wo + (long long)(h * kDh + rowB) * ld + (((lane & 7) ^ tile_swz(rowB)) * 8);
+    const uint32_t offB = (uint32_t)(rowB * a.d + (((lane & 7) ^ tile_swz(rowB)) * 8)) * 2u;
     const uint32_t ring0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)ring;
     uint32_t addrA[4], addrB[4];
     {
@@ -684,9 +681,9 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
 #define VD_ISSUE(BUF)                                                                               \
   {                                                                                                \
     unsigned char* sp = ring + (BUF) * STAGE + wave * 1024;                                        \
-    dma16(srcA[0] + fk * 64, sp);                                                                  \
-    dma16(srcA[1] + fk * 64, sp + 8192);                                                           \
-    dma16(srcB + fk * 64, sp + A_BYTES);                                                           \
+    dma16_buf(srcA, offA[0], fk * 128, sp);                                                            \
+    dma16_buf(srcA, offA[1], fk * 128, sp + 8192);                                                     \
+    dma16_buf(srcB, offB, fk * 128, sp + A_BYTES);                                                     \
     ++fk;                                                                                          \
   }
     VD_ISSUE(0)                         // the first slice goes ahead of the tile copies: the product starts on it
@@ -951,19 +948,15 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
   // them: the weight copies of the first slice go out first.  The indices are requested together with the count,
   // at positions clamped by the bound of the count (the caller's `sel` is readable that far); the entries at and
   // past the count are replaced once it is known.
-  const bf16_t* srcB[3];
-#pragma unroll
-  for (int u = 0; u < 3; ++u) {
-    const bf16_t* Wz = u == 0 ? a.Wq : (u == 1 ? a.Wk : a.Wv);
-    const int krow = wave * 8 + (lane >> 3);
-    srcB[u] = Wz + (long long)krow * ld + h * kDh + (((lane & 7) ^ swz_nc<64>(krow)) * 8);
-  }
+  const copy_src srcB[3] = {copy_source(a.Wq + h * kDh), copy_source(a.Wk + h * kDh), copy_source(a.Wv + h * kDh)};
+  const int krowB = wave * 8 + (lane >> 3);
+  const uint32_t offB = (uint32_t)(krowB * d + (((lane & 7) ^ swz_nc<64>(krowB)) * 8)) * 2u;
   int fk = 0;        // slice whose copies are issued next
 #define VD_ISSUE_W(BUF)                                                                             \
   {                                                                                                \
     unsigned char* sp = smem + (BUF) * STAGE + wave * 1024;                                        \
     _Pragma("unroll") for (int u = 0; u < 3; ++u)                                                  \
-      dma16(srcB[u] + (long long)fk * 64 * ld, sp + A_BYTES + u * BT);                             \
+      dma16_buf(srcB[u], offB, (uint32_t)(fk * d) * 128u, sp + A_BYTES + u * BT);                   \
   }
   VD_ISSUE_W(0)
   const int own_row = (wave & 3) * 32 + (lane & 31);         // the token this lane owns in the product below
@@ -983,7 +976,8 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
 
   // ---- copy sources of the token rows.  Copy u covers token rows 8*(8u + wave) .. +7; rows past the count stand
   // for the first token (any real token: they only have to be finite, every use of them is masked).
-  const bf16_t* srcA[2];
+  const copy_src srcA = copy_source(xs_b);
+  uint32_t offA[2];
   u32x4 kept[2];                  // this thread's 16 bytes of two gathered rows, columns of head h
   int src_row[2];                 // requested here, used after the first weight copies have been issued
   bool src_ok[2] = {true, true};  // an index outside [0, N) reads row 0 and stands for a zero row, as in the gather kernel
@@ -1020,14 +1014,14 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
 #define VD_ISSUE_X(BUF)                                                                             \
   {                                                                                                \
     unsigned char* sp = smem + (BUF) * STAGE + wave * 1024;                                        \
-    _Pragma("unroll") for (int u = 0; u < 2; ++u) dma16(srcA[u] + fk * 64, sp + u * 8192);         \
+    _Pragma("unroll") for (int u = 0; u < 2; ++u) dma16_buf(srcA, offA[u], fk * 128, sp + u * 8192);\
     ++fk;                                                                                          \
   }
 #define VD_ISSUE(BUF) { VD_ISSUE_W(BUF) VD_ISSUE_X(BUF) }
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     const int row = (u * 8 + wave) * 8 + (lane >> 3);
-    srcA[u] = xs_b + (long long)src_row[u] * ld + (((lane & 7) ^ tile_swz(row)) * 8);
+    offA[u] = (uint32_t)(src_row[u] * d + (((lane & 7) ^ tile_swz(row)) * 8)) * 2u;
   }
   VD_ISSUE_X(0)
 #pragma unroll

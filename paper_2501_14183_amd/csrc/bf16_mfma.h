@@ -63,10 +63,16 @@ __device__ inline void dma16(const bf16_t* gp, unsigned char* lp) {
   __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)gp,
                                    (__attribute__((address_space(3))) void*)lp, 16, 0, 0);
 }
-// the same from a uniform base plus a byte offset per lane (the copy's own addressing: no address arithmetic per copy)
-__device__ inline void dma16_at(const bf16_t* base, uint32_t off, unsigned char* lp) {
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((const char*)base + off),
-                                   (__attribute__((address_space(3))) void*)lp, 16, 0, 0);
+// The same through a buffer descriptor: descriptor and slice offset are scalars by the form of the instruction.  Use it
+// beside matrix instructions: with a 64-bit address per lane (what the compiler makes of a pointer that moves in a loop) a
+// copy takes two slots while 32 x 32 matrix instructions run on its SIMD, 32 instead of 64 bytes per clock and compute unit
+// (measured with nothing but the two kinds of instruction).
+typedef __amdgpu_buffer_rsrc_t copy_src;
+__device__ inline copy_src copy_source(const bf16_t* p) {
+  return __builtin_amdgcn_make_buffer_rsrc((void*)p, 0, 0xffffffff, 0x00020000);
+}
+__device__ inline void dma16_buf(copy_src src, uint32_t lane_off, uint32_t slice_off, unsigned char* lp) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(src, (__attribute__((address_space(3))) void*)lp, 16, lane_off, slice_off, 0, 0);
 }
 __device__ inline void lds_read16(u32x4& dst, uint32_t addr) {
   asm volatile("ds_read_b128 %0, %1" : "=v"(dst) : "v"(addr) : "memory");

@@ -154,33 +154,38 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
   // (about 32 bytes per clock), four reach the pipeline's 64-74.
   const bool producer = wave >= 4;
   const int w4 = wave & 3;
-  // source offsets (elements) of this copy wavefront's share: copy u fills LDS bytes [1024 (4 u + w4), + 1024) of the operand
-  //   k-contiguous: clamped row * ld + chunk * 8, the slice start is added per stage
-  //   mn-contiguous: column offset; the k-row krowX + u * 4 * RPx is clamped per stage
+  // Source offsets (bytes) of this copy wavefront's share from a scalar base that moves with the slice: copy u fills LDS
+  // bytes [1024 (4 u + w4), + 1024) of the operand
+  //   k-contiguous: clamped row * ld + chunk * 8
+  //   mn-contiguous: k-row (krowX + u * 4 * RPx) * ld + column; only in a slice that reaches past kend the k-row is clamped
+  // (scalar slice offset and 32-bit lane offsets: see dma16_buf; with 64-bit addresses the copies bounded every tile)
   static_assert((NS - 2) * LPS < 64, "the copy counter holds at most 63");
-  int goffA[IA], goffB[IB];
+  uint32_t goffA[IA], goffB[IB];
+  uint32_t coffA[AKC ? 1 : IA], coffB[BKC ? 1 : IB];              // the column's part of it (mn-contiguous)
   int krowA = 0, krowB = 0;
   if (producer) {
 #pragma unroll
     for (int u = 0; u < IA; ++u) {
       if constexpr (AKC) {
         const int row = (u * 4 + w4) * RPI + lane / CH;
-        goffA[u] = min(m0 + row, dm.M - 1) * g.lda + ((lane % CH) ^ swz_kc<BK>(row)) * 8;
+        goffA[u] = (uint32_t)(min(m0 + row, dm.M - 1) * g.lda + ((lane % CH) ^ swz_kc<BK>(row)) * 8) * 2u;
       } else {
         const int krow = (u * 4 + w4) * RPA + lane / CHA;
         if (u == 0) krowA = krow;
-        goffA[u] = min(m0 + ((lane % CHA) ^ swz_nc<BM>(krow)) * 8, dm.M - 8);
+        coffA[u] = (uint32_t)min(m0 + ((lane % CHA) ^ swz_nc<BM>(krow)) * 8, dm.M - 8) * 2u;
+        goffA[u] = (uint32_t)(krow * g.lda) * 2u + coffA[u];
       }
     }
 #pragma unroll
     for (int u = 0; u < IB; ++u) {
       if constexpr (BKC) {
         const int row = (u * 4 + w4) * RPI + lane / CH;
-        goffB[u] = min(n0 + row, g.N - 1) * g.ldb + ((lane % CH) ^ swz_kc<BK>(row)) * 8;
+        goffB[u] = (uint32_t)(min(n0 + row, g.N - 1) * g.ldb + ((lane % CH) ^ swz_kc<BK>(row)) * 8) * 2u;
       } else {
         const int krow = (u * 4 + w4) * RPB + lane / CHB;
         if (u == 0) krowB = krow;
-        goffB[u] = min(n0 + ((lane % CHB) ^ swz_nc<BN>(krow)) * 8, g.N - 8);
+        coffB[u] = (uint32_t)min(n0 + ((lane % CHB) ^ swz_nc<BN>(krow)) * 8, g.N - 8) * 2u;
+        goffB[u] = (uint32_t)(krow * g.ldb) * 2u + coffB[u];
       }
     }
   }
@@ -221,29 +226,31 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
 
   // ---- copy cursor (copy wavefront)
   int fseg = 0, fk = kbeg;
-  const bf16_t* Ap = A0;
-  const bf16_t* Bp = B0;
+  copy_src Ap = copy_source(A0), Bp = copy_source(B0);
 #define VD_ISSUE_STAGE(BUF)                                                                        \
   {                                                                                                \
     unsigned char* sp = smem + (BUF) * STAGE + w4 * 1024;                                          \
-    _Pragma("unroll") for (int u = 0; u < IA; ++u) {                                               \
-      const bf16_t* p;                                                                             \
-      if constexpr (AKC) p = Ap + fk + goffA[u];                                                   \
-      else p = Ap + (long long)min(fk + krowA + u * 4 * RPA, kend - 1) * g.lda + goffA[u];         \
-      dma16(p, sp + u * 4096);                                                                     \
-    }                                                                                              \
-    _Pragma("unroll") for (int u = 0; u < IB; ++u) {                                               \
-      const bf16_t* p;                                                                             \
-      if constexpr (BKC) p = Bp + fk + goffB[u];                                                   \
-      else p = Bp + (long long)min(fk + krowB + u * 4 * RPB, kend - 1) * g.ldb + goffB[u];         \
-      dma16(p, sp + A_BYTES + u * 4096);                                                           \
+    const uint32_t sa = (uint32_t)(AKC ? fk : fk * g.lda) * 2u, sb = (uint32_t)(BKC ? fk : fk * g.ldb) * 2u;\
+    if ((AKC && BKC) || fk + BK <= kend) {                                                         \
+      _Pragma("unroll") for (int u = 0; u < IA; ++u) dma16_buf(Ap, goffA[u], sa, sp + u * 4096);   \
+      _Pragma("unroll") for (int u = 0; u < IB; ++u) dma16_buf(Bp, goffB[u], sb, sp + A_BYTES + u * 4096);\
+    } else {                                                                                       \
+      const int last = kend - 1 - fk;                                                              \
+      _Pragma("unroll") for (int u = 0; u < IA; ++u) {                                             \
+        if constexpr (AKC) dma16_buf(Ap, goffA[u], sa, sp + u * 4096);                             \
+        else dma16_buf(Ap, (uint32_t)(min(krowA + u * 4 * RPA, last) * g.lda) * 2u + coffA[u], sa, sp + u * 4096);\
+      }                                                                                            \
+      _Pragma("unroll") for (int u = 0; u < IB; ++u) {                                             \
+        if constexpr (BKC) dma16_buf(Bp, goffB[u], sb, sp + A_BYTES + u * 4096);                   \
+        else dma16_buf(Bp, (uint32_t)(min(krowB + u * 4 * RPB, last) * g.ldb) * 2u + coffB[u], sb, sp + A_BYTES + u * 4096);\
+      }                                                                                            \
     }                                                                                              \
     fk += BK;                                                                                      \
     if (fk >= kend) {                                                                              \
       fk = kbeg;                                                                                   \
       ++fseg;                                                                                      \
-      Ap = fseg == 1 ? A1 : A2;                                                                    \
-      Bp = fseg == 1 ? B1 : B2;                                                                    \
+      Ap = copy_source(fseg == 1 ? A1 : A2);                                                       \
+      Bp = copy_source(fseg == 1 ? B1 : B2);                                                       \
     }                                                                                              \
   }
   if (producer) {
