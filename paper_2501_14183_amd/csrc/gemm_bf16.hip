@@ -502,8 +502,7 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_async_kernel(GemmBf16 g,
 }
 // The input gradient (gx: k-contiguous operands, up to three accumulated segments) and the weight
 // gradients (gw: mn-contiguous operands, K slices, fp32 partial products) depend on the same dQ, dK,
-// dV and on nothing of each other, so they share one launch: workgroups [0, nx) take tiles of gx,
-// the rest tiles of gw.  The longer-running input-gradient tiles are dispatched first.
+// dV and on nothing of each other, so they share one launch.
 // Tile shapes of the two kinds of workgroup: rows, k per copy stage, stages (BN = 128 always).
 template <int BMX_, int BKX_, int NSX_, int BMW_, int BKW_, int NSW_, bool KHW_ = false>
 struct PairCfg {
@@ -515,14 +514,18 @@ struct PairCfg {
 // few tokens: 128-row input-gradient tiles beside 64-row weight-gradient tiles (wavefronts in K halves), both on
 // three 64-k stages (96 KB of LDS; with two stages an input-gradient tile waits 1000 of 1700 clocks per slice for
 // its copies), one slice;
-// many tokens: 128-row tiles on four 32-k stages for both (64 KB)
+// many tokens: 128-row tiles for both, input gradients on two 64-k stages (whole 128-byte lines of their k-contiguous rows;
+// on four 32-k stages 174 -> 161 us at 15 400 rows of 768, 34.2 -> 30.6 at 6080 of 512), weight gradients on four 32-k stages
+// (two of 64 k: 168 us) (64 KB); three or four 64-k stages leave one workgroup a compute unit: 192 us
 typedef PairCfg<128, 64, 3, 64, 64, 3, true> PairSmall;
-typedef PairCfg<128, 32, 4, 128, 32, 4> PairLarge;
+typedef PairCfg<128, 64, 2, 128, 32, 4> PairLarge;
 template <typename CFG>
 __global__ __launch_bounds__(kGemmThreads, 2) void gemm_bwd_pair_kernel(GemmBf16 gx, GemmBf16 gw, int nzw) {
   // Each die takes a contiguous range of the input-gradient tiles (n fastest: a range shares its rows
   // of dQ, dK, dV) and a contiguous range of the weight-gradient tiles (n, then m, then K slice, then
-  // matrix: a range shares its K slice of both operands); its input-gradient tiles come first.
+  // matrix: a range shares its K slice of both operands).  The kind whose tiles walk over more K comes first, so that a late
+  // start never meets a long tile (with the input gradient always first, at 15 400 rows of 768 its 726 tiles of 36 slices held
+  // up the 288 weight-gradient tiles of 120: 161 us, 127 this way).
   GemmDims dx, dw;
   const bool has_x = gemm_resolve(gx, dx);
   if (!gemm_resolve(gw, dw)) return;          // (an invalid count; with no tokens only the weight-gradient tiles run)
@@ -532,13 +535,14 @@ __global__ __launch_bounds__(kGemmThreads, 2) void gemm_bwd_pair_kernel(GemmBf16
   const int nx = gxn * ((dx.M + BMX - 1) / BMX), nw = gwn * gwm * nzw * dw.splitk;
   if ((int)blockIdx.x >= nx + nw) return;
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int cntx = (nx >> 3) + (xcd < (nx & 7) ? 1 : 0);
-  const int startx = xcd_range_start(xcd, nx);
-  if (slot < cntx) {
-    const int t = startx + slot;
+  const bool w_first = dw.kchunk > 3 * gx.K;
+  const int n1 = w_first ? nw : nx;
+  const int cnt1 = (n1 >> 3) + (xcd < (n1 & 7) ? 1 : 0), start1 = xcd_range_start(xcd, n1);
+  const bool first = slot < cnt1;
+  const int t = first ? start1 + slot : xcd_range_start(xcd, nx + nw) - start1 + (slot - cnt1);
+  if (first != w_first) {
     gemm_async_tile<true, true, false, BMX, CFG::BKX, CFG::NSX>(gx, dx, t % gxn, t / gxn, 0);
   } else {
-    const int t = xcd_range_start(xcd, nx + nw) - startx + (slot - cntx);
     gemm_async_tile<false, false, true, BMW, CFG::BKW, CFG::NSW, CFG::KHW>(gw, dw, t % gwn, (t / gwn) % gwm, t / (gwn * gwm));
   }
 }
