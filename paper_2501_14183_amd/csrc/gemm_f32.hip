@@ -1,11 +1,23 @@
-// fp32 GEMMs on v_mfma_f32_32x32x2_f32 (fp32 operands, fp32 accumulation).
+// fp32 GEMMs: fp32 operands, results and accumulation; the products are formed on the bf16 matrix instruction where K is long.
 //
-// Bound by the fp32 matrix rate (157 TFLOP/s: one 32 x 32 x 2 instruction per 64 clocks and SIMD).  At 16 operand bytes
-// per clock and compute unit a 64 x 64 tile asks far less of L2 and LDS than they give, so the tile is small for the sake of many
-// workgroups (a selection of a few thousand token rows is 400 tiles), four wavefronts of one 32 x 32 block each.
-// Global memory goes through registers into two LDS buffers of 32 k each: edges and unaligned rows are handled there
-// with zeros, so the inner loop has no masks; loads are issued two slices ahead, one barrier per slice (1024 matrix clocks).
-// The plain multiply-add kernel this replaced ran at 4-8 TFLOP/s (K = 3328, 512 x 512: 394 us a matrix).
+// v_mfma_f32_32x32x2_f32 has a sixteenth of the bf16 rate and bounded these products (83-90 of its 157 TFLOP/s).  An fp32
+// number is exactly the sum of three bf16 numbers (hi, mid, lo: 8 bits of the significand each, cut off, not rounded), and
+// every product of two of those is exact in fp32.  Six of the nine products are formed, the other three lie 2^-24 and
+// more below the full one: hi hi, which has accumulators of its own, and hi mid, mid hi, mid mid, hi lo, lo hi in a second set,
+// added at the end.  Per 16 k the large sums are rounded once instead of eight times, so the result is closer to the exact
+// one than the fp32 instruction's: 1.4e-7 of the result's norm against 4.0e-7 for 3392 x 512 x 512, 2.4e-7 against 6.1e-7
+// with K = 3392, and two to three times closer in every output of an attention layer.
+// The split needs finite operands (inf - inf): a tile with a result that is not finite is computed once more with the fp32
+// instruction, so infinities and NaN come out as they did.
+//
+// Tiles of 64 x 64, four wavefronts of one 32 x 32 block each, for the sake of many workgroups (a selection of a few thousand
+// token rows is 400 tiles).  What bounds it: a slice of 32 k costs the LDS 24 KB of writes at 80 bytes a clock and 48 KB of
+// reads at 256 (500 clocks, one after the other), a SIMD 384 clocks of matrix instructions and 88 vector instructions of
+// splitting; three workgroups share a compute unit and reach 1080 clocks a slice.  3328 x 512 x 1536: 62 -> 48 us, the
+// gradient launch of the same layer 141 -> 100 us.  Tried: one LDS buffer and four workgroups 47 and 107; fp32 by
+// asynchronous copies, split behind the LDS read by every wavefront for itself 53 and 116 (128 x 64 tiles: 61 and 115).
+// Global memory goes through registers, where it is split, into two LDS buffers of 32 k: edges and unaligned rows are
+// handled there with zeros, so the inner loop has no masks; loads are issued two slices ahead, one barrier per slice.
 #include "bf16_mfma.h"
 #include "gemm_f32.h"
 
@@ -14,7 +26,9 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kT = 64, kK = 32;              // tile edge, k per LDS buffer
-constexpr int kOperand = kT * kK * 4;        // bytes of one operand in one buffer
+constexpr int kOperand = kT * kK * 4;        // bytes of one fp32 operand in one buffer
+constexpr int kPlane = kT * kK * 2;          // bytes of one bf16 part of an operand in one buffer
+constexpr int kLds = 2 * 2 * 3 * kPlane;     // two buffers of two operands in three parts
 
 template <typename T>
 __device__ inline T pick(int z, T p0, T p1, T p2, T p3) { return z == 0 ? p0 : (z == 1 ? p1 : (z == 2 ? p2 : p3)); }
@@ -71,6 +85,67 @@ __device__ inline void fetch(f32x4 (&v)[2], uint32_t& in_bits, const float* __re
     }
   }
 }
+// The same for a slice that lies inside [0, kend) (VEC): a scalar base that moves with the slice plus an offset per thread that
+// does not.  Rows or columns past the end repeat the last ones; their results are not stored.
+template <bool KC>
+__device__ inline void unit_offsets(uint32_t (&off)[2], int ld, int r0, int rows) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int i = u * 256 + threadIdx.x;
+    off[u] = KC ? (uint32_t)(min(i >> 3, rows - 1 - r0) * ld + 4 * (i & 7)) * 4u : (uint32_t)((i >> 4) * ld + min(4 * (i & 15), rows - 4 - r0)) * 4u;
+  }
+}
+template <bool KC>
+__device__ inline void fetch_inside(f32x4 (&v)[2], const float* __restrict__ P, int ld, int r0, int k0, const uint32_t (&off)[2]) {
+  const char* base = reinterpret_cast<const char*>(P + (KC ? (long long)r0 * ld + k0 : (long long)k0 * ld + r0));
+#pragma unroll
+  for (int u = 0; u < 2; ++u) v[u] = *reinterpret_cast<const f32x4*>(base + off[u]);
+}
+// The three bf16 parts of a unit (four fp32 values) as 8 bytes each, to the planes of the operand.
+//   KC: plane [64 rows][32 k], 64-byte rows, 16-byte chunk position XORed with swz_kc<32>(row)
+//   otherwise: plane [32 k][64], 128-byte rows, chunk position XORed with swz_nc<64>(k)
+template <bool KC>
+__device__ inline void put_split(unsigned char* lds, const f32x4 (&v)[2]) {
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int i = u * 256 + threadIdx.x;
+    const int c = KC ? i & 7 : i & 15, row = KC ? i >> 3 : i >> 4;
+    const int addr = row * (KC ? 64 : 128) + (((c >> 1) ^ (KC ? swz_kc<kK>(row) : swz_nc<kT>(row))) * 16) + (c & 1) * 8;
+    uint32_t h[4], m[4], l[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float x = v[u][e];
+      h[e] = __float_as_uint(x);
+      const float r1 = x - __uint_as_float(h[e] & 0xffff0000u);      // exact: the lower 16 bits of the significand
+      m[e] = __float_as_uint(r1);
+      l[e] = __float_as_uint(r1 - __uint_as_float(m[e] & 0xffff0000u));   // exact, at most 8 bits
+    }
+    const uint32_t up = 0x07060302u;                                  // the upper halves of two words
+    *reinterpret_cast<u32x2*>(lds + addr) = u32x2{__builtin_amdgcn_perm(h[1], h[0], up), __builtin_amdgcn_perm(h[3], h[2], up)};
+    *reinterpret_cast<u32x2*>(lds + kPlane + addr) = u32x2{__builtin_amdgcn_perm(m[1], m[0], up), __builtin_amdgcn_perm(m[3], m[2], up)};
+    *reinterpret_cast<u32x2*>(lds + 2 * kPlane + addr) = u32x2{__builtin_amdgcn_perm(l[1], l[0], up), __builtin_amdgcn_perm(l[3], l[2], up)};
+  }
+}
+// k = 16 ks + 8 half + 0..7 of row / column mn0 + lane % 32 of a plane
+template <bool KC>
+__device__ inline Frag frag_split(const unsigned char* plane, int mn0, int ks, int lane) {
+  Frag f;
+  const int half = lane >> 5;
+  if constexpr (KC) {
+    const int row = mn0 + (lane & 31);
+    f.q = *reinterpret_cast<const u32x4*>(plane + row * 64 + (((2 * ks + half) ^ swz_kc<kK>(row)) * 16));
+  } else {
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    const int mn = mn0 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+#pragma unroll
+    for (int rd = 0; rd < 2; ++rd) {
+      const int k = 16 * ks + 8 * half + 4 * rd + ((lane & 15) >> 2);
+      const unsigned char* p = plane + k * 128 + (((mn >> 3) ^ swz_nc<kT>(k)) * 16) + ((mn >> 2) & 1) * 8;
+      f.d[rd] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p));
+    }
+  }
+  return f;
+}
 template <bool KC, bool VEC>
 __device__ inline void put(unsigned char* lds, const f32x4 (&v)[2], uint32_t in_bits) {
 #pragma unroll
@@ -99,8 +174,10 @@ __device__ inline f32x4 frag(const unsigned char* lds, int mn, int g, int half) 
   }
 }
 
-template <bool AKC, bool BKC, bool VEC>
-__device__ __forceinline__ void gemm_f32_tile(const GemmF32& g, const DimsF32& dm, int bx, int by, int bz, unsigned char* smem) {
+// One tile of the product in `acc`: by bf16 parts (SPLIT), or with the fp32 instruction.
+template <bool AKC, bool BKC, bool VEC, bool SPLIT>
+__device__ __forceinline__ floatx16 gemm_f32_sum(const GemmF32& g, const DimsF32& dm, int bx, int by, int bz, unsigned char* smem) {
+  static_assert(VEC || !SPLIT, "by parts: aligned rows");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 1, wn = wave & 1, col = lane & 31, half = lane >> 5;
   const int z = bz / dm.splitk, slice = bz - z * dm.splitk;
@@ -114,14 +191,32 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32& g, const DimsF32& d
   const float* A0 = pick(z, g.A0, A1, A2, g.A3);
   const float* B0 = pick(z, g.B0, B1, B2, g.B3);
   const int lda = g.lda, ldb = g.ldb, M = dm.M, N = g.N;
-  floatx16 acc = zero16();
+  floatx16 acc = zero16(), low = zero16();     // low: the products of smaller parts
+  constexpr int operand = SPLIT ? 3 * kPlane : kOperand;
   f32x4 ra[2][2], rb[2][2];
   uint32_t ia[2], ib[2];
   int fk = kbeg, fseg = 0;                     // fetch cursor
   const float *Ap = A0, *Bp = B0;
+  uint32_t offa[2], offb[2];
+  if constexpr (SPLIT) {
+    unit_offsets<AKC>(offa, lda, m0, M);
+    unit_offsets<BKC>(offb, ldb, n0, N);
+  }
   auto load = [&](int s) {
-    fetch<AKC, VEC>(ra[s], ia[s], Ap, lda, m0, M, fk, kend);
-    fetch<BKC, VEC>(rb[s], ib[s], Bp, ldb, n0, N, fk, kend);
+    if (SPLIT && fk + kK <= kend) {
+      fetch_inside<AKC>(ra[s], Ap, lda, m0, fk, offa);
+      fetch_inside<BKC>(rb[s], Bp, ldb, n0, fk, offb);
+    } else {
+      fetch<AKC, VEC>(ra[s], ia[s], Ap, lda, m0, M, fk, kend);
+      fetch<BKC, VEC>(rb[s], ib[s], Bp, ldb, n0, N, fk, kend);
+      if constexpr (SPLIT) {                   // (the last slice of a K that is not a multiple of 32)
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          if (!((ia[s] >> u) & 1u)) ra[s][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+          if (!((ib[s] >> u) & 1u)) rb[s][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+      }
+    }
     fk += kK;
     if (fk >= kend && fseg + 1 < nseg) {       // (past the last slice: everything is outside and becomes zeros)
       fk = kbeg;
@@ -131,12 +226,35 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32& g, const DimsF32& d
     }
   };
   auto store = [&](int s) {
-    put<AKC, VEC>(smem + s * 2 * kOperand, ra[s], ia[s]);
-    put<BKC, VEC>(smem + s * 2 * kOperand + kOperand, rb[s], ib[s]);
+    if constexpr (SPLIT) {
+      put_split<AKC>(smem + s * 2 * operand, ra[s]);
+      put_split<BKC>(smem + s * 2 * operand + operand, rb[s]);
+    } else {
+      put<AKC, VEC>(smem + s * 2 * operand, ra[s], ia[s]);
+      put<BKC, VEC>(smem + s * 2 * operand + operand, rb[s], ib[s]);
+    }
   };
   auto compute = [&](int buf) {
-    const unsigned char* la = smem + buf * 2 * kOperand;
-    const unsigned char* lb = la + kOperand;
+    const unsigned char* la = smem + buf * 2 * operand;
+    const unsigned char* lb = la + operand;
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int ks = 0; ks < kK / 16; ++ks) {
+        Frag a[3], b[3];
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+          a[p] = frag_split<AKC>(la + p * kPlane, wm * 32, ks, lane);
+          b[p] = frag_split<BKC>(lb + p * kPlane, wn * 32, ks, lane);
+        }
+        acc = mfma(a[0], b[0], acc);
+        low = mfma(a[0], b[2], low);
+        low = mfma(a[2], b[0], low);
+        low = mfma(a[1], b[1], low);
+        low = mfma(a[0], b[1], low);
+        low = mfma(a[1], b[0], low);
+      }
+      return;
+    }
 #pragma unroll
     for (int q = 0; q < kK / 8; ++q) {
       const f32x4 a = frag<AKC>(la, wm * 32 + col, q, half), b = frag<BKC>(lb, wn * 32 + col, q, half);
@@ -158,11 +276,41 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32& g, const DimsF32& d
       load(s);
       compute(s);
       store(1 - s);
+      if constexpr (SPLIT) {
+        // matrix instructions first, each followed by its share of the next slice's split: one wavefront keeps both pipes busy
+        constexpr int RD = (AKC ? 3 : 6) + (BKC ? 3 : 6);
+        __builtin_amdgcn_sched_group_barrier(0x100, RD, 0);
+        __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, RD, 0);
+#pragma unroll
+        for (int i = 0; i < 11; ++i) {
+          __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);
+          __builtin_amdgcn_sched_group_barrier(0x2, 8, 0);
+          __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+        }
+      }
     }
   }
   if (total & 1) {
     __syncthreads();
     compute(0);
+  }
+  if constexpr (SPLIT) acc += low;
+  return acc;
+}
+
+template <bool AKC, bool BKC, bool VEC, bool SPLIT>
+__device__ __forceinline__ void gemm_f32_tile(const GemmF32& g, const DimsF32& dm, int bx, int by, int bz, unsigned char* smem) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int wm = wave >> 1, wn = wave & 1, col = lane & 31, half = lane >> 5;
+  const int z = bz / dm.splitk, m0 = by * kT, n0 = bx * kT;
+  floatx16 acc = gemm_f32_sum<AKC, BKC, VEC, SPLIT>(g, dm, bx, by, bz, smem);
+  if constexpr (SPLIT) {
+    bool finite = true;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) finite = finite && fabsf(acc[r]) < INFINITY;
+    if (__syncthreads_or(!finite)) acc = gemm_f32_sum<AKC, BKC, VEC, false>(g, dm, bx, by, bz, smem);
   }
   const float* bias = pick(z, g.bias0, g.bias1, g.bias2, g.bias3);
   float* C = pick(z, g.C0, g.C1, g.C2, g.C3);
@@ -182,32 +330,33 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32& g, const DimsF32& d
   }
 }
 
-template <bool AKC, bool BKC, bool VEC>
+template <bool AKC, bool BKC, bool VEC, bool SPLIT>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * kOperand];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[SPLIT ? kLds : 4 * kOperand];
   DimsF32 dm;
   if (!resolve_f32(g, dm, !AKC)) return;
   const int gx = (g.N + kT - 1) / kT, gy = (dm.M + kT - 1) / kT;
   const int total = gx * gy * g.nz * dm.splitk;
   if ((int)blockIdx.x >= total) return;        // (a grid sized for the bound of a device-side count)
   const int t = xcd_contiguous(blockIdx.x, total);
-  gemm_f32_tile<AKC, BKC, VEC>(g, dm, t % gx, (t / gx) % gy, t / (gx * gy), smem);
+  gemm_f32_tile<AKC, BKC, VEC, SPLIT>(g, dm, t % gx, (t / gx) % gy, t / (gx * gy), smem);
 }
 
 // Input gradient and weight gradients of one layer depend on the same dQ, dK, dV and on nothing of each other: one
 // launch, the weight-gradient tiles (K = all tokens: the longer chains) first.
+template <bool SPLIT>
 __global__ __launch_bounds__(256) void gemm_f32_bwd_pair_kernel(GemmF32 gx, GemmF32 gw) {
-  __shared__ __attribute__((aligned(16))) unsigned char smem[4 * kOperand];
+  __shared__ __attribute__((aligned(16))) unsigned char smem[SPLIT ? kLds : 4 * kOperand];
   DimsF32 dx, dw;
   if (!resolve_f32(gx, dx, false) || !resolve_f32(gw, dw, true)) return;
   const int wn = (gw.N + kT - 1) / kT, wm = (dw.M + kT - 1) / kT, nw = wn * wm * gw.nz * dw.splitk;
   const int xn = (gx.N + kT - 1) / kT, xm = (dx.M + kT - 1) / kT, nx = xn * xm;
   if ((int)blockIdx.x < nw) {
     const int t = xcd_contiguous(blockIdx.x, nw);
-    gemm_f32_tile<false, false, true>(gw, dw, t % wn, (t / wn) % wm, t / (wn * wm), smem);
+    gemm_f32_tile<false, false, true, SPLIT>(gw, dw, t % wn, (t / wn) % wm, t / (wn * wm), smem);
   } else if ((int)blockIdx.x < nw + nx) {
     const int t = xcd_contiguous(blockIdx.x - nw, nx);
-    gemm_f32_tile<true, true, true>(gx, dx, t % xn, t / xn, 0, smem);
+    gemm_f32_tile<true, true, true, SPLIT>(gx, dx, t % xn, t / xn, 0, smem);
   }
 }
 
@@ -250,13 +399,21 @@ int sum_slices(vardrop_ctx* ctx, const GemmF32& g, int bound, hipStream_t s) {
   return VARDROP_OK;
 }
 
+// By parts where a tile walks over at least 256 k.  Forward and backward of an attention layer, fp32 instruction -> by parts:
+// d = 64 18.3 -> 20.2 and 48.1 -> 48.5 us (two slices a tile: the longer start and end of the parts cost more than they
+// save), d = 256 26.9 -> 27.0 and 39.4 -> 38.5 (256 rows), 52.7 -> 48.4 and 77.9 -> 70.2 (3200 rows), d = 512 38.6 -> 35.6
+// and 63.9 -> 58.2 (128 rows), 100 -> 81 and 195 -> 151 (3200), d = 1024 307 -> 234 and 627 -> 475 (3200).
+// (With a device-side count its bound decides.)
+bool by_parts(long long k) { return k >= 256; }
+
 template <bool AKC, bool BKC>
 int launch_f32(vardrop_ctx* ctx, int kid, const GemmF32& g, int slices, hipStream_t s) {
   const long long grid = (long long)vd_ceil_div(g.N, kT) * vd_ceil_div(g.M, kT) * g.nz * slices;
   if (grid >= (1ll << 31)) return VARDROP_EUNSUPPORTED;
   VdTimer timer(ctx, kid, s);
-  if (aligned4(g, AKC, BKC)) VD_KERNEL(ctx, (gemm_f32_kernel<AKC, BKC, true>), dim3((unsigned)grid), dim3(256), 0, s, g);
-  else VD_KERNEL(ctx, (gemm_f32_kernel<AKC, BKC, false>), dim3((unsigned)grid), dim3(256), 0, s, g);
+  if (!aligned4(g, AKC, BKC)) VD_KERNEL(ctx, (gemm_f32_kernel<AKC, BKC, false, false>), dim3((unsigned)grid), dim3(256), 0, s, g);
+  else if (by_parts(AKC ? (long long)g.K * (g.nseg > 1 ? g.nseg : 1) : g.K / slices)) VD_KERNEL(ctx, (gemm_f32_kernel<AKC, BKC, true, true>), dim3((unsigned)grid), dim3(256), 0, s, g);
+  else VD_KERNEL(ctx, (gemm_f32_kernel<AKC, BKC, true, false>), dim3((unsigned)grid), dim3(256), 0, s, g);
   VD_LAUNCH_CHECK(ctx);
   return VARDROP_OK;
 }
@@ -282,7 +439,8 @@ int vd_gemm_f32_bwd_pair(vardrop_ctx* ctx, const GemmF32& gx, const GemmF32& gw,
   if (grid >= (1ll << 31)) return VARDROP_EUNSUPPORTED;
   {
     VdTimer timer(ctx, VARDROP_K_GEMM_DW_DXS, s);
-    VD_KERNEL(ctx, gemm_f32_bwd_pair_kernel, dim3((unsigned)grid), dim3(256), 0, s, gx, gw);
+    if (by_parts(3ll * gx.K)) VD_KERNEL(ctx, gemm_f32_bwd_pair_kernel<true>, dim3((unsigned)grid), dim3(256), 0, s, gx, gw);
+    else VD_KERNEL(ctx, gemm_f32_bwd_pair_kernel<false>, dim3((unsigned)grid), dim3(256), 0, s, gx, gw);
   }
   VD_LAUNCH_CHECK(ctx);
   return sum_slices(ctx, gw, slices, s);
