@@ -170,6 +170,10 @@ __device__ inline bool ring_block(SdpaArgs& a, int rows, int parts, int& xb, int
   lds_read8_tr<(SO) + (TILE) * kRingTile + ((KT) * 32 + 16) * 128>(F[2].d[1], ra.tr8[0]);          \
   lds_read8_tr<(SO) + (TILE) * kRingTile + ((KT) * 32 + 16) * 128>(F[3].d[0], ra.tr[1]);           \
   lds_read8_tr<(SO) + (TILE) * kRingTile + ((KT) * 32 + 16) * 128>(F[3].d[1], ra.tr8[1]);
+// fragment I of these alone
+#define VD_TR1(F, I, TILE, KT, SO)                                                                                   \
+  lds_read8_tr<(SO) + (TILE) * kRingTile + ((KT) * 32 + 16 * ((I) >> 1)) * 128>(F[I].d[0], ra.tr[(I) & 1]);          \
+  lds_read8_tr<(SO) + (TILE) * kRingTile + ((KT) * 32 + 16 * ((I) >> 1)) * 128>(F[I].d[1], ra.tr8[(I) & 1]);
 // runs STEP(stage constant, j) for j = 0 .. NB-1 with the stage j % 3
 #define VD_RING_LOOP(STEP, NB)                                          \
   for (int j = 0; j < (NB); j += kRingStages) {                         \
@@ -346,6 +350,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
 // 1924 tokens (B = 8, H = 12), the dK / dV part 224 -> 212 us, both parts in one launch 60 -> 53 us at 321 (B = 32, H = 8).
 // With the scale in Q (and, in the dK / dV part, scores that start at -log2(e) lse): 155 -> 151, 216 -> 208 and 58.6 -> 54.6
 // us on another box.
+// What bounds them: 12 and 16 matrix instructions per 32 x 32 scores (384 and 512 clocks) beside 240 clocks on the vector pipe and
+// 210 and 420 of the LDS; one wavefront does these one after the other, so three wavefronts a SIMD (168 registers) matter: in the
+// dK / dV part every Q^T fragment is requested when a dO^T fragment has been used and takes its registers (197 -> 182 us at
+// 1924 tokens, both parts in one launch 53 -> 46 at 321); in the dQ part scores start at -log2(e) lse too (145 -> 138).
 template <int NW, bool DLOCAL>
 __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int h, int b) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -379,9 +387,9 @@ __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int 
     nD = a.Dsum[srow + min(qi, n - 1)];
   }
   const float nlse2 = qi < n ? -a.lse[srow + qi] * kLog2e : -INFINITY;   // (-inf for a query past the end)
-  floatx16 nD16;
+  floatx16 nD16, nl16;                         // what the accumulators of dP and of the scores start with
 #pragma unroll
-  for (int r = 0; r < 16; ++r) nD16[r] = nD;
+  for (int r = 0; r < 16; ++r) { nD16[r] = nD; nl16[r] = nlse2; }
   const RingAddr ra = ring_addr(smem, lane);
   floatx16 acc[2] = {zero16(), zero16()};
   auto step = [&](auto stage, int j) __attribute__((always_inline)) {
@@ -403,15 +411,15 @@ __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int 
     Frag fk[4], fv[4], ft[4];                                                                            \
     VD_ROW4(fk, 0, KT, SO)              /* (the V fragments follow one by one: they can take the K fragments' registers) */ \
     __builtin_amdgcn_s_setprio(1);                                                                       \
-    VD_DQ_STEP(st, fk, qf, 0, zero16(), 3) VD_ROW1(fv, 0, 1, KT, SO)                                     \
-    VD_DQ_STEP(st, fk, qf, 1, zero16(), 3) VD_ROW1(fv, 1, 1, KT, SO)                                     \
-    VD_DQ_STEP(st, fk, qf, 2, zero16(), 3) VD_ROW1(fv, 2, 1, KT, SO)                                     \
-    VD_DQ_STEP(st, fk, qf, 3, zero16(), 3) VD_ROW1(fv, 3, 1, KT, SO)                                     \
+    VD_DQ_STEP(st, fk, qf, 0, nl16, 3)     VD_ROW1(fv, 0, 1, KT, SO)                                     \
+    VD_DQ_STEP(st, fk, qf, 1, nl16, 3)     VD_ROW1(fv, 1, 1, KT, SO)                                     \
+    VD_DQ_STEP(st, fk, qf, 2, nl16, 3)     VD_ROW1(fv, 2, 1, KT, SO)                                     \
+    VD_DQ_STEP(st, fk, qf, 3, nl16, 3)     VD_ROW1(fv, 3, 1, KT, SO)                                     \
     VD_DQ_STEP(dp, fv, dof, 0, nD16, 3) VD_DQ_STEP(dp, fv, dof, 1, nD16, 2)                              \
     VD_DQ_STEP(dp, fv, dof, 2, nD16, 1) VD_DQ_STEP(dp, fv, dof, 3, nD16, 0)                              \
     __builtin_amdgcn_s_setprio(0);                                                                       \
     VD_TR4(ft, 0, KT, SO)                                                                                \
-    _Pragma("unroll") for (int r = 0; r < 16; ++r) st[r] = fast_exp2(st[r] + nlse2) * dp[r];             \
+    _Pragma("unroll") for (int r = 0; r < 16; ++r) st[r] = fast_exp2(st[r]) * dp[r];                     \
     if (tail) {                                 /* a key past the end repeats the last one: its dS is dropped */ \
       _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                                   \
         const int key = j * 64 + (KT) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);                          \
@@ -524,13 +532,12 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
       }                                                                                                  \
     }                                                                                                    \
     __builtin_amdgcn_sched_barrier(0);                                                                   \
-    wait_lds_count<7>();                                                                                 \
-    VD_TR4(fq, 0, QT, SO)                       /* Q^T */                                                \
-    __builtin_amdgcn_s_setprio(1);                                                                       \
-    wait_lds<8>(fo[0]); accV[0] = mfma(fo[0], regs_to_frag(st.f, 0), accV[0]);                           \
-    wait_lds<8>(fo[1]); accV[1] = mfma(fo[1], regs_to_frag(st.f, 0), accV[1]);                           \
-    wait_lds<8>(fo[2]); accV[0] = mfma(fo[2], regs_to_frag(st.f, 1), accV[0]);                           \
-    wait_lds<8>(fo[3]); accV[1] = mfma(fo[3], regs_to_frag(st.f, 1), accV[1]);                           \
+    __builtin_amdgcn_s_setprio(1);              /* (each Q^T fragment takes the registers of a dO^T one) */\
+    wait_lds<6>(fo[0]); accV[0] = mfma(fo[0], regs_to_frag(st.f, 0), accV[0]); VD_TR1(fq, 0, 0, QT, SO)  \
+    wait_lds<6>(fo[1]); accV[1] = mfma(fo[1], regs_to_frag(st.f, 0), accV[1]); VD_TR1(fq, 1, 0, QT, SO)  \
+    wait_lds<6>(fo[2]); accV[0] = mfma(fo[2], regs_to_frag(st.f, 1), accV[0]); VD_TR1(fq, 2, 0, QT, SO)  \
+    wait_lds<6>(fo[3]); accV[1] = mfma(fo[3], regs_to_frag(st.f, 1), accV[1]); VD_TR1(fq, 3, 0, QT, SO)  \
+    __builtin_amdgcn_sched_barrier(0);                                                                   \
     wait_lds<6>(fq[0]); accK[0] = mfma(fq[0], regs_to_frag(dp.f, 0), accK[0]);                           \
     wait_lds<4>(fq[1]); accK[1] = mfma(fq[1], regs_to_frag(dp.f, 0), accK[1]);                           \
     wait_lds<2>(fq[2]); accK[0] = mfma(fq[2], regs_to_frag(dp.f, 1), accK[0]);                           \
@@ -557,6 +564,7 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
 #undef VD_ROW1
 #undef VD_ROW4
 #undef VD_TR4
+#undef VD_TR1
 
 // Many workgroups: two launches, -D = -rowsum(dO * O) and -log2(e) * lse written by the dQ kernel, whose matrix work
 // hides the read of O.
@@ -567,7 +575,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) vo
   sdpa_bwd_dq_body<NW, true>(a, xb, h, b);
 }
 template <int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void sdpa_bwd_dkv_bf16(SdpaArgs a) {
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 3 : 2))) void sdpa_bwd_dkv_bf16(SdpaArgs a) {
   int xb, h, b;
   if (!ring_block(a, NW * 32, 1, xb, h, b)) return;
   sdpa_bwd_dkv_body<NW>(a, xb, h, b);
@@ -576,7 +584,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) vo
 // (batch, head) pair the first half take query blocks (dQ), the second half key blocks (dK, dV); neither part
 // reads what the other writes: -D and -log2(e) * lse come with dO from the GEMM before.
 template <int NW>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2))) void sdpa_bwd_dqkv_bf16(SdpaArgs a) {
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 3 : 2))) void sdpa_bwd_dqkv_bf16(SdpaArgs a) {
   int xb, h, b;
   if (!ring_block(a, NW * 32, 2, xb, h, b)) return;
   const int nblk = (a.n + NW * 32 - 1) / (NW * 32);
