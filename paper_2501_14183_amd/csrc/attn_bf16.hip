@@ -36,11 +36,15 @@ __device__ inline void row_frags(Frag f[4], const bf16_t* P, long long ld, int r
 // accumulator (transposed: rows = head dims, column = this lane's token) -> out[token][32*ct + ...]
 __device__ inline void store_accT(bf16_t* out_row, const floatx16& acc, int ct, int half, float mul) {
 #pragma unroll
-  for (int g4 = 0; g4 < 4; ++g4) {
-    u32x2 w;
-    w.x = pack2(acc[4 * g4] * mul, acc[4 * g4 + 1] * mul);
-    w.y = pack2(acc[4 * g4 + 2] * mul, acc[4 * g4 + 3] * mul);
-    *reinterpret_cast<u32x2*>(out_row + ct * 32 + 8 * g4 + 4 * half) = w;
+  for (int g2 = 0; g2 < 4; g2 += 2) {
+    u32x2 w[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int r = 4 * (g2 + e);
+      w[e].x = pack2(acc[r] * mul, acc[r + 1] * mul);
+      w[e].y = pack2(acc[r + 2] * mul, acc[r + 3] * mul);
+    }
+    *reinterpret_cast<u32x4*>(out_row + ct * 32 + 8 * (g2 + half)) = quads16(w[0], w[1]);
   }
 }
 
@@ -439,13 +443,14 @@ __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int 
 #undef VD_DQ_ACC
   };
   VD_RING_LOOP(step, nb)
-  if (qi < n) {
-    bf16_t* row = a.dq + base + (long long)qi * ld;
-    store_accT(row, acc[0], 0, half, a.scale);
-    store_accT(row, acc[1], 1, half, a.scale);
-    if (DLOCAL && half == 0) {
-      a.Dsum[srow + qi] = nD;
-      a.nlse2[srow + qi] = nlse2;
+  const int lane2 = fresh_lane(), half2 = lane2 >> 5, qo = (qb * NW + wave) * 32 + (lane2 & 31);
+  if (qo < n) {
+    bf16_t* row = a.dq + base + (long long)qo * ld;
+    store_accT(row, acc[0], 0, half2, a.scale);
+    store_accT(row, acc[1], 1, half2, a.scale);
+    if (DLOCAL && half2 == 0) {
+      a.Dsum[srow + qo] = nD16[0];
+      a.nlse2[srow + qo] = nl16[0];
     }
   }
 }
@@ -551,13 +556,14 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
   };
   VD_RING_LOOP(step, nb)
 #undef VD_ISSUE_Q
-  if (kj < n) {
-    bf16_t* rk = a.dk + base + (long long)kj * ld;
-    bf16_t* rv = a.dv + base + (long long)kj * ld;
-    store_accT(rk, accK[0], 0, half, kLn2);
-    store_accT(rk, accK[1], 1, half, kLn2);
-    store_accT(rv, accV[0], 0, half, 1.f);
-    store_accT(rv, accV[1], 1, half, 1.f);
+  const int lane2 = fresh_lane(), half2 = lane2 >> 5, ko = (kb * NW + wave) * 32 + (lane2 & 31);
+  if (ko < n) {
+    bf16_t* rk = a.dk + base + (long long)ko * ld;
+    bf16_t* rv = a.dv + base + (long long)ko * ld;
+    store_accT(rk, accK[0], 0, half2, kLn2);
+    store_accT(rk, accK[1], 1, half2, kLn2);
+    store_accT(rv, accV[0], 0, half2, 1.f);
+    store_accT(rv, accV[1], 1, half2, 1.f);
   }
 }
 #undef VD_RING_LOOP
@@ -753,12 +759,14 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
     // register 4*q4 + e of the accumulator is dO[32*blk + col][32*part + 8*q4 + 4*half + e]
     const int row = blk * 32 + col;
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const int dim = part * 32 + 8 * q4 + 4 * half;
-      u32x2 o;
-      o.x = pack2(acc[4 * q4], acc[4 * q4 + 1]);
-      o.y = pack2(acc[4 * q4 + 2], acc[4 * q4 + 3]);
-      *reinterpret_cast<u32x2*>(dOs + row * 128 + (((dim >> 3) ^ tile_swz(row)) * 16) + ((dim >> 2) & 1) * 8) = o;
+    for (int g2 = 0; g2 < 4; g2 += 2) {
+      u32x2 o[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        o[e].x = pack2(acc[4 * (g2 + e)], acc[4 * (g2 + e) + 1]);
+        o[e].y = pack2(acc[4 * (g2 + e) + 2], acc[4 * (g2 + e) + 3]);
+      }
+      *reinterpret_cast<u32x4*>(dOs + row * 128 + (((4 * part + g2 + half) ^ tile_swz(row)) * 16)) = quads16(o[0], o[1]);
     }
   }
   __syncthreads();                      // the ring is free: the statistics and later dS^T may use its place
@@ -810,11 +818,14 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
         dp[r] = p * (dp[r] - Ds[iq]);
       }
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        u32x2 w;
-        w.x = pack2(dp[4 * q4], dp[4 * q4 + 1]);
-        w.y = pack2(dp[4 * q4 + 2], dp[4 * q4 + 3]);
-        *reinterpret_cast<u32x2*>(dSt + kj * kDsPitch + (qt * 32 + 8 * q4 + 4 * half) * 2) = w;
+      for (int g2 = 0; g2 < 4; g2 += 2) {
+        u32x2 w[2];
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          w[e].x = pack2(dp[4 * (g2 + e)], dp[4 * (g2 + e) + 1]);
+          w[e].y = pack2(dp[4 * (g2 + e) + 2], dp[4 * (g2 + e) + 3]);
+        }
+        *reinterpret_cast<u32x4*>(dSt + kj * kDsPitch + (qt * 32 + 8 * (g2 + half)) * 2) = quads16(w[0], w[1]);
       }
 #pragma unroll
       for (int s2 = 0; s2 < 2; ++s2) {
@@ -941,7 +952,7 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
   constexpr int LPS = 5;                                        // copies per wavefront and stage: 2 of xs, 3 of weights
   constexpr int OPK = 7;                                        // LDS reads per 16-k step: 1 + 3 * 2
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wr = wave & 3, wc = wave >> 2;
   const int col = lane & 31, half = lane >> 5;
   // heads fastest: a die's contiguous range covers whole batches, whose tokens it then fetches once
@@ -1099,21 +1110,26 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
   for (int j = 0; j < 3; ++j) {
     const int ct = 3 * wc + j, z = ct >> 1;
     const bf16_t* bias = z == 0 ? a.bq : (z == 1 ? a.bk : a.bv);
+    const int row = wr * 32 + col;
+    const float mul = z == 0 ? a.q_mul : 1.f;
+    if (bias) {
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const int dim = (ct & 1) * 32 + 8 * q4 + 4 * half;
-      float bv[4] = {0.f, 0.f, 0.f, 0.f};
-      if (bias) {
-        const u32x2 b4 = *reinterpret_cast<const u32x2*>(bias + h * kDh + dim);
-        bv[0] = __uint_as_float(b4.x << 16); bv[1] = __uint_as_float(b4.x & 0xffff0000u);
-        bv[2] = __uint_as_float(b4.y << 16); bv[3] = __uint_as_float(b4.y & 0xffff0000u);
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const u32x2 b4 = *reinterpret_cast<const u32x2*>(bias + h * kDh + (ct & 1) * 32 + 8 * q4 + 4 * half);
+        acc[j][4 * q4] += __uint_as_float(b4.x << 16); acc[j][4 * q4 + 1] += __uint_as_float(b4.x & 0xffff0000u);
+        acc[j][4 * q4 + 2] += __uint_as_float(b4.y << 16); acc[j][4 * q4 + 3] += __uint_as_float(b4.y & 0xffff0000u);
       }
-      const int row = wr * 32 + col;
-      const float mul = z == 0 ? a.q_mul : 1.f;
-      u32x2 o;
-      o.x = pack2((acc[j][4 * q4] + bv[0]) * mul, (acc[j][4 * q4 + 1] + bv[1]) * mul);
-      o.y = pack2((acc[j][4 * q4 + 2] + bv[2]) * mul, (acc[j][4 * q4 + 3] + bv[3]) * mul);
-      *reinterpret_cast<u32x2*>(smem + z * kSmallTile + row * 128 + (((dim >> 3) ^ tile_swz(row)) * 16) + ((dim >> 2) & 1) * 8) = o;
+    }
+#pragma unroll
+    for (int g2 = 0; g2 < 4; g2 += 2) {
+      u32x2 o[2];
+#pragma unroll
+      for (int e = 0; e < 2; ++e) {
+        const int r = 4 * (g2 + e);
+        o[e].x = pack2(acc[j][r] * mul, acc[j][r + 1] * mul);
+        o[e].y = pack2(acc[j][r + 2] * mul, acc[j][r + 3] * mul);
+      }
+      *reinterpret_cast<u32x4*>(smem + z * kSmallTile + row * 128 + (((4 * (ct & 1) + g2 + half) ^ tile_swz(row)) * 16)) = quads16(o[0], o[1]);
     }
   }
   __syncthreads();
@@ -1153,12 +1169,15 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
 #pragma unroll
       for (int s = 0; s < 4; ++s) st[k2] = mfma(small_row_frag(Ks, kt * 32 + col, 2 * s + half), qf[s], st[k2]);
     }
+    if (kt * 32 + 32 > n) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int j = kt * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-      st[k2][r] = j < n ? st[k2][r] : -INFINITY;
-      m = fmaxf(m, st[k2][r]);
+      for (int r = 0; r < 16; ++r) {
+        const int j = kt * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
+        st[k2][r] = j < n ? st[k2][r] : -INFINITY;
+      }
     }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) m = fmaxf(m, st[k2][r]);
   }
   m = fmaxf(m, __shfl_xor(m, 32, 64));
   // a wavefront whose key tiles are all past n has m = -inf: its probabilities must be zero, not NaN

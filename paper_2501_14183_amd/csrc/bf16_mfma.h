@@ -50,6 +50,16 @@ __device__ inline floatx16 zero16() {
 __device__ inline floatx16 mfma(const Frag& a, const Frag& b, floatx16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, b.v, c, 0, 0, 0);
 }
+// Two register quads of an accumulator (rows 8 g + 4 half + 0..3 and 8 (g + 1) + 4 half + 0..3) as bf16: the halves of a
+// wavefront exchange a quad, so that each lane holds the whole 16 bytes of rows 8 (g + half) + 0..7 of its column.  Half as
+// many stores, and free of the two-way bank conflict of 8-byte LDS writes.  (Both lanes of a column must be active.)
+// What the kernels write at their end: forward and backward of short selections 18.2 -> 16.9 and 18.6 -> 16.9 us (104 tokens,
+// B = 32, H = 8; with scalar branches in the forward's bias code), dQ / dK / dV of 190 tokens 27.6 -> 24.3, of 321 45.9 -> 42.4.
+__device__ inline u32x4 quads16(const u32x2& a, const u32x2& b) {
+  const auto x = __builtin_amdgcn_permlane32_swap(a.x, b.x, false, false);
+  const auto y = __builtin_amdgcn_permlane32_swap(a.y, b.y, false, false);
+  return u32x4{x[0], y[0], x[1], y[1]};
+}
 // eight accumulator registers (8*s2 .. 8*s2+7) as a bf16 right-hand operand
 __device__ inline Frag regs_to_frag(const floatx16& p, int s2) {
   Frag f;

@@ -368,26 +368,38 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
   if (!producer && kh == 0)
 #pragma unroll
   for (int j = 0; j < 2; ++j)
+    if constexpr (SPLIT) {
 #pragma unroll
-    for (int q4 = 0; q4 < 4; ++q4) {
-      const int nl = wn * 64 + j * 32 + 8 * q4 + 4 * half;
-      float bv[4] = {0.f, 0.f, 0.f, 0.f};
-      if (bias && n0 + nl < g.N) {                 // N is a multiple of 8: a quad is inside or outside
-        const u32x2 b4 = *reinterpret_cast<const u32x2*>(bias + n0 + nl);
-        bv[0] = __uint_as_float(b4.x << 16); bv[1] = __uint_as_float(b4.x & 0xffff0000u);
-        bv[2] = __uint_as_float(b4.y << 16); bv[3] = __uint_as_float(b4.y & 0xffff0000u);
-      }
+      for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
-      for (int i = 0; i < MI; ++i) {
-        unsigned char* p = smem + (wm * MROWS + i * 32 + col) * CPITCH + nl * ES;
-        if constexpr (SPLIT) {
-          float4 o = make_float4(acc[i][j][4 * q4], acc[i][j][4 * q4 + 1], acc[i][j][4 * q4 + 2], acc[i][j][4 * q4 + 3]);
-          *reinterpret_cast<float4*>(p) = o;
-        } else {
-          u32x2 o;
-          o.x = pack2((acc[i][j][4 * q4] + bv[0]) * cmul, (acc[i][j][4 * q4 + 1] + bv[1]) * cmul);
-          o.y = pack2((acc[i][j][4 * q4 + 2] + bv[2]) * cmul, (acc[i][j][4 * q4 + 3] + bv[3]) * cmul);
-          *reinterpret_cast<u32x2*>(p) = o;
+        for (int i = 0; i < MI; ++i)
+          *reinterpret_cast<float4*>(smem + (wm * MROWS + i * 32 + col) * CPITCH + (wn * 64 + j * 32 + 8 * q4 + 4 * half) * 4) =
+              make_float4(acc[i][j][4 * q4], acc[i][j][4 * q4 + 1], acc[i][j][4 * q4 + 2], acc[i][j][4 * q4 + 3]);
+    } else {
+#pragma unroll
+      for (int g2 = 0; g2 < 4; g2 += 2) {
+        float bv[2][4] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+        if (bias) {
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const int n = n0 + wn * 64 + j * 32 + 8 * (g2 + e) + 4 * half;
+            if (n < g.N) {                         // N is a multiple of 8: a quad is inside or outside
+              const u32x2 b4 = *reinterpret_cast<const u32x2*>(bias + n);
+              bv[e][0] = __uint_as_float(b4.x << 16); bv[e][1] = __uint_as_float(b4.x & 0xffff0000u);
+              bv[e][2] = __uint_as_float(b4.y << 16); bv[e][3] = __uint_as_float(b4.y & 0xffff0000u);
+            }
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i) {
+          u32x2 o[2];
+#pragma unroll
+          for (int e = 0; e < 2; ++e) {
+            const int r = 4 * (g2 + e);
+            o[e].x = pack2((acc[i][j][r] + bv[e][0]) * cmul, (acc[i][j][r + 1] + bv[e][1]) * cmul);
+            o[e].y = pack2((acc[i][j][r + 2] + bv[e][2]) * cmul, (acc[i][j][r + 3] + bv[e][3]) * cmul);
+          }
+          *reinterpret_cast<u32x4*>(smem + (wm * MROWS + i * 32 + col) * CPITCH + (wn * 64 + j * 32 + 8 * (g2 + half)) * 2) = quads16(o[0], o[1]);
         }
       }
     }
@@ -490,7 +502,8 @@ __device__ __forceinline__ bool gemm_resolve(const GemmBf16& g, GemmDims& dm) {
 // One-dimensional grid of at least nz * tiles workgroups (more when the launch was sized for the bound of a
 // device-side count: the surplus returns at once).
 template <bool AKC, bool BKC, bool SPLIT, int BM, int BK, int NS>
-__global__ __launch_bounds__(kGemmThreads, 2) void gemm_async_kernel(GemmBf16 g, int nz) {
+// (wavefronts a SIMD: two or three workgroups share a compute unit)
+__global__ __launch_bounds__(kGemmThreads, BM == 128 || NS > 2 ? 4 : 6) void gemm_async_kernel(GemmBf16 g, int nz) {
   GemmDims dm;
   if (!gemm_resolve(g, dm)) return;
   // tiles in the order n fastest, then m, then batch entry: a die's range shares its rows of A
@@ -520,7 +533,7 @@ struct PairCfg {
 typedef PairCfg<128, 64, 3, 64, 64, 3, true> PairSmall;
 typedef PairCfg<128, 64, 2, 128, 32, 4> PairLarge;
 template <typename CFG>
-__global__ __launch_bounds__(kGemmThreads, 2) void gemm_bwd_pair_kernel(GemmBf16 gx, GemmBf16 gw, int nzw) {
+__global__ __launch_bounds__(kGemmThreads, CFG::KHW ? 2 : 4) void gemm_bwd_pair_kernel(GemmBf16 gx, GemmBf16 gw, int nzw) {
   // Each die takes a contiguous range of the input-gradient tiles (n fastest: a range shares its rows
   // of dQ, dK, dV) and a contiguous range of the weight-gradient tiles (n, then m, then K slice, then
   // matrix: a range shares its K slice of both operands).  The kind whose tiles walk over more K comes first, so that a late
