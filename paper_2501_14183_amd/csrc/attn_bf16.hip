@@ -599,7 +599,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
 }
 
 // ---- backward for short selections (n <= 128, the regime variate dropping produces): one workgroup
-// per (batch, head) holds Q, K, V and O of the head in LDS (asynchronous copies), forms the head's dO tile
+// per (batch, head) holds Q, K and V of the head in LDS (asynchronous copies), forms the head's dO tile
 // from dy and Wo itself (dO never goes to memory), and forms S and dP once for all three gradients.
 //   phase 1, a wavefront owns 32 keys (lane = key):  S^T-free orientation S[query][key] = Q k^T and
 //            dP = dO v^T with the key fragments in registers; P and dS feed dV^T = dO^T P and
@@ -607,13 +607,19 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
 //            the dO and Q tiles; dS goes to LDS as dS^T[key][query].
 //   phase 2, a wavefront owns 32 queries (lane = query): dQ^T = K^T dS^T, both operands transposing
 //            reads (contraction over keys).
+// What bounds it (clock readings at 104 tokens, d = 512, 28 000 clocks in all): the dO product waited 10 500 clocks for eight
+// slices of which each took a round trip to memory; with a third copy stage, in the place of the dO tile and of an O tile that
+// registers replace (120 instead of 128 KB of LDS), and with scores and dP that start at -log2(e) lse and -D in their
+// accumulators 16.9 -> 15.0 us (89 tokens, 15.1 -> 12.9; a fourth stage 14.8 and 13.1).
 // Tiles are [token][64] with the 16-byte chunk position XORed with token % 8, as the copies write them.
 constexpr int kSmallN = 128;
 constexpr int kDsPitch = 272;                 // bytes per dS^T row: 128 queries * 2 + 16
 constexpr int kSmallTile = kSmallN * kDh * 2;  // bytes of one [128][64] tile
 constexpr int kBwdStage = kSmallN * 64 * 2 + 64 * 64 * 2;        // dy tile + Wo tile of one 64-k slice: 24 KB
-constexpr int kBwdStages = 2;
-constexpr int kSmallLds = 5 * kSmallTile + kBwdStages * kBwdStage;   // the ring overlays dS^T and the statistics
+constexpr int kBwdStages = 3;
+constexpr int kSmallLds = 3 * kSmallTile + kBwdStages * kBwdStage;   // the ring overlays the dO tile, dS^T and the statistics
+constexpr int kSmallTail = 3 * kSmallTile + kSmallTile + kSmallN * kDsPitch + 2 * kSmallN * 4;   // what is left behind them
+static_assert(kSmallTail + 2 * 8192 <= kSmallLds, "room for two of the eight blocks of the exchange after phase 1");
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 // 16-byte chunk (k = 8*chunk ..) of a token row of a swizzled tile
@@ -646,12 +652,10 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
   unsigned char* Qs = Ks + kSmallTile;
   unsigned char* Vs = Qs + kSmallTile;
   unsigned char* dOs = Vs + kSmallTile;
-  unsigned char* Os = dOs + kSmallTile;
-  unsigned char* dSt = Os + kSmallTile;                                   // [key][kDsPitch]
-  float* Ls = reinterpret_cast<float*>(dSt + kSmallN * kDsPitch);
-  float* Ds = Ls + kSmallN;
-  float* scratch = reinterpret_cast<float*>(Qs);                          // Q, V, dO, O tiles: free after phase 1
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  unsigned char* dSt = dOs + kSmallTile;                                  // [key][kDsPitch]
+  float* nLs = reinterpret_cast<float*>(dSt + kSmallN * kDsPitch);        // -log2(e) lse, -inf past the last query
+  float* nDs = nLs + kSmallN;                                             // -D
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blk = wave & 3, part = wave >> 2;
   const int col = lane & 31, half = lane >> 5;
   // heads fastest: a die's contiguous range covers whole batches, whose dy rows it then fetches once
@@ -664,11 +668,15 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
   const long long srow = ((long long)b * a.H + h) * n;
 
   // ---- dO tile of this head: dO[token][i] = sum_j dy[token][j] Wo[64 h + i][j], both operands k-contiguous,
-  // 64-k slices two stages deep in a ring that overlays the (not yet used) dS^T buffer.  Wavefront w
-  // computes token rows 32*(w % 4) .. +31, columns 32*(w / 4) .. +31.
+  // 64-k slices three stages deep in a ring that overlays the dO tile and the (not yet used) dS^T buffer.  Wavefront w
+  // computes token rows 32*(w % 4) .. +31, columns 32*(w / 4) .. +31.  A slice is little work, so the loop waits for memory:
+  // with two stages each slice took a whole round trip (1300 clocks).
+  // O is needed for D only: the lanes that form D hold it in registers, requested first.
+  Frag of[4];
+  if (part == 0) row_frags(of, a.o + base, ld, blk * 32 + col, n, half);
   {
     constexpr int NS = kBwdStages, STAGE = kBwdStage, A_BYTES = kSmallN * 64 * 2, LPS = 3;
-    unsigned char* ring = dSt;
+    unsigned char* ring = dOs;
     const bf16_t* dy_b = a.dy + (long long)b * n * ld;
     const copy_src srcA = copy_source(dy_b), srcB = copy_source(a.wo + (long long)h * kDh * ld);
     uint32_t offA[2];
@@ -701,12 +709,11 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
     ++fk;                                                                                          \
   }
     VD_ISSUE(0)                         // the first slice goes ahead of the tile copies: the product starts on it
-    // copies of K, Q, V, O.  A wavefront-wide copy fills 8 token rows; rows past n repeat row n-1.
+    // copies of K, Q, V.  A wavefront-wide copy fills 8 token rows; rows past n repeat row n-1.
     {
-      const bf16_t* src[5] = {a.k + base, a.q + base, a.v + base, nullptr, a.o + base};
+      const bf16_t* src[3] = {a.k + base, a.q + base, a.v + base};
 #pragma unroll
-      for (int t = 0; t < 5; ++t) {
-        if (t == 3) continue;           // the dO tile is what this block computes
+      for (int t = 0; t < 3; ++t) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
           const int row = (u * 8 + wave) * 8 + (lane >> 3);
@@ -715,7 +722,7 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
         }
       }
     }
-    constexpr int kTileCopies = 8;      // per wavefront
+    constexpr int kTileCopies = 6;      // per wavefront
 #pragma unroll
     for (int s = 1; s < NS - 1; ++s)
       if (s < total) VD_ISSUE(s)
@@ -726,9 +733,14 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
         if (t < total) {
           // slice t has landed once only younger copies are in flight: after slice 0 the tile copies and
           // the slices issued with them, later the slices issued since (the tile copies are older: done too)
+          const int ahead = min(total - 1 - t, NS - 2);
           if (t == 0) {
-            if (NS >= 3 && total >= 2) wait_vm<kTileCopies + LPS>(); else wait_vm<kTileCopies>();
-          } else if (NS >= 3 && total - 1 - t >= 1) wait_vm<LPS>(); else wait_vm<0>();
+            if (NS >= 4 && ahead >= 2) wait_vm<kTileCopies + 2 * LPS>();
+            else if (ahead >= 1) wait_vm<kTileCopies + LPS>();
+            else wait_vm<kTileCopies>();
+          } else if (NS >= 4 && ahead >= 2) wait_vm<2 * LPS>();
+          else if (ahead >= 1) wait_vm<LPS>();
+          else wait_vm<0>();
           __builtin_amdgcn_s_barrier();
           if (t + NS - 1 < total) VD_ISSUE((s + NS - 1) % NS)
           const uint32_t so = s * STAGE;
@@ -756,6 +768,7 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
 #undef VD_ISSUE_W
 #undef VD_ISSUE_X
     wait_vm<0>();                       // (with a single slice the tile copies can still be in flight here)
+    __builtin_amdgcn_s_barrier();       // everyone has read the last slice, whose place the dO tile may take
     // register 4*q4 + e of the accumulator is dO[32*blk + col][32*part + 8*q4 + 4*half + e]
     const int row = blk * 32 + col;
 #pragma unroll
@@ -769,10 +782,9 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
       *reinterpret_cast<u32x4*>(dOs + row * 128 + (((4 * part + g2 + half) ^ tile_swz(row)) * 16)) = quads16(o[0], o[1]);
     }
   }
-  __syncthreads();                      // the ring is free: the statistics and later dS^T may use its place
   if (threadIdx.x < kSmallN) {
     const int i = threadIdx.x;
-    Ls[i] = i < n ? a.lse[srow + i] * kLog2e : INFINITY;
+    nLs[i] = i < n ? a.lse[srow + i] * -kLog2e : -INFINITY;
   }
   __syncthreads();
   // D = rowsum(dO * O), one query per lane pair
@@ -781,12 +793,12 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
     float D = 0.f;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const Frag x = small_row_frag(dOs, qi, 2 * s + half), y = small_row_frag(Os, qi, 2 * s + half);
+      const Frag x = small_row_frag(dOs, qi, 2 * s + half);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) D = fmaf(bf2f(x.h[e]), bf2f(y.h[e]), D);
+      for (int e = 0; e < 8; ++e) D = fmaf(bf2f(x.h[e]), bf2f(of[s].h[e]), D);
     }
-    D += __shfl_xor(D, 32, 64);
-    if (half == 0) Ds[qi] = D;
+    D += other_half(D);
+    if (half == 0) nDs[qi] = -D;
   }
   __syncthreads();
 
@@ -804,7 +816,14 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
     for (int q2 = 0; q2 < 2; ++q2) {
       const int qt = 2 * part + q2;
       if (qt * 32 >= n) break;
-      floatx16 st = zero16(), dp = zero16();
+      // the accumulators start at -log2(e) lse and -D of the tile's queries
+      Acc16 st0, dp0;
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        st0.q[q4] = *reinterpret_cast<const u32x4*>(nLs + qt * 32 + 8 * q4 + 4 * half);
+        dp0.q[q4] = *reinterpret_cast<const u32x4*>(nDs + qt * 32 + 8 * q4 + 4 * half);
+      }
+      floatx16 st = st0.f, dp = dp0.f;
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         st = mfma(small_row_frag(Qs, qt * 32 + col, 2 * s + half), kf[s], st);     // S[query][key]
@@ -812,10 +831,15 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const int iq = qt * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-        const float p = kj < n ? fast_exp2(st[r] - Ls[iq]) : 0.f;      // Ls = +inf past the last query
-        st[r] = p;
-        dp[r] = p * (dp[r] - Ds[iq]);
+        st[r] = fast_exp2(st[r]);
+        dp[r] *= st[r];
+      }
+      if (blk * 32 + 32 > n) {            // a key past the end repeats the last one: dropped
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          st[r] = kj < n ? st[r] : 0.f;
+          dp[r] = kj < n ? dp[r] : 0.f;
+        }
       }
 #pragma unroll
       for (int g2 = 0; g2 < 4; g2 += 2) {
@@ -846,9 +870,10 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
   __syncthreads();                      // dS^T is complete; nobody reads the Q, V, dO, O tiles any more
   // The two wavefronts of a key block join their partial sums through LDS: the lower one hands over its
   // dV^T, the upper one its dK^T; then the lower one finishes and stores dK, the upper one dV.
-  // scratch[blk][part][16-byte register quad][lane]
+  // block[blk * 2 + part][16-byte register quad][lane], 8 KB each: six in the place of the Q, V and dO tiles, two at the end
+  auto exchange = [&](int i) { return reinterpret_cast<float4*>(i < 6 ? Qs + i * 8192 : smem + kSmallTail + (i - 6) * 8192) + lane; };
   {
-    float4* sp = reinterpret_cast<float4*>(scratch) + (blk * 2 + part) * (8 * 64) + lane;
+    float4* sp = exchange(blk * 2 + part);
     const floatx16* give = part == 0 ? accV : accK;
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt)
@@ -858,7 +883,7 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
   }
   __syncthreads();
   {
-    const float4* sp = reinterpret_cast<const float4*>(scratch) + (blk * 2 + (1 - part)) * (8 * 64) + lane;
+    const float4* sp = exchange(blk * 2 + (1 - part));
     floatx16* mine = part == 0 ? accK : accV;
 #pragma unroll
     for (int dt = 0; dt < 2; ++dt)
