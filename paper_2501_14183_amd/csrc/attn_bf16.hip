@@ -195,7 +195,7 @@ __device__ inline bool ring_block(SdpaArgs& a, int rows, int parts, int& xb, int
 // of a SIMD overlap them for 40 % of the matrix time only, so every vector instruction in the loop counts.
 // Without the maximum per block, with scalar copy addresses and immediate read offsets: 143 -> 117 us at 1924 tokens
 // (B = 8, H = 12; 0.84 PFLOP/s), 82 -> 69 us at 862 (B = 32, H = 8).  With the scale in Q and the accumulators of the
-// scores starting at minus the reference (no multiply-add per score): 119 -> 113 us and 84 -> 80 us on one box.  Tried:
+// scores starting at minus the reference (no multiply-add per score): 119 -> 113 us and 84 -> 80 us on one machine.  Tried:
 // fixed priorities by wavefront slot instead of priority while feeding the matrix pipe 125 us, no priorities 117 us.
 __device__ __forceinline__ float other_half(float v) {       // the value of lane ^ 32
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
@@ -353,7 +353,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
 // dP - D costs no vector instruction (the vector pipe bounds these loops, as in the forward kernel): 172 -> 151 us at
 // 1924 tokens (B = 8, H = 12), the dK / dV part 224 -> 212 us, both parts in one launch 60 -> 53 us at 321 (B = 32, H = 8).
 // With the scale in Q (and, in the dK / dV part, scores that start at -log2(e) lse): 155 -> 151, 216 -> 208 and 58.6 -> 54.6
-// us on another box.
+// us on another machine.
 // What bounds them: 12 and 16 matrix instructions per 32 x 32 scores (384 and 512 clocks) beside 240 clocks on the vector pipe and
 // 210 and 420 of the LDS; one wavefront does these one after the other, so three wavefronts a SIMD (168 registers) matter: in the
 // dK / dV part every Q^T fragment is requested when a dO^T fragment has been used and takes its registers (197 -> 182 us at
@@ -1285,7 +1285,9 @@ int launch_sdpa_fwd(vardrop_ctx* ctx, const SdpaArgs& a, hipStream_t s) {
 // Fewer than three rounds of the chip's 512 workgroup places per part: both parts in one launch.  Measured per step
 // at B = 32, H = 8: 1.2-1.8 % faster at 173, 205 and 321 tokens, 1.3 % at 422 (1024 workgroups per part), 0.9 % at 543
 // (1280); 1 % slower at 862 (1792) and at 1936 tokens with B = 8, H = 12 (1536), where the single launch gains
-// nothing and the row sums cost the dO GEMM more than they do inside the dQ kernel.
+// nothing and the row sums cost the dO GEMM more than they do inside the dQ kernel.  With the kernels as they are now the whole
+// backward takes (one launch / two) 59.5 / 63.3 us at 150 tokens, 109.6 / 111.5 at 321, 135.4 / 139.6 at 420, 185.3 / 185.9 at
+// 543, 236.2 / 234.0 at 700, 311.2 / 312.3 at 862; 470.9 / 468.1 at 1936 with B = 8, H = 12.
 bool sdpa_bwd_paired(const SdpaArgs& a) {
   return !ring_fills(a, 128) || (long long)vd_ceil_div(a.n, 128) * a.H * a.B < 1536;   // (64-row blocks: always)
 }

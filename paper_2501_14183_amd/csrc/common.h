@@ -140,6 +140,10 @@ __host__ __device__ static inline int vd_attn_bf16_splitk(int d, long long M, bo
 //     columns, long slices) and d = 704 54.0 -> 64.4 at 4830 (the three rounds are full).
 //   Two against two: d = 320 34.4 -> 36.3 at 9800, d = 384 36.3 -> 40.2 at 9800, d = 448 36.5 -> 40.8 at 6348.
 // d = 128: 34.9 -> 43.6 at 32000 (32 weight-gradient workgroups).  d = 512 with 3840 rows: 27.3 -> 25.9 + 4.8 for the sum.
+// (Those figures are from before the copies ran at their full rate.  The whole backward since, few -> many with the sum of
+// slices, B = 32, up to 4608 rows: d = 512 29.2 -> 38.2 us at 2048 rows, 37.5 -> 42.4 at 3328, 41.8 -> 44.9 at 4096; d = 768 53.4 ->
+// 61.7, 69.6 -> 68.9, 78.7 -> 76.4; d = 640 51.1 -> 54.4, 62.3 -> 60.8, 67.1 -> 64.1; d = 384 27.5 -> 34.1, 35.3 -> 36.5, 38.6 -> 37.9; d = 256
+// 24.1 -> 28.0, 33.0 -> 30.3, 36.9 -> 30.9.  What the last would gain, a count of half its bound would lose.)
 // With a device-side count the bound decides.  Counts near it gain as above, counts far below it lose: d = 512, bound 6144
 // rows, 6080 rows 43.2 -> 38.2, 4160 44.8 -> 31.9, 3200 27.4 -> 28.5; bound 6896, 4000 rows 31.8 -> 30.6, 720 20.2 -> 24.8.
 static inline bool vd_attn_bf16_many_tokens(int d, long long M) {
