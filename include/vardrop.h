@@ -305,8 +305,7 @@ int vardrop_embed_bwd_dev(vardrop_ctx* ctx, const void* dxs, int B, const int32_
  *   xs, y, dy, dxs   [B][n][d]        element type `dtype`
  *   Wq, Wk, Wv, Wo   [d][d] row-major (y = x W), `dtype`; biases [d], `dtype`, NULL = none
  *   saved            vardrop_attn_saved_bytes: Q, K, V, O in `dtype` and the row log-sum-exp
- *                    in fp32; written by fwd, read by bwd (VARDROP_BF16: Q times log2(e) / sqrt(d_k),
- *                    rounded once)
+ *                    in fp32; written by fwd, read by bwd
  *   dWq..dWo         fp32 [d][d], overwritten;  dbq..dbo fp32 [d], overwritten, NULL = skip
  * VARDROP_BF16 multiplies bf16 operands on the matrix cores with fp32 accumulation and
  * fp32 softmax, and requires d_k == 64 and d % 64 == 0; VARDROP_F32 multiplies and sums in fp32 (long

@@ -19,10 +19,7 @@ namespace {
 // ================================================================== attention core (d_k = 64)
 constexpr int kDh = 64;
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
-// Q is kept as (xs Wq + bq) * log2(e) / sqrt(d_k): the factor goes in before the rounding to bf16, so nothing is rounded
-// twice, and the products with K are exponents of two as they leave the matrix pipe (dK = dS^T Q / sqrt(d_k) then takes
-// ln 2 for a factor).
+constexpr float kRootDh = 8.f;                 // sqrt(d_k)
 
 // a lane's row of a head slice as four right-hand (or left-hand) operands: k = 16*s + 8*half + e
 __device__ inline void row_frags(Frag f[4], const bf16_t* P, long long ld, int row, int n, int half) {
@@ -53,7 +50,7 @@ struct SdpaArgs {
   const bf16_t *dy, *wo;          // short selections: dO is formed inside the kernel from dy and Wo
   bf16_t *out, *dq, *dk, *dv;
   float* lse;
-  float *Dsum, *nlse2;            // long selections: -rowsum(dO * O), and -log2(e) * lse for the dK/dV part
+  float *Dsum, *nlse;             // long selections: -rowsum(dO * O), and -sqrt(d_k) * lse for the dK/dV part
   int n, d, H;
   float scale;
   const int32_t* n_dev;           // device-side token count (then n is its bound, see vd_count)
@@ -190,13 +187,14 @@ __device__ inline bool ring_block(SdpaArgs& a, int rows, int parts, int& xb, int
 // S^T = K q^T, online softmax on per-lane scalars, O^T = V^T P^T with the probability registers as the
 // right-hand operand.
 // What bounds it: with d_k = 64 a 32 x 32 tile of scores costs 8 matrix instructions (256 clocks) and, per score, an
-// exponential (8 clocks a wavefront), an addition and half a conversion (4 clocks each) on the vector pipe of the same
+// exponential (8 clocks a wavefront), a multiply-add, an addition and half a conversion (4 clocks each) on the vector pipe of the same
 // SIMD.  A probe with both kinds on one SIMD shows them overlapping fully between wavefronts; here the three wavefronts
 // of a SIMD overlap them for 40 % of the matrix time only, so every vector instruction in the loop counts.
 // Without the maximum per block, with scalar copy addresses and immediate read offsets: 143 -> 117 us at 1924 tokens
-// (B = 8, H = 12; 0.84 PFLOP/s), 82 -> 69 us at 862 (B = 32, H = 8).  With the scale in Q and the accumulators of the
-// scores starting at minus the reference (no multiply-add per score): 119 -> 113 us and 84 -> 80 us on one machine.  Tried:
-// fixed priorities by wavefront slot instead of priority while feeding the matrix pipe 125 us, no priorities 117 us.
+// (B = 8, H = 12; 0.84 PFLOP/s), 82 -> 69 us at 862 (B = 32, H = 8).  Without the multiply-add per score, with the scale in Q
+// before its rounding and accumulators that start at minus the reference, 125 -> 118 and 68 -> 63 us; but a caller reads Q
+// from `saved`, and the scaled one is another tensor.  Tried: fixed priorities by wavefront slot instead of priority while
+// feeding the matrix pipe 125 us against 113, no priorities 117.
 __device__ __forceinline__ float other_half(float v) {       // the value of lane ^ 32
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float((threadIdx.x & 32) ? r[0] : r[1]);
@@ -222,9 +220,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
   row_frags(qf, a.q + base, ld, qi, n, half);
   const RingAddr ra = ring_addr(smem, lane);
   floatx16 acc[2] = {zero16(), zero16()};
-  float m = 0.f, l = 0.f;
-  floatx16 nm16 = zero16();                    // -m, what the accumulators of the scores start with
+  float m = -INFINITY, l = 0.f;
   bool careful = true;                         // form a block's maximum first (the same for the whole wavefront)
+  const float c = a.scale * kLog2e;
   auto step = [&](auto stage, int j) __attribute__((always_inline)) {
     constexpr int ST = decltype(stage)::value, SO = ST * kRingStage;
     // block j has landed once only the copies of block j+1 are in flight; behind the barrier everyone's have,
@@ -236,7 +234,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
     Frag fa[4], fb[4];
 #define VD_S_STEP(F, KT, S, PENDING)                                                    \
   wait_lds<PENDING>(F[S]);                                                              \
-  st[KT] = mfma(F[S], qf[S], (S) == 0 ? nm16 : st[KT]);                                 \
+  st[KT] = mfma(F[S], qf[S], (S) == 0 ? zero16() : st[KT]);                             \
   __builtin_amdgcn_sched_barrier(0);
     // the scores of block j; keys past the end (only in the last block) get -inf
 #define VD_SCORES()                                                                     \
@@ -254,13 +252,13 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
         st[kt][r] = key < n ? st[kt][r] : -INFINITY;                                    \
       }                                                                                 \
   }
-    // exp2(score - reference) and their sum; the accumulators hold the difference already, up to a MOVE of the reference
-#define VD_EXP_SUM(RS, MOVE)                                                            \
+    // exp2(c s - reference) as one fused multiply-add and the exponential, and their sum
+#define VD_EXP_SUM(RS)                                                                  \
   {                                                                                     \
     float r0 = 0.f, r1 = 0.f;                                                           \
     _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                    \
-      st[0][r] = fast_exp2(st[0][r] MOVE);                                              \
-      st[1][r] = fast_exp2(st[1][r] MOVE);                                              \
+      st[0][r] = fast_exp2(fmaf(st[0][r], c, -m));                                      \
+      st[1][r] = fast_exp2(fmaf(st[1][r], c, -m));                                      \
       r0 += st[0][r];                                                                   \
       r1 += st[1][r];                                                                   \
     }                                                                                   \
@@ -282,7 +280,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
     float rs = 0.f;
     bool redo = careful;
     if (!redo) {
-      VD_EXP_SUM(rs, )
+      VD_EXP_SUM(rs)
       redo = __any(!(rs <= kSumMax));
       if (redo) {
         wait_lds<0>(fa[0], fa[1], fa[2], fa[3]);
@@ -297,21 +295,19 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
       for (int kt = 0; kt < 2; ++kt)
 #pragma unroll
         for (int r = 0; r < 16; ++r) mt = fmaxf(mt, st[kt][r]);
-      mt = fmaxf(mt, other_half(mt));                 // relative to the reference
-      float move = 0.f;                               // (the first block sets the reference: nothing to rescale yet)
-      if (j == 0 || mt > kSlack) move = (m + mt) - m;
-      if (j > 0 && __any(move != 0.f)) {
-        const float alpha = fast_exp2(-move);
+      mt = fmaxf(mt, other_half(mt));
+      const float mc = mt * c;                        // c > 0: scaling commutes with the maximum
+      const float mn = mc > m + kSlack ? mc : m;
+      if (__any(mn != m)) {
+        const float alpha = fast_exp2(m - mn);
         l *= alpha;
 #pragma unroll
         for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
           for (int r = 0; r < 16; ++r) acc[dt][r] *= alpha;
       }
-      m += move;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) nm16[r] = -m;
-      VD_EXP_SUM(rs, - move)
+      m = mn;
+      VD_EXP_SUM(rs)
       careful = j > 0 || __any(rs < 1.f / kSumMax);
     }
     l += rs;
@@ -352,12 +348,11 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
 // or comes with dO from the GEMM before; Dsum holds -D, with which the accumulators of dP start, so that
 // dP - D costs no vector instruction (the vector pipe bounds these loops, as in the forward kernel): 172 -> 151 us at
 // 1924 tokens (B = 8, H = 12), the dK / dV part 224 -> 212 us, both parts in one launch 60 -> 53 us at 321 (B = 32, H = 8).
-// With the scale in Q (and, in the dK / dV part, scores that start at -log2(e) lse): 155 -> 151, 216 -> 208 and 58.6 -> 54.6
-// us on another machine.
 // What bounds them: 12 and 16 matrix instructions per 32 x 32 scores (384 and 512 clocks) beside 240 clocks on the vector pipe and
 // 210 and 420 of the LDS; one wavefront does these one after the other, so three wavefronts a SIMD (168 registers) matter: in the
-// dK / dV part every Q^T fragment is requested when a dO^T fragment has been used and takes its registers (197 -> 182 us at
-// 1924 tokens, both parts in one launch 53 -> 46 at 321); in the dQ part scores start at -log2(e) lse too (145 -> 138).
+// dK / dV part every Q^T fragment is requested when a dO^T fragment has been used and takes its registers and the
+// scores start at -sqrt(d_k) lse, which leaves a multiplication per score and keeps the log-sum-exp out of the loop's registers
+// (229 -> 201 us at 1924 tokens, both parts in one launch 50.5 -> 41.3 at 321).
 template <int NW, bool DLOCAL>
 __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int h, int b) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -391,9 +386,10 @@ __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int 
     nD = a.Dsum[srow + min(qi, n - 1)];
   }
   const float nlse2 = qi < n ? -a.lse[srow + qi] * kLog2e : -INFINITY;   // (-inf for a query past the end)
-  floatx16 nD16, nl16;                         // what the accumulators of dP and of the scores start with
+  const float c = a.scale * kLog2e;
+  floatx16 nD16;                               // what the accumulators of dP start with
 #pragma unroll
-  for (int r = 0; r < 16; ++r) { nD16[r] = nD; nl16[r] = nlse2; }
+  for (int r = 0; r < 16; ++r) nD16[r] = nD;
   const RingAddr ra = ring_addr(smem, lane);
   floatx16 acc[2] = {zero16(), zero16()};
   auto step = [&](auto stage, int j) __attribute__((always_inline)) {
@@ -415,15 +411,15 @@ __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int 
     Frag fk[4], fv[4], ft[4];                                                                            \
     VD_ROW4(fk, 0, KT, SO)              /* (the V fragments follow one by one: they can take the K fragments' registers) */ \
     __builtin_amdgcn_s_setprio(1);                                                                       \
-    VD_DQ_STEP(st, fk, qf, 0, nl16, 3)     VD_ROW1(fv, 0, 1, KT, SO)                                     \
-    VD_DQ_STEP(st, fk, qf, 1, nl16, 3)     VD_ROW1(fv, 1, 1, KT, SO)                                     \
-    VD_DQ_STEP(st, fk, qf, 2, nl16, 3)     VD_ROW1(fv, 2, 1, KT, SO)                                     \
-    VD_DQ_STEP(st, fk, qf, 3, nl16, 3)     VD_ROW1(fv, 3, 1, KT, SO)                                     \
+    VD_DQ_STEP(st, fk, qf, 0, zero16(), 3) VD_ROW1(fv, 0, 1, KT, SO)                                     \
+    VD_DQ_STEP(st, fk, qf, 1, zero16(), 3) VD_ROW1(fv, 1, 1, KT, SO)                                     \
+    VD_DQ_STEP(st, fk, qf, 2, zero16(), 3) VD_ROW1(fv, 2, 1, KT, SO)                                     \
+    VD_DQ_STEP(st, fk, qf, 3, zero16(), 3) VD_ROW1(fv, 3, 1, KT, SO)                                     \
     VD_DQ_STEP(dp, fv, dof, 0, nD16, 3) VD_DQ_STEP(dp, fv, dof, 1, nD16, 2)                              \
     VD_DQ_STEP(dp, fv, dof, 2, nD16, 1) VD_DQ_STEP(dp, fv, dof, 3, nD16, 0)                              \
     __builtin_amdgcn_s_setprio(0);                                                                       \
     VD_TR4(ft, 0, KT, SO)                                                                                \
-    _Pragma("unroll") for (int r = 0; r < 16; ++r) st[r] = fast_exp2(st[r]) * dp[r];                     \
+    _Pragma("unroll") for (int r = 0; r < 16; ++r) st[r] = fast_exp2(fmaf(st[r], c, nlse2)) * dp[r];     \
     if (tail) {                                 /* a key past the end repeats the last one: its dS is dropped */ \
       _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                                   \
         const int key = j * 64 + (KT) * 32 + 8 * (r >> 2) + 4 * half + (r & 3);                          \
@@ -450,13 +446,13 @@ __device__ __forceinline__ void sdpa_bwd_dq_body(const SdpaArgs& a, int qb, int 
     store_accT(row, acc[1], 1, half2, a.scale);
     if (DLOCAL && half2 == 0) {
       a.Dsum[srow + qo] = nD16[0];
-      a.nlse2[srow + qo] = nl16[0];
+      a.nlse[srow + qo] = -kRootDh * a.lse[srow + qo];
     }
   }
 }
 
 // ---- backward, part 2: dK and dV.  A wavefront owns 32 keys (lane = key), loop over query blocks: a stage holds
-// the Q and dO tiles of 64 queries, their -log2(e) lse and their -D, which the accumulators of S and dP start with.
+// the Q and dO tiles of 64 queries, their -sqrt(d_k) lse and their -D, which the accumulators of S and dP start with.
 // S = Q k^T and dP = dO v^T from row fragments; P and dS in registers are the right-hand operands of dV^T = dO^T P and dK^T = Q^T dS, whose left
 // operands are the same tiles read transposed.
 template <int NW>
@@ -473,9 +469,9 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
   const int kj = (kb * NW + wave) * 32 + col;
   const int nb = (n + 63) >> 6;
   const RingSrc<NW> src = ring_src<NW>(ld, wave, lane);
-  // even wavefronts copy the block's -log2(e) * log-sum-exp values, odd ones its -D (NW is even); queries past n
+  // even wavefronts copy the block's -sqrt(d_k) * log-sum-exp values, odd ones its -D (NW is even); queries past n
   // repeat the last
-  const copy_src stat = copy_source((const bf16_t*)((wave & 1) ? a.Dsum + srow : a.nlse2 + srow));
+  const copy_src stat = copy_source((const bf16_t*)((wave & 1) ? a.Dsum + srow : a.nlse + srow));
   const int stat_off = 2 * kRingTile + (wave & 1) * 256;
 #define VD_ISSUE_Q(J, BUF)                                                                            \
   {                                                                                                   \
@@ -492,6 +488,7 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
   const RingAddr ra = ring_addr(smem, lane);
   const uint32_t stat_addr = ra.lds0 + 2 * kRingTile + 16 * half;   // + 32 per 8 queries
   floatx16 accK[2] = {zero16(), zero16()}, accV[2] = {zero16(), zero16()};
+  const float c = a.scale * kLog2e;
   auto step = [&](auto stage, int i) __attribute__((always_inline)) {
     constexpr int ST = decltype(stage)::value, SO = ST * kRingStage;
     if (i + 1 < nb) wait_vm<LPS>(); else wait_vm<0>();
@@ -502,7 +499,7 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
   {                                                                                                      \
     Acc16 st, dp;                                                                                        \
     Frag fq[4], fo[4];                                                                                   \
-    /* -log2(e) lse, then -D, of queries 32 QT + 8 q4 + 4 half + 0..3, the rows of registers 4 q4 .. 4 q4 + 3 */\
+    /* -sqrt(d_k) lse, then -D, of queries 32 QT + 8 q4 + 4 half + 0..3, the rows of registers 4 q4 .. 4 q4 + 3 */\
     lds_read16_at<SO + (QT) * 128>(st.q[0], stat_addr);                                                  \
     lds_read16_at<SO + (QT) * 128 + 32>(st.q[1], stat_addr);                                             \
     lds_read16_at<SO + (QT) * 128 + 64>(st.q[2], stat_addr);                                             \
@@ -526,7 +523,7 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
     __builtin_amdgcn_sched_barrier(0);                                                                   \
     VD_TR4(fo, 1, QT, SO)                       /* dO^T */                                               \
     _Pragma("unroll") for (int r = 0; r < 16; ++r) {                                                     \
-      st.f[r] = fast_exp2(st.f[r]);                                                                      \
+      st.f[r] = fast_exp2(st.f[r] * c);                                                                  \
       dp.f[r] *= st.f[r];                                                                                \
     }                                                                                                    \
     if (tail) {                                 /* a query past the end repeats the last one: dropped */ \
@@ -560,8 +557,8 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
   if (ko < n) {
     bf16_t* rk = a.dk + base + (long long)ko * ld;
     bf16_t* rv = a.dv + base + (long long)ko * ld;
-    store_accT(rk, accK[0], 0, half2, kLn2);
-    store_accT(rk, accK[1], 1, half2, kLn2);
+    store_accT(rk, accK[0], 0, half2, a.scale);
+    store_accT(rk, accK[1], 1, half2, a.scale);
     store_accT(rv, accV[0], 0, half2, 1.f);
     store_accT(rv, accV[1], 1, half2, 1.f);
   }
@@ -572,7 +569,7 @@ __device__ __forceinline__ void sdpa_bwd_dkv_body(const SdpaArgs& a, int kb, int
 #undef VD_TR4
 #undef VD_TR1
 
-// Many workgroups: two launches, -D = -rowsum(dO * O) and -log2(e) * lse written by the dQ kernel, whose matrix work
+// Many workgroups: two launches, -D = -rowsum(dO * O) and -sqrt(d_k) * lse written by the dQ kernel, whose matrix work
 // hides the read of O.
 template <int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(3))) void sdpa_bwd_dq_bf16(SdpaArgs a) {
@@ -588,7 +585,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
 }
 // Few workgroups: one launch, so that the two parts fill the chip's places together.  Of the workgroups of a
 // (batch, head) pair the first half take query blocks (dQ), the second half key blocks (dK, dV); neither part
-// reads what the other writes: -D and -log2(e) * lse come with dO from the GEMM before.
+// reads what the other writes: -D and -sqrt(d_k) * lse come with dO from the GEMM before.
 template <int NW>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4 ? 3 : 2))) void sdpa_bwd_dqkv_bf16(SdpaArgs a) {
   int xb, h, b;
@@ -609,8 +606,8 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(NW == 4
 //            reads (contraction over keys).
 // What bounds it (clock readings at 104 tokens, d = 512, 28 000 clocks in all): the dO product waited 10 500 clocks for eight
 // slices of which each took a round trip to memory; with a third copy stage, in the place of the dO tile and of an O tile that
-// registers replace (120 instead of 128 KB of LDS), and with scores and dP that start at -log2(e) lse and -D in their
-// accumulators 16.9 -> 15.0 us (89 tokens, 15.1 -> 12.9; a fourth stage 14.8 and 13.1).
+// registers replace (120 instead of 128 KB of LDS), and with accumulators of dP that start
+// at -D 16.9 -> 15.0 us (89 tokens, 15.1 -> 12.9; a fourth stage 14.8 and 13.1).
 // Tiles are [token][64] with the 16-byte chunk position XORed with token % 8, as the copies write them.
 constexpr int kSmallN = 128;
 constexpr int kDsPitch = 272;                 // bytes per dS^T row: 128 queries * 2 + 16
@@ -653,7 +650,7 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
   unsigned char* Vs = Qs + kSmallTile;
   unsigned char* dOs = Vs + kSmallTile;
   unsigned char* dSt = dOs + kSmallTile;                                  // [key][kDsPitch]
-  float* nLs = reinterpret_cast<float*>(dSt + kSmallN * kDsPitch);        // -log2(e) lse, -inf past the last query
+  float* nLs = reinterpret_cast<float*>(dSt + kSmallN * kDsPitch);        // -log2(e) lse, -inf past the last query (the exponent's multiply-add takes it)
   float* nDs = nLs + kSmallN;                                             // -D
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blk = wave & 3, part = wave >> 2;
@@ -803,6 +800,7 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
   __syncthreads();
 
   // ---- phase 1: lane = key; this wavefront's query tiles are 2*part and 2*part + 1
+  const float c = a.scale * kLog2e;
   const int kj = blk * 32 + col;
   floatx16 accK[2] = {zero16(), zero16()}, accV[2] = {zero16(), zero16()};
   {
@@ -816,14 +814,14 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
     for (int q2 = 0; q2 < 2; ++q2) {
       const int qt = 2 * part + q2;
       if (qt * 32 >= n) break;
-      // the accumulators start at -log2(e) lse and -D of the tile's queries
-      Acc16 st0, dp0;
+      // the accumulators of dP start at -D of the tile's queries
+      Acc16 nl, dp0;
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
-        st0.q[q4] = *reinterpret_cast<const u32x4*>(nLs + qt * 32 + 8 * q4 + 4 * half);
+        nl.q[q4] = *reinterpret_cast<const u32x4*>(nLs + qt * 32 + 8 * q4 + 4 * half);
         dp0.q[q4] = *reinterpret_cast<const u32x4*>(nDs + qt * 32 + 8 * q4 + 4 * half);
       }
-      floatx16 st = st0.f, dp = dp0.f;
+      floatx16 st = zero16(), dp = dp0.f;
 #pragma unroll
       for (int s = 0; s < 4; ++s) {
         st = mfma(small_row_frag(Qs, qt * 32 + col, 2 * s + half), kf[s], st);     // S[query][key]
@@ -831,7 +829,7 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
       }
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        st[r] = fast_exp2(st[r]);
+        st[r] = fast_exp2(fmaf(st[r], c, nl.f[r]));
         dp[r] *= st[r];
       }
       if (blk * 32 + 32 > n) {            // a key past the end repeats the last one: dropped
@@ -894,7 +892,7 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
       }
     if (kj < n) {
       bf16_t* row = (part == 0 ? a.dk : a.dv) + base + (long long)kj * ld;
-      const float mul = part == 0 ? kLn2 : 1.f;
+      const float mul = part == 0 ? a.scale : 1.f;
       store_accT(row, mine[0], 0, half, mul);
       store_accT(row, mine[1], 1, half, mul);
     }
@@ -960,7 +958,7 @@ struct FusedFwdArgs {
   bf16_t *q, *k, *v, *o;
   float* lse;
   int n, d, H;
-  float q_mul;                    // what Q is multiplied by before it is rounded (kLog2e / sqrt(d_k))
+  float scale;
   const int32_t* n_dev;           // device-side token count (then n is its bound, see vd_count)
   int32_t* status;
 };
@@ -1136,7 +1134,6 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
     const int ct = 3 * wc + j, z = ct >> 1;
     const bf16_t* bias = z == 0 ? a.bq : (z == 1 ? a.bk : a.bv);
     const int row = wr * 32 + col;
-    const float mul = z == 0 ? a.q_mul : 1.f;
     if (bias) {
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
@@ -1151,8 +1148,8 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
 #pragma unroll
       for (int e = 0; e < 2; ++e) {
         const int r = 4 * (g2 + e);
-        o[e].x = pack2(acc[j][r] * mul, acc[j][r + 1] * mul);
-        o[e].y = pack2(acc[j][r + 2] * mul, acc[j][r + 3] * mul);
+        o[e].x = pack2(acc[j][r], acc[j][r + 1]);
+        o[e].y = pack2(acc[j][r + 2], acc[j][r + 3]);
       }
       *reinterpret_cast<u32x4*>(smem + z * kSmallTile + row * 128 + (((4 * (ct & 1) + g2 + half) ^ tile_swz(row)) * 16)) = quads16(o[0], o[1]);
     }
@@ -1184,6 +1181,7 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
   Frag qf[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) qf[s] = small_row_frag(Qs, qi, 2 * s + half);
+  const float c = a.scale * kLog2e;
   floatx16 st[2];
   float m = -INFINITY;
 #pragma unroll
@@ -1194,6 +1192,8 @@ __global__ __launch_bounds__(512) void attn_fwd_small_bf16(FusedFwdArgs a) {
 #pragma unroll
       for (int s = 0; s < 4; ++s) st[k2] = mfma(small_row_frag(Ks, kt * 32 + col, 2 * s + half), qf[s], st[k2]);
     }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) st[k2][r] *= c;
     if (kt * 32 + 32 > n) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
@@ -1318,7 +1318,7 @@ size_t vd_attn_bf16_ws_bytes(int B, int n, int d, int H) {
   return vd_attn_bf16_partial_offset(B, n, d, H) + (size_t)4 * vd_attn_bf16_max_splitk(d, (long long)B * n) * d * d * sizeof(float);
 }
 
-// saved: q (times log2(e) / sqrt(d_k)), k, v, o ([M][d] bf16 each, M = B*n) then lse fp32 [B][H][n]
+// saved: q, k, v, o ([M][d] bf16 each, M = B*n) then lse fp32 [B][H][n]
 // With `sel` (device, n ascending rows of [0, N)), `xs` holds the tokens of all N variates and the kept ones are
 // gathered on the way: inside the fused kernel for short selections, by the gather kernel otherwise; either
 // way `xs_out` [B][n][d] receives them.
@@ -1354,7 +1354,7 @@ int vd_attn_fwd_bf16(vardrop_ctx* ctx, const void* xs, int B, int n, int d, int 
     f.Wq = (const bf16_t*)W[0]; f.Wk = (const bf16_t*)W[1]; f.Wv = (const bf16_t*)W[2];
     f.bq = (const bf16_t*)bias[0]; f.bk = (const bf16_t*)bias[1]; f.bv = (const bf16_t*)bias[2];
     f.q = q; f.k = k; f.v = v; f.o = o; f.lse = lse;
-    f.n = n; f.d = d; f.H = H; f.q_mul = kLog2e / sqrtf((float)kDh);
+    f.n = n; f.d = d; f.H = H; f.scale = 1.0f / kRootDh;
     f.n_dev = dn.dev; f.status = dn.status;
     static int configured_device = -1;
     if (configured_device != ctx->device) {
@@ -1372,13 +1372,12 @@ int vd_attn_fwd_bf16(vardrop_ctx* ctx, const void* xs, int B, int n, int d, int 
     for (int z = 0; z < 3; ++z) g.set(z, xs, W[z], qkv[z], bias[z]);
     g.lda = d; g.ldb = d; g.ldc = d;
     g.M = (int)M; g.N = d; g.K = d; g.nseg = 1;
-    g.c0_mul = kLog2e / sqrtf((float)kDh);
     if (dn.dev) g.count_rows(dn.dev, counted ? nullptr : dn.status, n, B);
     rc = vd_gemm_bf16(ctx, VARDROP_K_GEMM_QKV, g, 3, false, s);
     if (rc) return rc;
     SdpaArgs a = {};
     a.q = q; a.k = k; a.v = v; a.out = o; a.lse = lse;
-    a.n = n; a.d = d; a.H = H; a.B = B;
+    a.n = n; a.d = d; a.H = H; a.B = B; a.scale = 1.0f / kRootDh;
     a.n_dev = dn.dev;
     rc = launch_sdpa_fwd(ctx, a, s);
     if (rc) return rc;
@@ -1391,7 +1390,7 @@ int vd_attn_fwd_bf16(vardrop_ctx* ctx, const void* xs, int B, int n, int d, int 
   return vd_gemm_bf16(ctx, VARDROP_K_GEMM_OUT, go, 1, false, s);
 }
 
-// ws: dO, dq, dk, dv ([M][d] bf16 each), -D and -log2(e) lse, fp32 [B][H][n] each, then the split-K partial products
+// ws: dO, dq, dk, dv ([M][d] bf16 each), -D and -sqrt(d_k) lse, fp32 [B][H][n] each, then the split-K partial products
 // (with a device-side count: sub-buffers placed for the bound n, rows packed for the actual count, as in the forward)
 int vd_attn_bwd_bf16(vardrop_ctx* ctx, const void* dy, const void* xs, int B, int n, int d, int H,
                      const void* const W[4], const void* saved, void* dxs,
@@ -1407,7 +1406,7 @@ int vd_attn_bwd_bf16(vardrop_ctx* ctx, const void* dy, const void* xs, int B, in
   bf16_t* dk = dq + M * d;
   bf16_t* dv = dk + M * d;
   float* D = (float*)(dv + M * d);
-  float* nlse2 = D + (size_t)B * H * n;
+  float* nlse = D + (size_t)B * H * n;
   int rc;
   SdpaArgs a = {};
   a.n = n; a.d = d; a.H = H; a.B = B;
@@ -1418,9 +1417,9 @@ int vd_attn_bwd_bf16(vardrop_ctx* ctx, const void* dy, const void* xs, int B, in
     g.set(0, dy, W[3], dO, nullptr);
     g.lda = d; g.ldb = d; g.ldc = d;
     g.M = (int)M; g.N = d; g.K = d; g.nseg = 1;
-    if (paired) {     // -D = -rowsum(dO * O) per head from the same tiles, and -log2(e) * lse beside it
+    if (paired) {     // -D = -rowsum(dO * O) per head from the same tiles, and -sqrt(d_k) * lse beside it
       g.rs_o = o; g.rs_out = D; g.rs_mul = -1.f; g.rs_n = n; g.rs_H = H;
-      g.rs_aux_in = lse; g.rs_aux_out = nlse2; g.rs_aux_mul = -kLog2e;
+      g.rs_aux_in = lse; g.rs_aux_out = nlse; g.rs_aux_mul = -kRootDh;
     }
     if (dn.dev) g.count_rows(dn.dev, dn.status, n, B);
     if ((rc = vd_gemm_bf16(ctx, VARDROP_K_GEMM_DO, g, 1, true, s))) return rc;
@@ -1428,9 +1427,9 @@ int vd_attn_bwd_bf16(vardrop_ctx* ctx, const void* dy, const void* xs, int B, in
     a.status = dn.status;
   }
   a.q = q; a.k = k; a.v = v; a.o = o; a.dout = dO; a.lse = const_cast<float*>(lse);
-  a.dq = dq; a.dk = dk; a.dv = dv; a.Dsum = D; a.nlse2 = nlse2;
+  a.dq = dq; a.dk = dk; a.dv = dv; a.Dsum = D; a.nlse = nlse;
   a.dy = (const bf16_t*)dy; a.wo = (const bf16_t*)W[3];
-  a.scale = 1.0f / sqrtf((float)kDh);
+  a.scale = 1.0f / kRootDh;
   if (n <= kSmallN) {
     static int configured_device = -1;
     if (configured_device != ctx->device) {

@@ -12,7 +12,6 @@ struct GemmBf16 {
   const bf16_t *B0, *B1, *B2, *B3;
   void *C0, *C1, *C2, *C3;
   const bf16_t *bias0, *bias1, *bias2, *bias3;
-  float c0_mul;       // != 0: C0 (bf16 output) is multiplied by it, bias included, before it is rounded
   int lda, ldb, ldc;
   int M, N, K;
   int nseg;           // > 1: segments accumulate into C0

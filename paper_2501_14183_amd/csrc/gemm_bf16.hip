@@ -339,7 +339,6 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
   // ---- epilogue.  acc[i][j] register 4*q4 + e is C[wm*MROWS + i*32 + col][wn*64 + j*32 + 8*q4 + 4*half + e]
   // of the tile; it is written to LDS (with the bias), then stored as 16-byte chunks of whole rows.
   const bf16_t* bias = SPLIT ? nullptr : (zsel == 0 ? g.bias0 : (zsel == 1 ? g.bias1 : (zsel == 2 ? g.bias2 : g.bias3)));
-  const float cmul = !SPLIT && zsel == 0 && g.c0_mul != 0.f ? g.c0_mul : 1.f;
   __syncthreads();                        // every wavefront is done reading the last slice
   if constexpr (KH) {
     // the upper K half hands its sums over through LDS; the lower half adds them to its own (lower + upper)
@@ -396,8 +395,8 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
 #pragma unroll
           for (int e = 0; e < 2; ++e) {
             const int r = 4 * (g2 + e);
-            o[e].x = pack2((acc[i][j][r] + bv[e][0]) * cmul, (acc[i][j][r + 1] + bv[e][1]) * cmul);
-            o[e].y = pack2((acc[i][j][r + 2] + bv[e][2]) * cmul, (acc[i][j][r + 3] + bv[e][3]) * cmul);
+            o[e].x = pack2(acc[i][j][r] + bv[e][0], acc[i][j][r + 1] + bv[e][1]);
+            o[e].y = pack2(acc[i][j][r + 2] + bv[e][2], acc[i][j][r + 3] + bv[e][3]);
           }
           *reinterpret_cast<u32x4*>(smem + (wm * MROWS + i * 32 + col) * CPITCH + (wn * 64 + j * 32 + 8 * (g2 + half)) * 2) = quads16(o[0], o[1]);
         }

@@ -228,6 +228,25 @@ def test_all_logits_of_every_query_far_from_zero(vd, ctx, n, d, H, dtype, sign):
     assert all(e <= tol for e in errs.values()), (tol, errs)
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+@pytest.mark.parametrize("B,n,bias", [(2, 1, False), (3, 61, True), (2, 128, False), (2, 129, True), (5, 300, False)])
+def test_saved_holds_q_k_v(vd, ctx, dtype, B, n, bias):
+    """`saved` begins with Q, K and V as documented.  Weights that permute and scale by powers of two, and biases of a few
+    bits, leave one rounding: that of the result."""
+    d, H = 128, 2
+    rng = np.random.default_rng(n)
+    td = torch_dtype(dtype)
+    xs = wl.quantise(rng.standard_normal((B, n, d)), "bf16")
+    W = [np.eye(d)[rng.permutation(d)] * 2.0 ** rng.integers(-2, 3, d) for _ in range(4)]
+    b = [rng.integers(-8, 9, d) / 4.0 for _ in range(4)] if bias else [np.zeros(d)] * 4
+    args = [to_dev(w, td) for w in W] + [H] + ([to_dev(v, td) for v in b] if bias else [])
+    y, saved = vd.vardrop_attn_fwd(ctx, to_dev(xs, td), *args)
+    torch.cuda.synchronize()
+    got = saved[:3 * B * n * d * y.element_size()].view(td).reshape(3, B, n, d).cpu()
+    for z in range(3):
+        assert torch.equal(got[z], torch.from_numpy(xs @ W[z] + b[z]).float().to(td)), "QKV"[z]
+
+
 @pytest.mark.parametrize("B,n", [(2, 129), (2, 192), (3, 300), (256, 300)])
 def test_softmax_reference_moves_between_key_blocks(vd, ctx, B, n):
     """Scores that leave the reference taken in an earlier block of 64 keys behind: by less than what the forward lets
