@@ -308,8 +308,10 @@ int vardrop_embed_bwd_dev(vardrop_ctx* ctx, const void* dxs, int B, const int32_
  *                    in fp32; written by fwd, read by bwd
  *   dWq..dWo         fp32 [d][d], overwritten;  dbq..dbo fp32 [d], overwritten, NULL = skip
  * VARDROP_BF16 multiplies bf16 operands on the matrix cores with fp32 accumulation and
- * fp32 softmax, and requires d_k == 64 and d % 64 == 0; VARDROP_F32 multiplies and sums in fp32 (long
- * products as six exact products of bf16 parts, closer to the exact sum) and requires d_k in {16, 32, 64, 128}.  n == 0 is a no-op (weight gradients zero-filled).
+ * fp32 softmax, and requires d_k == 64 and d % 64 == 0; VARDROP_F32 multiplies and sums in fp32 and
+ * requires d_k in {16, 32, 64, 128}.  (In long sums a product is six exact products of rounded bf16 parts:
+ * a sum of many like terms comes out closer to the exact one, a single term within 2^-23 instead of 2^-24.)
+ * n == 0 is a no-op (weight gradients zero-filled).
  * The backward recomputes the attention probabilities from Q, K and the saved
  * log-sum-exp; it does not store them.  VARDROP_BF16 also requires B*n*d < 2^31
  * (EUNSUPPORTED otherwise).  Sizes returned for n tokens also serve any call with fewer

@@ -1,20 +1,24 @@
 // fp32 GEMMs: fp32 operands, results and accumulation; the products are formed on the bf16 matrix instruction where K is long.
 //
 // v_mfma_f32_32x32x2_f32 has a sixteenth of the bf16 rate and bounded these products (83-90 of its 157 TFLOP/s).  An fp32
-// number is exactly the sum of three bf16 numbers (hi, mid, lo: 8 bits of the significand each, cut off, not rounded), and
-// every product of two of those is exact in fp32.  Six of the nine products are formed, the other three lie 2^-24 and
-// more below the full one: hi hi, which has accumulators of its own, and hi mid, mid hi, mid mid, hi lo, lo hi in a second set,
-// added at the end.  Per 16 k the large sums are rounded once instead of eight times, so the result is closer to the exact
-// one than the fp32 instruction's: 1.4e-7 of the result's norm against 4.0e-7 for 3392 x 512 x 512, 2.4e-7 against 6.1e-7
-// with K = 3392, and two to three times closer in every output of an attention layer.
-// The split needs finite operands (inf - inf): a tile with a result that is not finite is computed once more with the fp32
-// instruction, so infinities and NaN come out as they did.
+// number of magnitude 2^-110 and more is exactly the sum of three bf16 numbers: hi, mid, lo, each the nearest one to what is left.
+// Every product of two of those is exact in fp32, and six of the nine are formed: hi hi, which has accumulators of its own, and
+// hi mid, mid hi, mid mid, hi lo, lo hi in a second set, added at the end.  Of the others mid lo and lo mid are at most 2^-25
+// of the full one each, of either sign.  So a product by itself is off by at most 2 units of 2^-24 (1.69 over four million pairs,
+// rms 0.43) where the fp32 instruction rounds it once (1, rms 0.42); with parts cut off instead of rounded it was 7.2, rms 1.02, and
+// always short.  A running sum is rounded once per 16 k instead of eight times, which counts where many terms make the result:
+// 1.3e-7 of the result's norm from fp64 against 4.0e-7 for 3392 x 512 x 512, 1.7e-7 against 5.2e-7 with K = 3392, 1.5e-7 against
+// 3.8e-7 with scales spread over 2^24 along k, and 4.0-6.1e-7 against 8.6-14e-7 in the outputs of an attention layer.
+// What three bf16 numbers do not hold is found and computed once more with the fp32 instruction, a tile at a time: a number with
+// bits below 2^-133, the smallest bf16 number (lower bits of the remainder are set then), and infinities and NaN
+// (inf - inf: the result is not finite, as where hi rounds to infinity).  They come out as with that instruction alone.
 //
 // Tiles of 64 x 64, four wavefronts of one 32 x 32 block each, for the sake of many workgroups (a selection of a few thousand
 // token rows is 400 tiles).  What bounds it: a slice of 32 k costs the LDS 24 KB of writes at 80 bytes a clock and 48 KB of
-// reads at 256 (500 clocks, one after the other), a SIMD 384 clocks of matrix instructions and 88 vector instructions of
-// splitting; three workgroups share a compute unit and reach 1080 clocks a slice.  3328 x 512 x 1536: 62 -> 48 us, the
-// gradient launch of the same layer 141 -> 100 us.  Tried: one LDS buffer and four workgroups 47 and 107; fp32 by
+// reads at 256 (500 clocks, one after the other), a SIMD 384 clocks of matrix instructions and 104 vector instructions of
+// splitting; three workgroups share a compute unit and reach 1080 clocks a slice.  3328 x 512 x 1536: 66 -> 50 us, the
+// gradient launch of the same layer 150 -> 102 us (by parts cut off 47 and 98; with mid lo and lo mid too, whose products by themselves
+// are as good as the fp32 instruction's, forward and backward of the layer 86 + 158 -> 93 + 174 us).  Tried: one LDS buffer and four workgroups 47 and 107; fp32 by
 // asynchronous copies, split behind the LDS read by every wavefront for itself 53 and 116 (128 x 64 tiles: 61 and 115).
 // Global memory goes through registers, where it is split, into two LDS buffers of 32 k: edges and unaligned rows are
 // handled there with zeros, so the inner loop has no masks; loads are issued two slices ahead, one barrier per slice.
@@ -101,29 +105,33 @@ __device__ inline void fetch_inside(f32x4 (&v)[2], const float* __restrict__ P, 
 #pragma unroll
   for (int u = 0; u < 2; ++u) v[u] = *reinterpret_cast<const f32x4*>(base + off[u]);
 }
-// The three bf16 parts of a unit (four fp32 values) as 8 bytes each, to the planes of the operand.
+// The three bf16 parts of a unit (four fp32 values) as 8 bytes each, to the planes of the operand.  `lost` collects what is left
+// for the last part: the lower 16 bits of that say whether it is more than a bf16 number holds.
 //   KC: plane [64 rows][32 k], 64-byte rows, 16-byte chunk position XORed with swz_kc<32>(row)
 //   otherwise: plane [32 k][64], 128-byte rows, chunk position XORed with swz_nc<64>(k)
 template <bool KC>
-__device__ inline void put_split(unsigned char* lds, const f32x4 (&v)[2]) {
+__device__ inline void put_split(unsigned char* lds, const f32x4 (&v)[2], uint32_t& lost) {
 #pragma unroll
   for (int u = 0; u < 2; ++u) {
     const int i = u * 256 + threadIdx.x;
     const int c = KC ? i & 7 : i & 15, row = KC ? i >> 3 : i >> 4;
     const int addr = row * (KC ? 64 : 128) + (((c >> 1) ^ (KC ? swz_kc<kK>(row) : swz_nc<kT>(row))) * 16) + (c & 1) * 8;
-    uint32_t h[4], m[4], l[4];
+    u32x2 h, m, l;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float x = v[u][e];
-      h[e] = __float_as_uint(x);
-      const float r1 = x - __uint_as_float(h[e] & 0xffff0000u);      // exact: the lower 16 bits of the significand
-      m[e] = __float_as_uint(r1);
-      l[e] = __float_as_uint(r1 - __uint_as_float(m[e] & 0xffff0000u));   // exact, at most 8 bits
+    for (int e = 0; e < 4; e += 2) {
+      const float x0 = v[u][e], x1 = v[u][e + 1];
+      const uint32_t hw = pack2(x0, x1);
+      const float r0 = x0 - __uint_as_float(hw << 16), r1 = x1 - __uint_as_float(hw & 0xffff0000u);   // exact
+      const uint32_t mw = pack2(r0, r1);
+      const uint32_t l0 = __float_as_uint(r0 - __uint_as_float(mw << 16)), l1 = __float_as_uint(r1 - __uint_as_float(mw & 0xffff0000u));
+      lost |= l0 | l1;
+      h[e >> 1] = hw;
+      m[e >> 1] = mw;
+      l[e >> 1] = __builtin_amdgcn_perm(l1, l0, 0x07060302u);
     }
-    const uint32_t up = 0x07060302u;                                  // the upper halves of two words
-    *reinterpret_cast<u32x2*>(lds + addr) = u32x2{__builtin_amdgcn_perm(h[1], h[0], up), __builtin_amdgcn_perm(h[3], h[2], up)};
-    *reinterpret_cast<u32x2*>(lds + kPlane + addr) = u32x2{__builtin_amdgcn_perm(m[1], m[0], up), __builtin_amdgcn_perm(m[3], m[2], up)};
-    *reinterpret_cast<u32x2*>(lds + 2 * kPlane + addr) = u32x2{__builtin_amdgcn_perm(l[1], l[0], up), __builtin_amdgcn_perm(l[3], l[2], up)};
+    *reinterpret_cast<u32x2*>(lds + addr) = h;
+    *reinterpret_cast<u32x2*>(lds + kPlane + addr) = m;
+    *reinterpret_cast<u32x2*>(lds + 2 * kPlane + addr) = l;
   }
 }
 // k = 16 ks + 8 half + 0..7 of row / column mn0 + lane % 32 of a plane
@@ -174,9 +182,9 @@ __device__ inline f32x4 frag(const unsigned char* lds, int mn, int g, int half) 
   }
 }
 
-// One tile of the product in `acc`: by bf16 parts (SPLIT), or with the fp32 instruction.
+// One tile of the product: by bf16 parts (SPLIT; `lost`: see put_split), or with the fp32 instruction.
 template <bool AKC, bool BKC, bool VEC, bool SPLIT>
-__device__ __forceinline__ floatx16 gemm_f32_sum(const GemmF32& g, const DimsF32& dm, int bx, int by, int bz, unsigned char* smem) {
+__device__ __forceinline__ floatx16 gemm_f32_sum(const GemmF32& g, const DimsF32& dm, int bx, int by, int bz, unsigned char* smem, uint32_t& lost) {
   static_assert(VEC || !SPLIT, "by parts: aligned rows");
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 1, wn = wave & 1, col = lane & 31, half = lane >> 5;
@@ -227,8 +235,8 @@ __device__ __forceinline__ floatx16 gemm_f32_sum(const GemmF32& g, const DimsF32
   };
   auto store = [&](int s) {
     if constexpr (SPLIT) {
-      put_split<AKC>(smem + s * 2 * operand, ra[s]);
-      put_split<BKC>(smem + s * 2 * operand + operand, rb[s]);
+      put_split<AKC>(smem + s * 2 * operand, ra[s], lost);
+      put_split<BKC>(smem + s * 2 * operand + operand, rb[s], lost);
     } else {
       put<AKC, VEC>(smem + s * 2 * operand, ra[s], ia[s]);
       put<BKC, VEC>(smem + s * 2 * operand + operand, rb[s], ib[s]);
@@ -305,12 +313,13 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32& g, const DimsF32& d
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave >> 1, wn = wave & 1, col = lane & 31, half = lane >> 5;
   const int z = bz / dm.splitk, m0 = by * kT, n0 = bx * kT;
-  floatx16 acc = gemm_f32_sum<AKC, BKC, VEC, SPLIT>(g, dm, bx, by, bz, smem);
+  uint32_t lost = 0;
+  floatx16 acc = gemm_f32_sum<AKC, BKC, VEC, SPLIT>(g, dm, bx, by, bz, smem, lost);
   if constexpr (SPLIT) {
-    bool finite = true;
+    bool good = (lost & 0xffffu) == 0;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) finite = finite && fabsf(acc[r]) < INFINITY;
-    if (__syncthreads_or(!finite)) acc = gemm_f32_sum<AKC, BKC, VEC, false>(g, dm, bx, by, bz, smem);
+    for (int r = 0; r < 16; ++r) good = good && fabsf(acc[r]) < INFINITY;
+    if (__syncthreads_or(!good)) acc = gemm_f32_sum<AKC, BKC, VEC, false>(g, dm, bx, by, bz, smem, lost);
   }
   const float* bias = pick(z, g.bias0, g.bias1, g.bias2, g.bias3);
   float* C = pick(z, g.C0, g.C1, g.C2, g.C3);
@@ -330,8 +339,9 @@ __device__ __forceinline__ void gemm_f32_tile(const GemmF32& g, const DimsF32& d
   }
 }
 
+// (by parts: three workgroups a compute unit, the most its LDS holds; left to itself the compiler takes registers for two)
 template <bool AKC, bool BKC, bool VEC, bool SPLIT>
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g) {
+__global__ __launch_bounds__(256, SPLIT ? 3 : 1) void gemm_f32_kernel(GemmF32 g) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[SPLIT ? kLds : 4 * kOperand];
   DimsF32 dm;
   if (!resolve_f32(g, dm, !AKC)) return;
@@ -345,7 +355,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmF32 g) {
 // Input gradient and weight gradients of one layer depend on the same dQ, dK, dV and on nothing of each other: one
 // launch, the weight-gradient tiles (K = all tokens: the longer chains) first.
 template <bool SPLIT>
-__global__ __launch_bounds__(256) void gemm_f32_bwd_pair_kernel(GemmF32 gx, GemmF32 gw) {
+__global__ __launch_bounds__(256, SPLIT ? 3 : 1) void gemm_f32_bwd_pair_kernel(GemmF32 gx, GemmF32 gw) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[SPLIT ? kLds : 4 * kOperand];
   DimsF32 dx, dw;
   if (!resolve_f32(gx, dx, false) || !resolve_f32(gw, dw, true)) return;
