@@ -413,8 +413,8 @@ int sum_slices(vardrop_ctx* ctx, const GemmF32& g, int bound, hipStream_t s) {
 // d = 64 18.3 -> 20.2 and 48.1 -> 48.5 us (two slices a tile: the longer start and end of the parts cost more than they
 // save), d = 256 26.9 -> 27.0 and 39.4 -> 38.5 (256 rows), 52.7 -> 48.4 and 77.9 -> 70.2 (3200 rows), d = 512 38.6 -> 35.6
 // and 63.9 -> 58.2 (128 rows), 100 -> 81 and 195 -> 151 (3200), d = 1024 307 -> 234 and 627 -> 475 (3200).
-// (With a device-side count its bound decides.)
-bool by_parts(long long k) { return k >= 256; }
+// (With a device-side count its bound decides.)  Offsets within a tile have 32 bits there: up to 64 rows of 2^24.
+bool by_parts(const GemmF32& g, long long k) { return k >= 256 && g.lda <= (1 << 24) && g.ldb <= (1 << 24); }
 
 template <bool AKC, bool BKC>
 int launch_f32(vardrop_ctx* ctx, int kid, const GemmF32& g, int slices, hipStream_t s) {
@@ -422,7 +422,7 @@ int launch_f32(vardrop_ctx* ctx, int kid, const GemmF32& g, int slices, hipStrea
   if (grid >= (1ll << 31)) return VARDROP_EUNSUPPORTED;
   VdTimer timer(ctx, kid, s);
   if (!aligned4(g, AKC, BKC)) VD_KERNEL(ctx, (gemm_f32_kernel<AKC, BKC, false, false>), dim3((unsigned)grid), dim3(256), 0, s, g);
-  else if (by_parts(AKC ? (long long)g.K * (g.nseg > 1 ? g.nseg : 1) : g.K / slices)) VD_KERNEL(ctx, (gemm_f32_kernel<AKC, BKC, true, true>), dim3((unsigned)grid), dim3(256), 0, s, g);
+  else if (by_parts(g, AKC ? (long long)g.K * (g.nseg > 1 ? g.nseg : 1) : g.K / slices)) VD_KERNEL(ctx, (gemm_f32_kernel<AKC, BKC, true, true>), dim3((unsigned)grid), dim3(256), 0, s, g);
   else VD_KERNEL(ctx, (gemm_f32_kernel<AKC, BKC, true, false>), dim3((unsigned)grid), dim3(256), 0, s, g);
   VD_LAUNCH_CHECK(ctx);
   return VARDROP_OK;
@@ -449,7 +449,7 @@ int vd_gemm_f32_bwd_pair(vardrop_ctx* ctx, const GemmF32& gx, const GemmF32& gw,
   if (grid >= (1ll << 31)) return VARDROP_EUNSUPPORTED;
   {
     VdTimer timer(ctx, VARDROP_K_GEMM_DW_DXS, s);
-    if (by_parts(3ll * gx.K)) VD_KERNEL(ctx, gemm_f32_bwd_pair_kernel<true>, dim3((unsigned)grid), dim3(256), 0, s, gx, gw);
+    if (by_parts(gx, 3ll * gx.K)) VD_KERNEL(ctx, gemm_f32_bwd_pair_kernel<true>, dim3((unsigned)grid), dim3(256), 0, s, gx, gw);
     else VD_KERNEL(ctx, gemm_f32_bwd_pair_kernel<false>, dim3((unsigned)grid), dim3(256), 0, s, gx, gw);
   }
   VD_LAUNCH_CHECK(ctx);

@@ -140,3 +140,19 @@ def test_overflow(vd, L):
     clean[150] = False
     assert_close(xs[clean], x[0][clean], We, 4 * BOUND)
     assert not bool(torch.isfinite(xs[150][want[150].abs() > 3.5e38]).any())
+
+
+def test_very_wide_rows(vd):
+    """32 rows of the weights span more than 2^32 bytes."""
+    L, d = 256, 36_000_000
+    if torch.cuda.mem_get_info()[0] < 100 << 30:
+        pytest.skip("needs 100 GiB of free device memory")
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x, We = torch.randn((1, 1, L), generator=g, device="cuda"), torch.randn((L, d), generator=g, device="cuda")
+    xs, _ = vd.vardrop_embed_fwd(vd.Context(0), x, torch.zeros(1, dtype=torch.int32, device="cuda"), 1, We, None, False)
+    want, scale = (torch.zeros(d, dtype=torch.float64, device="cuda") for _ in range(2))
+    for k in range(L):
+        want += x[0, 0, k].double() * We[k]
+        scale += (x[0, 0, k].double() * We[k]).abs()
+    # (the fp32 instruction: 128 roundings of 2^-24 of at most all terms together)
+    assert bool(((xs[0, 0] - want).abs() <= 2.0 ** -17 * scale).all())
