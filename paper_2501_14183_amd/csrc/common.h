@@ -130,22 +130,24 @@ __host__ __device__ static inline int vd_attn_bf16_splitk(int d, long long M, bo
 // Many tokens begin at 512 input-gradient tiles of 128 rows, and earlier, from 148 on, where that adds no launch (more than
 // 4608 rows have several slices either way, a d of 1024 has one either way), d gives the weight gradients tiles enough, and
 // the launch needs fewer rounds of the chip: 512 places for the many-token workgroups, 256 for the others.
-//   One round (few -> many, with the sum of slices): d = 256 34.8 -> 26.5 us at 10425 rows, 45.0 -> 42.1 at 24500, the last
-//     that fit; d = 384 40.4 -> 28.8 at 8680; d = 448 35.8 -> 30.6 at 6116; d = 512 36.0 -> 32.0 at 4692, 43.0 -> 40.2 at
-//     8037; d = 768 66.7 -> 49.8 at 4692; d = 1024 64.1 -> 48.3 at 2397, 73.7 -> 65.3 at 4060.
-//   Two rounds against four or more: d = 512 92.5 -> 77.6 at 13622; d = 704 71.6 -> 66.9 at 5217; d = 832 105 -> 80.5 at
-//     5460; d = 960 128 -> 102 at 5320; d = 1024 123 -> 107 at 4830.
-//   Two against three: d = 320 43.9 -> 43.3 at 14000, d = 384 51.0 -> 45.4 at 12880, d = 448 55.0 -> 48.9 at 9452, d = 512
-//     55.2 -> 54.1 at 8260, d = 576 53.8 -> 52.7 at 5600, d = 640 58.3 -> 58.3 at 6116; but d = 256 45.5 -> 59.2 at 24920 (few
-//     columns, long slices) and d = 704 54.0 -> 64.4 at 4830 (the three rounds are full).
-//   Two against two: d = 320 34.4 -> 36.3 at 9800, d = 384 36.3 -> 40.2 at 9800, d = 448 36.5 -> 40.8 at 6348.
-// d = 128: 34.9 -> 43.6 at 32000 (32 weight-gradient workgroups).  d = 512 with 3840 rows: 27.3 -> 25.9 + 4.8 for the sum.
-// (Those figures are from before the copies ran at their full rate.  The whole backward since, few -> many with the sum of
-// slices, B = 32, up to 4608 rows: d = 512 29.2 -> 38.2 us at 2048 rows, 37.5 -> 42.4 at 3328, 41.8 -> 44.9 at 4096; d = 768 53.4 ->
-// 61.7, 69.6 -> 68.9, 78.7 -> 76.4; d = 640 51.1 -> 54.4, 62.3 -> 60.8, 67.1 -> 64.1; d = 384 27.5 -> 34.1, 35.3 -> 36.5, 38.6 -> 37.9; d = 256
-// 24.1 -> 28.0, 33.0 -> 30.3, 36.9 -> 30.9.  What the last would gain, a count of half its bound would lose.)
+// Whole backward, few -> many with the sum of slices, B = 32, us:
+//   One round: d = 256 53.4 -> 51.8 at 9600 rows, 66.7 -> 63.9 at 12800 (49.5 -> 50.8 for d = 320 at 6400); d = 384 63.4 -> 62.7 at
+//     8544; d = 448 55.2 -> 51.3 at 4800; d = 512 58.4 -> 55.7 at 4800, 71.5 -> 68.7 at 8000; d = 640 84.6 -> 73.0 at 4800; d =
+//     704 92.7 -> 83.5 at 4704; d = 768 106 -> 87.0 at 4640; d = 1024 71.2 -> 60.8 at 2400, 94.2 -> 83.9 at 4000.
+//   Two rounds against four: d = 512 138 -> 131 at 13440; d = 704 109 -> 104 at 5248; d = 768 126 -> 122 at 7680; d = 832 128 -> 111 at
+//     5472; d = 960 142 -> 125 at 4800; d = 1024 152 -> 133 at 4800.
+//   Two against three that are full for the most part (over 680 of 768 places): d = 320 129 -> 121 at 18784; d = 384 134 -> 130 at
+//     17056; d = 448 102 -> 96.2 at 11040; d = 512 107 -> 105 at 10560, 114 -> 109 at 12000; d = 576 110 -> 107 at 8448; d = 640
+//     101 -> 103 at 7424, 123 -> 121 at 9216; but d = 704 93.5 -> 101 at 4864 and d = 256 187 -> 188 at 32000.
+//   Two against three that are not: d = 384 92.0 -> 96.1 at 12800; d = 448 87.1 -> 89.7 at 9920; d = 512 93.0 -> 96.0 at 8320; d = 576
+//     75.5 -> 80.9 at 5504, 85.2 -> 92.9 at 6656; d = 640 90.7 -> 96.2 at 6272 (but d = 320 93.4 -> 91.7 at 15360).
+//   Two against two: d = 320 74.2 -> 78.8 at 10464, d = 384 77.7 -> 84.6 at 11104, d = 448 69.6 -> 77.0 at 7360.
+//   Up to 4608 rows: d = 512 29.2 -> 38.2 at 2048, 37.5 -> 42.4 at 3328, 41.8 -> 44.9 at 4096; d = 768 53.4 -> 61.7, 69.6 -> 68.9, 78.7 ->
+//     76.4; d = 640 51.1 -> 54.4, 62.3 -> 60.8, 67.1 -> 64.1; d = 384 27.5 -> 34.1, 35.3 -> 36.5, 38.6 -> 37.9; d = 256 24.1 -> 28.0,
+//     33.0 -> 30.3, 36.9 -> 30.9.  What the later of these would gain, a device-side count of half its bound would lose.
 // With a device-side count the bound decides.  Counts near it gain as above, counts far below it lose: d = 512, bound 6144
-// rows, 6080 rows 43.2 -> 38.2, 4160 44.8 -> 31.9, 3200 27.4 -> 28.5; bound 6896, 4000 rows 31.8 -> 30.6, 720 20.2 -> 24.8.
+// rows, 6080 rows 67.8 -> 65.5, 4160 56.3 -> 57.1, 3200 40.6 -> 45.6; bound 6880, 4000 rows 45.2 -> 47.3, 704 28.5 -> 38.2; bound
+// 8320, 8000 rows 77.1 -> 73.9, 6400 68.8 -> 67.3, 4160 55.8 -> 56.8.
 static inline bool vd_attn_bf16_many_tokens(int d, long long M) {
   const int cols = vd_ceil_div(d, 128), weight_tiles = vd_attn_bf16_weight_tiles(d);
   const long long tiles = (long long)vd_ceil_div((int)M, 128) * cols;
@@ -153,7 +155,7 @@ static inline bool vd_attn_bf16_many_tokens(int d, long long M) {
   if (tiles < 148 || d < 256 || (M <= kFewSliceRows && weight_tiles < 512)) return false;
   const long long many = tiles + 4 * cols * cols * vd_attn_bf16_splitk(d, M, true, nullptr);
   const long long few = tiles + weight_tiles * vd_attn_bf16_splitk(d, M, false, nullptr);
-  return many <= 512 || few > 768 || (few > 512 && d >= 320 && d <= 640);
+  return many <= 512 || few > 768 || (few > 680 && d >= 320 && d <= 640);
 }
 // Most slices of any count of up to M rows.  The few-token side has more than kManySlices only while one column of tiles
 // (d <= 128) keeps it going past 36864 rows: 15 at its end, 511 tiles.  Grows with M.
