@@ -73,15 +73,15 @@ constexpr float kSlack = 8.f;                   // a maximum that far (log2) abo
 constexpr float kSumMax = 8192.f;               // a sum of 32 unnormalised probabilities up to this is let pass: 32 scores at
                                                 // kSlack reach it, a single score at 13 (see the forward kernel)
 
-// Copies rows [j0, j0 + 64) of two head slices into a stage; a wavefront-wide copy fills 8 token rows and rows past n
-// repeat row n-1.  `off` holds this lane's byte offsets of its share of a whole block, so that a copy costs no vector
-// instruction but itself (the block's offset is a scalar of it); only the last block computes clamped ones.
 // the lane, read afresh: what is derived from it is not kept in registers over the loop before
 __device__ __forceinline__ int fresh_lane() {
   int lane;
   asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=&v"(lane));
   return lane;
 }
+// Copies rows [j0, j0 + 64) of two head slices into a stage; a wavefront-wide copy fills 8 token rows and rows past n
+// repeat row n-1.  `off` holds this lane's byte offsets of its share of a whole block, so that a copy costs no vector
+// instruction but itself (the block's offset is a scalar of it); only the last block computes clamped ones.
 template <int NW>
 struct RingSrc {
   uint32_t off[8 / NW];
@@ -650,7 +650,7 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
   unsigned char* Vs = Qs + kSmallTile;
   unsigned char* dOs = Vs + kSmallTile;
   unsigned char* dSt = dOs + kSmallTile;                                  // [key][kDsPitch]
-  float* nLs = reinterpret_cast<float*>(dSt + kSmallN * kDsPitch);        // -log2(e) lse, -inf past the last query (the exponent's multiply-add takes it)
+  float* nLs = reinterpret_cast<float*>(dSt + kSmallN * kDsPitch);        // -log2(e) lse, -inf past the last query
   float* nDs = nLs + kSmallN;                                             // -D
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int blk = wave & 3, part = wave >> 2;
@@ -865,7 +865,7 @@ __global__ __launch_bounds__(512) void sdpa_bwd_small_bf16(SdpaArgs a) {
   }
   // query tiles that phase 1 skipped were never written: their dS^T columns are read below only for
   // queries >= n, whose results are not stored
-  __syncthreads();                      // dS^T is complete; nobody reads the Q, V, dO, O tiles any more
+  __syncthreads();                      // dS^T is complete; nobody reads the Q, V, dO tiles any more
   // The two wavefronts of a key block join their partial sums through LDS: the lower one hands over its
   // dV^T, the upper one its dK^T; then the lower one finishes and stores dK, the upper one dV.
   // block[blk * 2 + part][16-byte register quad][lane], 8 KB each: six in the place of the Q, V and dO tiles, two at the end
@@ -1282,12 +1282,11 @@ int launch_sdpa_fwd(vardrop_ctx* ctx, const SdpaArgs& a, hipStream_t s) {
   if (ring_fills(a, 128)) return launch_ring(ctx, VARDROP_K_SDPA_FWD, sdpa_fwd_bf16<4>, 128, 1, a, s);
   return launch_ring(ctx, VARDROP_K_SDPA_FWD, sdpa_fwd_bf16<2>, 64, 1, a, s);
 }
-// Fewer than three rounds of the chip's 512 workgroup places per part: both parts in one launch.  Measured per step
-// at B = 32, H = 8: 1.2-1.8 % faster at 173, 205 and 321 tokens, 1.3 % at 422 (1024 workgroups per part), 0.9 % at 543
-// (1280); 1 % slower at 862 (1792) and at 1936 tokens with B = 8, H = 12 (1536), where the single launch gains
-// nothing and the row sums cost the dO GEMM more than they do inside the dQ kernel.  With the kernels as they are now the whole
-// backward takes (one launch / two) 59.5 / 63.3 us at 150 tokens, 109.6 / 111.5 at 321, 135.4 / 139.6 at 420, 185.3 / 185.9 at
-// 543, 236.2 / 234.0 at 700, 311.2 / 312.3 at 862; 470.9 / 468.1 at 1936 with B = 8, H = 12.
+// Fewer than 1536 workgroups per part: both parts in one launch, whose partly filled last rounds become one (three workgroups
+// share a compute unit: 768 places).  Whole backward at B = 32, H = 8, one launch / two: 56.9 / 60.1 us at 150 tokens (512
+// workgroups per part), 59.8 / 63.9 at 190, 101.6 / 106.0 at 321, 128.5 / 134.2 at 420, 177.9 / 178.4 at 543 (1280).  With more
+// the row sums, which then come from the dO GEMM, are worth what the rounds are: 227.2 / 227.7 at 700 tokens (1536) and 462.4 / 462.0
+// at 1936 with B = 8, H = 12 (1536); but 303.9 / 312.0 at 862 (1792), whose last rounds are two thirds empty.
 bool sdpa_bwd_paired(const SdpaArgs& a) {
   return !ring_fills(a, 128) || (long long)vd_ceil_div(a.n, 128) * a.H * a.B < 1536;   // (64-row blocks: always)
 }

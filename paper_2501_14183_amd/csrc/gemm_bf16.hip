@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(SplitkReduce a) {
 // (SPLIT) an fp32 partial product per K slice.  Each operand is either k-contiguous ([M][K] / [N][K])
 // or mn-contiguous ([K][M] / [K][N]).
 //
-// Global memory is copied straight into LDS (global_load_lds_dwordx4: every lane names its own 16
+// Global memory is copied straight into LDS (dma16_buf: every lane names its own 16
 // source bytes, the wavefront's 64 chunks land in 1 KB of consecutive LDS), NS stages deep, so
 // that the copies of the next NS-1 slices are in flight while the matrix cores work on the
 // current one and no register or LDS-store instruction is spent on staging.  Because the LDS side
@@ -537,7 +537,12 @@ __global__ __launch_bounds__(kGemmThreads, CFG::KHW ? 2 : 4) void gemm_bwd_pair_
   // of dQ, dK, dV) and a contiguous range of the weight-gradient tiles (n, then m, then K slice, then
   // matrix: a range shares its K slice of both operands).  The kind whose tiles walk over more K comes first, so that a late
   // start never meets a long tile (with the input gradient always first, at 15 400 rows of 768 its 726 tiles of 36 slices held
-  // up the 288 weight-gradient tiles of 120: 161 us, 127 this way).
+  // up the 288 weight-gradient tiles of 120: 161 us, 127 this way).  Whole backward, input gradient first -> by this rule:
+  //   many tokens: d = 512 106 -> 102 us at 10 272 rows, 343 -> 310 at 27 584; d = 768 274 -> 257 at 15 400; d = 1024 259 -> 236 at 9600,
+  //     153 -> 141 at 5760, but 124 -> 132 at 4224 (32 tiles more than the chip has places);
+  //   few tokens: d = 512 and less within 0.3 %; d = 576 53.3 -> 47.4 at 3520, d = 640 52.3 -> 50.5 at 2784, d = 832 104 -> 98.4 at 4576;
+  //     d = 704 55.0 -> 56.7 at 3200, d = 768 57.4 -> 58.9 at 3200, 59.7 -> 62.2 at 3520 (264 and 288 weight-gradient tiles on 256 places),
+  //     81.8 -> 80.8 at 4224.
   GemmDims dx, dw;
   const bool has_x = gemm_resolve(gx, dx);
   if (!gemm_resolve(gw, dw)) return;          // (an invalid count; with no tokens only the weight-gradient tiles run)

@@ -17,9 +17,10 @@
 // token rows is 400 tiles).  What bounds it: a slice of 32 k costs the LDS 24 KB of writes at 80 bytes a clock and 48 KB of
 // reads at 256 (500 clocks, one after the other), a SIMD 384 clocks of matrix instructions and 104 vector instructions of
 // splitting; three workgroups share a compute unit and reach 1080 clocks a slice.  3328 x 512 x 1536: 66 -> 50 us, the
-// gradient launch of the same layer 150 -> 102 us (by parts cut off 47 and 98; with mid lo and lo mid too, whose products by themselves
-// are as good as the fp32 instruction's, forward and backward of the layer 86 + 158 -> 93 + 174 us).  Tried: one LDS buffer and four workgroups 47 and 107; fp32 by
-// asynchronous copies, split behind the LDS read by every wavefront for itself 53 and 116 (128 x 64 tiles: 61 and 115).
+// gradient launch of the same layer 150 -> 102 us (by parts cut off 47 and 98).  Tried: mid lo and lo mid too, with which a
+// product by itself is as good as the fp32 instruction's: forward and backward of the layer 86 + 158 -> 93 + 174 us; one LDS
+// buffer and four workgroups 47 and 107; fp32 by asynchronous copies, split behind the LDS read by every wavefront for itself
+// 53 and 116 (128 x 64 tiles: 61 and 115).
 // Global memory goes through registers, where it is split, into two LDS buffers of 32 k: edges and unaligned rows are
 // handled there with zeros, so the inner loop has no masks; loads are issued two slices ahead, one barrier per slice.
 #include "bf16_mfma.h"
@@ -409,10 +410,15 @@ int sum_slices(vardrop_ctx* ctx, const GemmF32& g, int bound, hipStream_t s) {
   return VARDROP_OK;
 }
 
-// By parts where a tile walks over at least 256 k.  Forward and backward of an attention layer, fp32 instruction -> by parts:
-// d = 64 18.3 -> 20.2 and 48.1 -> 48.5 us (two slices a tile: the longer start and end of the parts cost more than they
-// save), d = 256 26.9 -> 27.0 and 39.4 -> 38.5 (256 rows), 52.7 -> 48.4 and 77.9 -> 70.2 (3200 rows), d = 512 38.6 -> 35.6
-// and 63.9 -> 58.2 (128 rows), 100 -> 81 and 195 -> 151 (3200), d = 1024 307 -> 234 and 627 -> 475 (3200).
+// By parts where a tile walks over at least 256 k; the gradient launch of a layer, where its input-gradient tiles do (3 d), weight
+// gradients of few rows included.  Forward and backward of an attention layer, fp32 instruction -> by parts everywhere:
+//   d = 64: 16.1 -> 18.0 and 19.5 -> 20.8 us (36 rows), 25.8 -> 27.4 and 38.3 -> 38.4 (3200), 45.3 -> 46.5 and 82.3 -> 80.8 (9600): two
+//     slices a tile, the longer start and end of the parts cost more than they save;
+//   d = 128: 20.6 -> 21.9 and 27.7 -> 27.9 (36), 37.6 -> 37.7 and 58.9 -> 56.6 (3200), 71.2 -> 70.8 and 140.9 -> 131.1 (9600);
+//   d = 192: 23.4 -> 24.0 and 33.2 -> 32.4 (36), 43.1 -> 42.0 and 65.8 -> 60.8 (3200), 104.8 -> 98.5 and 215.0 -> 193.1 (9600);
+//   d = 256: 26.1 -> 26.0 and 38.2 -> 35.9 (36), 26.9 -> 26.6 and 39.4 -> 37.6 (256), 53.6 -> 48.8 and 79.6 -> 70.3 (3200);
+//   d = 512: 37.7 -> 35.0 and 62.2 -> 56.2 (36), 102 -> 84.4 and 196 -> 154 (3200); d = 1024: 308 -> 239 and 628 -> 479 (3200).
+// With only the gradient launch by parts, d = 96 to 224: -4 to 0 % of the backward at 9 to 80 rows, -5 to -11 % from 3200 on.
 // (With a device-side count its bound decides.)  Offsets within a tile have 32 bits there: up to 64 rows of 2^24.
 bool by_parts(const GemmF32& g, long long k) { return k >= 256 && g.lda <= (1 << 24) && g.ldb <= (1 << 24); }
 
