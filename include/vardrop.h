@@ -125,10 +125,10 @@ const char* vardrop_kernel_name(int kernel_id);
  * k bins of largest mean amplitude in descending order, ties to the lower bin (step 4),
  * and hash[n] = sum_j topk[n][j] * R^(k-1-j) with R = floor(L/2)+1 (step 5).
  *
- *   x      fp32 [B][N][L] with element strides sb, sn >= 0 and st >= 1.  The kernel reads time-contiguous
- *          rows (st = 1).  Any other layout -- in particular a time-major batch [B][L][N], sb = L N,
- *          sn = 1, st = N -- is first copied into time-contiguous rows in the workspace `ws`, which
- *          must then hold vardrop_hash_strided_workspace_bytes(B, N, L) bytes, 16-byte aligned
+ *   x      fp32 [B][N][L] with element strides sb, sn >= 0 and st >= 1.  Read as it is with time-contiguous
+ *          rows (st = 1) and as a time-major batch [B][L][N] (sn = 1, for instance sb = L N, st = N; the sums
+ *          of a part of the windows then go through the workspace `ws`); any other layout is first copied into
+ *          time-contiguous rows in `ws`.  With st != 1 `ws` must hold vardrop_hash_strided_workspace_bytes(B, N, L) bytes, 16-byte aligned
  *          (EWORKSPACE otherwise; B <= 65535 on this path); with st = 1 no workspace is used
  *   topk   int32 [N][k]   bin indices, rank 1 first
  *   hash   uint64 [N]

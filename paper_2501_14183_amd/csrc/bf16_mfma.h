@@ -153,13 +153,5 @@ __device__ inline void mask_frag(Frag& f, int kvalid) {
     f.w[e] &= kvalid >= 2 * e + 2 ? 0xffffffffu : (kvalid == 2 * e + 1 ? 0x0000ffffu : 0u);
 }
 
-// Workgroups are handed to the eight accelerator dies (XCDs) in turn, and every die has an L2 of its
-// own.  These helpers turn a workgroup's linear id into its place in an order in which each die works
-// through ONE contiguous range of the tiles, so that tiles sharing an operand meet in the same L2
-// instead of each die fetching its own copy from memory.
-__device__ inline int xcd_range_start(int xcd, int total) { return xcd * (total >> 3) + min(xcd, total & 7); }
-__device__ inline int xcd_contiguous(int id, int total) { return xcd_range_start(id & 7, total) + (id >> 3); }
-
-
 }  // namespace
 #endif  // VARDROP_BF16_MFMA_H

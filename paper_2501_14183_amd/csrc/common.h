@@ -96,6 +96,13 @@ __device__ inline bool vd_count(const int32_t* n_dev, int bound, int& n, int32_t
   return false;
 }
 
+// Workgroups are handed to the eight accelerator dies (XCDs) in turn, and every die has an L2 of its
+// own.  These helpers turn a workgroup's linear id into its place in an order in which each die works
+// through ONE contiguous range of the tiles, so that tiles sharing an operand meet in the same L2
+// instead of each die fetching its own copy from memory.
+__device__ static inline int xcd_range_start(int xcd, int total) { return xcd * (total >> 3) + min(xcd, total & 7); }
+__device__ static inline int xcd_contiguous(int id, int total) { return xcd_range_start(id & 7, total) + (id >> 3); }
+
 __host__ __device__ static inline size_t vd_align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 static inline bool vd_aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 __host__ __device__ static inline int vd_ceil_div(int a, int b) { return (a + b - 1) / b; }

@@ -38,6 +38,7 @@
 // matrix-fragment order (it stays in L2) and is rebuilt when L or the candidate bins change.  A
 // wavefront owns a tile of 32 bins at a time and runs the whole contraction for it, real and
 // imaginary part together, so nothing is exchanged between wavefronts until the batch sums.
+#include <algorithm>
 #include "common.h"
 
 typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
@@ -125,8 +126,8 @@ __global__ void twiddle_kernel(halfx8* tw, int L, BinMap m, int f_max, int T, in
   for (int q = 0; q < 4; ++q) tw[base + (size_t)q * 64] = out[q];
 }
 
-// Windows whose time stride is not 1 (time-major batches [B][L][N], as forecasting loaders hand them over) are
-// first copied into time-contiguous rows: 32 x 32 tiles through LDS, read with the variate index fastest
+// Windows whose time stride is not 1 and whose variate stride is not 1 either (or whose operands and sums do not fit the LDS
+// together) are first copied into time-contiguous rows: 32 x 32 tiles through LDS, read with the variate index fastest
 // (coalesced when the variate stride is 1), written with time fastest.
 __global__ __launch_bounds__(256) void time_contiguous_kernel(const float* x, float* out, int N, int L,
                                                               long long sb, long long sn, long long st) {
@@ -173,6 +174,13 @@ struct KdfhArgs {
   int nct;        // bin tiles of 32
   int pitch;      // LDS row pitch of an operand piece, in 16-byte units (odd)
   float inv_B;
+  // windows with the variate index contiguous (time-major batches):
+  long long st;   // stride of time
+  int vec4;       // four variates are one aligned 16-byte copy
+  int units;      // 16-byte units of the LDS that hold the staged windows, then the operand pieces
+  int trunc;      // split as the pipelined kernel does
+  float* part;    // [row blocks][N][F] sums of a row block's windows,
+  float* stray;   // [kMaxStray][B][N] amplitudes of the stray bins
 };
 
 // One step's right-hand pieces of a wavefront.
@@ -212,6 +220,52 @@ __device__ inline int wave_reduce(int v) {
   return __builtin_amdgcn_readlane(v, 63);
 }
 
+// Time-major windows in LDS: [window][point in time][variate] as asynchronous copies of 1 KB leave them, 32 floats behind each
+// and 16 behind a window.  A wavefront reads one point in time of all 32 rows and, in its other half, the one 16 later: with 16
+// variates and two windows these are 64 different banks.
+constexpr int kStagePitch = 256 + 32;
+struct Staged {
+  int lv, tlog;                                // log2 of the variates of a row block, and of the points in time a copy holds
+  __device__ Staged(const KdfhArgs& a) : lv(5 - a.log2_rpv), tlog(8 - lv) {}
+  __device__ int window(int L) const { return ((L + (1 << tlog) - 1) >> tlog) * kStagePitch + 16; }
+  __device__ int at(int t) const { return (t >> tlog) * kStagePitch + ((t & ((1 << tlog) - 1)) << lv); }
+};
+// copies the windows of row block rb of the variates from n0 on; what lies past the end repeats something inside (those rows
+// are zeroed where they are read)
+__device__ __forceinline__ void stage_time_major(const KdfhArgs& a, int n0, int rb, float* raw) {
+  typedef __attribute__((address_space(1))) void* global_ptr;
+  typedef __attribute__((address_space(3))) void* lds_ptr;
+  const Staged sg(a);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), L = a.L;
+  const int copies = (L + (1 << sg.tlog) - 1) >> sg.tlog;
+  const int vl = sg.lv - (a.vec4 ? 2 : 0);                   // log2 of the lanes that share a point in time
+  const int v = (lane & ((1 << vl) - 1)) << (a.vec4 ? 2 : 0), tl = lane >> vl;
+  const float* src = a.x + (n0 + v < a.N ? n0 + v : 0);
+  for (int w = 0; w < (1 << a.log2_rpv); ++w) {
+    const float* win = src + (long long)min((rb << a.log2_rpv) + w, a.B - 1) * a.sb;
+    float* dst = raw + w * sg.window(L);
+    for (int c = wave; c < copies; c += kWaves) {
+      const int t0 = c << sg.tlog;
+      if (a.vec4) {
+        __builtin_amdgcn_global_load_lds((global_ptr)(win + min(t0 + tl, L - 1) * a.st), (lds_ptr)(dst + c * kStagePitch), 16, 0, 0);
+      } else {
+        const int per = 64 >> vl;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          __builtin_amdgcn_global_load_lds((global_ptr)(win + min(t0 + u * per + tl, L - 1) * a.st), (lds_ptr)(dst + c * kStagePitch + u * 64), 4, 0, 0);
+      }
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+}
+// item i of the time-major instances: the wavefront's lanes take the 32 rows, its halves eight-sample groups two apart
+__device__ __forceinline__ void staged_item(int i, int KG, int& r, int& g) {
+  const int q = i >> 6, half = (i >> 5) & 1;
+  r = i & 31;
+  g = 4 * (q >> 1) + ((KG & 2) && q == (KG >> 1) - 1 ? half : (q & 1) + 2 * half);
+}
+
 // VEC: rows can be read as aligned float4 (L and the strides multiples of 4, aligned base).
 // R2: radix-2 step before the fold (needs VEC, L a multiple of 8 and at least 64).
 // ITEMS: 8-sample items a thread reads per row block; RING: contraction steps whose table pieces are in
@@ -221,7 +275,11 @@ __device__ inline int wave_reduce(int v) {
 // leave 376 of them waiting for a second round: 14.9 us instead of 11.7).  (Three for ITEMS = 2, which the LDS
 // would hold at L = 336, costs spills and was slower.)
 // STRAY: the instance that also contracts stray bins (R2 only).
-template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false, int WPE = (ITEMS == 1 ? 4 : (ITEMS <= 4 ? 2 : 1))>
+// TM: the variate index is contiguous instead of time.  A workgroup owns one block of 1 << log2_rpv windows of Vb variates,
+// stages their samples in LDS by asynchronous copies (where the operand pieces go later), goes on as with rows in memory and
+// leaves the sums of its windows in `part`; kdfh_rank_kernel adds those up and ranks.  Bound by the same chain of phases as
+// with rows in memory; three workgroups a compute unit at up to 384 folded items (the samples wait in LDS, not in registers).
+template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false, int WPE = (ITEMS == 1 ? 4 : (ITEMS <= 4 ? 2 : 1)), bool TM = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE))) void kdfh_kernel(KdfhArgs a) {
   extern __shared__ halfx8 lds8[];
   const int L = a.L, F = a.F, T = a.T;
@@ -229,19 +287,23 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
   const int col = lane & 31, half = lane >> 5;
   const int rpv = 1 << a.log2_rpv;
   const int Vb = 32 >> a.log2_rpv;               // variates per block
-  const int n0 = blockIdx.x * Vb;
+  const int nblk = (a.N + Vb - 1) / Vb;
+  const int bid = TM ? xcd_contiguous(blockIdx.x, gridDim.x) : blockIdx.x;   // (neighbours share 128-byte lines: one die)
+  const int rb0 = TM ? bid / nblk : 0;
+  const int n0 = (TM ? bid - rb0 * nblk : bid) * Vb;
   const int KG = 2 * a.KS;                       // groups of 8 folded samples per row
   const int pitch = a.pitch;
   // [4][32][pitch]: cosine operand hi, lo, sine operand hi, lo; with R2 a second set of four for the odd bins
   halfx8* opnd = lds8;
-  unsigned* rowmax = reinterpret_cast<unsigned*>(opnd + (R2 ? 8 : 4) * 32 * pitch);   // [32] bits of the largest |x| of a row
+  unsigned* rowmax = reinterpret_cast<unsigned*>(opnd + (TM ? a.units : (R2 ? 8 : 4) * 32 * pitch));   // [32] bits of the largest |x| of a row
   float* rowinv = reinterpret_cast<float*>(rowmax + 32);                   // [32] 1 / scale of a row
   float* xn1 = rowinv + 32;      // [32] scaled middle term of the cosine sum: x[L/2] (0 when L is odd); R2: u[L/4], even bins
   float* xn2 = xn1 + 32;         // [32] R2: scaled middle term of the sine sum, v[L/4], odd bins
   float* samp = xn2 + 32;        // [kMaxStray][32] amplitudes of the stray bins, per row
   float* asum = samp + kMaxStray * 32;                                     // [Vb][F]
 
-  for (int i = tid; i < Vb * F; i += kThreads) asum[i] = 0.f;
+  if constexpr (!TM)
+    for (int i = tid; i < Vb * F; i += kThreads) asum[i] = 0.f;
   const bool even = (L & 1) == 0;
   // which wavefront takes the odd bin tile out rotates with the block, so that the blocks that share a
   // compute unit do not all load the same one of its four matrix pipelines
@@ -251,9 +313,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
   Tw w0, w1, w2, w3;                                                 // right-hand pieces in flight (w2, w3: RING = 4)
   const int ctp = min(ct0, a.nct - 1);                               // (a wavefront without a tile loads one all the same)
 
-  for (int rb = 0; rb < a.nrb; ++rb) {
+  float* raw = reinterpret_cast<float*>(lds8);                             // TM: the staged windows
+  const Staged sg(a);
+  for (int rb = rb0; rb < (TM ? rb0 + 1 : a.nrb); ++rb) {
     __syncthreads();                             // the operands of the previous block have been used
     if (tid < 32) rowmax[tid] = 0u;
+    if constexpr (TM) stage_time_major(a, n0, rb, raw);
     // In the short-window instances the item coordinates and row addresses below are formed from an opaque copy
     // of the thread index, so that they are computed here and not ahead of the loop: hoisted, they would live
     // across it (most launches run it once) and cost registers these instances do not have (they spilled).  The
@@ -287,22 +352,50 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
       {
         int row = tid;
         asm volatile("" : "+v"(row));              // (keeps this address out of the registers that live across the loop)
-        const int nn = n0 + (row >> a.log2_rpv), bb = rb * 32 + (row & (rpv - 1));
+        const int nn = n0 + (row >> a.log2_rpv), bb = (rb << a.log2_rpv) + (row & (rpv - 1));
         if (tid < 32 && nn < a.N && bb < a.B) {
-          const float* p = a.x + (long long)bb * a.sb + (long long)nn * a.sn;
-          n1 = p[T];
-          n2 = p[T + M];
+          if constexpr (TM) {
+            const float* p = raw + (row & (rpv - 1)) * sg.window(L) + (row >> a.log2_rpv);
+            n1 = p[sg.at(T)];
+            n2 = p[sg.at(T + M)];
+          } else {
+            const float* p = a.x + (long long)bb * a.sb + (long long)nn * a.sn;
+            n1 = p[T];
+            n2 = p[T + M];
+          }
         }
       }
 #pragma unroll
       for (int it = 0; it < ITEMS; ++it) {
         const int i = min(it * kThreads + tl, 32 * KG - 1);    // (a thread past the last item repeats it and stores nothing)
-        const int r = i / KG;
-        const int g = i - r * KG;
+        int r = i / KG, g = i - r * KG;
+        if constexpr (TM) staged_item(i, KG, r, g);
         ir[it] = r;
         ig[it] = g;
         const int t0 = 8 * g;
-        const int nn = n0 + (r >> a.log2_rpv), bb = rb * 32 + (r & (rpv - 1));
+        const int nn = n0 + (r >> a.log2_rpv), bb = (rb << a.log2_rpv) + (r & (rpv - 1));
+        if constexpr (TM) {
+          const float* p = raw + (r & (rpv - 1)) * sg.window(L) + (r >> a.log2_rpv);
+          const int Vb_ = 1 << sg.lv;
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {            // four points in time from a multiple of four on lie in one copy
+            const float* pa = p + sg.at(t0 + 4 * q);
+            const float* pb = p + sg.at(M + t0 + 4 * q);
+            const float* pc = p + sg.at(M - t0 - 4 * q - 4);
+            const float* pd = p + sg.at(L - t0 - 4 * q - 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              xa[it][4 * q + e] = pa[e * Vb_];
+              xb[it][4 * q + e] = pb[e * Vb_];
+              if (4 * q + 4 - e < 8) {
+                xc[it][4 * q + 4 - e] = pc[e * Vb_];
+                xd[it][4 * q + 4 - e] = pd[e * Vb_];
+              }
+            }
+          }
+          xc[it][0] = p[sg.at(M - t0)];
+          xd[it][0] = p[sg.at(min(L - t0, L - 1))];  // (t = 0 has no mirror image)
+        } else {
         const float* p = a.x + (long long)min(bb, a.B - 1) * a.sb + (long long)min(nn, a.N - 1) * a.sn;
         const float4* pa4 = reinterpret_cast<const float4*>(p + t0);
         const float4* pb4 = reinterpret_cast<const float4*>(p + M + t0);
@@ -320,13 +413,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
         xc[it][5] = c0.w; xc[it][6] = c0.z; xc[it][7] = c0.y;
         xd[it][1] = d1.w; xd[it][2] = d1.z; xd[it][3] = d1.y; xd[it][4] = d1.x;
         xd[it][5] = d0.w; xd[it][6] = d0.z; xd[it][7] = d0.y;
+        }
       }
       // ---- zero what lies outside the fold or the input; largest magnitude of every row; the four folded
       // sequences replace the samples: cosine / sine operand of the even bins, then of the odd bins
 #pragma unroll
       for (int it = 0; it < ITEMS; ++it) {
         const int r = ir[it], t0 = 8 * ig[it];
-        const int nn = n0 + (r >> a.log2_rpv), bb = rb * 32 + (r & (rpv - 1));
+        const int nn = n0 + (r >> a.log2_rpv), bb = (rb << a.log2_rpv) + (r & (rpv - 1));
         const bool ok = nn < a.N && bb < a.B;                  // rows past the end are zero windows
         float mx = 0.f;
 #pragma unroll
@@ -369,10 +463,17 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
           s3[j] = xd[it][j] * sc;
         }
         Pieces p0, p1, p2, p3;
-        split8(s0, p0);
-        split8(s1, p1);
-        split8(s2, p2);
-        split8(s3, p3);
+        if (TM && a.trunc) {
+          split8_trunc(s0, p0);
+          split8_trunc(s1, p1);
+          split8_trunc(s2, p2);
+          split8_trunc(s3, p3);
+        } else {
+          split8(s0, p0);
+          split8(s1, p1);
+          split8(s2, p2);
+          split8(s3, p3);
+        }
         if (it * kThreads + tid < 32 * KG) {
           halfx8* q = opnd + r * pitch + g;
           q[0] = p0.hi;
@@ -394,18 +495,27 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
     {
       int row = tid;
       asm volatile("" : "+v"(row));                // (keeps this address out of the registers that live across the loop)
-      const int nn = n0 + (row >> a.log2_rpv), bb = rb * 32 + (row & (rpv - 1));
-      if (tid < 32 && even && nn < a.N && bb < a.B) nyv = a.x[(long long)bb * a.sb + (long long)nn * a.sn + (L >> 1)];
+      const int nn = n0 + (row >> a.log2_rpv), bb = (rb << a.log2_rpv) + (row & (rpv - 1));
+      if (tid < 32 && even && nn < a.N && bb < a.B)
+        nyv = TM ? raw[(row & (rpv - 1)) * sg.window(L) + (row >> a.log2_rpv) + sg.at(L >> 1)] : a.x[(long long)bb * a.sb + (long long)nn * a.sn + (L >> 1)];
     }
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
       const int i = min(it * kThreads + tl, 32 * KG - 1);    // (a thread past the last item repeats it and stores nothing)
-      const int r = i / KG;
-      const int g = i - r * KG;
+      int r = i / KG, g = i - r * KG;
+      if constexpr (TM) staged_item(i, KG, r, g);
       ir[it] = r;
       ig[it] = g;
       const int t0 = 8 * g;
-      const int nn = n0 + (r >> a.log2_rpv), bb = rb * 32 + (r & (rpv - 1));
+      const int nn = n0 + (r >> a.log2_rpv), bb = (rb << a.log2_rpv) + (r & (rpv - 1));
+      if constexpr (TM) {
+        const float* p = raw + (r & (rpv - 1)) * sg.window(L) + (r >> a.log2_rpv);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          dv[it][j] = p[sg.at(min(t0 + j, L - 1))];
+          mv[it][j] = p[sg.at(min(max(L - t0 - j, 0), L - 1))];
+        }
+      } else {
       const float* p = a.x + (long long)min(bb, a.B - 1) * a.sb + (long long)min(nn, a.N - 1) * a.sn;
       if (VEC) {
         // L is a multiple of 4 and at least 8 here.  The mirror images x[L - t0 - 7 .. L - t0] are the aligned
@@ -427,12 +537,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
           mv[it][j] = p[min(max(L - t0 - j, 0), L - 1)];
         }
       }
+      }
     }
     // ---- zero what lies outside the window or the input; largest magnitude of every row
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
       const int r = ir[it], t0 = 8 * ig[it];
-      const int nn = n0 + (r >> a.log2_rpv), bb = rb * 32 + (r & (rpv - 1));
+      const int nn = n0 + (r >> a.log2_rpv), bb = (rb << a.log2_rpv) + (r & (rpv - 1));
       const bool ok = nn < a.N && bb < a.B;                  // rows past the end are zero windows
       float mx = 0.f;
 #pragma unroll
@@ -585,7 +696,39 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
 #pragma unroll
       for (int q = 0; q < 4; ++q) qs[q] = (amp[4 * q] + amp[4 * q + 1]) + (amp[4 * q + 2] + amp[4 * q + 3]);
       const bool live = c < F;                     // (bins step by 2 with R2, so the tile's last columns may lie past f_max)
-      if (a.log2_rpv >= 3) {
+      if constexpr (TM) {
+        // (one, two or four windows of a variate: never more than a register quad)
+        float* out = a.part + ((long long)rb * a.N + n0) * F;
+        const int vend = live ? min(Vb, a.N - n0) : 0;
+        int v = (4 * half) >> a.log2_rpv, at = v * F + c;
+        if (a.log2_rpv == 1) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            if (v < vend) out[at] = amp[4 * q] + amp[4 * q + 1];
+            if (v + 1 < vend) out[at + F] = amp[4 * q + 2] + amp[4 * q + 3];
+            v += 4;
+            at += 4 * F;
+          }
+        } else if (a.log2_rpv == 2) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            if (v < vend) out[at] = qs[q];
+            v += 2;
+            at += 2 * F;
+          }
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              if (v + e < vend) out[at] = amp[4 * q + e];
+              at += F;
+            }
+            v += 8;
+            at += 4 * F;
+          }
+        }
+      } else if (a.log2_rpv >= 3) {
         // a variate spans 8, 16 or 32 rows: both lane halves hold four rows of every 8
         float vs[4];
         if (a.log2_rpv == 3) {
@@ -653,6 +796,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
           }
         }
         __syncthreads();
+        if constexpr (TM) {
+          for (int i = tid; i < a.bins.n_stray * 32; i += kThreads) {
+            const int nn = n0 + (i & 31) / rpv, bb = (rb << a.log2_rpv) + (i & (rpv - 1));
+            if (nn < a.N && bb < a.B) a.stray[((long long)(i >> 5) * a.B + bb) * a.N + nn] = samp[i];
+          }
+        } else
         for (int i = tid; i < a.bins.n_stray * Vb; i += kThreads) {
           const int si = i / Vb, v = i - si * Vb;
           float tot = 0.f;
@@ -664,6 +813,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
   }
   __syncthreads();
 
+  if constexpr (TM) return;                       // kdfh_rank_kernel adds the blocks' sums and ranks
   // ---- ranked top-k and hash; the variates of the block are shared out over the wavefronts
   const unsigned long long R = (unsigned long long)(L / 2 + 1);
   for (int v = wave; v < Vb; v += kWaves) {
@@ -1002,6 +1152,46 @@ __device__ __forceinline__ void pipe_rank(const KdfhArgs& a, float* asum, int n0
   }
 }
 
+// Batch sums from the sums of row blocks that the time-major instances leave, and ranked top-k: a wavefront per variate.
+// The windows of a batch are added in the order in which a workgroup that owns all of them adds them (32 rows of the matrix
+// instruction at a time, its halves and register quads): the layout of the input does not show in the result.
+__global__ __launch_bounds__(256) void kdfh_rank_kernel(KdfhArgs a) {
+  __shared__ float asum[4 * 64 * kMaxBinsPerLane];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n = blockIdx.x * 4 + wave, F = a.F, rpv = 1 << a.log2_rpv;
+  if (n < a.N) {
+    const long long stride = (long long)a.N * F;
+    for (int c = lane; c < F; c += 64) {
+      const float* p = a.part + (long long)n * F + c;
+      float sum = 0.f;
+      for (int b0 = 0; b0 < a.B; b0 += 32) {
+        float q[8];                                      // windows b0 + 4 j .. + 3
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const int b = b0 + 4 * j, i = b >> a.log2_rpv;
+          q[j] = b < a.B ? p[i * stride] : 0.f;
+          if (rpv == 2 && b + 2 < a.B) q[j] += p[(i + 1) * stride];
+        }
+        sum += ((q[0] + q[2]) + (q[4] + q[6])) + ((q[1] + q[3]) + (q[5] + q[7]));
+      }
+      asum[wave * F + c] = sum;
+    }
+    for (int si = 0; si < a.bins.n_stray; ++si) {        // the stray bins: a window after the other
+      const float* p = a.stray + (long long)si * a.B * a.N + n;
+      float sum = 0.f;
+      for (int b0 = 0; b0 < a.B; b0 += 32) {
+        const float mine = lane < 32 && b0 + lane < a.B ? p[(long long)(b0 + lane) * a.N] : 0.f;
+        float tot = 0.f;
+        for (int j = 0; j < min(32, a.B - b0); ++j) tot += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), j));
+        sum += tot;
+      }
+      if (lane == 0) asum[wave * F + (a.bins.stray_f[si] - a.f_min)] = sum;
+    }
+  }
+  a.log2_rpv = 3;                                        // four variates a workgroup, one a wavefront
+  pipe_rank(a, asum, blockIdx.x * 4, wave, lane);
+}
+
 // Workgroup barrier that orders LDS accesses only: outstanding global loads (the next block's rows, the table
 // pieces) and stores (the previous group's results) stay in flight across it.
 __device__ inline void pipe_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
@@ -1272,6 +1462,23 @@ int launch_kdfh_pipe(vardrop_ctx* ctx, const KdfhArgs& a, int ngroups, size_t ld
   return VARDROP_OK;
 }
 
+// Time-major windows: the block sums, then their totals and the ranking (timed as one: the first launch carries the start
+// event, the second the completion).
+template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false>
+int launch_kdfh_tm(vardrop_ctx* ctx, const KdfhArgs& a, int grid, size_t lds, hipStream_t s) {
+  constexpr int WPE = ITEMS == 1 ? 4 : (ITEMS == 2 ? 3 : (ITEMS == 4 ? 2 : 1));
+  const auto kernel = kdfh_kernel<ITEMS, RING, VEC, R2, STRAY, WPE, true>;
+  if (lds > 65536) VD_HIP(ctx, hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  VdTimer timer(ctx, VARDROP_K_HASH, s);
+  if (ctx->prof_e0) hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, s, ctx->prof_e0, nullptr, 0, a);
+  else hipLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, s, a);
+  VD_LAUNCH_CHECK(ctx);
+  if (ctx->prof_e1) hipExtLaunchKernelGGL(kdfh_rank_kernel, dim3(vd_ceil_div(a.N, 4)), dim3(256), 0, s, nullptr, ctx->prof_e1, 0, a);
+  else hipLaunchKernelGGL(kdfh_rank_kernel, dim3(vd_ceil_div(a.N, 4)), dim3(256), 0, s, a);
+  VD_LAUNCH_CHECK(ctx);
+  return VARDROP_OK;
+}
+
 template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false, int WPE = (ITEMS == 1 ? 4 : (ITEMS <= 4 ? 2 : 1))>
 int launch_kdfh(vardrop_ctx* ctx, const KdfhArgs& a, int grid, size_t lds, hipStream_t s) {
   if (lds > 65536)
@@ -1323,16 +1530,8 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
   if (L > kMaxHashL || F > 64 * kMaxBinsPerLane) return VARDROP_EUNSUPPORTED;
   hipStream_t s = (hipStream_t)stream;
   if (st != 1) {
-    // time-contiguous copy of the windows in the workspace; the kernel below then reads that
     if (!ws || ws_bytes < vardrop_hash_strided_workspace_bytes(B, N, L) || !vd_aligned(ws, 16)) return VARDROP_EWORKSPACE;
     if (B > 65535) return VARDROP_EUNSUPPORTED;
-    hipLaunchKernelGGL(time_contiguous_kernel, dim3(vd_ceil_div(N, 32), vd_ceil_div(L, 32), B), dim3(256), 0, s,
-                       x, (float*)ws, N, L, (long long)sb, (long long)sn, (long long)st);
-    VD_LAUNCH_CHECK(ctx);
-    x = (const float*)ws;
-    sb = (int64_t)N * L;
-    sn = L;
-    st = 1;
   }
 
   int log2_rpv = 5, nrb = vd_ceil_div(B, 32);
@@ -1342,7 +1541,7 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
     nrb = 1;
   }
   const int Vb = 32 >> log2_rpv;
-  const bool vec = L % 4 == 0 && L >= 8 && sb % 4 == 0 && sn % 4 == 0 && vd_aligned(x, 16);
+  const bool vec = L % 4 == 0 && L >= 8 && (st != 1 || (sb % 4 == 0 && sn % 4 == 0 && vd_aligned(x, 16)));
   // the radix-2 step pays when it saves contraction steps (they come in fours): from L = 136 on
   const bool r2 = vec && L % 8 == 0 && L >= 64 &&
                   ((vd_ceil_div(L / 4, 16) + 3) & ~3) < ((vd_ceil_div((L + 1) / 2, 16) + 3) & ~3);
@@ -1377,6 +1576,28 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
   const int pitch = (2 * KS) | 1;
   const size_t lds = kdfh_lds_bytes(pitch, F, Vb, r2);
   if (lds > (size_t)ctx->lds_per_block) return VARDROP_EUNSUPPORTED;
+  // Windows with the variate index contiguous are read as they are: a workgroup takes 32 rows, four windows of eight variates or two
+  // of 16, 32 or 64 contiguous bytes of every point in time, and leaves their sums in the workspace.  Four windows leave half as
+  // many sums to add up, two fetch half as many lines a byte, which counts where batch and windows do not stay in the caches: us with
+  // four / two windows 15.3 / 16.9 (32 x 862 x 96), 24.4 / 25.1 (8 x 8192 x 96), 32.1 / 33.7 (32 x 862 x 336), 67.8 / 74.7
+  // (64 x 300 x 720), 34.2 / 33.9 (16 x 2048 x 336), 85.5 / 83.6 (32 x 2048 x 512), 49.7 / 44.3 (8 x 4096 x 512), 88.0 / 78.4 (8 x 8192 x 512).
+  // (With a copy into time-contiguous rows in front: 19.6, 30.1, 45.8, 94.7, 49.7, 133, 67.8, 124.)
+  const int tm_log2_rpv = B <= 1 ? 0 : (B == 2 || (N >= 2048 && L >= 256) ? 1 : 2);
+  const int tm_tlog = 3 + tm_log2_rpv;                    // log2 of the points in time a copy of 1 KB holds
+  const size_t tm_staged = ((size_t)vd_ceil_div(L, 1 << tm_tlog) * kStagePitch + 16) * sizeof(float) << tm_log2_rpv;
+  const int tm_units = std::max((r2 ? 8 : 4) * 32 * pitch, (int)(tm_staged / 16));
+  const size_t tm_lds = (size_t)tm_units * 16 + sizeof(float) * (4 + (bins.n_stray > 0 ? kMaxStray : 0)) * 32;
+  const bool tm = st != 1 && sn == 1 && tm_lds <= (size_t)ctx->lds_per_block;
+  if (st != 1 && !tm) {
+    // time-contiguous copy of the windows in the workspace; the kernel below then reads that
+    hipLaunchKernelGGL(time_contiguous_kernel, dim3(vd_ceil_div(N, 32), vd_ceil_div(L, 32), B), dim3(256), 0, s,
+                       x, (float*)ws, N, L, (long long)sb, (long long)sn, (long long)st);
+    VD_LAUNCH_CHECK(ctx);
+    x = (const float*)ws;
+    sb = (int64_t)N * L;
+    sn = L;
+    st = 1;
+  }
   if (stw_off + (size_t)kMaxStray * Tp * 2 * sizeof(float) > kTwiddleBytes) return VARDROP_EUNSUPPORTED;   // (cannot happen within the limits above)
 
   if (ctx->twiddle_L != L || ctx->twiddle_fmin != f_min || ctx->twiddle_F != F || ctx->twiddle_r2 != bins.r2) {
@@ -1392,7 +1613,7 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
     ctx->twiddle_F = F;
     ctx->twiddle_r2 = bins.r2;
   }
-  KdfhArgs a;
+  KdfhArgs a = {};
   a.x = x;
   a.tw = (const halfx8*)ctx->twiddle;
   a.stw = (const float*)((const char*)ctx->twiddle + stw_off);
@@ -1423,7 +1644,38 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
   // kernel is as fast or faster and stays).
   const size_t plds = pipe_lds_bytes(pitch, F, Vb, r2);
   const int iw = vd_ceil_div(8 * 2 * KS, 64);             // items per producer lane: two sets of them must fit the registers
-  if (r2 && L >= 384 && iw <= 2 && plds <= (size_t)ctx->lds_per_block && (long long)grid * nrb >= 4ll * ctx->num_cus) {
+  const bool pipe = r2 && L >= 384 && iw <= 2 && plds <= (size_t)ctx->lds_per_block && (long long)grid * nrb >= 4ll * ctx->num_cus;
+  if (tm) {
+    a.st = st;
+    a.vec4 = N % 4 == 0 && sb % 4 == 0 && st % 4 == 0 && vd_aligned(x, 16);
+    a.units = tm_units;
+    a.trunc = pipe;
+    a.part = (float*)ws;
+    a.stray = a.part + (size_t)vd_ceil_div(B, 1 << tm_log2_rpv) * N * F;
+    a.log2_rpv = tm_log2_rpv;
+    const int tm_grid = vd_ceil_div(N, 32 >> tm_log2_rpv) * vd_ceil_div(B, 1 << tm_log2_rpv);
+    if (r2 && bins.n_stray > 0) {
+      if (items <= 1) return launch_kdfh_tm<1, 2, true, true, true>(ctx, a, tm_grid, tm_lds, s);
+      if (items <= 2) return launch_kdfh_tm<2, 4, true, true, true>(ctx, a, tm_grid, tm_lds, s);
+      return launch_kdfh_tm<4, 4, true, true, true>(ctx, a, tm_grid, tm_lds, s);
+    }
+    if (r2) {
+      if (items <= 1) return launch_kdfh_tm<1, 2, true, true>(ctx, a, tm_grid, tm_lds, s);
+      if (items <= 2) return launch_kdfh_tm<2, 4, true, true>(ctx, a, tm_grid, tm_lds, s);
+      return launch_kdfh_tm<4, 4, true, true>(ctx, a, tm_grid, tm_lds, s);
+    }
+    if (vec) {
+      if (items <= 1) return launch_kdfh_tm<1, 2, true, false>(ctx, a, tm_grid, tm_lds, s);
+      if (items <= 2) return launch_kdfh_tm<2, 4, true, false>(ctx, a, tm_grid, tm_lds, s);
+      if (items <= 4) return launch_kdfh_tm<4, 4, true, false>(ctx, a, tm_grid, tm_lds, s);
+      return launch_kdfh_tm<8, 4, true, false>(ctx, a, tm_grid, tm_lds, s);
+    }
+    if (items <= 1) return launch_kdfh_tm<1, 2, false, false>(ctx, a, tm_grid, tm_lds, s);
+    if (items <= 2) return launch_kdfh_tm<2, 4, false, false>(ctx, a, tm_grid, tm_lds, s);
+    if (items <= 4) return launch_kdfh_tm<4, 4, false, false>(ctx, a, tm_grid, tm_lds, s);
+    return launch_kdfh_tm<8, 4, false, false>(ctx, a, tm_grid, tm_lds, s);
+  }
+  if (pipe) {
     if (bins.n_stray > 0) return launch_kdfh_pipe<2, true, true>(ctx, a, grid, plds, s);
     return launch_kdfh_pipe<2, true, false>(ctx, a, grid, plds, s);
   }
