@@ -47,6 +47,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 namespace {
 
 constexpr int kMaxBinsPerLane = 8;
+enum { kDirect, kStaged, kTimeMajor };       // how a workgroup gets its windows: see kdfh_kernel
 constexpr int kWaves = 4;
 constexpr int kThreads = 64 * kWaves;
 constexpr float kLoUnscale = 1.f / 2048.f;   // 2^-11: the table's low pieces are stored times 2^11
@@ -172,11 +173,12 @@ struct KdfhArgs {
   int KS;         // contraction steps of 16 that hold them
   int steps;      // steps the kernel runs (KS rounded up to the unroll; the table is zero there)
   int nct;        // bin tiles of 32
-  int pitch;      // LDS row pitch of an operand piece, in 16-byte units (odd)
+  int pitch;      // LDS row pitch of an operand piece, in 16-byte units (odd): pipelined kernel
+  int plane, skew;   // otherwise: 16-byte units of a plane of 32 rows, rows that one unit shifts the next ones by (log2)
   float inv_B;
   // windows with the variate index contiguous (time-major batches):
   long long st;   // stride of time
-  int vec4;       // four variates are one aligned 16-byte copy
+  int vec4;       // four variates (rows in memory: four points in time) are one aligned 16-byte copy
   int units;      // 16-byte units of the LDS that hold the staged windows, then the operand pieces
   int trunc;      // split as the pipelined kernel does
   float* part;    // [row blocks][N][F] sums of a row block's windows,
@@ -259,6 +261,25 @@ __device__ __forceinline__ void stage_time_major(const KdfhArgs& a, int n0, int 
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
 }
+// Time-contiguous windows in LDS: rows of staged_pitch floats (an odd number of 16-byte units), what lies past the end as above
+__host__ __device__ inline int staged_pitch(int L) { return (((L + 3) >> 2) | 1) * 4; }
+__device__ __forceinline__ void stage_rows(const KdfhArgs& a, int n0, int rb, float* raw) {
+  typedef __attribute__((address_space(1))) void* global_ptr;
+  typedef __attribute__((address_space(3))) void* lds_ptr;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), L = a.L;
+  const int per = a.vec4 ? 4 : 1, units = staged_pitch(L) / per;             // of a row
+  const float inv = 1.f / (float)units;
+  for (int c = wave; c * 64 < 32 * units; c += kWaves) {
+    const int u = min(c * 64 + lane, 32 * units - 1);
+    const int row = (int)(((float)u + 0.5f) * inv), t = (u - row * units) * per;   // (u < 2^16: the quotient is exact)
+    const int nn = n0 + (row >> a.log2_rpv), bb = (rb << a.log2_rpv) + (row & ((1 << a.log2_rpv) - 1));
+    const float* p = a.x + (long long)min(bb, a.B - 1) * a.sb + (long long)min(nn, a.N - 1) * a.sn + min(t, L - per);
+    if (a.vec4) __builtin_amdgcn_global_load_lds((global_ptr)p, (lds_ptr)(raw + c * 256), 16, 0, 0);
+    else __builtin_amdgcn_global_load_lds((global_ptr)p, (lds_ptr)(raw + c * 64), 4, 0, 0);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+}
 // item i of the time-major instances: the wavefront's lanes take the 32 rows, its halves eight-sample groups two apart
 __device__ __forceinline__ void staged_item(int i, int KG, int& r, int& g) {
   const int q = i >> 6, half = (i >> 5) & 1;
@@ -275,16 +296,17 @@ __device__ __forceinline__ void staged_item(int i, int KG, int& r, int& g) {
 // leave 376 of them waiting for a second round: 14.9 us instead of 11.7).  (Three for ITEMS = 2, which the LDS
 // would hold at L = 336, costs spills and was slower.)
 // STRAY: the instance that also contracts stray bins (R2 only).
-// TM: the variate index is contiguous instead of time.  A workgroup owns one block of 1 << log2_rpv windows of Vb variates,
+// LOAD: kDirect reads the samples of an item from memory into registers; kStaged copies the rows into LDS first.
+// kTimeMajor (TM): the variate index is contiguous instead of time.  A workgroup owns one block of 1 << log2_rpv windows of Vb variates,
 // stages their samples in LDS by asynchronous copies (where the operand pieces go later), goes on as with rows in memory and
 // leaves the sums of its windows in `part`; kdfh_rank_kernel adds those up and ranks.  Bound by the same chain of phases as
 // with rows in memory; three workgroups a compute unit at up to 384 folded items (the samples wait in LDS, not in registers).
-template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false, int WPE = (ITEMS == 1 ? 4 : (ITEMS <= 4 ? 2 : 1)), bool TM = false>
+template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false, int WPE = (ITEMS == 1 ? 4 : (ITEMS <= 4 ? 2 : 1)), int LOAD = kDirect>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE))) void kdfh_kernel(KdfhArgs a) {
+  constexpr bool TM = LOAD == kTimeMajor;
   extern __shared__ halfx8 lds8[];
   const int L = a.L, F = a.F, T = a.T;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int col = lane & 31, half = lane >> 5;
   const int rpv = 1 << a.log2_rpv;
   const int Vb = 32 >> a.log2_rpv;               // variates per block
   const int nblk = (a.N + Vb - 1) / Vb;
@@ -292,15 +314,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
   const int rb0 = TM ? bid / nblk : 0;
   const int n0 = (TM ? bid - rb0 * nblk : bid) * Vb;
   const int KG = 2 * a.KS;                       // groups of 8 folded samples per row
-  const int pitch = a.pitch;
-  // [4][32][pitch]: cosine operand hi, lo, sine operand hi, lo; with R2 a second set of four for the odd bins
+  const int plane = a.plane, skew = a.skew;      // operand pieces: row r of a plane starts at r KG + (r >> skew)
+  // four planes of 32 rows: cosine operand hi, lo, sine operand hi, lo; with R2 a second set of four for the odd bins
   halfx8* opnd = lds8;
-  unsigned* rowmax = reinterpret_cast<unsigned*>(opnd + (TM ? a.units : (R2 ? 8 : 4) * 32 * pitch));   // [32] bits of the largest |x| of a row
+  unsigned* rowmax = reinterpret_cast<unsigned*>(opnd + a.units);   // [32] bits of the largest |x| of a row
   float* rowinv = reinterpret_cast<float*>(rowmax + 32);                   // [32] 1 / scale of a row
   float* xn1 = rowinv + 32;      // [32] scaled middle term of the cosine sum: x[L/2] (0 when L is odd); R2: u[L/4], even bins
   float* xn2 = xn1 + 32;         // [32] R2: scaled middle term of the sine sum, v[L/4], odd bins
   float* samp = xn2 + 32;        // [kMaxStray][32] amplitudes of the stray bins, per row
-  float* asum = samp + kMaxStray * 32;                                     // [Vb][F]
+  float* asum = samp + (STRAY ? kMaxStray * 32 : 0);                                     // [Vb][F]
 
   if constexpr (!TM)
     for (int i = tid; i < Vb * F; i += kThreads) asum[i] = 0.f;
@@ -315,22 +337,25 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
 
   float* raw = reinterpret_cast<float*>(lds8);                             // TM: the staged windows
   const Staged sg(a);
+  const int P = staged_pitch(L);
   for (int rb = rb0; rb < (TM ? rb0 + 1 : a.nrb); ++rb) {
     __syncthreads();                             // the operands of the previous block have been used
     if (tid < 32) rowmax[tid] = 0u;
     if constexpr (TM) stage_time_major(a, n0, rb, raw);
+    if constexpr (LOAD == kStaged) stage_rows(a, n0, rb, raw);
     // In the short-window instances the item coordinates and row addresses below are formed from an opaque copy
     // of the thread index, so that they are computed here and not ahead of the loop: hoisted, they would live
     // across it (most launches run it once) and cost registers these instances do not have (they spilled).  The
     // long-window instances have the registers and are faster with the addresses ready.
     int tl = tid;
-    if constexpr (ITEMS == 1) asm volatile("" : "+v"(tl));
+    if constexpr (ITEMS == 1 || (ITEMS == 2 && LOAD == kStaged)) asm volatile("" : "+v"(tl));
+    const int ll = tl & 63, col = ll & 31, half = ll >> 5;
     // the first steps of the wavefront's first bin tile are requested before the windows are when
     // the windows leave the registers for it (short windows), else right before the contraction
     constexpr bool kEarly = false;
 #define KDFH_PRIME()                                        \
   {                                                         \
-    const halfx8* tb = a.tw + (size_t)ctp * 256 + lane;     \
+    const halfx8* tb = a.tw + (size_t)ctp * 256 + ll;       \
     const size_t sstride = (size_t)a.nct * 256;             \
     load_tw(w0, tb);                                        \
     load_tw(w1, tb + sstride);                              \
@@ -359,7 +384,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
             n1 = p[sg.at(T)];
             n2 = p[sg.at(T + M)];
           } else {
-            const float* p = a.x + (long long)bb * a.sb + (long long)nn * a.sn;
+            const float* p = LOAD == kStaged ? raw + row * P : a.x + (long long)bb * a.sb + (long long)nn * a.sn;
             n1 = p[T];
             n2 = p[T + M];
           }
@@ -370,6 +395,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
         const int i = min(it * kThreads + tl, 32 * KG - 1);    // (a thread past the last item repeats it and stores nothing)
         int r = i / KG, g = i - r * KG;
         if constexpr (TM) staged_item(i, KG, r, g);
+        if constexpr (LOAD == kStaged) r = i & 31, g = i >> 5;
         ir[it] = r;
         ig[it] = g;
         const int t0 = 8 * g;
@@ -396,7 +422,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
           xc[it][0] = p[sg.at(M - t0)];
           xd[it][0] = p[sg.at(min(L - t0, L - 1))];  // (t = 0 has no mirror image)
         } else {
-        const float* p = a.x + (long long)min(bb, a.B - 1) * a.sb + (long long)min(nn, a.N - 1) * a.sn;
+        const float* p = LOAD == kStaged ? raw + r * P : a.x + (long long)min(bb, a.B - 1) * a.sb + (long long)min(nn, a.N - 1) * a.sn;
         const float4* pa4 = reinterpret_cast<const float4*>(p + t0);
         const float4* pb4 = reinterpret_cast<const float4*>(p + M + t0);
         const float4* pc4 = reinterpret_cast<const float4*>(p + (M - 8 - t0));     // x[M - t0 - 8 .. M - t0 - 1]
@@ -475,15 +501,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
           split8(s3, p3);
         }
         if (it * kThreads + tid < 32 * KG) {
-          halfx8* q = opnd + r * pitch + g;
+          halfx8* q = opnd + r * KG + (r >> skew) + g;
           q[0] = p0.hi;
-          q[32 * pitch] = p0.lo;
-          q[64 * pitch] = p1.hi;
-          q[96 * pitch] = p1.lo;
-          q[128 * pitch] = p2.hi;
-          q[160 * pitch] = p2.lo;
-          q[192 * pitch] = p3.hi;
-          q[224 * pitch] = p3.lo;
+          q[plane] = p0.lo;
+          q[2 * plane] = p1.hi;
+          q[3 * plane] = p1.lo;
+          q[4 * plane] = p2.hi;
+          q[5 * plane] = p2.lo;
+          q[6 * plane] = p3.hi;
+          q[7 * plane] = p3.lo;
         }
       }
     } else {
@@ -497,13 +523,15 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
       asm volatile("" : "+v"(row));                // (keeps this address out of the registers that live across the loop)
       const int nn = n0 + (row >> a.log2_rpv), bb = (rb << a.log2_rpv) + (row & (rpv - 1));
       if (tid < 32 && even && nn < a.N && bb < a.B)
-        nyv = TM ? raw[(row & (rpv - 1)) * sg.window(L) + (row >> a.log2_rpv) + sg.at(L >> 1)] : a.x[(long long)bb * a.sb + (long long)nn * a.sn + (L >> 1)];
+        nyv = TM ? raw[(row & (rpv - 1)) * sg.window(L) + (row >> a.log2_rpv) + sg.at(L >> 1)]
+                 : LOAD == kStaged ? raw[row * P + (L >> 1)] : a.x[(long long)bb * a.sb + (long long)nn * a.sn + (L >> 1)];
     }
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
       const int i = min(it * kThreads + tl, 32 * KG - 1);    // (a thread past the last item repeats it and stores nothing)
       int r = i / KG, g = i - r * KG;
       if constexpr (TM) staged_item(i, KG, r, g);
+      if constexpr (LOAD == kStaged) r = i & 31, g = i >> 5;
       ir[it] = r;
       ig[it] = g;
       const int t0 = 8 * g;
@@ -516,7 +544,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
           mv[it][j] = p[sg.at(min(max(L - t0 - j, 0), L - 1))];
         }
       } else {
-      const float* p = a.x + (long long)min(bb, a.B - 1) * a.sb + (long long)min(nn, a.N - 1) * a.sn;
+      const float* p = LOAD == kStaged ? raw + r * P : a.x + (long long)min(bb, a.B - 1) * a.sb + (long long)min(nn, a.N - 1) * a.sn;
       if (VEC) {
         // L is a multiple of 4 and at least 8 here.  The mirror images x[L - t0 - 7 .. L - t0] are the aligned
         // float4 at L - t0 - 8 (its last three samples), the one at L - t0 - 4 and one more sample.  An item that
@@ -583,11 +611,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
       split8(sum, ps);
       split8(dif, pd);
       if (it * kThreads + tid < 32 * KG) {
-        halfx8* q = opnd + r * pitch + g;
+        halfx8* q = opnd + r * KG + (r >> skew) + g;
         q[0] = ps.hi;
-        q[32 * pitch] = ps.lo;
-        q[64 * pitch] = pd.hi;
-        q[96 * pitch] = pd.lo;
+        q[plane] = ps.lo;
+        q[2 * plane] = pd.hi;
+        q[3 * plane] = pd.lo;
       }
     }
     }
@@ -604,8 +632,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
       const int ct = ct0 + kWaves * ti;
       floatx16 re = {}, im = {};
       // left operands of this tile and of the wavefront's next one (even and odd bins have sets of their own)
-      const halfx8* pa = opnd + ((R2 && ct >= a.bins.nct_e) ? 128 * pitch : 0) + col * pitch;
-      const halfx8* pn = opnd + ((R2 && ct + kWaves >= a.bins.nct_e) ? 128 * pitch : 0) + col * pitch;
+      const halfx8* pa = opnd + ((R2 && ct >= a.bins.nct_e) ? 4 * plane : 0) + col * KG + (col >> skew);
+      const halfx8* pn = opnd + ((R2 && ct + kWaves >= a.bins.nct_e) ? 4 * plane : 0) + col * KG + (col >> skew);
       const halfx8 lo_unscale = {(_Float16)kLoUnscale, (_Float16)kLoUnscale, (_Float16)kLoUnscale, (_Float16)kLoUnscale,
                                  (_Float16)kLoUnscale, (_Float16)kLoUnscale, (_Float16)kLoUnscale, (_Float16)kLoUnscale};
       // the pieces of step S + RING replace those of step S; past the tile's last step they are the first of
@@ -618,9 +646,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
     const halfx8* pl = nx ? pn : pa;                                                      \
     const int g = min(2 * (nx ? 0 : (S)) + half, KG - 1); /* steps past KS: the table is zero there */ \
     A.sh = pl[g];                                                                         \
-    A.sl = pl[32 * pitch + g];                                                            \
-    A.dh = pl[64 * pitch + g];                                                            \
-    A.dl = pl[96 * pitch + g];                                                            \
+    A.sl = pl[plane + g];                                                            \
+    A.dh = pl[2 * plane + g];                                                            \
+    A.dl = pl[3 * plane + g];                                                            \
   }
 #define KDFH_STEP(W, A, AN, S)                                                            \
   {                                                                                       \
@@ -638,7 +666,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
       const bool wrap = (S) + RING >= a.steps;                                            \
       const int s2 = wrap ? (ti + 1 < nt ? (S) + RING - a.steps : a.steps - 1) : (S) + RING; \
       const int c2 = (wrap && ti + 1 < nt) ? ct + kWaves : ct;                            \
-      load_tw(W, a.tw + ((size_t)s2 * a.nct + c2) * 256 + lane);                          \
+      load_tw(W, a.tw + ((size_t)s2 * a.nct + c2) * 256 + ll);                            \
     }                                                                                     \
     __builtin_amdgcn_sched_barrier(0);                                                    \
   }
@@ -769,11 +797,11 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
         const int Tp = 8 * KG;
         for (int si = 0; si < a.bins.n_stray; ++si) {
           const int f = a.bins.stray_f[si];
-          const halfx8* base = opnd + ((f & 1) ? 128 * pitch : 0) + r * pitch;
+          const halfx8* base = opnd + ((f & 1) ? 4 * plane : 0) + r * KG + (r >> skew);
           const float4* tw4 = reinterpret_cast<const float4*>(a.stw + (size_t)si * Tp * 2);
           float re = 0.f, im = 0.f;
           for (int g = part; g < KG; g += 8) {
-            const halfx8 ch = base[g], cl = base[32 * pitch + g], sh = base[64 * pitch + g], sl = base[96 * pitch + g];
+            const halfx8 ch = base[g], cl = base[plane + g], sh = base[2 * plane + g], sl = base[3 * plane + g];
 #pragma unroll
             for (int j2 = 0; j2 < 4; ++j2) {
               const float4 w = tw4[4 * g + j2];            // cos, sin of t = 8 g + 2 j2 and of the next sample
@@ -1467,7 +1495,7 @@ int launch_kdfh_pipe(vardrop_ctx* ctx, const KdfhArgs& a, int ngroups, size_t ld
 template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false>
 int launch_kdfh_tm(vardrop_ctx* ctx, const KdfhArgs& a, int grid, size_t lds, hipStream_t s) {
   constexpr int WPE = ITEMS == 1 ? 4 : (ITEMS == 2 ? 3 : (ITEMS == 4 ? 2 : 1));
-  const auto kernel = kdfh_kernel<ITEMS, RING, VEC, R2, STRAY, WPE, true>;
+  const auto kernel = kdfh_kernel<ITEMS, RING, VEC, R2, STRAY, WPE, kTimeMajor>;
   if (lds > 65536) VD_HIP(ctx, hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   VdTimer timer(ctx, VARDROP_K_HASH, s);
   if (ctx->prof_e0) hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, s, ctx->prof_e0, nullptr, 0, a);
@@ -1479,13 +1507,14 @@ int launch_kdfh_tm(vardrop_ctx* ctx, const KdfhArgs& a, int grid, size_t lds, hi
   return VARDROP_OK;
 }
 
-template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false, int WPE = (ITEMS == 1 ? 4 : (ITEMS <= 4 ? 2 : 1))>
+template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false, int LOAD = kDirect>
 int launch_kdfh(vardrop_ctx* ctx, const KdfhArgs& a, int grid, size_t lds, hipStream_t s) {
-  if (lds > 65536)
-    VD_HIP(ctx, hipFuncSetAttribute((const void*)kdfh_kernel<ITEMS, RING, VEC, R2, STRAY, WPE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+  constexpr int WPE = ITEMS == 1 ? 4 : (ITEMS == 2 && LOAD == kStaged ? 3 : (ITEMS <= 4 ? 2 : 1));
+  const auto kernel = kdfh_kernel<ITEMS, RING, VEC, R2, STRAY, WPE, LOAD>;
+  if (lds > 65536) VD_HIP(ctx, hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   {
     VdTimer timer(ctx, VARDROP_K_HASH, s);
-    VD_KERNEL(ctx, (kdfh_kernel<ITEMS, RING, VEC, R2, STRAY, WPE>), dim3(grid), dim3(kThreads), lds, s, a);
+    VD_KERNEL(ctx, kernel, dim3(grid), dim3(kThreads), lds, s, a);
   }
   VD_LAUNCH_CHECK(ctx);
   return VARDROP_OK;
@@ -1574,8 +1603,18 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
   const int Tp = 16 * KS;                                 // samples per row the operand entries cover
   const size_t stw_off = (size_t)steps * nct * 4096;     // the stray bins' twiddles follow the table
   const int pitch = (2 * KS) | 1;
-  const size_t lds = kdfh_lds_bytes(pitch, F, Vb, r2);
-  if (lds > (size_t)ctx->lds_per_block) return VARDROP_EUNSUPPORTED;
+  if (kdfh_lds_bytes(pitch, F, Vb, r2) > (size_t)ctx->lds_per_block) return VARDROP_EUNSUPPORTED;
+  // Rows of a plane follow each other without gaps but for one unit after every 16 / gcd(2 KS, 16): 16 consecutive rows then
+  // start in 16 different units of the 256 bytes a clock of reads covers.  (With an odd pitch instead, 336-sample windows
+  // would leave room for two workgroups a compute unit, not three.)
+  const int KG = 2 * KS;
+  const int skew = KG % 16 == 0 ? 0 : (KG % 8 == 0 ? 1 : (KG % 4 == 0 ? 2 : 3));
+  const int plane = 32 * KG + (32 >> skew);
+  const int items = vd_ceil_div(32 * KG, kThreads);
+  const int staged_units = items > 1 ? (32 * staged_pitch(L) / 4 + 63) & ~63 : 0;
+  const int units = std::max((r2 ? 8 : 4) * plane, staged_units);
+  const size_t stat_bytes = sizeof(float) * (4 + (bins.n_stray > 0 ? kMaxStray : 0)) * 32;
+  const size_t lds = (size_t)units * 16 + stat_bytes + sizeof(float) * Vb * F;
   // Windows with the variate index contiguous are read as they are: a workgroup takes 32 rows, four windows of eight variates or two
   // of 16, 32 or 64 contiguous bytes of every point in time, and leaves their sums in the workspace.  Four windows leave half as
   // many sums to add up, two fetch half as many lines a byte, which counts where batch and windows do not stay in the caches: us with
@@ -1585,8 +1624,8 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
   const int tm_log2_rpv = B <= 1 ? 0 : (B == 2 || (N >= 2048 && L >= 256) ? 1 : 2);
   const int tm_tlog = 3 + tm_log2_rpv;                    // log2 of the points in time a copy of 1 KB holds
   const size_t tm_staged = ((size_t)vd_ceil_div(L, 1 << tm_tlog) * kStagePitch + 16) * sizeof(float) << tm_log2_rpv;
-  const int tm_units = std::max((r2 ? 8 : 4) * 32 * pitch, (int)(tm_staged / 16));
-  const size_t tm_lds = (size_t)tm_units * 16 + sizeof(float) * (4 + (bins.n_stray > 0 ? kMaxStray : 0)) * 32;
+  const int tm_units = std::max((r2 ? 8 : 4) * plane, (int)(tm_staged / 16));
+  const size_t tm_lds = (size_t)tm_units * 16 + stat_bytes;
   const bool tm = st != 1 && sn == 1 && tm_lds <= (size_t)ctx->lds_per_block;
   if (st != 1 && !tm) {
     // time-contiguous copy of the windows in the workspace; the kernel below then reads that
@@ -1636,9 +1675,12 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
   a.steps = steps;
   a.nct = nct;
   a.pitch = pitch;
+  a.plane = plane;
+  a.skew = skew;
+  a.units = units;
+  a.vec4 = vec;
   a.inv_B = 1.0f / (float)B;
   const int grid = vd_ceil_div(N, Vb);
-  const int items = vd_ceil_div(32 * 2 * KS, kThreads);
   // Long aligned windows with several row blocks per compute unit: the pipelined kernel (measured at 8192 variates
   // of 8 windows of 512 samples: 61 against 67 microseconds; at 336 samples and below the one-block-per-workgroup
   // kernel is as fast or faster and stays).
@@ -1679,24 +1721,35 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
     if (bins.n_stray > 0) return launch_kdfh_pipe<2, true, true>(ctx, a, grid, plds, s);
     return launch_kdfh_pipe<2, true, false>(ctx, a, grid, plds, s);
   }
+  // Rows staged in LDS by asynchronous copies leave registers for a third workgroup a compute unit at up to 512 items of eight folded
+  // samples; that pays once the registers' two do not hold the grid: us direct -> staged 28.7 -> 25.5 (16 x 2048 x 336), 59.0 -> 49.7
+  // (16 x 4000 x 272), 25.2 -> 23.5 (32 x 862 x 336), 41.6 -> 34.7 (16 x 4000 x 180), 36.6 -> 30.5 (16 x 3000 x 167); but 12.6 -> 13.0
+  // (32 x 321 x 336), 10.8 -> 12.0 (32 x 100 x 167).  Longer rows that are no aligned float4 are staged always: their samples
+  // come one by one, from LDS instead of memory (63.8 -> 37.7 at 32 x 862 x 335, 155 -> 134 at 719, 18.8 -> 16.7 at 32 x 100 x 335);
+  // longer aligned ones gain nothing (67.3 -> 72.7 at 64 x 1000 x 500, 20.5 -> 21.9 at 8 x 500 x 768, 74.9 -> 73.2 at 32 x 862 x 720).
+  const bool many = grid > 2 * ctx->num_cus;
   if (r2 && bins.n_stray > 0) {
     if (items <= 1) return launch_kdfh<1, 2, true, true, true>(ctx, a, grid, lds, s);
+    if (items <= 2 && many) return launch_kdfh<2, 4, true, true, true, kStaged>(ctx, a, grid, lds, s);
     if (items <= 2) return launch_kdfh<2, 4, true, true, true>(ctx, a, grid, lds, s);
     return launch_kdfh<4, 4, true, true, true>(ctx, a, grid, lds, s);
   }
   if (r2) {
     if (items <= 1) return launch_kdfh<1, 2, true, true>(ctx, a, grid, lds, s);
+    if (items <= 2 && many) return launch_kdfh<2, 4, true, true, false, kStaged>(ctx, a, grid, lds, s);
     if (items <= 2) return launch_kdfh<2, 4, true, true>(ctx, a, grid, lds, s);
     return launch_kdfh<4, 4, true, true>(ctx, a, grid, lds, s);
   }
   if (vec) {
     if (items <= 1) return launch_kdfh<1, 2, true, false>(ctx, a, grid, lds, s);
+    if (items <= 2 && many) return launch_kdfh<2, 4, true, false, false, kStaged>(ctx, a, grid, lds, s);
     if (items <= 2) return launch_kdfh<2, 4, true, false>(ctx, a, grid, lds, s);
     if (items <= 4) return launch_kdfh<4, 4, true, false>(ctx, a, grid, lds, s);
     return launch_kdfh<8, 4, true, false>(ctx, a, grid, lds, s);
   }
   if (items <= 1) return launch_kdfh<1, 2, false, false>(ctx, a, grid, lds, s);
+  if (items <= 2 && many) return launch_kdfh<2, 4, false, false, false, kStaged>(ctx, a, grid, lds, s);
   if (items <= 2) return launch_kdfh<2, 4, false, false>(ctx, a, grid, lds, s);
-  if (items <= 4) return launch_kdfh<4, 4, false, false>(ctx, a, grid, lds, s);
-  return launch_kdfh<8, 4, false, false>(ctx, a, grid, lds, s);
+  if (items <= 4) return launch_kdfh<4, 4, false, false, false, kStaged>(ctx, a, grid, lds, s);
+  return launch_kdfh<8, 4, false, false, false, kStaged>(ctx, a, grid, lds, s);
 }

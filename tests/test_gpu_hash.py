@@ -241,6 +241,22 @@ def test_time_major_mean_amplitudes_bit_equal(vd, ctx, B, N, L, k):
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("B,N,L,part", [(16, 1056, 336, 22), (16, 1090, 264, 31), (33, 530, 252, 7), (8, 2100, 167, 41), (40, 520, 180, 5),
+                                        (3, 4200, 335, 9), (2, 9000, 140, 17)])
+def test_many_variates_bit_equal_to_few(vd, ctx, B, N, L, part):
+    """A variate's spectrum does not depend on how many there are: grids whose rows are staged in LDS against a short slice of the
+    same batch, whose rows are not; with rows of which none, some or all are aligned."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(N + L)
+    x = torch.randn((B, N, L + 1), generator=g, device="cuda")
+    for view in (x[:, :, :L].contiguous(), x[:, :, 1:]):
+        got = vd.vardrop_hash(ctx, view, 3, want_abar=True)
+        for lo in (0, N - part):
+            want = vd.vardrop_hash(ctx, view[:, lo:lo + part], 3, want_abar=True)
+            for a, b in zip(got, want):
+                assert torch.equal(a[lo:lo + part], b)
+
+
 def test_error_codes(vd, ctx):
     x = torch.zeros((2, 3, 96), device="cuda")
     for kwargs, code in [(dict(k=30), -1), (dict(k=0), -1), (dict(k=3, f_min=5, f_max=4), -1),
