@@ -211,8 +211,8 @@ int vd_attn_fwd_bf16(vardrop_ctx*, const void* xs, int B, int n, int d, int H,
 int vd_attn_bwd_bf16(vardrop_ctx*, const void* dy, const void* xs, int B, int n, int d, int H,
                      const void* const W[4], const void* saved, void* dxs,
                      float* const dW[4], float* const db[4], void* ws, hipStream_t s, VdDevCount dn = {nullptr, nullptr});
-// column sums of up to four [rows][d] matrices (colsum.hip)
-int vd_colsum(vardrop_ctx*, int dtype, const void* const src[4], float* const dst[4], long long rows, int d,
+// column sums of up to four [rows][d] fp32 matrices (colsum.hip; bf16 ones come with the weight gradients)
+int vd_colsum(vardrop_ctx*, const float* const src[4], float* const dst[4], long long rows, int d,
               void* scratch, hipStream_t s, VdDevCount dn, int n_max, int n_mul, int nz = 4);
 // gather / scatter with an optional device-side count (gather.hip); argument checks are done by the caller
 int vd_gather(vardrop_ctx*, const void* tokens, int B, int N, int d, int dtype, const int32_t* sel, int n_sel,

@@ -259,21 +259,16 @@ __global__ __launch_bounds__(256, 2) void embed_fwd_fused_kernel(EmbedFused a) {
   }
 }
 
-// Bias gradient of the paths whose product does not form it: column sums of dxs (colsum.hip: 16-byte loads of row
-// slices) when rows are whole 16-byte units, else a thread per column and slice, rows ascending, then the slices in order
-// (3008 x 512 bf16: 13.2 + 3.9 us that way, 5.8 + 2.6 with the wide loads).
+// Bias gradient in fp32 (the bf16 products form it): column sums of dxs (colsum.hip: 16-byte loads of row slices) when rows
+// are whole 16-byte units, else a thread per column and slice, rows ascending, then the slices in order.
 constexpr int kColSlices = 64;
-template <typename T>
-__global__ __launch_bounds__(256) void embed_colsum_part_kernel(const T* __restrict__ src, float* __restrict__ part,
+__global__ __launch_bounds__(256) void embed_colsum_part_kernel(const float* __restrict__ src, float* __restrict__ part,
                                                                long long rows, long long per, int d) {
   const int c = blockIdx.x * 256 + threadIdx.x;
   if (c >= d) return;
   const long long r0 = blockIdx.y * per, r1 = min(rows, r0 + per);
   float s = 0.f;
-  for (long long r = r0; r < r1; ++r) {
-    if constexpr (sizeof(T) == 2) s += bf2f(src[r * d + c]);
-    else s += src[r * d + c];
-  }
+  for (long long r = r0; r < r1; ++r) s += src[r * d + c];
   part[(long long)blockIdx.y * d + c] = s;
 }
 __global__ __launch_bounds__(256) void embed_colsum_final_kernel(const float* __restrict__ part, float* __restrict__ dst, int d) {
@@ -283,16 +278,14 @@ __global__ __launch_bounds__(256) void embed_colsum_final_kernel(const float* __
   for (int j = 0; j < kColSlices; ++j) s += part[(long long)j * d + c];
   dst[c] = s;
 }
-int embed_colsum(vardrop_ctx* ctx, const void* src, int dtype, float* part, float* dst, long long rows, int d, hipStream_t s) {
-  if (vd_aligned(src, 16) && d % (dtype == VARDROP_BF16 ? 8 : 4) == 0) {
-    const void* from[4] = {src, nullptr, nullptr, nullptr};
+int embed_colsum(vardrop_ctx* ctx, const float* src, float* part, float* dst, long long rows, int d, hipStream_t s) {
+  if (vd_aligned(src, 16) && d % 4 == 0) {
+    const float* from[4] = {src, nullptr, nullptr, nullptr};
     float* to[4] = {dst, nullptr, nullptr, nullptr};
-    return vd_colsum(ctx, dtype, from, to, rows, d, part, s, VdDevCount{nullptr, nullptr}, 0, 0, 1);
+    return vd_colsum(ctx, from, to, rows, d, part, s, VdDevCount{nullptr, nullptr}, 0, 0, 1);
   }
   const long long per = (rows + kColSlices - 1) / kColSlices;
-  const dim3 grid(vd_ceil_div(d, 256), kColSlices);
-  if (dtype == VARDROP_BF16) hipLaunchKernelGGL(embed_colsum_part_kernel<bf16_t>, grid, dim3(256), 0, s, (const bf16_t*)src, part, rows, per, d);
-  else hipLaunchKernelGGL(embed_colsum_part_kernel<float>, grid, dim3(256), 0, s, (const float*)src, part, rows, per, d);
+  hipLaunchKernelGGL(embed_colsum_part_kernel, dim3(vd_ceil_div(d, 256), kColSlices), dim3(256), 0, s, src, part, rows, per, d);
   hipLaunchKernelGGL(embed_colsum_final_kernel, dim3(vd_ceil_div(d, 256)), dim3(256), 0, s, part, dst, d);
   VD_LAUNCH_CHECK(ctx);
   return VARDROP_OK;
@@ -464,16 +457,12 @@ int embed_bwd(vardrop_ctx* ctx, const void* dxs, int B, int n_sel, int L, int d,
     int kchunk = 0;
     g.splitk = embed_splitk(L, d, M, &kchunk);
     g.kchunk = kchunk;
-    if (g.splitk > 1) {
-      g.part = slices;
-      if ((rc = vd_gemm_bf16_wgrad_split(ctx, VARDROP_K_GEMM_DWE, g, s))) return rc;
-      float* out[4] = {dWe, nullptr, nullptr, nullptr};
-      if ((rc = vd_gemm_bf16_sum_slices(ctx, slices, out, (long long)L * d, g.splitk, s, 1))) return rc;
-    } else if ((rc = vd_gemm_bf16_wgrad_split(ctx, VARDROP_K_GEMM_DWE, g, s))) {
-      return rc;
-    }
-    if (dbe) return embed_colsum(ctx, dxs, dtype, colpart, dbe, M, d, s);
-    return VARDROP_OK;
+    g.part = slices;
+    g.set_sum(0, dbe);
+    g.sum_part = colpart;
+    if ((rc = vd_gemm_bf16_wgrad_split(ctx, VARDROP_K_GEMM_DWE, g, s)) || g.splitk == 1) return rc;
+    float* out[4] = {dWe, nullptr, nullptr, nullptr};
+    return vd_gemm_bf16_sum_slices(ctx, slices, out, (long long)L * d, g.splitk, s, g, 1);
   }
   // fp32: dWe(t, c) = sum_r z[r][t] dxs[r][c]
   GemmF32 g = {};
@@ -482,7 +471,7 @@ int embed_bwd(vardrop_ctx* ctx, const void* dxs, int B, int n_sel, int L, int d,
   g.M = L; g.N = d; g.K = (int)M; g.nz = 1; g.nseg = 1;
   g.part = slices;
   if ((rc = vd_gemm_f32_wgrad(ctx, VARDROP_K_GEMM_DWE, g, s))) return rc;
-  if (dbe) return embed_colsum(ctx, dxs, dtype, colpart, dbe, M, d, s);
+  if (dbe) return embed_colsum(ctx, (const float*)dxs, colpart, dbe, M, d, s);
   return VARDROP_OK;
 }
 }  // namespace

@@ -22,6 +22,10 @@ struct GemmBf16 {
   int many;           // weight gradients: tiles and slices for many tokens (vd_attn_bf16_many_tokens; set with n_role 1 or bwd_pair)
   int a_kpad;         // != 0: the rows of a k-contiguous A hold zeros from K up to the next multiple of 64, so K
                       // itself need not be one (B must then be n-contiguous: its last k-row is re-read, times zero)
+  // Weight gradients: column sums of B[z] over K (the bias gradients) into sum[z] (fp32, nullptr: none), formed by the copy
+  // wavefronts of the tiles of the first rows; with several slices the sums of slice s go to sum_part + (z * splitk + s) * N
+  float *sum0, *sum1, *sum2, *sum3;
+  float* sum_part;
   // rs_out != nullptr (bf16 output, one matrix, N a multiple of 64): the epilogue also writes, per row m = b * rs_n + q
   // and per 64-column head h, rs_out[(b * rs_H + h) * rs_n + q] = rs_mul * sum_c C[m][64 h + c] * rs_o[m][64 h + c] in fp32
   // from the rounded C (rs_o has C's shape and leading dimension)
@@ -42,6 +46,7 @@ struct GemmBf16 {
   int n_max, n_mul, n_role;
   void count_rows(const int32_t* dev, int32_t* st, int nmax, int mul) { n_dev = dev; status = st; n_max = nmax; n_mul = mul; n_role = 0; }
   void count_k(const int32_t* dev, int nmax, int mul) { n_dev = dev; status = nullptr; n_max = nmax; n_mul = mul; n_role = 1; }
+  void set_sum(int z, float* p) { (z == 0 ? sum0 : (z == 1 ? sum1 : (z == 2 ? sum2 : sum3))) = p; }
   void set(int z, const void* a, const void* b, void* c, const void* bias) {
     const bf16_t* pa = (const bf16_t*)a;
     const bf16_t* pb = (const bf16_t*)b;
@@ -61,16 +66,17 @@ int vd_gemm_bf16(vardrop_ctx* ctx, int kid, const GemmBf16& g, int nz, bool b_k_
 // One launch for the input gradient gx (k-contiguous operands, up to three segments) and the nzw weight
 // gradients gw (mn-contiguous operands, gw.splitk K slices, fp32 partial products in gw.part).
 int vd_gemm_bf16_bwd_pair(vardrop_ctx* ctx, const GemmBf16& gx, const GemmBf16& gw, int nzw, hipStream_t s);
-// out[z][i] = sum_s part[z * splitk + s][i] for four matrices of `count` elements, slices in ascending order.
-// With `like` (a weight-gradient product with a device-side count) the slice count is the one that product's
-// kernel derives from the count; a single slice means the product wrote its result itself and nothing is done.
+// out[z][i] = sum_s part[z * splitk + s][i] for nz matrices of `count` elements, slices in ascending order, and the same for the
+// column sums of `gw` (the product the slices are from) where it has any.
+// With a device-side count in gw the slice count is the one that product's kernel derives from the count; a single slice means
+// the product wrote its result itself and nothing is done.
 int vd_gemm_bf16_sum_slices(vardrop_ctx* ctx, const float* part, float* const out[4], long long count, int splitk,
-                            hipStream_t s, int nz = 4, const GemmBf16* like = nullptr);
+                            hipStream_t s, const GemmBf16& gw, int nz = 4);
 // C = A^T * B in fp32 for one matrix, both operands mn-contiguous, K cut into g.splitk slices of g.kchunk: the
 // partial products go to g.part ([splitk][M][N] fp32) when splitk > 1, the result itself (C0, ldc) when it is 1.
 int vd_gemm_bf16_wgrad_split(vardrop_ctx* ctx, int kid, const GemmBf16& g, hipStream_t s);
 // Sums `splitk` partial matrices ([splitk][stride] fp32, slices in ascending order) into two destinations: the first
-// `count0` elements of a matrix go to out0, the next `count1` to out1 (nullable); `like`: as for vd_gemm_bf16_sum_slices.
+// `count0` elements of a matrix go to out0, the next `count1` to out1 (nullable); `like`: a product with a device-side count, as above.
 int vd_gemm_bf16_sum_rows(vardrop_ctx* ctx, const float* part, float* out0, long long count0, float* out1, long long count1,
                           long long stride, int splitk, hipStream_t s, const GemmBf16* like);
 #endif  // VARDROP_GEMM_BF16_H

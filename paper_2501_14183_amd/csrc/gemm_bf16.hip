@@ -10,6 +10,9 @@ struct SplitkReduce {
   const float* part;
   float* out[4];
   long long count;     // elements per matrix
+  const float* sum_part;   // and of the column sums that ride along (nullptr: none), N a matrix
+  float* sum[4];
+  int N;
   int splitk;
   // device-side token count: the slice count is the one the weight-gradient kernel derived from it (d = dn_d)
   const int32_t* n_dev;
@@ -68,6 +71,14 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(SplitkReduce a) {
     }
     dst[i] = s;
   }
+  if (a.sum_part && a.sum[z] && blockIdx.x == 0) {
+    for (int c = threadIdx.x; c < a.N; c += blockDim.x) {
+      const float* p = a.sum_part + (long long)z * a.splitk * a.N + c;
+      float s = 0.f;
+      for (int k = 0; k < a.splitk; ++k) s += p[(long long)k * a.N];
+      a.sum[z][c] = s;
+    }
+  }
 }
 
 // ================================================================== GEMM with asynchronous LDS fill
@@ -115,8 +126,10 @@ struct GemmDims {
 // then owns all 64 rows, reads 2 KB + 2 KB of fragments per 16-k step instead of 1 KB + 2 KB for half the matrix
 // instructions' worth of it (32 KB of LDS reads per slice instead of 48 KB, which is what bounds this tile), and
 // the two K halves are added through LDS before the epilogue, lower half first.
-template <bool AKC, bool BKC, bool SPLIT, int BM, int BK, int NS, bool KH = false>
+// SUMS: column sums of B as well (GemmBf16::sum0 ..).
+template <bool AKC, bool BKC, bool SPLIT, int BM, int BK, int NS, bool KH = false, bool SUMS = false>
 __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDims& dm, const int bx, const int by, const int bz) {
+  static_assert(!SUMS || (SPLIT && !BKC), "column sums: of a weight gradient's right-hand operand");
   static_assert(!KH || (!AKC && !BKC && SPLIT && BM == 64 && BK == 64), "K halves: 64-row weight-gradient tiles on 64-k stages");
   constexpr int BN = 128, MI = KH ? 2 : BM / 64, KS = BK / 16;
   constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2, STAGE = A_BYTES + B_BYTES;
@@ -253,6 +266,15 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
       Bp = copy_source(fseg == 1 ? B1 : B2);                                                       \
     }                                                                                              \
   }
+  // Column sums of B, by the copy wavefronts (they wait for most of a slice; a launch of their own that reads B again took 11.5 + 5.0 us
+  // for the four of 10 272 x 512, 5.7 + 2.3 for one of 3008 x 512; here dense training at 10 272 rows 196 -> 183 us a step, the
+  // embedding of 3008 windows of 720 samples 35.0 -> 32.1).  Lane c + 16 j of copy wavefront w4 takes the eight columns of 16-byte chunk c in k-rows
+  // BK / 4 w4 + j + {0, 4, ..} of every slice, adds those of a slice up first and the slices in order.
+  float* sum_out = nullptr;
+  float csum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if constexpr (SUMS) {
+    if (by == 0) sum_out = zsel == 0 ? g.sum0 : (zsel == 1 ? g.sum1 : (zsel == 2 ? g.sum2 : g.sum3));
+  }
   if (producer) {
 #pragma unroll
     for (int s = 0; s < NS - 1; ++s)
@@ -267,6 +289,31 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
           wait_ahead<NS - 2, LPS>(ahead);
           __builtin_amdgcn_s_barrier();     // slice t is in; everyone is done with slice t-1, whose buffer is filled next
           if (t + NS - 1 < total) VD_ISSUE_STAGE((s + NS - 1) % NS)
+          if constexpr (SUMS) {
+            if (sum_out) {
+              const int krow = (BK / 4) * w4 + (lane >> 4), live = kend - (kbeg + t * BK) - krow;
+              const uint32_t at = lds0 + s * STAGE + A_BYTES + krow * (BN * 2) + (((lane & 15) ^ swz_nc<BN>(krow)) * 16);
+              Frag f[4];
+              lds_read16(f[0].q, at);
+              lds_read16_at<4 * BN * 2>(f[1].q, at);
+              if constexpr (BK == 64) {
+                lds_read16_at<8 * BN * 2>(f[2].q, at);
+                lds_read16_at<12 * BN * 2>(f[3].q, at);
+                wait_lds<0>(f[0], f[1], f[2], f[3]);
+              } else {
+                wait_lds<0>(f[0], f[1]);
+              }
+#pragma unroll
+              for (int i = 0; i < BK / 16; ++i)
+                if (live <= 4 * i) f[i].q = u32x4{0u, 0u, 0u, 0u};       // (a k-row past the end repeats the last one)
+#pragma unroll
+              for (int e = 0; e < 8; ++e) {
+                float v = bf2f(f[0].h[e]) + bf2f(f[1].h[e]);
+                if constexpr (BK == 64) v += bf2f(f[2].h[e]) + bf2f(f[3].h[e]);
+                csum[e] += v;
+              }
+            }
+          }
         }
       }
     }
@@ -340,6 +387,17 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
   // of the tile; it is written to LDS (with the bias), then stored as 16-byte chunks of whole rows.
   const bf16_t* bias = SPLIT ? nullptr : (zsel == 0 ? g.bias0 : (zsel == 1 ? g.bias1 : (zsel == 2 ? g.bias2 : g.bias3)));
   __syncthreads();                        // every wavefront is done reading the last slice
+  float* csum_lds = reinterpret_cast<float*>(smem + BM * CPITCH);         // [4 copy wavefronts][128 columns], behind the tile
+  if constexpr (SUMS) {
+    if (sum_out && producer) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        csum[e] += __shfl_xor(csum[e], 16, 64);
+        csum[e] += __shfl_xor(csum[e], 32, 64);
+        if (lane < 16) csum_lds[w4 * BN + 8 * lane + e] = csum[e];
+      }
+    }
+  }
   if constexpr (KH) {
     // the upper K half hands its sums over through LDS; the lower half adds them to its own (lower + upper)
 #pragma unroll
@@ -419,6 +477,13 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
     Cb = reinterpret_cast<unsigned char*>(zsel == 0 ? g.C0 : (zsel == 1 ? g.C1 : (zsel == 2 ? g.C2 : g.C3)));
     ldc_bytes = (long long)g.ldc * 2;
   }
+  if constexpr (SUMS) {
+    const int c = threadIdx.x - 256;
+    if (sum_out && producer && c < BN && n0 + c < g.N) {
+      if (dm.splitk > 1) sum_out = g.sum_part + (long long)bz * g.N;
+      sum_out[n0 + c] = ((csum_lds[c] + csum_lds[BN + c]) + csum_lds[2 * BN + c]) + csum_lds[3 * BN + c];
+    }
+  }
   if (producer) return;                   // (no barrier follows)
 #pragma unroll
   for (int u = 0; u < BM * CPR / 256; ++u) {
@@ -465,14 +530,14 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
   }
 }
 
-// LDS a workgroup of the asynchronous GEMM needs: the staging ring, or the output tile if that is larger
-template <bool SPLIT, int BM, int BK, int NS>
+// LDS a workgroup of the asynchronous GEMM needs: the staging ring, or the output tile (and column sums behind it) if that is larger
+template <bool SPLIT, int BM, int BK, int NS, bool SUMS = false>
 constexpr int gemm_async_lds() {
-  constexpr int ring = NS * (BM + 128) * BK * 2, out = BM * (128 * (SPLIT ? 4 : 2) + 16);
+  constexpr int ring = NS * (BM + 128) * BK * 2, out = BM * (128 * (SPLIT ? 4 : 2) + 16) + (SUMS ? 4 * 128 * 4 : 0);
   return ring > out ? ring : out;
 }
-template <bool SPLIT, int BM, int BK, int NS>
-constexpr int gemm_async_lds_v = gemm_async_lds<SPLIT, BM, BK, NS>();
+template <bool SPLIT, int BM, int BK, int NS, bool SUMS = false>
+constexpr int gemm_async_lds_v = gemm_async_lds<SPLIT, BM, BK, NS, SUMS>();
 // The product's dimensions, with a device-side token count (GemmBf16::n_dev) resolved; false: nothing to do.
 __device__ __forceinline__ bool gemm_resolve(const GemmBf16& g, GemmDims& dm) {
   dm.M = g.M; dm.K = g.K; dm.splitk = g.splitk; dm.kchunk = g.kchunk; dm.rs_n = g.rs_n;
@@ -500,7 +565,7 @@ __device__ __forceinline__ bool gemm_resolve(const GemmBf16& g, GemmDims& dm) {
 }
 // One-dimensional grid of at least nz * tiles workgroups (more when the launch was sized for the bound of a
 // device-side count: the surplus returns at once).
-template <bool AKC, bool BKC, bool SPLIT, int BM, int BK, int NS>
+template <bool AKC, bool BKC, bool SPLIT, int BM, int BK, int NS, bool SUMS = false>
 // (wavefronts a SIMD: two or three workgroups share a compute unit)
 __global__ __launch_bounds__(kGemmThreads, BM == 128 || NS > 2 ? 4 : 6) void gemm_async_kernel(GemmBf16 g, int nz) {
   GemmDims dm;
@@ -510,17 +575,18 @@ __global__ __launch_bounds__(kGemmThreads, BM == 128 || NS > 2 ? 4 : 6) void gem
   const int total = gx * gy * nz * (SPLIT ? dm.splitk : 1);
   if ((int)blockIdx.x >= total) return;
   const int t = xcd_contiguous(blockIdx.x, total);
-  gemm_async_tile<AKC, BKC, SPLIT, BM, BK, NS>(g, dm, t % gx, (t / gx) % gy, t / (gx * gy));
+  gemm_async_tile<AKC, BKC, SPLIT, BM, BK, NS, false, SUMS>(g, dm, t % gx, (t / gx) % gy, t / (gx * gy));
 }
 // The input gradient (gx: k-contiguous operands, up to three accumulated segments) and the weight
 // gradients (gw: mn-contiguous operands, K slices, fp32 partial products) depend on the same dQ, dK,
 // dV and on nothing of each other, so they share one launch.
 // Tile shapes of the two kinds of workgroup: rows, k per copy stage, stages (BN = 128 always).
-template <int BMX_, int BKX_, int NSX_, int BMW_, int BKW_, int NSW_, bool KHW_ = false>
+template <int BMX_, int BKX_, int NSX_, int BMW_, int BKW_, int NSW_, bool KHW_, bool SUMS_>
 struct PairCfg {
   static constexpr int BMX = BMX_, BKX = BKX_, NSX = NSX_, BMW = BMW_, BKW = BKW_, NSW = NSW_;
+  static constexpr bool SUMS = SUMS_;              // bias gradients as well
   static constexpr bool KHW = KHW_;                // the weight-gradient tiles' wavefronts split every K slice in halves
-  static constexpr int ldsx = gemm_async_lds_v<false, BMX_, BKX_, NSX_>, ldsw = gemm_async_lds_v<true, BMW_, BKW_, NSW_>;
+  static constexpr int ldsx = gemm_async_lds_v<false, BMX_, BKX_, NSX_>, ldsw = gemm_async_lds_v<true, BMW_, BKW_, NSW_, SUMS_>;
   static constexpr int lds = ldsx > ldsw ? ldsx : ldsw;
 };
 // few tokens: 128-row input-gradient tiles beside 64-row weight-gradient tiles (wavefronts in K halves), both on
@@ -529,8 +595,8 @@ struct PairCfg {
 // many tokens: 128-row tiles for both, input gradients on two 64-k stages (whole 128-byte lines of their k-contiguous rows;
 // on four 32-k stages 174 -> 161 us at 15 400 rows of 768, 34.2 -> 30.6 at 6080 of 512), weight gradients on four 32-k stages
 // (two of 64 k: 168 us) (64 KB); three or four 64-k stages leave one workgroup a compute unit: 192 us
-typedef PairCfg<128, 64, 3, 64, 64, 3, true> PairSmall;
-typedef PairCfg<128, 64, 2, 128, 32, 4> PairLarge;
+template <bool SUMS> using PairSmall = PairCfg<128, 64, 3, 64, 64, 3, true, SUMS>;
+template <bool SUMS> using PairLarge = PairCfg<128, 64, 2, 128, 32, 4, false, SUMS>;
 template <typename CFG>
 __global__ __launch_bounds__(kGemmThreads, CFG::KHW ? 2 : 4) void gemm_bwd_pair_kernel(GemmBf16 gx, GemmBf16 gw, int nzw) {
   // Each die takes a contiguous range of the input-gradient tiles (n fastest: a range shares its rows
@@ -560,7 +626,7 @@ __global__ __launch_bounds__(kGemmThreads, CFG::KHW ? 2 : 4) void gemm_bwd_pair_
   if (first != w_first) {
     gemm_async_tile<true, true, false, BMX, CFG::BKX, CFG::NSX>(gx, dx, t % gxn, t / gxn, 0);
   } else {
-    gemm_async_tile<false, false, true, BMW, CFG::BKW, CFG::NSW, CFG::KHW>(gw, dw, t % gwn, (t / gwn) % gwm, t / (gwn * gwm));
+    gemm_async_tile<false, false, true, BMW, CFG::BKW, CFG::NSW, CFG::KHW, CFG::SUMS>(gw, dw, t % gwn, (t / gwn) % gwm, t / (gwn * gwm));
   }
 }
 
@@ -568,13 +634,13 @@ __global__ __launch_bounds__(kGemmThreads, CFG::KHW ? 2 : 4) void gemm_bwd_pair_
 // keep every compute unit busy with two workgroups; otherwise 64 x 128 tiles, three stages deep while
 // two workgroups still fit beside each other in LDS (at most 512 tiles), else two stages and three
 // workgroups per compute unit.
-template <bool AKC, bool BKC, bool SPLIT, int BM, int NS>
+template <bool AKC, bool BKC, bool SPLIT, int BM, int NS, bool SUMS = false>
 int launch_gemm_async_cfg(vardrop_ctx* ctx, int kid, const GemmBf16& g, int nz, hipStream_t s) {
   constexpr int BK = 64;
-  constexpr int lds = gemm_async_lds<SPLIT, BM, BK, NS>();
+  constexpr int lds = gemm_async_lds<SPLIT, BM, BK, NS, SUMS>();
   static int configured_device = -1;     // raising the dynamic LDS limit is a per-device, per-function setting
   if (configured_device != ctx->device) {
-    VD_HIP(ctx, hipFuncSetAttribute((const void*)gemm_async_kernel<AKC, BKC, SPLIT, BM, BK, NS>,
+    VD_HIP(ctx, hipFuncSetAttribute((const void*)gemm_async_kernel<AKC, BKC, SPLIT, BM, BK, NS, SUMS>,
                                     hipFuncAttributeMaxDynamicSharedMemorySize, lds));
     configured_device = ctx->device;
   }
@@ -583,7 +649,7 @@ int launch_gemm_async_cfg(vardrop_ctx* ctx, int kid, const GemmBf16& g, int nz, 
   if (grid >= (1ll << 31)) return VARDROP_EUNSUPPORTED;
   {
     VdTimer timer(ctx, kid, s);
-    VD_KERNEL(ctx, (gemm_async_kernel<AKC, BKC, SPLIT, BM, BK, NS>), dim3((unsigned)grid), dim3(kGemmThreads), lds, s, g, nz);
+    VD_KERNEL(ctx, (gemm_async_kernel<AKC, BKC, SPLIT, BM, BK, NS, SUMS>), dim3((unsigned)grid), dim3(kGemmThreads), lds, s, g, nz);
   }
   VD_LAUNCH_CHECK(ctx);
   return VARDROP_OK;
@@ -613,8 +679,9 @@ int launch_gemm_bwd_pair(vardrop_ctx* ctx, const GemmBf16& gx, const GemmBf16& g
       (long long)gw.K * gw.lda >= (1ll << 31) || (long long)gw.K * gw.ldb >= (1ll << 31))
     return VARDROP_EUNSUPPORTED;
   // (with a device-side count the choice is made for its bound, tiles and slices alike)
-  if (gw.many) return launch_gemm_bwd_pair_cfg<PairLarge>(ctx, gx, gw, nzw, s);
-  return launch_gemm_bwd_pair_cfg<PairSmall>(ctx, gx, gw, nzw, s);
+  const bool sums = gw.sum0 || gw.sum1 || gw.sum2 || gw.sum3;
+  if (gw.many) return sums ? launch_gemm_bwd_pair_cfg<PairLarge<true>>(ctx, gx, gw, nzw, s) : launch_gemm_bwd_pair_cfg<PairLarge<false>>(ctx, gx, gw, nzw, s);
+  return sums ? launch_gemm_bwd_pair_cfg<PairSmall<true>>(ctx, gx, gw, nzw, s) : launch_gemm_bwd_pair_cfg<PairSmall<false>>(ctx, gx, gw, nzw, s);
 }
 
 template <bool BKC>
@@ -646,6 +713,7 @@ int vd_gemm_bf16_wgrad_split(vardrop_ctx* ctx, int kid, const GemmBf16& g, hipSt
   if (g.M % 8 != 0 || g.N % 8 != 0 || g.splitk < 1 || g.kchunk % 64 != 0 ||
       (long long)g.K * g.lda >= (1ll << 31) || (long long)g.K * g.ldb >= (1ll << 31))
     return VARDROP_EUNSUPPORTED;
+  if (g.sum0) return launch_gemm_async_cfg<false, false, true, 64, 2, true>(ctx, kid, g, 1, s);
   return launch_gemm_async_cfg<false, false, true, 64, 2>(ctx, kid, g, 1, s);
 }
 
@@ -675,15 +743,18 @@ int vd_gemm_bf16_sum_rows(vardrop_ctx* ctx, const float* part, float* out0, long
 }
 
 int vd_gemm_bf16_sum_slices(vardrop_ctx* ctx, const float* part, float* const out[4], long long count, int splitk,
-                            hipStream_t s, int nz, const GemmBf16* like) {
+                            hipStream_t s, const GemmBf16& gw, int nz) {
   SplitkReduce r = {};
-  if (like && like->n_dev) {
-    r.n_dev = like->n_dev;
-    r.n_max = like->n_max;
-    r.n_mul = like->n_mul;
-    r.dn_d = like->M;
-    r.many = like->many;
+  if (gw.n_dev) {
+    r.n_dev = gw.n_dev;
+    r.n_max = gw.n_max;
+    r.n_mul = gw.n_mul;
+    r.dn_d = gw.M;
+    r.many = gw.many;
   }
+  r.sum_part = gw.sum_part;
+  r.sum[0] = gw.sum0; r.sum[1] = gw.sum1; r.sum[2] = gw.sum2; r.sum[3] = gw.sum3;
+  r.N = gw.N;
   r.part = part;
   for (int z = 0; z < nz; ++z) r.out[z] = out[z];
   r.count = count;

@@ -349,7 +349,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
     // long-window instances have the registers and are faster with the addresses ready.
     int tl = tid;
     if constexpr (ITEMS == 1 || (ITEMS == 2 && LOAD == kStaged)) asm volatile("" : "+v"(tl));
-    const int ll = tl & 63, col = ll & 31, half = ll >> 5;
+    const int ll = ITEMS == 2 && LOAD == kStaged ? tl & 63 : lane, col = ll & 31, half = ll >> 5;
     // the first steps of the wavefront's first bin tile are requested before the windows are when
     // the windows leave the registers for it (short windows), else right before the contraction
     constexpr bool kEarly = false;

@@ -134,6 +134,27 @@ def test_bias_gradients_over_row_slices(vd, ctx, B, n, d, H, dtype):
     compare(got, want, dtype, ("dbq", "dbk", "dbv", "dbo"))
 
 
+@pytest.mark.parametrize("B,n,d", [(1, 1, 64), (1, 63, 64), (3, 43, 192), (5, 129, 128), (32, 145, 128), (65, 160, 256), (20, 480, 512)])
+def test_bias_gradients_beside_the_weight_gradients(vd, ctx, B, n, d):
+    """bf16 column sums come from the tiles of the weight gradients: K slices of one row to several slices, a last slice a row short
+    or over, few- and many-token tiles, a width whose last tile is half empty.  dbo = colsum(dy) against float64 (sums of some
+    1e4 positive terms in groups of four: below 1e-6); with the count on the device and with one sum left out the same bits."""
+    xs, W, dy, _ = random_case(B + n, B, n, d, "bf16", bias=False)
+    td = torch.bfloat16
+    xs_t, W_t, dy_t = to_dev(xs, td), [to_dev(w, td) for w in W], to_dev(np.abs(dy), td)
+    H = d // 64
+    y, saved = vd.vardrop_attn_fwd(ctx, xs_t, *W_t, H)
+    out = vd.vardrop_attn_bwd(ctx, dy_t, xs_t, *W_t, H, saved, bias_grads=True)
+    want = dy_t.double().reshape(-1, d).sum(0)
+    assert ((out[8].double() - want).abs() / want).max().item() <= 1e-6
+    ws = torch.empty(vd.load_library().vardrop_attn_workspace_bytes(B, n, d, H, vd.BF16), dtype=torch.uint8, device="cuda")
+    n_dev = torch.tensor([n], dtype=torch.int32, device="cuda")
+    again = [torch.full_like(t, float("nan")) for t in out]
+    again[6] = None
+    vd.vardrop_attn_bwd_dev(ctx, dy_t, xs_t, n_dev, n, *W_t, H, saved, ws, tuple(again))
+    assert all(b is None or torch.equal(a, b) for a, b in zip(out, again))
+
+
 @pytest.mark.parametrize("B,n,d,H", [(2, 32, 64, 1), (2, 33, 64, 1), (1, 128, 128, 1), (2, 129, 32, 2), (3, 97, 192, 3),
                                      (1, 257, 128, 1), (2, 65, 96, 3), (4, 128, 64, 1), (9, 300, 80, 5)])
 def test_fp32_matrix_core_tiles(vd, ctx, B, n, d, H):

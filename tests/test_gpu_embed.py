@@ -113,6 +113,23 @@ def test_strided_batch_constant_window_and_bad_index(vd, ctx):
     assert torch.count_nonzero(xs[:, 1]) == 0
 
 
+@pytest.mark.parametrize("B,n,L,d", [(1, 1, 384, 8), (1, 65, 1024, 72), (3, 43, 448, 136), (16, 188, 720, 512), (40, 100, 384, 64)])
+def test_bias_gradient_of_long_windows(vd, ctx, B, n, L, d):
+    """dbe = colsum(dxs), which the product forms beside dWe: one slice, several, columns past the last whole tile."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n + L)
+    x = torch.randn((B, n, L), generator=g, device="cuda")
+    sel = torch.arange(n, dtype=torch.int32, device="cuda")
+    We = torch.randn((L, d), generator=g, device="cuda").to(torch.bfloat16)
+    xs, saved = vd.vardrop_embed_fwd(ctx, x, sel, n, We)
+    dxs = torch.rand((B, n, d), generator=g, device="cuda").to(torch.bfloat16) + 0.5
+    dWe, dbe = vd.vardrop_embed_bwd(ctx, dxs, L, saved)
+    want = dxs.double().reshape(-1, d).sum(0)
+    assert ((dbe.double() - want).abs() / want).max().item() <= 1e-6
+    alone, none = vd.vardrop_embed_bwd(ctx, dxs, L, saved, want_bias=False)
+    assert torch.equal(alone, dWe)
+
+
 def test_empty_selection_and_error_codes(vd, ctx):
     x = torch.zeros((2, 6, 96), device="cuda")
     We = torch.zeros((96, 64), device="cuda", dtype=torch.bfloat16)
