@@ -222,6 +222,32 @@ __device__ inline int wave_reduce(int v) {
   return __builtin_amdgcn_readlane(v, 63);
 }
 
+// Ranked top-k of up to 32 mean amplitudes: lane b of either half holds bin b and counts over half of the bins how many beat it (a
+// larger amplitude, or an equal one of a lower bin); the lanes of rank 0 .. k-1 are the result.  Returns the hash.
+__device__ __forceinline__ unsigned long long rank_short(const KdfhArgs& a, const float* amp, int n, int lane) {
+  const int F = a.F, b = lane & 31, j0 = (lane >> 5) * 16;
+  const float mine = b < F ? amp[b] : -2.f;
+  float other[16];
+#pragma unroll
+  for (int u = 0; u < 16; ++u) other[u] = amp[min(j0 + u, F - 1)];
+  int rank = 0;
+#pragma unroll
+  for (int u = 0; u < 16; ++u) {
+    const int j = j0 + u;
+    rank += j < F && (other[u] > mine || (other[u] == mine && j < b)) ? 1 : 0;
+  }
+  rank += __shfl_xor(rank, 32, 64);
+  const unsigned long long R = (unsigned long long)(a.L / 2 + 1);
+  unsigned long long h = 0;
+  for (int r = 0; r < a.k; ++r) {
+    const unsigned long long mask = __ballot(lane < F && rank == r);
+    const int fsel = a.f_min + (__ffsll((long long)mask) - 1);
+    if (lane == 0) a.topk[(long long)n * a.k + r] = fsel;
+    h = h * R + (unsigned long long)(unsigned)fsel;
+  }
+  return h;
+}
+
 // Time-major windows in LDS: [window][point in time][variate] as asynchronous copies of 1 KB leave them, 32 floats behind each
 // and 16 behind a window.  A wavefront reads one point in time of all 32 rows and, in its other half, the one 16 later: with 16
 // variates and two windows these are 64 different banks.
@@ -296,12 +322,17 @@ __device__ __forceinline__ void staged_item(int i, int KG, int& r, int& g) {
 // leave 376 of them waiting for a second round: 14.9 us instead of 11.7).  (Three for ITEMS = 2, which the LDS
 // would hold at L = 336, costs spills and was slower.)
 // STRAY: the instance that also contracts stray bins (R2 only).
+// G (short windows, ITEMS = 1, of one or two bin tiles): 4 or 2 wavefronts share the four contraction steps of a tile.  A
+// wavefront with a tile of its own leaves the others idle over 24 dependent matrix instructions and 16 square roots a lane:
+// 32 x 862 x 96 10.7 -> 8.9 us, 64 x 862 x 96 16.7 -> 12.5, 8 x 8192 x 96 19.4 -> 16.3, 4 x 32 x 96 7.7 -> 7.2, 32 x 862 x 128 (two tiles)
+// 11.8 -> 10.8; with the radix-2 step (two tiles) 9.9 -> 10.5 at 32 x 321 x 168, 14.3 -> 14.4 at 32 x 862 x 192: not there.
 // LOAD: kDirect reads the samples of an item from memory into registers; kStaged copies the rows into LDS first.
 // kTimeMajor (TM): the variate index is contiguous instead of time.  A workgroup owns one block of 1 << log2_rpv windows of Vb variates,
 // stages their samples in LDS by asynchronous copies (where the operand pieces go later), goes on as with rows in memory and
 // leaves the sums of its windows in `part`; kdfh_rank_kernel adds those up and ranks.  Bound by the same chain of phases as
 // with rows in memory; three workgroups a compute unit at up to 384 folded items (the samples wait in LDS, not in registers).
-template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false, int WPE = (ITEMS == 1 ? 4 : (ITEMS <= 4 ? 2 : 1)), int LOAD = kDirect>
+template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false, int WPE = (ITEMS == 1 ? 4 : (ITEMS <= 4 ? 2 : 1)), int LOAD = kDirect,
+          int G = 1>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE))) void kdfh_kernel(KdfhArgs a) {
   constexpr bool TM = LOAD == kTimeMajor;
   extern __shared__ halfx8 lds8[];
@@ -314,7 +345,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
   const int rb0 = TM ? bid / nblk : 0;
   const int n0 = (TM ? bid - rb0 * nblk : bid) * Vb;
   const int KG = 2 * a.KS;                       // groups of 8 folded samples per row
-  const int plane = a.plane, skew = a.skew;      // operand pieces: row r of a plane starts at r KG + (r >> skew)
+  const int plane = a.plane, skew = a.skew, pitch = KG | 1;
+  const auto row_at = [&](int r) { return ITEMS > 1 ? r * KG + (r >> skew) : r * pitch; };   // where row r of a plane of operand pieces starts
   // four planes of 32 rows: cosine operand hi, lo, sine operand hi, lo; with R2 a second set of four for the odd bins
   halfx8* opnd = lds8;
   unsigned* rowmax = reinterpret_cast<unsigned*>(opnd + a.units);   // [32] bits of the largest |x| of a row
@@ -332,6 +364,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
   const int rot = (blockIdx.x + (blockIdx.x >> 8)) & (kWaves - 1);
   const int ct0 = (wave + rot) & (kWaves - 1);                       // first bin tile of this wavefront
   const int nt = ct0 < a.nct ? (a.nct - ct0 + kWaves - 1) / kWaves : 0;   // and how many it takes
+  const int share = wave & (G - 1);
   Tw w0, w1, w2, w3;                                                 // right-hand pieces in flight (w2, w3: RING = 4)
   const int ctp = min(ct0, a.nct - 1);                               // (a wavefront without a tile loads one all the same)
 
@@ -350,9 +383,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
     int tl = tid;
     if constexpr (ITEMS == 1 || (ITEMS == 2 && LOAD == kStaged)) asm volatile("" : "+v"(tl));
     const int ll = ITEMS == 2 && LOAD == kStaged ? tl & 63 : lane, col = ll & 31, half = ll >> 5;
-    // the first steps of the wavefront's first bin tile are requested before the windows are when
-    // the windows leave the registers for it (short windows), else right before the contraction
-    constexpr bool kEarly = false;
+    // the first steps of the wavefront's first bin tile are requested right before the contraction
 #define KDFH_PRIME()                                        \
   {                                                         \
     const halfx8* tb = a.tw + (size_t)ctp * 256 + ll;       \
@@ -364,7 +395,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
       load_tw(w3, tb + 3 * sstride);                        \
     }                                                       \
   }
-    if (kEarly) KDFH_PRIME()
+    // (shared tiles: its one or two steps behind the windows' loads)
+    const auto prime_share = [&]() {
+      const halfx8* tb = a.tw + ((size_t)(share * (4 / G)) * a.nct + wave / G) * 256 + ll;
+      load_tw(w0, tb);
+      if (G == 2) load_tw(w1, tb + (size_t)a.nct * 256);
+    };
     __syncthreads();
 
     if constexpr (R2) {
@@ -377,7 +413,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
       {
         int row = tid;
         asm volatile("" : "+v"(row));              // (keeps this address out of the registers that live across the loop)
-        const int nn = n0 + (row >> a.log2_rpv), bb = (rb << a.log2_rpv) + (row & (rpv - 1));
+        const int nn = n0 + (row >> a.log2_rpv), bb = (TM ? rb << a.log2_rpv : rb * 32) + (row & (rpv - 1));
         if (tid < 32 && nn < a.N && bb < a.B) {
           if constexpr (TM) {
             const float* p = raw + (row & (rpv - 1)) * sg.window(L) + (row >> a.log2_rpv);
@@ -399,7 +435,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
         ir[it] = r;
         ig[it] = g;
         const int t0 = 8 * g;
-        const int nn = n0 + (r >> a.log2_rpv), bb = (rb << a.log2_rpv) + (r & (rpv - 1));
+        const int nn = n0 + (r >> a.log2_rpv), bb = (TM ? rb << a.log2_rpv : rb * 32) + (r & (rpv - 1));
         if constexpr (TM) {
           const float* p = raw + (r & (rpv - 1)) * sg.window(L) + (r >> a.log2_rpv);
           const int Vb_ = 1 << sg.lv;
@@ -446,7 +482,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
 #pragma unroll
       for (int it = 0; it < ITEMS; ++it) {
         const int r = ir[it], t0 = 8 * ig[it];
-        const int nn = n0 + (r >> a.log2_rpv), bb = (rb << a.log2_rpv) + (r & (rpv - 1));
+        const int nn = n0 + (r >> a.log2_rpv), bb = (TM ? rb << a.log2_rpv : rb * 32) + (r & (rpv - 1));
         const bool ok = nn < a.N && bb < a.B;                  // rows past the end are zero windows
         float mx = 0.f;
 #pragma unroll
@@ -501,7 +537,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
           split8(s3, p3);
         }
         if (it * kThreads + tid < 32 * KG) {
-          halfx8* q = opnd + r * KG + (r >> skew) + g;
+          halfx8* q = opnd + row_at(r) + g;
           q[0] = p0.hi;
           q[plane] = p0.lo;
           q[2 * plane] = p1.hi;
@@ -521,7 +557,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
     {
       int row = tid;
       asm volatile("" : "+v"(row));                // (keeps this address out of the registers that live across the loop)
-      const int nn = n0 + (row >> a.log2_rpv), bb = (rb << a.log2_rpv) + (row & (rpv - 1));
+      const int nn = n0 + (row >> a.log2_rpv), bb = (TM ? rb << a.log2_rpv : rb * 32) + (row & (rpv - 1));
       if (tid < 32 && even && nn < a.N && bb < a.B)
         nyv = TM ? raw[(row & (rpv - 1)) * sg.window(L) + (row >> a.log2_rpv) + sg.at(L >> 1)]
                  : LOAD == kStaged ? raw[row * P + (L >> 1)] : a.x[(long long)bb * a.sb + (long long)nn * a.sn + (L >> 1)];
@@ -535,7 +571,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
       ir[it] = r;
       ig[it] = g;
       const int t0 = 8 * g;
-      const int nn = n0 + (r >> a.log2_rpv), bb = (rb << a.log2_rpv) + (r & (rpv - 1));
+      const int nn = n0 + (r >> a.log2_rpv), bb = (TM ? rb << a.log2_rpv : rb * 32) + (r & (rpv - 1));
       if constexpr (TM) {
         const float* p = raw + (r & (rpv - 1)) * sg.window(L) + (r >> a.log2_rpv);
 #pragma unroll
@@ -567,11 +603,12 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
       }
       }
     }
+    if constexpr (G > 1) prime_share();
     // ---- zero what lies outside the window or the input; largest magnitude of every row
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
       const int r = ir[it], t0 = 8 * ig[it];
-      const int nn = n0 + (r >> a.log2_rpv), bb = (rb << a.log2_rpv) + (r & (rpv - 1));
+      const int nn = n0 + (r >> a.log2_rpv), bb = (TM ? rb << a.log2_rpv : rb * 32) + (r & (rpv - 1));
       const bool ok = nn < a.N && bb < a.B;                  // rows past the end are zero windows
       float mx = 0.f;
 #pragma unroll
@@ -611,7 +648,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
       split8(sum, ps);
       split8(dif, pd);
       if (it * kThreads + tid < 32 * KG) {
-        halfx8* q = opnd + r * KG + (r >> skew) + g;
+        halfx8* q = opnd + row_at(r) + g;
         q[0] = ps.hi;
         q[plane] = ps.lo;
         q[2 * plane] = pd.hi;
@@ -619,9 +656,113 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
       }
     }
     }
-    if (!kEarly) KDFH_PRIME()
+    if constexpr (G == 1) KDFH_PRIME()
 #undef KDFH_PRIME
     __syncthreads();
+
+    if constexpr (G > 1) {
+      // ---- short windows of one or two bin tiles: the wavefronts share the four contraction steps of a tile, hand each other
+      // their partial sums of 16 / G accumulator registers through LDS (where the operands were) and finish those rows
+      constexpr int per = 4 / G;
+      const int ct = wave / G;
+      const halfx8 lo_unscale = {(_Float16)kLoUnscale, (_Float16)kLoUnscale, (_Float16)kLoUnscale, (_Float16)kLoUnscale,
+                                 (_Float16)kLoUnscale, (_Float16)kLoUnscale, (_Float16)kLoUnscale, (_Float16)kLoUnscale};
+      static_assert(!R2, "shared tiles: no radix-2 step");
+      const halfx8* pa = opnd + row_at(col);
+      floatx16 re = {}, im = {};
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        if (u < per) {
+          const Tw& w = u == 0 ? w0 : w1;
+          const int g = min(2 * (share * per + u) + half, KG - 1);     // (steps past KS: the table is zero there)
+          const halfx8 sh = pa[g], sl = pa[plane + g], dh = pa[2 * plane + g], dl = pa[3 * plane + g];
+          const halfx8 shs = sh * lo_unscale, dhs = dh * lo_unscale;
+          re = __builtin_amdgcn_mfma_f32_32x32x16_f16(sh, w.ch, re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f32_32x32x16_f16(dh, w.sh, im, 0, 0, 0);
+          re = __builtin_amdgcn_mfma_f32_32x32x16_f16(shs, w.cl, re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f32_32x32x16_f16(dhs, w.sl, im, 0, 0, 0);
+          re = __builtin_amdgcn_mfma_f32_32x32x16_f16(sl, w.ch, re, 0, 0, 0);
+          im = __builtin_amdgcn_mfma_f32_32x32x16_f16(dl, w.sh, im, 0, 0, 0);
+        }
+      }
+      __syncthreads();                           // the operands have been used
+      float4* part = reinterpret_cast<float4*>(lds8);                  // [quad][tile and share of the giver][re, im][lane]
+      float* qsum = reinterpret_cast<float*>(lds8) + 4 * 4 * 2 * 64 * 4;   // [tile][8 quads of rows][32 bins]
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (q / per != share) {
+          part[((q * 4 + wave) * 2) * 64 + ll] = make_float4(re[4 * q], re[4 * q + 1], re[4 * q + 2], re[4 * q + 3]);
+          part[((q * 4 + wave) * 2 + 1) * 64 + ll] = make_float4(im[4 * q], im[4 * q + 1], im[4 * q + 2], im[4 * q + 3]);
+        }
+      __syncthreads();
+      const int f = bin_of(a.bins, ct, col), c = f - a.f_min;
+      const bool live = c < F;
+      const float cr = (f & 1) ? -1.f : 1.f;     // of the middle term of the cosine sum
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (q / per == share) {
+          float4 r4 = make_float4(0.f, 0.f, 0.f, 0.f), i4 = r4;
+#pragma unroll
+          for (int src = 0; src < 4; ++src)                            // the shares in order
+            if (src < G) {
+              float4 pr, pi;
+              if (src == share) {
+                pr = make_float4(re[4 * q], re[4 * q + 1], re[4 * q + 2], re[4 * q + 3]);
+                pi = make_float4(im[4 * q], im[4 * q + 1], im[4 * q + 2], im[4 * q + 3]);
+              } else {
+                pr = part[((q * 4 + ct * G + src) * 2) * 64 + ll];
+                pi = part[((q * 4 + ct * G + src) * 2 + 1) * 64 + ll];
+              }
+              r4.x += pr.x; r4.y += pr.y; r4.z += pr.z; r4.w += pr.w;
+              i4.x += pi.x; i4.y += pi.y; i4.z += pi.z; i4.w += pi.w;
+            }
+          const float4 inv4 = *reinterpret_cast<const float4*>(rowinv + 8 * q + 4 * half);
+          const float4 m14 = *reinterpret_cast<const float4*>(xn1 + 8 * q + 4 * half);
+          const float rv[4] = {r4.x + cr * m14.x, r4.y + cr * m14.y, r4.z + cr * m14.z, r4.w + cr * m14.w};
+          const float iv[4] = {i4.x, i4.y, i4.z, i4.w};
+          const float inv[4] = {inv4.x, inv4.y, inv4.z, inv4.w};
+          float amp[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) amp[e] = sqrtf(rv[e] * rv[e] + iv[e] * iv[e]) * inv[e];
+          // rows 8 q + 4 half + 0..3: of one variate, of two or of four
+          const int v = (8 * q + 4 * half) >> a.log2_rpv;
+          float* out = TM ? a.part + ((long long)rb * a.N + n0) * F : asum;
+          const int vend = live ? (TM ? min(Vb, a.N - n0) : Vb) : 0, at = v * F + c;
+          const auto put = [&](int i, float x) {
+            if (v + i < vend) out[at + i * F] = TM ? x : out[at + i * F] + x;
+          };
+          if (a.log2_rpv == 0) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) put(e, amp[e]);
+          } else if (a.log2_rpv == 1) {
+            put(0, amp[0] + amp[1]);
+            put(1, amp[2] + amp[3]);
+          } else {
+            const float qs = (amp[0] + amp[1]) + (amp[2] + amp[3]);
+            if (a.log2_rpv == 2) put(0, qs);
+            else qsum[(ct * 8 + 2 * q + half) * 32 + col] = qs;
+          }
+        }
+      if (!TM && a.log2_rpv >= 3) {
+        // a variate's 8, 16 or 32 rows: first the quads of even, then of odd index (the order of the other kernels)
+        __syncthreads();
+        const int i = tid >> 5, tile = i & (a.nct - 1), vv = i >> (a.nct - 1);     // (nct is 1 or 2)
+        const int fb = bin_of(a.bins, tile, tid & 31) - a.f_min;
+        if (vv < Vb && fb < F) {
+          const float* Q = qsum + (tile * 8 + (vv << (a.log2_rpv - 2))) * 32 + (tid & 31);
+          float even = Q[0], odd = Q[32];
+          if (a.log2_rpv >= 4) {
+            even += Q[64];
+            odd += Q[96];
+          }
+          if (a.log2_rpv == 5) {
+            even += Q[128] + Q[192];
+            odd += Q[160] + Q[224];
+          }
+          asum[vv * F + fb] += even + odd;
+        }
+      }
+    } else {
 
     // ---- spectrum of the 32 rows; a wavefront takes 32 bins at a time.
     // Operand layout of v_mfma_f32_32x32x16_f16: left lane holds row lane % 32, k = 8 (lane / 32) + 0..7;
@@ -632,8 +773,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
       const int ct = ct0 + kWaves * ti;
       floatx16 re = {}, im = {};
       // left operands of this tile and of the wavefront's next one (even and odd bins have sets of their own)
-      const halfx8* pa = opnd + ((R2 && ct >= a.bins.nct_e) ? 4 * plane : 0) + col * KG + (col >> skew);
-      const halfx8* pn = opnd + ((R2 && ct + kWaves >= a.bins.nct_e) ? 4 * plane : 0) + col * KG + (col >> skew);
+      const halfx8* pa = opnd + ((R2 && ct >= a.bins.nct_e) ? 4 * plane : 0) + row_at(col);
+      const halfx8* pn = opnd + ((R2 && ct + kWaves >= a.bins.nct_e) ? 4 * plane : 0) + row_at(col);
       const halfx8 lo_unscale = {(_Float16)kLoUnscale, (_Float16)kLoUnscale, (_Float16)kLoUnscale, (_Float16)kLoUnscale,
                                  (_Float16)kLoUnscale, (_Float16)kLoUnscale, (_Float16)kLoUnscale, (_Float16)kLoUnscale};
       // the pieces of step S + RING replace those of step S; past the tile's last step they are the first of
@@ -789,6 +930,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
       }
     }
 
+    }
+
     // ---- stray bins on the vector units: eight threads per row share the folded samples (operand pieces added
     // back together), then one thread per (bin, variate) adds the rows of the variate in ascending order
     if constexpr (R2 && STRAY) {
@@ -797,7 +940,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
         const int Tp = 8 * KG;
         for (int si = 0; si < a.bins.n_stray; ++si) {
           const int f = a.bins.stray_f[si];
-          const halfx8* base = opnd + ((f & 1) ? 4 * plane : 0) + r * KG + (r >> skew);
+          const halfx8* base = opnd + ((f & 1) ? 4 * plane : 0) + row_at(r);
           const float4* tw4 = reinterpret_cast<const float4*>(a.stw + (size_t)si * Tp * 2);
           float re = 0.f, im = 0.f;
           for (int g = part; g < KG; g += 8) {
@@ -826,7 +969,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
         __syncthreads();
         if constexpr (TM) {
           for (int i = tid; i < a.bins.n_stray * 32; i += kThreads) {
-            const int nn = n0 + (i & 31) / rpv, bb = (rb << a.log2_rpv) + (i & (rpv - 1));
+            const int nn = n0 + (i & 31) / rpv, bb = (TM ? rb << a.log2_rpv : rb * 32) + (i & (rpv - 1));
             if (nn < a.N && bb < a.B) a.stray[((long long)(i >> 5) * a.B + bb) * a.N + nn] = samp[i];
           }
         } else
@@ -854,7 +997,9 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
       vals[j] = idx < F ? asum[v * F + idx] : -2.f;
     }
     unsigned long long h = 0;
-    if (F <= 64) {
+    if (G == 4 && Vb <= 8) {                     // (more of them in sequence: its LDS reads cost more than the loop below)
+      h = rank_short(a, asum + v * F, n, lane);
+    } else if (F <= 64) {
       // every lane holds one bin: its rank is the number of bins that beat it (larger mean amplitude, or
       // equal and lower index); the lanes of rank 0 .. k-1 are the ranked top-k
       const float mine = vals[0];
@@ -1122,6 +1267,7 @@ __device__ __forceinline__ void pipe_produce(RawRows<IW, R2>& w, const KdfhArgs&
 
 // ranked top-k and hash (Alg. 1 steps 4-5) of the variates v = cw, cw + 4, ... of a group, from its batch sums;
 // (the stray bins' row amplitudes of the group's last block have been added by the caller)
+template <bool SHORT = false>
 __device__ __forceinline__ void pipe_rank(const KdfhArgs& a, float* asum, int n0, int cw, int lane) {
   const int F = a.F, Vb = 32 >> a.log2_rpv;
   const unsigned long long R = (unsigned long long)(a.L / 2 + 1);
@@ -1136,7 +1282,9 @@ __device__ __forceinline__ void pipe_rank(const KdfhArgs& a, float* asum, int n0
         vals[j] = (j < nslot && idx < F) ? asum[v * F + idx] : -2.f;
       }
       unsigned long long h = 0;
-      if (F <= 64) {
+      if (SHORT && F <= 32) {
+        h = rank_short(a, asum + v * F, n, lane);
+      } else if (F <= 64) {
         const float mine = vals[0];
         int rank = 0;
         for (int j = 0; j < F; ++j) {
@@ -1217,7 +1365,7 @@ __global__ __launch_bounds__(256) void kdfh_rank_kernel(KdfhArgs a) {
     }
   }
   a.log2_rpv = 3;                                        // four variates a workgroup, one a wavefront
-  pipe_rank(a, asum, blockIdx.x * 4, wave, lane);
+  pipe_rank<true>(a, asum, blockIdx.x * 4, wave, lane);
 }
 
 // Workgroup barrier that orders LDS accesses only: outstanding global loads (the next block's rows, the table
@@ -1492,10 +1640,10 @@ int launch_kdfh_pipe(vardrop_ctx* ctx, const KdfhArgs& a, int ngroups, size_t ld
 
 // Time-major windows: the block sums, then their totals and the ranking (timed as one: the first launch carries the start
 // event, the second the completion).
-template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false>
+template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false, int G = 1>
 int launch_kdfh_tm(vardrop_ctx* ctx, const KdfhArgs& a, int grid, size_t lds, hipStream_t s) {
   constexpr int WPE = ITEMS == 1 ? 4 : (ITEMS == 2 ? 3 : (ITEMS == 4 ? 2 : 1));
-  const auto kernel = kdfh_kernel<ITEMS, RING, VEC, R2, STRAY, WPE, kTimeMajor>;
+  const auto kernel = kdfh_kernel<ITEMS, RING, VEC, R2, STRAY, WPE, kTimeMajor, G>;
   if (lds > 65536) VD_HIP(ctx, hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   VdTimer timer(ctx, VARDROP_K_HASH, s);
   if (ctx->prof_e0) hipExtLaunchKernelGGL(kernel, dim3(grid), dim3(kThreads), lds, s, ctx->prof_e0, nullptr, 0, a);
@@ -1507,10 +1655,10 @@ int launch_kdfh_tm(vardrop_ctx* ctx, const KdfhArgs& a, int grid, size_t lds, hi
   return VARDROP_OK;
 }
 
-template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false, int LOAD = kDirect>
+template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false, int LOAD = kDirect, int G = 1>
 int launch_kdfh(vardrop_ctx* ctx, const KdfhArgs& a, int grid, size_t lds, hipStream_t s) {
   constexpr int WPE = ITEMS == 1 ? 4 : (ITEMS == 2 && LOAD == kStaged ? 3 : (ITEMS <= 4 ? 2 : 1));
-  const auto kernel = kdfh_kernel<ITEMS, RING, VEC, R2, STRAY, WPE, LOAD>;
+  const auto kernel = kdfh_kernel<ITEMS, RING, VEC, R2, STRAY, WPE, LOAD, G>;
   if (lds > 65536) VD_HIP(ctx, hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   {
     VdTimer timer(ctx, VARDROP_K_HASH, s);
@@ -1606,13 +1754,14 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
   if (kdfh_lds_bytes(pitch, F, Vb, r2) > (size_t)ctx->lds_per_block) return VARDROP_EUNSUPPORTED;
   // Rows of a plane follow each other without gaps but for one unit after every 16 / gcd(2 KS, 16): 16 consecutive rows then
   // start in 16 different units of the 256 bytes a clock of reads covers.  (With an odd pitch instead, 336-sample windows
-  // would leave room for two workgroups a compute unit, not three.)
+  // would leave room for two workgroups a compute unit, not three; the shortest windows keep it.)
   const int KG = 2 * KS;
   const int skew = KG % 16 == 0 ? 0 : (KG % 8 == 0 ? 1 : (KG % 4 == 0 ? 2 : 3));
-  const int plane = 32 * KG + (32 >> skew);
   const int items = vd_ceil_div(32 * KG, kThreads);
+  const int plane = items > 1 ? 32 * KG + (32 >> skew) : 32 * pitch;
   const int staged_units = items > 1 ? (32 * staged_pitch(L) / 4 + 63) & ~63 : 0;
-  const int units = std::max((r2 ? 8 : 4) * plane, staged_units);
+  const int share_units = items == 1 && nct <= 2 && !r2 ? (4 * 4 * 2 * 64 * 16 + 2 * 8 * 32 * 4) / 16 : 0;   // partial sums of shared tiles
+  const int units = std::max({(r2 ? 8 : 4) * plane, staged_units, share_units});
   const size_t stat_bytes = sizeof(float) * (4 + (bins.n_stray > 0 ? kMaxStray : 0)) * 32;
   const size_t lds = (size_t)units * 16 + stat_bytes + sizeof(float) * Vb * F;
   // Windows with the variate index contiguous are read as they are: a workgroup takes 32 rows, four windows of eight variates or two
@@ -1624,7 +1773,7 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
   const int tm_log2_rpv = B <= 1 ? 0 : (B == 2 || (N >= 2048 && L >= 256) ? 1 : 2);
   const int tm_tlog = 3 + tm_log2_rpv;                    // log2 of the points in time a copy of 1 KB holds
   const size_t tm_staged = ((size_t)vd_ceil_div(L, 1 << tm_tlog) * kStagePitch + 16) * sizeof(float) << tm_log2_rpv;
-  const int tm_units = std::max((r2 ? 8 : 4) * plane, (int)(tm_staged / 16));
+  const int tm_units = std::max({(r2 ? 8 : 4) * plane, (int)(tm_staged / 16), share_units});
   const size_t tm_lds = (size_t)tm_units * 16 + stat_bytes;
   const bool tm = st != 1 && sn == 1 && tm_lds <= (size_t)ctx->lds_per_block;
   if (st != 1 && !tm) {
@@ -1707,11 +1856,15 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
       return launch_kdfh_tm<4, 4, true, true>(ctx, a, tm_grid, tm_lds, s);
     }
     if (vec) {
+      if (items <= 1 && nct == 1) return launch_kdfh_tm<1, 2, true, false, false, 4>(ctx, a, tm_grid, tm_lds, s);
+      if (items <= 1 && nct == 2) return launch_kdfh_tm<1, 2, true, false, false, 2>(ctx, a, tm_grid, tm_lds, s);
       if (items <= 1) return launch_kdfh_tm<1, 2, true, false>(ctx, a, tm_grid, tm_lds, s);
       if (items <= 2) return launch_kdfh_tm<2, 4, true, false>(ctx, a, tm_grid, tm_lds, s);
       if (items <= 4) return launch_kdfh_tm<4, 4, true, false>(ctx, a, tm_grid, tm_lds, s);
       return launch_kdfh_tm<8, 4, true, false>(ctx, a, tm_grid, tm_lds, s);
     }
+    if (items <= 1 && nct == 1) return launch_kdfh_tm<1, 2, false, false, false, 4>(ctx, a, tm_grid, tm_lds, s);
+    if (items <= 1 && nct == 2) return launch_kdfh_tm<1, 2, false, false, false, 2>(ctx, a, tm_grid, tm_lds, s);
     if (items <= 1) return launch_kdfh_tm<1, 2, false, false>(ctx, a, tm_grid, tm_lds, s);
     if (items <= 2) return launch_kdfh_tm<2, 4, false, false>(ctx, a, tm_grid, tm_lds, s);
     if (items <= 4) return launch_kdfh_tm<4, 4, false, false>(ctx, a, tm_grid, tm_lds, s);
@@ -1741,12 +1894,16 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
     return launch_kdfh<4, 4, true, true>(ctx, a, grid, lds, s);
   }
   if (vec) {
+    if (items <= 1 && nct == 1) return launch_kdfh<1, 2, true, false, false, kDirect, 4>(ctx, a, grid, lds, s);
+    if (items <= 1 && nct == 2) return launch_kdfh<1, 2, true, false, false, kDirect, 2>(ctx, a, grid, lds, s);
     if (items <= 1) return launch_kdfh<1, 2, true, false>(ctx, a, grid, lds, s);
     if (items <= 2 && many) return launch_kdfh<2, 4, true, false, false, kStaged>(ctx, a, grid, lds, s);
     if (items <= 2) return launch_kdfh<2, 4, true, false>(ctx, a, grid, lds, s);
     if (items <= 4) return launch_kdfh<4, 4, true, false>(ctx, a, grid, lds, s);
     return launch_kdfh<8, 4, true, false>(ctx, a, grid, lds, s);
   }
+  if (items <= 1 && nct == 1) return launch_kdfh<1, 2, false, false, false, kDirect, 4>(ctx, a, grid, lds, s);
+  if (items <= 1 && nct == 2) return launch_kdfh<1, 2, false, false, false, kDirect, 2>(ctx, a, grid, lds, s);
   if (items <= 1) return launch_kdfh<1, 2, false, false>(ctx, a, grid, lds, s);
   if (items <= 2 && many) return launch_kdfh<2, 4, false, false, false, kStaged>(ctx, a, grid, lds, s);
   if (items <= 2) return launch_kdfh<2, 4, false, false>(ctx, a, grid, lds, s);
