@@ -393,38 +393,62 @@ int run_sample(vardrop_ctx* ctx, const uint64_t* hash, int N,
 // per member adds up its squared distances in ascending bins.
 // Single-precision IEEE operations without fused multiply-add throughout: these values decide which
 // members are kept, and the test oracle evaluates them in the same arithmetic and order.
-// Loads of eight members (or bins) are in flight while the sums go on in order; a walk over all variates with one load
-// at a time took 123 us at N = 2048, F = 85, and the distances another 28 us; this kernel takes 18.
+// Bound by its serial chains: loads of 32 members (or bins) are in flight while the sums go on in order, of four blocks of hashes
+// while the group is listed.  With the distances of N = 2048, F = 85, 120 groups the whole call takes 16.7 us (17.9 with eight loads and one
+// block), of one group of 2048 84 (103), of 8192 341 (415).  A piece of the rows at a time through LDS instead: 180 and 711 us.
 // key[n] = bits of sum_f (abar[n][f] - mean[f])^2 in the upper half: non-negative floats order like their bit patterns
 __global__ __launch_bounds__(256) void group_distance_kernel(const uint64_t* __restrict__ hash, const float* __restrict__ abar,
                                                             float* __restrict__ mean, uint64_t* __restrict__ keys, int N, int F) {
   __shared__ uint16_t list[kMaxN];
-  __shared__ int wcnt[4];
+  __shared__ int wcnt[16];
   const int n = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t h = hash[n];
   int earlier = 0;
-  for (int m = tid; m < n; m += 256) earlier |= hash[m] == h ? 1 : 0;
+  for (int m0 = 0; m0 < n; m0 += 4 * 256) {              // (four loads in flight; past n: n - 1 again)
+    uint64_t v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = hash[min(m0 + u * 256 + tid, n - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) earlier |= v[u] == h ? 1 : 0;
+  }
   if (__syncthreads_or(earlier)) return;
   int size = 0;
-  for (int m0 = n; m0 < N; m0 += 256) {
-    const int m = m0 + tid;
-    const bool in = m < N && hash[m] == h;
-    const unsigned long long b = __ballot(in);
-    if (lane == 0) wcnt[wave] = __popcll(b);
-    __syncthreads();
-    int at = size;
+  for (int m0 = n; m0 < N; m0 += 4 * 256) {              // the list: four blocks of 256 at a time
+    uint64_t v[4];
+    unsigned long long b[4];
+    bool in[4];
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      if (w < wave) at += wcnt[w];
-      size += wcnt[w];
+    for (int u = 0; u < 4; ++u) v[u] = hash[min(m0 + u * 256 + tid, N - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      in[u] = m0 + u * 256 + tid < N && v[u] == h;
+      b[u] = __ballot(in[u]);
+      if (lane == 0) wcnt[u * 4 + wave] = __popcll(b[u]);
     }
-    if (in) list[at + __popcll(b & ((1ull << lane) - 1ull))] = (uint16_t)m;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      int at = size;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        if (w < wave) at += wcnt[u * 4 + w];
+        size += wcnt[u * 4 + w];
+      }
+      if (in[u]) list[at + __popcll(b[u] & ((1ull << lane) - 1ull))] = (uint16_t)(m0 + u * 256 + tid);
+    }
     __syncthreads();
   }
   float* mu = mean + (long long)n * F;                   // (a group's mean lies at its first member's place)
   for (int f = tid; f < F; f += 256) {
     float acc = 0.f;
     int i = 0;
+    for (; i + 32 <= size; i += 32) {
+      float x[32];
+#pragma unroll
+      for (int u = 0; u < 32; ++u) x[u] = abar[(long long)list[i + u] * F + f];
+#pragma unroll
+      for (int u = 0; u < 32; ++u) acc = acc + x[u];
+    }
     for (; i + 8 <= size; i += 8) {
       float x[8];
 #pragma unroll
@@ -443,6 +467,16 @@ __global__ __launch_bounds__(256) void group_distance_kernel(const uint64_t* __r
     {
 #pragma clang fp contract(off)                  // product and sum are rounded separately (no fused multiply-add)
       int f = 0;
+      for (; f + 32 <= F; f += 32) {
+        float x[32];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) x[u] = row[f + u] - mu[f + u];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) {
+          const float sq = x[u] * x[u];
+          d = d + sq;
+        }
+      }
       for (; f + 8 <= F; f += 8) {
         float x[8];
 #pragma unroll
