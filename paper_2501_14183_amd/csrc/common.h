@@ -180,12 +180,14 @@ int vd_static_scratch_address(void** out);
 size_t vd_attn_f32_ws_bytes(int B, int n, int d);
 
 // attention back ends (attn_f32.hip, attn_bf16.hip); argument checks are done by the caller
-// K slices of the embedding's weight gradient dWe = z^T dxs (K = B * n_sel rows; tiles of 64 x 128): enough of them
-// to give the chip two workgroups per compute unit, at least 128 rows each, at most 16.  (Host and device.)
+// K slices of the embedding's weight gradient dWe = z^T dxs (K = M = B * n_sel rows, L x d results): a slice fewer is a partial
+// product fewer to write and to sum (1.1 us at 720 x 512), a longer slice 0.45 us per 64 rows, which meet at s^2 = 2600 M / (L d).
+// At most 16, at least 128 rows each.  dWe and its sum, with slices that gave the chip two workgroups a compute unit and two copy
+// stages -> with these and three stages, us: 22.1 -> 15.8 (3008 rows, 720 x 512), 26.7 -> 18.0 (4000, 384 x 768), 16.1 -> 11.5 (960, 1024 x
+// 512), 10.0 -> 7.5 (400, 720 x 512), 29.0 -> 25.7 (10 272, 720 x 512), 20.9 -> 14.7 (27 584, 96 x 512), 9.3 -> 8.8 (3680, 96 x 512).  (Host and device.)
 __host__ __device__ static inline int vd_embed_splitk(int L, int d, long long M, int* kchunk) {
-  const int tiles = vd_ceil_div(L, 64) * vd_ceil_div(d, 128);
-  int s = vd_ceil_div(512, tiles);
-  if (s > 16) s = 16;
+  int s = 1;
+  while (s < 16 && (long long)(s + 1) * (s + 1) * L * d <= 2600 * M) ++s;
   while (s > 1 && M / s < 128) --s;
   int chunk = (int)vd_align_up((size_t)vd_ceil_div((int)M, s), 64);
   if (chunk < 64) chunk = 64;

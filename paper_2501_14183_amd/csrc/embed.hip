@@ -4,7 +4,8 @@
 //
 // Short windows in bf16 (at most 383 samples) take one kernel forward: the standardisation happens inside the
 // operand load of the product (embed_fwd_fused_kernel below), and one product backward, which also yields the bias
-// gradient (a column of ones rides beside the window in the saved operand).  Everything else takes two steps.
+// gradient (a column of ones rides beside the window in the saved operand).  Longer ones take one kernel forward where few
+// workgroups read a window (embed_fwd_long_kernel).  Everything else takes two steps.
 //
 // Two steps.  (1) One wavefront per kept window reads it from the raw batch through `sel` (coalesced:
 // consecutive lanes read consecutive samples), takes mean and variance with wavefront reductions in a
@@ -259,6 +260,159 @@ __global__ __launch_bounds__(256, 2) void embed_fwd_fused_kernel(EmbedFused a) {
   }
 }
 
+// ------------------------------------------------------------------ one launch forward, longer windows (bf16)
+// The same tile of 64 windows x 128 columns for windows whose We panel does not fit the LDS: the whole z tile lies there, We passes
+// through a ring of NS stages of 64 k-rows.  Eight wavefronts: eight threads per window read and standardise it, a wavefront forms
+// 32 x 32 of the product.  One workgroup a compute unit.  All sums run in the order of the two launches it stands for: same bits.
+// Bound by its phases: the windows' loads, the standardisation, UL short slices, the stores (figures at the rule in embed_fwd).
+template <int UL, int NS>   // Lp / 64, stages
+__global__ __launch_bounds__(512, 2) void embed_fwd_long_kernel(EmbedFused a) {
+  constexpr int BM = 64, BN = 128, A_SLICE = BM * 64 * 2, STAGE = 64 * BN * 2, CPITCH = BN * 2 + 16;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+  const int gx = (a.d + BN - 1) / BN, gy = (int)((a.M + BM - 1) / BM);
+  const int t = xcd_contiguous(blockIdx.x, gx * gy);
+  const int bx = t % gx, by = t / gx, m0 = by * BM, n0 = bx * BN, L = a.L;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), col = lane & 31, half = lane >> 5;
+  unsigned char* ring = smem + UL * A_SLICE;
+  // ---- We: copy u of a stage covers k-rows 32 u + 4 wave .. + 3 (past L the last row again: those meet zeros of z)
+  const int cc = min(n0 + (((lane & 15) ^ swz_nc<BN>(lane >> 4)) * 8), a.d - 8);        // (a row's swizzle depends on row % 4)
+  const auto issue = [&](int kt) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int kr = kt * 64 + u * 32 + wave * 4 + (lane >> 4);
+      dma16(a.We + (long long)min(kr, L - 1) * a.d + cc, ring + (kt % NS) * STAGE + u * 8192 + wave * 1024);
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < NS - 1; ++s) issue(s);
+  // ---- the windows: thread j of a row takes its 16-byte chunks (8 samples) j, j + 8, ...
+  {
+    const int r = threadIdx.x >> 3, j = threadIdx.x & 7;
+    const long long m = m0 + r;
+    bool live = m < a.M;
+    const long long b = live ? m / a.n_sel : 0;
+    const int n = live ? a.sel[(int)(m - b * a.n_sel)] : 0;
+    live = live && (unsigned)n < (unsigned)a.N;            // an index out of range stands for a zero window
+    const float* p = a.x + b * a.sb + (long long)(live ? n : 0) * a.sn;
+    const int nchunk = L >> 3;                             // (L is a multiple of 8)
+    float v[UL][8];
+#pragma unroll
+    for (int u = 0; u < UL; ++u) {
+      const int c = j + 8 * u;
+      const float* q = p + 8 * (c < nchunk ? c : 0);
+      if (a.vec) {
+        const float4 lo = reinterpret_cast<const float4*>(q)[0], hi = reinterpret_cast<const float4*>(q)[1];
+        v[u][0] = lo.x; v[u][1] = lo.y; v[u][2] = lo.z; v[u][3] = lo.w;
+        v[u][4] = hi.x; v[u][5] = hi.y; v[u][6] = hi.z; v[u][7] = hi.w;
+      } else {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[u][e] = q[e];
+      }
+    }
+    // (a sample's place in its 64, 8 j + e, is the lane embed_rows_kernel gives it to: the same sums in the same order)
+    const auto total = [](float (&s)[8]) {
+#pragma unroll
+      for (int o = 4; o >= 1; o >>= 1)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s[e] += __shfl_xor(s[e], o, 64);
+      return ((s[0] + s[4]) + (s[2] + s[6])) + ((s[1] + s[5]) + (s[3] + s[7]));
+    };
+    float part[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int u = 0; u < UL; ++u)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        v[u][e] = live && j + 8 * u < nchunk ? v[u][e] : 0.f;
+        part[e] += v[u][e];
+      }
+    if (a.standardise) {
+      const float mean = total(part) / (float)L;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) part[e] = 0.f;
+#pragma unroll
+      for (int u = 0; u < UL; ++u)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          v[u][e] = j + 8 * u < nchunk ? v[u][e] - mean : 0.f;
+          part[e] = fmaf(v[u][e], v[u][e], part[e]);
+        }
+      const float var = total(part) / (float)L;
+      const float inv = var > 0.f ? 1.0f / sqrtf(var) : 1.0f;      // (a constant window is all zeros already)
+#pragma unroll
+      for (int u = 0; u < UL; ++u)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[u][e] *= inv;
+    }
+#pragma unroll
+    for (int u = 0; u < UL; ++u) {
+      u32x4 z;
+      z.x = pack2(v[u][0], v[u][1]); z.y = pack2(v[u][2], v[u][3]);
+      z.z = pack2(v[u][4], v[u][5]); z.w = pack2(v[u][6], v[u][7]);
+      *reinterpret_cast<u32x4*>(smem + u * A_SLICE + r * 128 + ((j ^ swz_kc<64>(r)) * 16)) = z;
+      if (bx == 0 && m < a.M) *reinterpret_cast<u32x4*>(a.saved + m * a.Lp + 8 * (j + 8 * u)) = z;
+    }
+  }
+  wait_vm<0>();                                            // (the stages on the way are in, too; the stores count as well)
+
+  // ---- product, formed transposed: wavefront (wm, wn) takes rows 32 wm .. + 31, columns 32 wn .. + 31
+  const int wm = wave >> 2, wn = wave & 3, ra = wm * 32 + col;
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char*)smem;
+  uint32_t addrA[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) addrA[ks] = lds0 + ra * 128 + (((2 * ks + half) ^ swz_kc<64>(ra)) * 16);
+  const int krow = 8 * half + ((lane & 15) >> 2), mn = wn * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+  const uint32_t addrB = lds0 + UL * A_SLICE + krow * (BN * 2) + (((mn >> 3) ^ swz_nc<BN>(krow)) * 16) + ((mn >> 2) & 1) * 8;
+  floatx16 acc = zero16();
+#pragma unroll
+  for (int kt = 0; kt < UL; ++kt) {
+    // slice kt has landed once only the copies of the slices after it are in flight (the first NS - 1 are in already)
+    if (kt == 0) {
+      __syncthreads();                                     // the z tile is in
+    } else {
+      if (kt >= NS - 1) {
+        if (NS == 3 && kt + 1 < UL) wait_vm<2>(); else wait_vm<0>();
+      }
+      __builtin_amdgcn_s_barrier();                        // everyone has seen slice kt land and is done with slice kt - 1
+    }
+    if (kt + NS - 1 < UL) issue(kt + NS - 1);
+    Frag fa[4], fb[4];
+    const uint32_t so = (kt % NS) * STAGE;
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) {
+      lds_read16(fa[ks].q, addrA[ks] + kt * A_SLICE);
+      lds_read8_tr<0>(fb[ks].d[0], addrB + so + ks * 16 * BN * 2);
+      lds_read8_tr<4 * BN * 2>(fb[ks].d[1], addrB + so + ks * 16 * BN * 2);
+    }
+    wait_lds<9>(fa[0], fb[0]); acc = mfma(fb[0], fa[0], acc);
+    wait_lds<6>(fa[1], fb[1]); acc = mfma(fb[1], fa[1], acc);
+    wait_lds<3>(fa[2], fb[2]); acc = mfma(fb[2], fa[2], acc);
+    wait_lds<0>(fa[3], fb[3]); acc = mfma(fb[3], fa[3], acc);
+  }
+  // ---- output tile through LDS (bias added), then 16-byte chunks of whole rows
+  __syncthreads();
+#pragma unroll
+  for (int q4 = 0; q4 < 4; ++q4) {
+    const int nl = wn * 32 + 8 * q4 + 4 * half;
+    float bv[4] = {0.f, 0.f, 0.f, 0.f};
+    if (a.be && n0 + nl < a.d) {
+      const u32x2 b4 = *reinterpret_cast<const u32x2*>(a.be + n0 + nl);
+      bv[0] = __uint_as_float(b4.x << 16); bv[1] = __uint_as_float(b4.x & 0xffff0000u);
+      bv[2] = __uint_as_float(b4.y << 16); bv[3] = __uint_as_float(b4.y & 0xffff0000u);
+    }
+    u32x2 o;
+    o.x = pack2(acc[4 * q4] + bv[0], acc[4 * q4 + 1] + bv[1]);
+    o.y = pack2(acc[4 * q4 + 2] + bv[2], acc[4 * q4 + 3] + bv[3]);
+    *reinterpret_cast<u32x2*>(smem + ra * CPITCH + nl * 2) = o;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < BM * 16 / 512; ++u) {
+    const int idx = u * 512 + threadIdx.x, row = idx >> 4, c = idx & 15;
+    if (m0 + row < a.M && n0 + c * 8 < a.d)
+      *reinterpret_cast<u32x4*>(a.xs + (m0 + row) * (long long)a.d + n0 + c * 8) = *reinterpret_cast<const u32x4*>(smem + row * CPITCH + c * 16);
+  }
+}
+
 // Bias gradient in fp32 (the bf16 products form it): column sums of dxs (colsum.hip: 16-byte loads of row slices) when rows
 // are whole 16-byte units, else a thread per column and slice, rows ascending, then the slices in order.
 constexpr int kColSlices = 64;
@@ -353,6 +507,19 @@ int launch_embed_fused(vardrop_ctx* ctx, const EmbedFused& a, long long M_bound,
   return VARDROP_OK;
 }
 
+template <int UL>
+int launch_embed_long(vardrop_ctx* ctx, const EmbedFused& a, hipStream_t s) {
+  constexpr int NS = UL <= 14 ? 3 : 2, lds = UL * 64 * 64 * 2 + NS * 64 * 128 * 2;
+  VD_HIP(ctx, hipFuncSetAttribute((const void*)embed_fwd_long_kernel<UL, NS>, hipFuncAttributeMaxDynamicSharedMemorySize, lds));
+  const long long grid = (long long)vd_ceil_div(a.d, 128) * ((a.M + 63) / 64);
+  {
+    VdTimer timer(ctx, VARDROP_K_EMBED_FUSED, s);
+    VD_KERNEL(ctx, (embed_fwd_long_kernel<UL, NS>), dim3((unsigned)grid), dim3(512), lds, s, a);
+  }
+  VD_LAUNCH_CHECK(ctx);
+  return VARDROP_OK;
+}
+
 // n_sel is the count, or with dn.dev its bound
 int embed_fwd(vardrop_ctx* ctx, const float* x, int B, int N, int L, int64_t sb, int64_t sn,
               const int32_t* sel, int n_sel, int standardise, const void* We, const void* be, int d, int dtype,
@@ -365,8 +532,15 @@ int embed_fwd(vardrop_ctx* ctx, const float* x, int B, int N, int L, int64_t sb,
   if (!x || !sel || !We || !xs || !saved) return VARDROP_EINVAL;
   if (!vd_aligned(saved, 256)) return VARDROP_EWORKSPACE;
   const int pitch = embed_pitch(L, dtype);
-  if (embed_fused(L, dtype)) {
-    if (!vd_aligned(We, 16) || !vd_aligned(xs, 16)) return VARDROP_EINVAL;
+  const bool aligned = vd_aligned(We, 16) && vd_aligned(xs, 16);
+  // Longer windows in one launch where its workgroups, one a compute unit, are resident together or a window is read by at most two
+  // of them.  Forward, two launches -> one, us: 13.8 -> 10.9 (3008 windows of 720 samples, d = 512), 11.0 -> 6.8 (3008 of 384, 512),
+  // 12.2 -> 8.3 (3200 of 512, 512), 16.0 -> 13.9 (3008 of 1000, 512), 19.6 -> 13.2 (10 272 of 720, 128), 35.9 -> 32.3 (32 000 of 400, 256),
+  // 10.6 -> 8.8 (40 of 720, 64); but 13.6 -> 13.7 (3008 of 448, 1024), 27.2 -> 31.7 (10 272 of 720, 512), 49.9 -> 71.2 (27 584 of 720, 512).
+  const bool one_launch = dtype == VARDROP_BF16 && !embed_fused(L, dtype) && !dn.dev && aligned &&
+                          (d <= 256 || vd_ceil_div(d, 128) * ((M + 63) / 64) <= ctx->num_cus);
+  if (embed_fused(L, dtype) || one_launch) {
+    if (!aligned) return VARDROP_EINVAL;
     EmbedFused a = {};
     a.x = x; a.sel = sel; a.We = (const bf16_t*)We; a.be = (const bf16_t*)be;
     a.xs = (bf16_t*)xs; a.saved = (bf16_t*)saved;
@@ -379,7 +553,17 @@ int embed_fwd(vardrop_ctx* ctx, const float* x, int B, int N, int L, int64_t sb,
       case 3: return launch_embed_fused<3>(ctx, a, M, s);
       case 4: return launch_embed_fused<4>(ctx, a, M, s);
       case 5: return launch_embed_fused<5>(ctx, a, M, s);
-      default: return launch_embed_fused<6>(ctx, a, M, s);
+      case 6: return embed_fused(L, dtype) ? launch_embed_fused<6>(ctx, a, M, s) : launch_embed_long<6>(ctx, a, s);
+      case 7: return launch_embed_long<7>(ctx, a, s);
+      case 8: return launch_embed_long<8>(ctx, a, s);
+      case 9: return launch_embed_long<9>(ctx, a, s);
+      case 10: return launch_embed_long<10>(ctx, a, s);
+      case 11: return launch_embed_long<11>(ctx, a, s);
+      case 12: return launch_embed_long<12>(ctx, a, s);
+      case 13: return launch_embed_long<13>(ctx, a, s);
+      case 14: return launch_embed_long<14>(ctx, a, s);
+      case 15: return launch_embed_long<15>(ctx, a, s);
+      default: return launch_embed_long<16>(ctx, a, s);
     }
   }
   if (dn.dev) return VARDROP_EUNSUPPORTED;      // the two-step path takes a host count

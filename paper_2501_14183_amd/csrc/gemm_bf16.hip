@@ -719,8 +719,9 @@ int vd_gemm_bf16_wgrad_split(vardrop_ctx* ctx, int kid, const GemmBf16& g, hipSt
   if (g.M % 8 != 0 || g.N % 8 != 0 || g.splitk < 1 || g.kchunk % 64 != 0 ||
       (long long)g.K * g.lda >= (1ll << 31) || (long long)g.K * g.ldb >= (1ll << 31))
     return VARDROP_EUNSUPPORTED;
-  if (g.sum0) return launch_gemm_async_cfg<false, false, true, 64, 2, true>(ctx, kid, g, 1, s);
-  return launch_gemm_async_cfg<false, false, true, 64, 2>(ctx, kid, g, 1, s);
+  // (three stages: with two 20.9 -> 15.0 us and their sum at 27 584 rows of 96 x 512, 26.6 -> 25.5 at 10 272 of 720 x 512)
+  if (g.sum0) return launch_gemm_async_cfg<false, false, true, 64, 3, true>(ctx, kid, g, 1, s);
+  return launch_gemm_async_cfg<false, false, true, 64, 3>(ctx, kid, g, 1, s);
 }
 
 int vd_gemm_bf16_sum_rows(vardrop_ctx* ctx, const float* part, float* out0, long long count0, float* out1, long long count1,

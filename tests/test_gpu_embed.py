@@ -81,6 +81,39 @@ def test_fp32_rows_off_the_16_byte_grid(vd, ctx, B, N, L, d, n_sel):
     check(vd, ctx, x, np.sort(rng.choice(N, n_sel, replace=False)), d, "fp32", standardise=L > 2, bias=True, seed=5)
 
 
+@pytest.mark.parametrize("B,N,L,d,n_sel,lead", [(2, 40, 384, 136, 33, 0), (1, 5, 448, 8, 1, 1), (3, 70, 720, 72, 65, 2), (2, 70, 896, 512, 64, 0),
+                                                (1, 90, 904, 264, 90, 0), (2, 40, 960, 256, 37, 4), (1, 70, 1024, 128, 70, 0)])
+def test_long_windows_in_one_launch(vd, ctx, B, N, L, d, n_sel, lead):
+    """Windows of 384 samples and more at the ends of its range of slices (6 to 16, three stages up to 14), ragged rows and widths,
+    rows that are no aligned float4."""
+    rng = np.random.default_rng([B, N, L, d])
+    big = (rng.standard_normal((B, N, L + lead)) * rng.uniform(0.1, 10, (1, N, 1)) + rng.uniform(-3, 3, (1, N, 1))).astype(np.float32)
+    sel = np.sort(rng.choice(N, n_sel, replace=False)).astype(np.int32)
+    x = np.ascontiguousarray(big[:, :, lead:])
+    want = check(vd, ctx, x, sel, d, "bf16")
+    We, be = embedding_weights(L, d, "bf16", 0)
+    got, _ = vd.vardrop_embed_fwd(ctx, to_dev(big)[:, :, lead:], to_dev(sel), n_sel, to_dev(We, torch.bfloat16), to_dev(be, torch.bfloat16))
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("L", [384, 720, 904, 1024])
+def test_long_windows_in_one_launch_equal_two(vd, ctx, L):
+    """2060 rows of width 1024 take two launches, 74 of them one: the same bits."""
+    rng = np.random.default_rng(L)
+    x = to_dev(rng.standard_normal((2, 1030, L)).astype(np.float32) + 3.0)
+    We, be = embedding_weights(L, 1024, "bf16", 0)
+    Wd, bd = to_dev(We, torch.bfloat16), to_dev(be, torch.bfloat16)
+    sel = np.sort(rng.choice(1030, 37, replace=False)).astype(np.int32)
+    full, saved_full = vd.vardrop_embed_fwd(ctx, x, to_dev(np.arange(1030, dtype=np.int32)), 1030, Wd, bd)
+    kept, saved = vd.vardrop_embed_fwd(ctx, x, to_dev(sel), 37, Wd, bd)
+    torch.cuda.synchronize()
+    at = torch.from_numpy(sel).long().cuda()
+    pitch = (L + 63) // 64 * 64
+    rows = lambda t, n: t[:2 * n * pitch * 2].view(torch.bfloat16).view(2, n, pitch)
+    assert torch.equal(kept, full[:, at]) and torch.equal(rows(saved, 37), rows(saved_full, 1030)[:, at])
+
+
 def test_kept_only_equals_gather_of_the_full_embedding(vd, ctx):
     """Rows of the kept-only embedding are bit-identical to the same rows of the all-variate embedding."""
     rng = np.random.default_rng(3)
