@@ -241,6 +241,23 @@ def test_time_major_mean_amplitudes_bit_equal(vd, ctx, B, N, L, k):
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("B", [1, 2, 3, 8, 13, 32, 37])
+@pytest.mark.parametrize("L,f_min,f_max", [(62, 0, 31), (64, 1, 32), (66, 1, 33), (97, 0, 48), (100, 1, None), (127, 1, 33), (128, 0, 63)])
+def test_short_windows_whose_bin_tiles_are_shared(vd, ctx, B, L, f_min, f_max):
+    """Exactly one bin tile, one bin more, two full ones, the shortest and longest sums the wavefronts share, with every number of rows a variate
+    takes in a block, both layouts of the input, the last block of variates ragged."""
+    rng = np.random.default_rng(B * 1000 + L)
+    x = rng.standard_normal((B, 35, L)).astype(np.float32)
+    x += (6.0 * np.sin(2 * np.pi * 5 * np.arange(L) / L)).astype(np.float32)
+    x *= np.exp(rng.uniform(-3, 3, size=(1, 35, 1))).astype(np.float32)
+    topk, hsh, want_topk, want_hash, flips, flips_screened, ok = compare(vd, ctx, x, 2, f_min=f_min, f_max=f_max)
+    assert flips_screened == 0 and np.array_equal(hsh[ok], want_hash[ok])
+    xt = torch.from_numpy(x).cuda()
+    rows = vd.vardrop_hash(ctx, xt, 2, f_min, f_max, want_abar=True)
+    time_major = vd.vardrop_hash(ctx, xt.transpose(1, 2).contiguous().transpose(1, 2), 2, f_min, f_max, want_abar=True)
+    assert all(torch.equal(u, v) for u, v in zip(rows, time_major))
+
+
 @pytest.mark.parametrize("B,N,L,part", [(16, 1056, 336, 22), (16, 1090, 264, 31), (33, 530, 252, 7), (8, 2100, 167, 41), (40, 520, 180, 5),
                                         (3, 4200, 335, 9), (2, 9000, 140, 17)])
 def test_many_variates_bit_equal_to_few(vd, ctx, B, N, L, part):
