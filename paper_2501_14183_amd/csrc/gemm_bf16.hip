@@ -127,7 +127,7 @@ struct GemmDims {
 // instructions' worth of it (32 KB of LDS reads per slice instead of 48 KB, which is what bounds this tile), and
 // the two K halves are added through LDS before the epilogue, lower half first.
 // SUMS: column sums of B as well (GemmBf16::sum0 ..).
-template <bool AKC, bool BKC, bool SPLIT, int BM, int BK, int NS, bool KH = false, bool SUMS = false, bool ROT = false>
+template <bool AKC, bool BKC, bool SPLIT, int BM, int BK, int NS, bool KH = false, bool SUMS = false>
 __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDims& dm, const int bx, const int by, const int bz) {
   static_assert(!SUMS || (SPLIT && !BKC), "column sums: of a weight gradient's right-hand operand");
   static_assert(!KH || (!AKC && !BKC && SPLIT && BM == 64 && BK == 64), "K halves: 64-row weight-gradient tiles on 64-k stages");
@@ -237,12 +237,8 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
 #pragma unroll
     for (int j = 0; j < 2; ++j) acc[i][j] = zero16();
 
-  // ---- copy cursor (copy wavefront).  With ROT a product of two k-contiguous operands (dO = dy Wo^T) walks over K from a slice that depends on
-  // the tile and wraps: with all tiles on the same k at a time, the tiles of a row and of a column ask for the same 128 bytes of
-  // their rows at once, 4 to 8 of 16 L2 channels at these row lengths.  dO of 27 584 x 512 26.6 -> 23.8 us, 15 440 x 768 32.4 -> 28.3,
-  // 10 272 x 512 15.4 -> 13.4, 6080 x 512 11.2 -> 10.0; with an n-contiguous right operand 0-8 % slower, input gradients 0-4 %.
-  int fseg = 0, fdone = 0;
-  int fk = kbeg + (ROT && nseg == 1 && nk > 0 ? BK * ((by + 2 * bx) % nk) : 0);
+  // ---- copy cursor (copy wavefront)
+  int fseg = 0, fk = kbeg;
   copy_src Ap = copy_source(A0), Bp = copy_source(B0);
 #define VD_ISSUE_STAGE(BUF)                                                                        \
   {                                                                                                \
@@ -263,10 +259,8 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
       }                                                                                            \
     }                                                                                              \
     fk += BK;                                                                                      \
-    if (ROT && fk >= kend) fk = kbeg;                                                              \
-    if (ROT ? ++fdone == nk : fk >= kend) {                                                        \
+    if (fk >= kend) {                                                                              \
       fk = kbeg;                                                                                   \
-      fdone = 0;                                                                                   \
       ++fseg;                                                                                      \
       Ap = copy_source(fseg == 1 ? A1 : A2);                                                       \
       Bp = copy_source(fseg == 1 ? B1 : B2);                                                       \
@@ -581,7 +575,7 @@ __global__ __launch_bounds__(kGemmThreads, BM == 128 || NS > 2 ? 4 : 6) void gem
   const int total = gx * gy * nz * (SPLIT ? dm.splitk : 1);
   if ((int)blockIdx.x >= total) return;
   const int t = xcd_contiguous(blockIdx.x, total);
-  gemm_async_tile<AKC, BKC, SPLIT, BM, BK, NS, false, SUMS, AKC && BKC && !SPLIT>(g, dm, t % gx, (t / gx) % gy, t / (gx * gy));
+  gemm_async_tile<AKC, BKC, SPLIT, BM, BK, NS, false, SUMS>(g, dm, t % gx, (t / gx) % gy, t / (gx * gy));
 }
 // The input gradient (gx: k-contiguous operands, up to three accumulated segments) and the weight
 // gradients (gw: mn-contiguous operands, K slices, fp32 partial products) depend on the same dQ, dK,

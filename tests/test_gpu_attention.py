@@ -134,6 +134,18 @@ def test_bias_gradients_over_row_slices(vd, ctx, B, n, d, H, dtype):
     compare(got, want, dtype, ("dbq", "dbk", "dbv", "dbo"))
 
 
+@pytest.mark.parametrize("B,n,d", [(7, 150, 192), (40, 129, 256), (86, 193, 512)])
+def test_gradients_do_not_depend_on_the_place_in_the_batch(vd, ctx, B, n, d):
+    """Equal windows get equal bits wherever they lie in the batch: 64- and 128-row tiles of dO, windows that share tiles."""
+    xs, W, dy, _ = random_case(B + n, 1, n, d, "bf16", bias=False)
+    td = torch.bfloat16
+    rep = lambda a: to_dev(a, td).expand(B, n, d).contiguous()
+    xs_t, dy_t, W_t = rep(xs), rep(dy), [to_dev(w, td) for w in W]
+    y, saved = vd.vardrop_attn_fwd(ctx, xs_t, *W_t, d // 64)
+    dxs = vd.vardrop_attn_bwd(ctx, dy_t, xs_t, *W_t, d // 64, saved)[0]
+    assert torch.equal(y, y[:1].expand_as(y)) and torch.equal(dxs, dxs[:1].expand_as(dxs))
+
+
 @pytest.mark.parametrize("B,n,d", [(1, 1, 64), (1, 63, 64), (3, 43, 192), (5, 129, 128), (32, 145, 128), (65, 160, 256), (20, 480, 512)])
 def test_bias_gradients_beside_the_weight_gradients(vd, ctx, B, n, d):
     """bf16 column sums come from the tiles of the weight gradients: K slices of one row to several slices, a last slice a row short

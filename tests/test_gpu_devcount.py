@@ -163,6 +163,28 @@ def test_weight_gradient_slices_follow_the_bound(vd, ctx, B, d, H, n_max, counts
             assert rel_err(got, ref.double().cpu().numpy()) <= TOL["bf16"], n
 
 
+def test_token_gradients_do_not_depend_on_the_bound(vd, ctx):
+    """Bounds of 13 600 and 16 800 rows take 64- and 128-row tiles for dO and the same attention kernels: y and dxs bit for bit."""
+    rng = np.random.default_rng(8)
+    B, d, H, n = 40, 512, 8, 340
+    td = torch.bfloat16
+    tok_t = to_dev(rng.standard_normal((B, n, d)).astype(np.float32), td)
+    W_t = [to_dev((rng.standard_normal((d, d)) / np.sqrt(d)).astype(np.float32), td) for _ in range(4)]
+    dy_t = to_dev(rng.standard_normal((B, n, d)).astype(np.float32), td)
+    sel = torch.arange(n, dtype=torch.int32, device="cuda")
+    n_dev = torch.tensor([n], dtype=torch.int32, device="cuda")
+    out = []
+    for n_max in (n, 420):
+        bufs = Buffers(vd, B, n_max, d, H, td, n_max)
+        wide = torch.zeros((B, n_max, d), dtype=td, device="cuda")
+        wide[:, :n] = tok_t
+        run_dev(vd, ctx, bufs, wide, sel, n_dev, W_t, H, dy_t)
+        torch.cuda.synchronize()
+        assert int(bufs.status[0]) == 0
+        out.append([bufs.packed(t, B, n).clone() for t in (bufs.y, bufs.dxs)])
+    assert all(torch.equal(a, b) for a, b in zip(*out))
+
+
 def test_count_outside_the_bound_raises_the_status_and_writes_nothing(vd, ctx):
     rng = np.random.default_rng(5)
     B, N, d, H = 2, 200, 128, 2
