@@ -1443,6 +1443,7 @@ int vd_attn_bwd_bf16(vardrop_ctx* ctx, const void* dy, const void* xs, int B, in
   } else {
     if ((rc = launch_sdpa_bwd(ctx, a, s))) return rc;
   }
+  bool sums_inside;
   {
     // dxs = dq Wq^T + dk Wk^T + dv Wv^T
     GemmBf16 gx = {};
@@ -1464,8 +1465,11 @@ int vd_attn_bwd_bf16(vardrop_ctx* ctx, const void* dy, const void* xs, int B, in
     float* part = (float*)((char*)ws + vd_attn_bf16_partial_offset(B, n, d, H));
     gw.part = part;
     // bias gradients: column sums of the same right-hand operands (their slices in the dO rows, which have served their purpose)
-    for (int z = 0; z < 4; ++z) gw.set_sum(z, db[z]);
-    gw.sum_part = (float*)dO;
+    sums_inside = vd_attn_bf16_sums_inside(d, M, gw.many != 0, gw.splitk, kchunk, ctx->num_cus);
+    if (sums_inside) {
+      for (int z = 0; z < 4; ++z) gw.set_sum(z, db[z]);
+      gw.sum_part = (float*)dO;
+    }
     if (dn.dev) {
       // the kernels derive the slices from the count; the grid is sized for the largest number of them
       gx.count_rows(dn.dev, nullptr, n, B);
@@ -1475,6 +1479,10 @@ int vd_attn_bwd_bf16(vardrop_ctx* ctx, const void* dy, const void* xs, int B, in
     if ((rc = vd_gemm_bf16_bwd_pair(ctx, gx, gw, 4, s))) return rc;
     // a single slice is written as the result itself
     if (gw.splitk > 1 && (rc = vd_gemm_bf16_sum_slices(ctx, part, dW, (long long)d * d, gw.splitk, s, gw))) return rc;
+  }
+  if (!sums_inside && (db[0] || db[1] || db[2] || db[3])) {
+    const void* src[4] = {dq, dk, dv, dy};
+    return vd_colsum(ctx, VARDROP_BF16, src, db, M, d, dO, s, dn, n, B);
   }
   return VARDROP_OK;
 }

@@ -425,8 +425,8 @@ int vd_attn_bwd_f32(vardrop_ctx* ctx, const float* dy, const float* xs, int B, i
   if ((rc = vd_gemm_f32_bwd_pair(ctx, gx, gw, s))) return rc;
   if (db[0] || db[1] || db[2] || db[3]) {
     // (the dO rows of the workspace have served their purpose)
-    const float* src[4] = {dqkv[0], dqkv[1], dqkv[2], dy};
-    return vd_colsum(ctx, src, db, M, d, dO, s, dn, n, B);
+    const void* src[4] = {dqkv[0], dqkv[1], dqkv[2], dy};
+    return vd_colsum(ctx, VARDROP_F32, src, db, M, d, dO, s, dn, n, B);
   }
   return VARDROP_OK;
 }

@@ -164,6 +164,21 @@ static inline bool vd_attn_bf16_many_tokens(int d, long long M) {
   const long long few = tiles + weight_tiles * vd_attn_bf16_splitk(d, M, false, nullptr);
   return many <= 512 || few > 768 || (few > 680 && d >= 320 && d <= 640);
 }
+// Bias gradients: the copy wavefronts of the weight-gradient tiles add up the columns of their right-hand operand while they
+// wait (GemmBf16::sum0 ..), or the two launches of colsum.hip read that operand again.  With few tokens, one workgroup a compute unit,
+// the launch is as long as one weight-gradient tile's chain of slices while there are places for all tiles, and the sums lengthen every
+// slice of it by about 0.1 us: inside only for short chains, or with a tenth more tiles than places.  Whole backward, launches of
+// their own -> inside, us:
+//   d = 64 25.7 -> 25.4 at 1536 rows, 24.4 -> 25.1 at 1792, 34.6 -> 42.0 at 4096; d = 128 23.8 -> 23.0 at 1536, 26.9 -> 27.5 at 2048, 37.6 ->
+//   43.2 at 4096; d = 192 27.0 -> 26.6 at 1792, 28.2 -> 28.7 at 2048; d = 256 31.8 -> 30.9 at 2048, 36.8 -> 38.5 at 3072; d = 384 35.3 -> 34.6 at
+//   2304, 45.0 -> 46.2 at 3072; d = 512 27.1 -> 20.6 at 256, 39.5 -> 38.8 at 2560, 48.2 -> 50.2 at 3584;
+//   several slices: d = 64 40.0 -> 44.8 at 8192 (two of 4096), d = 256 45.9 -> 43.9 at 5120 (two of 2560), 50.9 -> 54.1 at 8192;
+//   more tiles than places: d = 512 61.5 -> 65.0 at 4608 (272 tiles), d = 192 57.5 -> 59.8 at 12 288 (264), d = 384 58.1 -> 56.4 at 6144 (288),
+//   d = 320 1.08x at 12 288 (468), d = 448 1.08x at 8192 (480), from d = 576 on 1.1-1.25x at every count.  Many tokens: 1.01-1.14x.
+static inline bool vd_attn_bf16_sums_inside(int d, long long M, bool many, int splitk, int kchunk, int num_cus) {
+  const long long tiles = (long long)vd_ceil_div(d, 128) * ((M + 127) / 128) + (long long)vd_attn_bf16_weight_tiles(d) * splitk;
+  return many || kchunk <= (d < 384 ? 1024 + 4 * d : 2560) || 10 * tiles >= 11ll * num_cus;
+}
 // Most slices of any count of up to M rows.  The few-token side has more than kManySlices only while one column of tiles
 // (d <= 128) keeps it going past 36864 rows: 15 at its end, 511 tiles.  Grows with M.
 static inline int vd_attn_bf16_max_splitk(int d, long long M) {
@@ -213,8 +228,8 @@ int vd_attn_fwd_bf16(vardrop_ctx*, const void* xs, int B, int n, int d, int H,
 int vd_attn_bwd_bf16(vardrop_ctx*, const void* dy, const void* xs, int B, int n, int d, int H,
                      const void* const W[4], const void* saved, void* dxs,
                      float* const dW[4], float* const db[4], void* ws, hipStream_t s, VdDevCount dn = {nullptr, nullptr});
-// column sums of up to four [rows][d] fp32 matrices (colsum.hip; bf16 ones come with the weight gradients)
-int vd_colsum(vardrop_ctx*, const float* const src[4], float* const dst[4], long long rows, int d,
+// column sums of up to four [rows][d] matrices (colsum.hip)
+int vd_colsum(vardrop_ctx*, int dtype, const void* const src[4], float* const dst[4], long long rows, int d,
               void* scratch, hipStream_t s, VdDevCount dn, int n_max, int n_mul, int nz = 4);
 // gather / scatter with an optional device-side count (gather.hip); argument checks are done by the caller
 int vd_gather(vardrop_ctx*, const void* tokens, int B, int N, int d, int dtype, const int32_t* sel, int n_sel,

@@ -434,9 +434,9 @@ __global__ __launch_bounds__(256) void embed_colsum_final_kernel(const float* __
 }
 int embed_colsum(vardrop_ctx* ctx, const float* src, float* part, float* dst, long long rows, int d, hipStream_t s) {
   if (vd_aligned(src, 16) && d % 4 == 0) {
-    const float* from[4] = {src, nullptr, nullptr, nullptr};
+    const void* from[4] = {src, nullptr, nullptr, nullptr};
     float* to[4] = {dst, nullptr, nullptr, nullptr};
-    return vd_colsum(ctx, from, to, rows, d, part, s, VdDevCount{nullptr, nullptr}, 0, 0, 1);
+    return vd_colsum(ctx, VARDROP_F32, from, to, rows, d, part, s, VdDevCount{nullptr, nullptr}, 0, 0, 1);
   }
   const long long per = (rows + kColSlices - 1) / kColSlices;
   hipLaunchKernelGGL(embed_colsum_part_kernel, dim3(vd_ceil_div(d, 256), kColSlices), dim3(256), 0, s, src, part, rows, per, d);

@@ -148,7 +148,7 @@ def test_gradients_do_not_depend_on_the_place_in_the_batch(vd, ctx, B, n, d):
 
 @pytest.mark.parametrize("B,n,d", [(1, 1, 64), (1, 63, 64), (3, 43, 192), (5, 129, 128), (32, 145, 128), (65, 160, 256), (20, 480, 512)])
 def test_bias_gradients_beside_the_weight_gradients(vd, ctx, B, n, d):
-    """bf16 column sums come from the tiles of the weight gradients: K slices of one row to several slices, a last slice a row short
+    """bf16 column sums come from the tiles of the weight gradients, at 32 x 145 x 128 from launches of their own: K slices of one row to several slices, a last slice a row short
     or over, few- and many-token tiles, a width whose last tile is half empty.  dbo = colsum(dy) against float64 (sums of some
     1e4 positive terms in groups of four: below 1e-6); with the count on the device and with one sum left out the same bits."""
     xs, W, dy, _ = random_case(B + n, B, n, d, "bf16", bias=False)

@@ -185,6 +185,28 @@ def test_token_gradients_do_not_depend_on_the_bound(vd, ctx):
     assert all(torch.equal(a, b) for a, b in zip(*out))
 
 
+@pytest.mark.parametrize("B,d,H,n_max,counts", [(20, 512, 8, 480, (480, 300, 30, 1, 0)), (20, 384, 6, 250, (250, 231, 200, 1, 0)),
+                                                (40, 64, 1, 120, (120, 60, 1, 0)), (8, 512, 8, 128, (128, 77, 0))])
+def test_bias_gradients_under_bounds_of_several_slices(vd, ctx, B, d, H, n_max, counts):
+    """Bounds of several slices (many- and few-token tiles, sums in launches of their own) and of one, with counts that give as many
+    slices, fewer, one and none: all four bias gradients against the float64 column sums of dQ, dK, dV (packed behind the dO rows of the
+    workspace) and dy, from buffers of NaN.  At most 256 additions follow each other in a sum: 256 * 2^-24 of the sum of magnitudes."""
+    rng = np.random.default_rng(n_max)
+    td = torch.bfloat16
+    tok_t = to_dev(rng.standard_normal((B, n_max, d)).astype(np.float32), td)
+    W_t = [to_dev((rng.standard_normal((d, d)) / np.sqrt(d)).astype(np.float32), td) for _ in range(4)]
+    sel = torch.arange(n_max, dtype=torch.int32, device="cuda")
+    for n in counts:
+        bufs = Buffers(vd, B, n_max, d, H, td, n_max, bias_grads=True)
+        dy_t = to_dev(rng.standard_normal((B, max(n, 1), d)).astype(np.float32), td)
+        run_dev(vd, ctx, bufs, tok_t, sel, torch.tensor([n], dtype=torch.int32, device="cuda"), W_t, H, dy_t)
+        torch.cuda.synchronize()
+        assert int(bufs.status[0]) == 0
+        rows = bufs.ws[:4 * B * n_max * d * 2].view(td).view(4, B * n_max, d)[1:, :B * n].double()
+        for got, src in zip(bufs.db, (*rows, dy_t.reshape(-1, d)[:B * n].double())):
+            assert ((got.double() - src.sum(0)).abs() <= 2.0 ** -16 * src.abs().sum(0)).all(), n
+
+
 def test_count_outside_the_bound_raises_the_status_and_writes_nothing(vd, ctx):
     rng = np.random.default_rng(5)
     B, N, d, H = 2, 200, 128, 2
