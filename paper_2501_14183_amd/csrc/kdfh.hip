@@ -1886,21 +1886,23 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
     return launch_kdfh_pipe<2, true, false>(ctx, a, grid, plds, s);
   }
   // Rows staged in LDS by asynchronous copies leave registers for a third workgroup a compute unit at up to 512 items of eight folded
-  // samples; that pays once the registers' two do not hold the grid: us direct -> staged 28.7 -> 25.5 (16 x 2048 x 336), 59.0 -> 49.7
-  // (16 x 4000 x 272), 25.2 -> 23.5 (32 x 862 x 336), 41.6 -> 34.7 (16 x 4000 x 180), 36.6 -> 30.5 (16 x 3000 x 167); but 12.6 -> 13.0
-  // (32 x 321 x 336), 10.8 -> 12.0 (32 x 100 x 167).  Longer rows that are no aligned float4 are staged always: their samples
+  // samples; that pays once the registers' two do not hold the grid and the LDS holds three (384 samples with the radix-2 step):
+  // us direct -> staged 28.7 -> 25.5 (16 x 2048 x 336), 59.0 -> 49.7 (16 x 4000 x 272), 25.2 -> 23.5 (32 x 862 x 336), 41.6 -> 34.7
+  // (16 x 4000 x 180), 36.6 -> 30.5 (16 x 3000 x 167), each back to back; but 12.6 -> 13.0 (32 x 321 x 336), 10.8 -> 12.0 (32 x 100 x 167), and where
+  // the LDS holds two 25.6 -> 27.6 (32 x 862 x 400), 25.2 -> 27.3 (448), 33.0 -> 35.4 (512), 25.4 -> 29.5 (16 x 1300 x 512).
+  // Longer rows that are no aligned float4 are staged always: their samples
   // come one by one, from LDS instead of memory (63.8 -> 37.7 at 32 x 862 x 335, 155 -> 134 at 719, 18.8 -> 16.7 at 32 x 100 x 335);
   // longer aligned ones gain nothing (67.3 -> 72.7 at 64 x 1000 x 500, 20.5 -> 21.9 at 8 x 500 x 768, 74.9 -> 73.2 at 32 x 862 x 720).
-  const bool many = grid > 2 * ctx->num_cus;
+  const bool staged = grid > 2 * ctx->num_cus && 3 * lds <= (size_t)ctx->lds_per_block;   // (a workgroup may have all of a unit's LDS)
   if (r2 && bins.n_stray > 0) {
     if (items <= 1) return launch_kdfh<1, 2, true, true, true>(ctx, a, grid, lds, s);
-    if (items <= 2 && many) return launch_kdfh<2, 4, true, true, true, kStaged>(ctx, a, grid, lds, s);
+    if (items <= 2 && staged) return launch_kdfh<2, 4, true, true, true, kStaged>(ctx, a, grid, lds, s);
     if (items <= 2) return launch_kdfh<2, 4, true, true, true>(ctx, a, grid, lds, s);
     return launch_kdfh<4, 4, true, true, true>(ctx, a, grid, lds, s);
   }
   if (r2) {
     if (items <= 1) return launch_kdfh<1, 2, true, true>(ctx, a, grid, lds, s);
-    if (items <= 2 && many) return launch_kdfh<2, 4, true, true, false, kStaged>(ctx, a, grid, lds, s);
+    if (items <= 2 && staged) return launch_kdfh<2, 4, true, true, false, kStaged>(ctx, a, grid, lds, s);
     if (items <= 2) return launch_kdfh<2, 4, true, true>(ctx, a, grid, lds, s);
     return launch_kdfh<4, 4, true, true>(ctx, a, grid, lds, s);
   }
@@ -1908,7 +1910,7 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
     if (items <= 1 && nct == 1) return launch_kdfh<1, 2, true, false, false, kDirect, 4>(ctx, a, grid, lds, s);
     if (items <= 1 && nct == 2) return launch_kdfh<1, 2, true, false, false, kDirect, 2>(ctx, a, grid, lds, s);
     if (items <= 1) return launch_kdfh<1, 2, true, false>(ctx, a, grid, lds, s);
-    if (items <= 2 && many) return launch_kdfh<2, 4, true, false, false, kStaged>(ctx, a, grid, lds, s);
+    if (items <= 2 && staged) return launch_kdfh<2, 4, true, false, false, kStaged>(ctx, a, grid, lds, s);
     if (items <= 2) return launch_kdfh<2, 4, true, false>(ctx, a, grid, lds, s);
     if (items <= 4) return launch_kdfh<4, 4, true, false>(ctx, a, grid, lds, s);
     return launch_kdfh<8, 4, true, false>(ctx, a, grid, lds, s);
@@ -1916,7 +1918,7 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
   if (items <= 1 && nct == 1) return launch_kdfh<1, 2, false, false, false, kDirect, 4>(ctx, a, grid, lds, s);
   if (items <= 1 && nct == 2) return launch_kdfh<1, 2, false, false, false, kDirect, 2>(ctx, a, grid, lds, s);
   if (items <= 1) return launch_kdfh<1, 2, false, false>(ctx, a, grid, lds, s);
-  if (items <= 2 && many) return launch_kdfh<2, 4, false, false, false, kStaged>(ctx, a, grid, lds, s);
+  if (items <= 2 && staged) return launch_kdfh<2, 4, false, false, false, kStaged>(ctx, a, grid, lds, s);
   if (items <= 2) return launch_kdfh<2, 4, false, false>(ctx, a, grid, lds, s);
   if (items <= 4) return launch_kdfh<4, 4, false, false, false, kStaged>(ctx, a, grid, lds, s);
   return launch_kdfh<8, 4, false, false, false, kStaged>(ctx, a, grid, lds, s);
