@@ -14,6 +14,7 @@
 // Up to 192 variates one workgroup does both in one launch.
 // Measured (both launches; before: one workgroup ordering the variates in LDS): N = 32 3.0 us (8.1), 321 4.3 + 1.8
 // (9.5), 862 6.3 + 2.1 (14.0), 2048 8.9 + 4.7 (25.5), 8192 34 + 5.8 (142).
+#include <type_traits>
 #include "common.h"
 
 namespace {
@@ -404,30 +405,36 @@ __global__ __launch_bounds__(256) void group_distance_kernel(const uint64_t* __r
   const int n = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t h = hash[n];
   int earlier = 0;
-  for (int m0 = 0; m0 < n; m0 += 4 * 256) {              // (four loads in flight; past n: n - 1 again)
-    uint64_t v[4];
+  {                                                      // (four loads in flight; past n: n - 1 again)
+    int m0 = 0;
+    for (; m0 + 256 < n; m0 += 4 * 256) {
+      uint64_t v[4];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = hash[min(m0 + u * 256 + tid, n - 1)];
+      for (int u = 0; u < 4; ++u) v[u] = hash[min(m0 + u * 256 + tid, n - 1)];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) earlier |= v[u] == h ? 1 : 0;
+      for (int u = 0; u < 4; ++u) earlier |= v[u] == h ? 1 : 0;
+    }
+    if (m0 + tid < n) earlier |= hash[m0 + tid] == h ? 1 : 0;
   }
   if (__syncthreads_or(earlier)) return;
   int size = 0;
-  for (int m0 = n; m0 < N; m0 += 4 * 256) {              // the list: four blocks of 256 at a time
-    uint64_t v[4];
-    unsigned long long b[4];
-    bool in[4];
+  // the list: four blocks of 256 at a time, the last one alone
+  const auto collect = [&](int m0, auto blocks) {
+    constexpr int U = decltype(blocks)::value;
+    uint64_t v[U];
+    unsigned long long b[U];
+    bool in[U];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) v[u] = hash[min(m0 + u * 256 + tid, N - 1)];
+    for (int u = 0; u < U; ++u) v[u] = hash[min(m0 + u * 256 + tid, N - 1)];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < U; ++u) {
       in[u] = m0 + u * 256 + tid < N && v[u] == h;
       b[u] = __ballot(in[u]);
       if (lane == 0) wcnt[u * 4 + wave] = __popcll(b[u]);
     }
     __syncthreads();
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < U; ++u) {
       int at = size;
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
@@ -437,6 +444,11 @@ __global__ __launch_bounds__(256) void group_distance_kernel(const uint64_t* __r
       if (in[u]) list[at + __popcll(b[u] & ((1ull << lane) - 1ull))] = (uint16_t)(m0 + u * 256 + tid);
     }
     __syncthreads();
+  };
+  {
+    int m0 = n;
+    for (; m0 + 256 < N; m0 += 4 * 256) collect(m0, std::integral_constant<int, 4>());
+    if (m0 < N) collect(m0, std::integral_constant<int, 1>());
   }
   float* mu = mean + (long long)n * F;                   // (a group's mean lies at its first member's place)
   for (int f = tid; f < F; f += 256) {

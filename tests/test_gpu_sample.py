@@ -238,6 +238,20 @@ def test_representatives_sizes_ties_and_large_groups(vd, ctx, N, F, n_distinct, 
     check_nearest(vd, ctx, h, A, gs, num, den)
 
 
+@pytest.mark.parametrize("N", [255, 256, 257, 513, 1024, 1025, 1280, 1281, 2305])
+def test_representatives_groups_across_blocks_of_variates(vd, ctx, N):
+    """Group lists are made from blocks of 256 variates, four at a time and the last one alone: groups that begin and end at either side
+    of a block, one that spans all."""
+    rng = np.random.default_rng(N)
+    h = np.full(N, 3, dtype=np.uint64)
+    for i, at in enumerate(range(255, N, 256)):
+        h[at - 2:at + 3] = 10 + i
+    h[-1] = h[N // 2] = 7
+    A = np.abs(rng.standard_normal((N, 19))) + 1.0
+    check_nearest(vd, ctx, h, A, 0, 1, 4)
+    check_nearest(vd, ctx, h, A, 2, 1, 1)
+
+
 def test_representatives_clear_gaps_are_exact(vd, ctx):
     """Members at well separated distances from the group mean (geometric spacing): every group is decided, so the
     selection equals the oracle's exactly."""
