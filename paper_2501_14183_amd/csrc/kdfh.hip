@@ -222,21 +222,34 @@ __device__ inline int wave_reduce(int v) {
   return __builtin_amdgcn_readlane(v, 63);
 }
 
-// Ranked top-k of up to 32 mean amplitudes: lane b of either half holds bin b and counts over half of the bins how many beat it (a
-// larger amplitude, or an equal one of a lower bin); the lanes of rank 0 .. k-1 are the result.  Returns the hash.
-__device__ __forceinline__ unsigned long long rank_short(const KdfhArgs& a, const float* amp, int n, int lane) {
-  const int F = a.F, b = lane & 31, j0 = (lane >> 5) * 16;
-  const float mine = b < F ? amp[b] : -2.f;
-  float other[16];
-#pragma unroll
-  for (int u = 0; u < 16; ++u) other[u] = amp[min(j0 + u, F - 1)];
+// Ranked top-k of up to 64 mean amplitudes: lane b holds bin b and counts the bins that beat it (a larger amplitude, or an equal one of
+// a lower bin); the lanes of rank 0 .. k-1 are the result.  Up to 32 bins either half of the wavefront counts over half of them, eight
+// LDS reads in flight; more come one by one from the lanes that hold them (from LDS, eight at a time: 22.2 -> 28.1 us at 1 x 321 x 136, 8.1 ->
+// 8.9 at 16 x 321 x 136; from the lanes four at a time: 26.0 and 8.6).  Returns the hash.
+__device__ __forceinline__ unsigned long long rank_few(const KdfhArgs& a, const float* amp, int n, int lane) {
+  const int F = a.F;
   int rank = 0;
+  if (F <= 32) {
+    const int b = lane & 31, cnt = (F + 1) >> 1, j0 = (lane >> 5) * cnt, j1 = min(j0 + cnt, F);
+    const float mine = b < F ? amp[b] : -2.f;
+    for (int u0 = 0; u0 < cnt; u0 += 8) {
+      float other[8];
 #pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    const int j = j0 + u;
-    rank += j < F && (other[u] > mine || (other[u] == mine && j < b)) ? 1 : 0;
+      for (int u = 0; u < 8; ++u) other[u] = amp[min(j0 + u0 + u, F - 1)];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const int j = j0 + u0 + u;
+        rank += j < j1 && (other[u] > mine || (other[u] == mine && j < b)) ? 1 : 0;
+      }
+    }
+    rank += __shfl_xor(rank, 32, 64);
+  } else {
+    const float mine = lane < F ? amp[lane] : -2.f;
+    for (int j = 0; j < F; ++j) {
+      const float other = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), j));
+      rank += other > mine || (other == mine && j < lane) ? 1 : 0;
+    }
   }
-  rank += __shfl_xor(rank, 32, 64);
   const unsigned long long R = (unsigned long long)(a.L / 2 + 1);
   unsigned long long h = 0;
   for (int r = 0; r < a.k; ++r) {
@@ -990,31 +1003,16 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
   for (int v = wave; v < Vb; v += kWaves) {
     const int n = n0 + v;
     if (n >= a.N) break;
-    float vals[kMaxBinsPerLane];
-#pragma unroll
-    for (int j = 0; j < kMaxBinsPerLane; ++j) {
-      const int idx = lane + 64 * j;
-      vals[j] = idx < F ? asum[v * F + idx] : -2.f;
-    }
     unsigned long long h = 0;
-    if (G == 4 && Vb <= 8) {                     // (more of them in sequence: its LDS reads cost more than the loop below)
-      h = rank_short(a, asum + v * F, n, lane);
-    } else if (F <= 64) {
-      // every lane holds one bin: its rank is the number of bins that beat it (larger mean amplitude, or
-      // equal and lower index); the lanes of rank 0 .. k-1 are the ranked top-k
-      const float mine = vals[0];
-      int rank = 0;
-      for (int j = 0; j < F; ++j) {
-        const float vj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), j));
-        rank += (vj > mine || (vj == mine && j < lane)) ? 1 : 0;
-      }
-      for (int r = 0; r < a.k; ++r) {
-        const unsigned long long mask = __ballot(lane < F && rank == r);
-        const int fsel = a.f_min + (__ffsll((long long)mask) - 1);
-        if (lane == 0) a.topk[(long long)n * a.k + r] = fsel;
-        h = h * R + (unsigned long long)(unsigned)fsel;
-      }
+    if (F <= 64) {
+      h = rank_few(a, asum + v * F, n, lane);
     } else {
+      float vals[kMaxBinsPerLane];
+#pragma unroll
+      for (int j = 0; j < kMaxBinsPerLane; ++j) {
+        const int idx = lane + 64 * j;
+        vals[j] = idx < F ? asum[v * F + idx] : -2.f;
+      }
       // k rounds of a wavefront-wide arg-max.  Mean amplitudes are not negative, so their bit patterns order
       // like signed integers (the -2 of a used or absent bin is below all of them).
       for (int r = 0; r < a.k; ++r) {
@@ -1267,37 +1265,23 @@ __device__ __forceinline__ void pipe_produce(RawRows<IW, R2>& w, const KdfhArgs&
 
 // ranked top-k and hash (Alg. 1 steps 4-5) of the variates v = cw, cw + 4, ... of a group, from its batch sums;
 // (the stray bins' row amplitudes of the group's last block have been added by the caller)
-template <bool SHORT = false>
 __device__ __forceinline__ void pipe_rank(const KdfhArgs& a, float* asum, int n0, int cw, int lane) {
   const int F = a.F, Vb = 32 >> a.log2_rpv;
   const unsigned long long R = (unsigned long long)(a.L / 2 + 1);
   for (int v = cw; v < Vb; v += 4) {
     const int n = n0 + v;
     if (n < a.N) {
-      const int nslot = (F + 63) >> 6;             // bin lane + 64 j lives in slot j: only these slots hold bins
-      float vals[kMaxBinsPerLane];
-#pragma unroll
-      for (int j = 0; j < kMaxBinsPerLane; ++j) {
-        const int idx = lane + 64 * j;
-        vals[j] = (j < nslot && idx < F) ? asum[v * F + idx] : -2.f;
-      }
       unsigned long long h = 0;
-      if (SHORT && F <= 32) {
-        h = rank_short(a, asum + v * F, n, lane);
-      } else if (F <= 64) {
-        const float mine = vals[0];
-        int rank = 0;
-        for (int j = 0; j < F; ++j) {
-          const float vj = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), j));
-          rank += (vj > mine || (vj == mine && j < lane)) ? 1 : 0;
-        }
-        for (int r = 0; r < a.k; ++r) {
-          const unsigned long long mask = __ballot(lane < F && rank == r);
-          const int fsel = a.f_min + (__ffsll((long long)mask) - 1);
-          if (lane == 0) a.topk[(long long)n * a.k + r] = fsel;
-          h = h * R + (unsigned long long)(unsigned)fsel;
-        }
+      if (F <= 64) {
+        h = rank_few(a, asum + v * F, n, lane);
       } else {
+        const int nslot = (F + 63) >> 6;           // bin lane + 64 j lives in slot j: only these slots hold bins
+        float vals[kMaxBinsPerLane];
+#pragma unroll
+        for (int j = 0; j < kMaxBinsPerLane; ++j) {
+          const int idx = lane + 64 * j;
+          vals[j] = (j < nslot && idx < F) ? asum[v * F + idx] : -2.f;
+        }
         // k rounds: the largest value by one wavefront reduction, then the lowest bin that holds it: bin lane + 64 j
         // grows with j before it grows with the lane, so it is the first set lane of the first non-empty ballot
         for (int r = 0; r < a.k; ++r) {
@@ -1376,7 +1360,7 @@ __global__ __launch_bounds__(256) void kdfh_rank_kernel(KdfhArgs a) {
     }
   }
   a.log2_rpv = 3;                                        // four variates a workgroup, one a wavefront
-  pipe_rank<true>(a, asum, blockIdx.x * 4, wave, lane);
+  pipe_rank(a, asum, blockIdx.x * 4, wave, lane);
 }
 
 // Workgroup barrier that orders LDS accesses only: outstanding global loads (the next block's rows, the table

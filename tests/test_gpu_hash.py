@@ -241,6 +241,24 @@ def test_time_major_mean_amplitudes_bit_equal(vd, ctx, B, N, L, k):
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("F", [1, 2, 7, 8, 9, 16, 17, 31, 32, 33, 63, 64, 65])
+@pytest.mark.parametrize("B", [1, 3, 6, 20])
+def test_ranking_of_few_bins(vd, ctx, B, F):
+    """Ranks by counting: bins in one batch of eight reads, a bin more, both halves of the wavefront, more than 32, with ties
+    (windows of zeros: every amplitude equal, the lowest bins win) and with k = all bins, both layouts of the input."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B * 100 + F)
+    x = torch.randn((B, 21, 160), generator=g, device="cuda")
+    x[:, 4] = 0.0
+    k = min(F, 5)
+    for view in (x, x.transpose(1, 2).contiguous().transpose(1, 2)):
+        topk, hsh, abar = vd.vardrop_hash(ctx, view, k, 2, F + 1, want_abar=True)
+        a = abar.cpu().numpy()
+        order = np.argsort(-a, axis=1, kind="stable")[:, :k] + 2
+        assert np.array_equal(topk.cpu().numpy(), order)
+        assert order[4].tolist() == list(range(2, 2 + k))
+
+
 @pytest.mark.parametrize("B", [1, 2, 3, 8, 13, 32, 37])
 @pytest.mark.parametrize("L,f_min,f_max", [(62, 0, 31), (64, 1, 32), (66, 1, 33), (97, 0, 48), (100, 1, None), (127, 1, 33), (128, 0, 63)])
 def test_short_windows_whose_bin_tiles_are_shared(vd, ctx, B, L, f_min, f_max):
