@@ -127,8 +127,7 @@ __global__ void twiddle_kernel(halfx8* tw, int L, BinMap m, int f_max, int T, in
   for (int q = 0; q < 4; ++q) tw[base + (size_t)q * 64] = out[q];
 }
 
-// Windows whose time stride is not 1 and whose variate stride is not 1 either (or whose operands and sums do not fit the LDS
-// together) are first copied into time-contiguous rows: 32 x 32 tiles through LDS, read with the variate index fastest
+// Windows whose time stride is not 1 and whose variate stride is not 1 either (and small batches: see vardrop_hash) are first copied into time-contiguous rows: 32 x 32 tiles through LDS, read with the variate index fastest
 // (coalesced when the variate stride is 1), written with time fastest.
 __global__ __launch_bounds__(256) void time_contiguous_kernel(const float* x, float* out, int N, int L,
                                                               long long sb, long long sn, long long st) {
@@ -1770,7 +1769,15 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
   const size_t tm_staged = ((size_t)vd_ceil_div(L, 1 << tm_tlog) * kStagePitch + 16) * sizeof(float) << tm_log2_rpv;
   const int tm_units = std::max({(r2 ? 8 : 4) * plane, (int)(tm_staged / 16), share_units});
   const size_t tm_lds = (size_t)tm_units * 16 + stat_bytes;
-  const bool tm = st != 1 && sn == 1 && tm_lds <= (size_t)ctx->lds_per_block;
+  const bool tm_vec4 = N % 4 == 0 && sb % 4 == 0 && st % 4 == 0 && vd_aligned(x, 16);
+  // A few variates of 5 to 32 windows (3 and 4 if long) are copied: the sums of their blocks and the launch that adds them up cost more than
+  // the copy of so little, more so when four variates are no aligned 16 bytes.  us, copy / as they are, aligned: 14.4 / 15.8 (8 x 8 x 512),
+  // 12.4 / 12.7 (24 x 16 x 336), 13.4 / 13.0 (6 x 148 x 336), 11.6 / 11.2 (8 x 148 x 168); not aligned: 15.2 / 17.7 (12 x 50 x 512), 12.8 / 14.1 (16 x 34 x 336),
+  // 11.4 / 12.0 (24 x 34 x 168), 16.0 / 16.4 (8 x 202 x 512), 14.1 / 14.0 (24 x 102 x 336), 13.8 / 13.2 (20 x 102 x 240), 24.3 / 25.4 (4 x 34 x 1000), 15.3 / 15.2 (4 x
+  // 202 x 336).  Where wavefronts share a bin tile the windows are read as they are at every size (10.0 / 9.6 at 8 x 8 x 96).
+  const int tm_few = tm_vec4 ? (B > 4 ? 700 : 0) : (B > 4 ? 2048 : (L > 256 ? 700 : 0));
+  const bool copied = B > 2 && B <= 32 && share_units == 0 && (long long)B * N < tm_few;
+  const bool tm = st != 1 && sn == 1 && !copied && tm_lds <= (size_t)ctx->lds_per_block;
   if (st != 1 && !tm) {
     // time-contiguous copy of the windows in the workspace; the kernel below then reads that
     hipLaunchKernelGGL(time_contiguous_kernel, dim3(vd_ceil_div(N, 32), vd_ceil_div(L, 32), B), dim3(256), 0, s,
@@ -1833,7 +1840,7 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
   const bool pipe = r2 && L >= 384 && iw <= 2 && plds <= (size_t)ctx->lds_per_block && (long long)grid * nrb >= 4ll * ctx->num_cus;
   if (tm) {
     a.st = st;
-    a.vec4 = N % 4 == 0 && sb % 4 == 0 && st % 4 == 0 && vd_aligned(x, 16);
+    a.vec4 = tm_vec4;
     a.units = tm_units;
     a.trunc = pipe;
     a.part = (float*)ws;

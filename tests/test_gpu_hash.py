@@ -241,6 +241,20 @@ def test_time_major_mean_amplitudes_bit_equal(vd, ctx, B, N, L, k):
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("B,N,L", [(9, 227, 136), (9, 229, 136), (17, 121, 720), (32, 20, 300), (32, 24, 300), (4, 149, 335), (4, 205, 335),
+                                   (5, 3, 260), (32, 66, 252), (8, 256, 512)])
+def test_time_major_batches_around_the_size_that_is_copied(vd, ctx, B, N, L):
+    """Small batches go through a time-contiguous copy, larger ones are read as they are: the same bits on either side of the line,
+    with aligned variates and without."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(B * N + L)
+    for pad in (0, 1):
+        view = torch.randn((B, L, N + pad), generator=g, device="cuda")[:, :, pad:].transpose(1, 2)
+        got = vd.vardrop_hash(ctx, view, 3, want_abar=True)
+        want = vd.vardrop_hash(ctx, view.contiguous(), 3, want_abar=True)
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+
+
 @pytest.mark.parametrize("F", [1, 2, 7, 8, 9, 16, 17, 31, 32, 33, 63, 64, 65])
 @pytest.mark.parametrize("B", [1, 3, 6, 20])
 def test_ranking_of_few_bins(vd, ctx, B, F):
