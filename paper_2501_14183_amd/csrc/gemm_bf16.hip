@@ -13,6 +13,7 @@ struct SplitkReduce {
   const float* sum_part;   // and of the column sums that ride along (nullptr: none), N a matrix
   float* sum[4];
   int N;
+  int blocks;          // workgroups of a matrix; those behind them add up its column sums
   int splitk;
   // device-side token count: the slice count is the one the weight-gradient kernel derived from it (d = dn_d)
   const int32_t* n_dev;
@@ -30,6 +31,31 @@ struct SplitkReduceRows {
   const int32_t* n_dev;
   int n_max, n_mul, dn_m, dn_n;
 };
+// add(get(0)), add(get(1)), ... add(get(n - 1)) in order, up to eight in flight.  (A loop that takes four at a time and the rest one by
+// one waits four times for seven slices; one branch per slice costs a single slice 0.3 us.)
+template <int U, typename GET, typename ADD>
+__device__ __forceinline__ void add_slices_fixed(int k0, GET get, ADD add) {
+  decltype(get(0)) v[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) v[u] = get(k0 + u);
+#pragma unroll
+  for (int u = 0; u < U; ++u) add(v[u]);
+}
+template <typename GET, typename ADD>
+__device__ __forceinline__ void add_slices(int n, GET get, ADD add) {
+  int k0 = 0;
+  for (; k0 + 8 <= n; k0 += 8) add_slices_fixed<8>(k0, get, add);
+  switch (n - k0) {
+    case 1: add_slices_fixed<1>(k0, get, add); break;
+    case 2: add_slices_fixed<2>(k0, get, add); break;
+    case 3: add_slices_fixed<3>(k0, get, add); break;
+    case 4: add_slices_fixed<4>(k0, get, add); break;
+    case 5: add_slices_fixed<5>(k0, get, add); break;
+    case 6: add_slices_fixed<6>(k0, get, add); break;
+    case 7: add_slices_fixed<7>(k0, get, add); break;
+    default: break;
+  }
+}
 __global__ __launch_bounds__(256) void splitk_reduce_rows_kernel(SplitkReduceRows a) {
   int splitk = a.splitk;
   if (a.n_dev) {
@@ -41,43 +67,38 @@ __global__ __launch_bounds__(256) void splitk_reduce_rows_kernel(SplitkReduceRow
   for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (long long)gridDim.x * blockDim.x) {
     const float* p = a.part + i;
     float s = 0.f;
-    int k = 0;
-    for (; k + 4 <= splitk; k += 4) {            // four loads in flight, added in slice order
-      const float p0 = p[(long long)k * a.stride], p1 = p[(long long)(k + 1) * a.stride];
-      const float p2 = p[(long long)(k + 2) * a.stride], p3 = p[(long long)(k + 3) * a.stride];
-      s = ((s + p0) + p1) + p2 + p3;
-    }
-    for (; k < splitk; ++k) s += p[(long long)k * a.stride];
+    add_slices(splitk, [&](int k) { return p[(long long)k * a.stride]; }, [&](float v) { s += v; });
     if (i < a.count0) a.out0[i] = s; else a.out1[i - a.count0] = s;
   }
 }
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(SplitkReduce a) {
+  int splitk = a.splitk;
   if (a.n_dev) {
     int n;
     if (!vd_count(a.n_dev, a.n_max, n)) return;
-    a.splitk = vd_attn_bf16_splitk(a.dn_d, (long long)a.n_mul * n, a.many != 0, nullptr);
-    if (a.splitk <= 1 && n > 0) return;          // a single slice was written as the result itself
-    if (n == 0) a.splitk = 0;                    // no tokens: the gradients are zero
+    splitk = vd_attn_bf16_splitk(a.dn_d, (long long)a.n_mul * n, a.many != 0, nullptr);
+    if (splitk <= 1 && n > 0) return;            // a single slice was written as the result itself
+    if (n == 0) splitk = 0;                      // no tokens: the gradients are zero
   }
   const int z = blockIdx.y;
-  const float4* src = reinterpret_cast<const float4*>(a.part + (long long)z * a.splitk * a.count);
-  float4* dst = reinterpret_cast<float4*>(a.out[z]);
-  const long long n4 = a.count >> 2;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += (long long)gridDim.x * blockDim.x) {
-    float4 s = a.splitk > 0 ? src[i] : make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int k = 1; k < a.splitk; ++k) {
-      const float4 v = src[(long long)k * n4 + i];
-      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-    }
-    dst[i] = s;
+  if ((int)blockIdx.x >= a.blocks) {
+    const int c = ((int)blockIdx.x - a.blocks) * blockDim.x + threadIdx.x;
+    float* dst = z == 0 ? a.sum[0] : (z == 1 ? a.sum[1] : (z == 2 ? a.sum[2] : a.sum[3]));
+    if (!dst || c >= a.N) return;
+    const float* p = a.sum_part + (long long)z * splitk * a.N + c;
+    float s = 0.f;
+    add_slices(splitk, [&](int k) { return p[(long long)k * a.N]; }, [&](float v) { s += v; });
+    dst[c] = s;
+    return;
   }
-  if (a.sum_part && a.sum[z] && blockIdx.x == 0) {
-    for (int c = threadIdx.x; c < a.N; c += blockDim.x) {
-      const float* p = a.sum_part + (long long)z * a.splitk * a.N + c;
-      float s = 0.f;
-      for (int k = 0; k < a.splitk; ++k) s += p[(long long)k * a.N];
-      a.sum[z][c] = s;
-    }
+  const long long n4 = a.count >> 2;
+  const float4* src = reinterpret_cast<const float4*>(a.part) + (long long)z * splitk * n4;
+  float4* dst = reinterpret_cast<float4*>(z == 0 ? a.out[0] : (z == 1 ? a.out[1] : (z == 2 ? a.out[2] : a.out[3])));
+  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n4; i += (long long)a.blocks * blockDim.x) {
+    float4 s = splitk > 0 ? src[i] : make_float4(0.f, 0.f, 0.f, 0.f);
+    add_slices(splitk - 1, [&](int k) { return src[(long long)(k + 1) * n4 + i]; },
+               [&](const float4& v) { s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w; });
+    dst[i] = s;
   }
 }
 
@@ -760,9 +781,11 @@ int vd_gemm_bf16_sum_slices(vardrop_ctx* ctx, const float* part, float* const ou
   for (int z = 0; z < nz; ++z) r.out[z] = out[z];
   r.count = count;
   r.splitk = splitk;
+  r.blocks = vd_ceil_div((int)(count / 4), 256);
   {
     VdTimer timer(ctx, VARDROP_K_REDUCE_DW, s);
-    VD_KERNEL(ctx, splitk_reduce_kernel, dim3(vd_ceil_div((int)(count / 4), 256), nz), dim3(256), 0, s, r);
+    const bool sums = r.sum_part && (r.sum[0] || r.sum[1] || r.sum[2] || r.sum[3]);
+    VD_KERNEL(ctx, splitk_reduce_kernel, dim3(r.blocks + (sums ? vd_ceil_div(r.N, 256) : 0), nz), dim3(256), 0, s, r);
   }
   VD_LAUNCH_CHECK(ctx);
   return VARDROP_OK;
