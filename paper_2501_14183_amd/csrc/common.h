@@ -197,12 +197,15 @@ size_t vd_attn_f32_ws_bytes(int B, int n, int d);
 // attention back ends (attn_f32.hip, attn_bf16.hip); argument checks are done by the caller
 // K slices of the embedding's weight gradient dWe = z^T dxs (K = M = B * n_sel rows, L x d results): a slice fewer is a partial
 // product fewer to write and to sum (1.1 us at 720 x 512), a longer slice 0.45 us per 64 rows, which meet at s^2 = 2600 M / (L d).
-// At most 16, at least 128 rows each.  dWe and its sum, with slices that gave the chip two workgroups a compute unit and two copy
-// stages -> with these and three stages, us: 22.1 -> 15.8 (3008 rows, 720 x 512), 26.7 -> 18.0 (4000, 384 x 768), 16.1 -> 11.5 (960, 1024 x
-// 512), 10.0 -> 7.5 (400, 720 x 512), 29.0 -> 25.7 (10 272, 720 x 512), 20.9 -> 14.7 (27 584, 96 x 512), 9.3 -> 8.8 (3680, 96 x 512).  (Host and device.)
+// At most 16, at least 128 rows each, and no more than leave all tiles resident together (10 272 rows of 1024 x 1024 with five of 128
+// tiles 48.1 us, with four 35.7).  dWe and its sum back to back, with slices that gave the chip two workgroups a compute unit and two copy
+// stages -> with these and three stages, us: 24.8 -> 15.4 (3008 rows, 720 x 512; inside a step 18 -> 16), 33.8 -> 22.9 (10 272), 33.3 -> 25.3
+// (10 272, 1024 x 512), 21.8 -> 15.4 (27 584, 96 x 512), 9.4 -> 8.7 (3680, 96 x 512; inside a step 11.4 -> 11.4), 7.9 -> 8.0 (800, 240 x 512), 18.3 ->
+// 18.9 (10 272, 240 x 1024).  (Host and device.)
 __host__ __device__ static inline int vd_embed_splitk(int L, int d, long long M, int* kchunk) {
+  const int most = 512 / (vd_ceil_div(L, 64) * vd_ceil_div(d, 128));       // slices whose tiles are resident together
   int s = 1;
-  while (s < 16 && (long long)(s + 1) * (s + 1) * L * d <= 2600 * M) ++s;
+  while (s < 16 && s < most && (long long)(s + 1) * (s + 1) * L * d <= 2600 * M) ++s;
   while (s > 1 && M / s < 128) --s;
   int chunk = (int)vd_align_up((size_t)vd_ceil_div((int)M, s), 64);
   if (chunk < 64) chunk = 64;
