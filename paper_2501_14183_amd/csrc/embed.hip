@@ -533,12 +533,21 @@ int embed_fwd(vardrop_ctx* ctx, const float* x, int B, int N, int L, int64_t sb,
   if (!vd_aligned(saved, 256)) return VARDROP_EWORKSPACE;
   const int pitch = embed_pitch(L, dtype);
   const bool aligned = vd_aligned(We, 16) && vd_aligned(xs, 16);
-  // Longer windows in one launch where its workgroups, one a compute unit, are resident together or a window is read by at most two
-  // of them.  Forward, two launches -> one, us: 13.8 -> 10.9 (3008 windows of 720 samples, d = 512), 11.0 -> 6.8 (3008 of 384, 512),
-  // 12.2 -> 8.3 (3200 of 512, 512), 16.0 -> 13.9 (3008 of 1000, 512), 19.6 -> 13.2 (10 272 of 720, 128), 35.9 -> 32.3 (32 000 of 400, 256),
-  // 10.6 -> 8.8 (40 of 720, 64); but 13.6 -> 13.7 (3008 of 448, 1024), 27.2 -> 31.7 (10 272 of 720, 512), 49.9 -> 71.2 (27 584 of 720, 512).
+  // Longer windows in one launch where its workgroups, one a compute unit, are resident together; windows that one workgroup reads also
+  // up to 512 samples, and up to 896 from one and a half rounds of the chip on; windows that two read up to 512 samples and as many
+  // rounds.  From 961 samples on two copy stages are left, which pays from 1000 rows on.  Forward, two launches -> one, us, back to back:
+  //   resident: 13.9 -> 12.1 (3008 windows of 720 samples, d = 512; inside a step 6.2 + 8.8 -> 13.7), 11.0 -> 6.8 (3008 of 384, 512), 12.2 -> 8.3 (3200
+  //     of 512, 512), 20.3 -> 15.1 (10 272 of 720, 128), 10.6 -> 8.8 (40 of 720, 64), 16.1 -> 14.7 (3008 of 1024, 512), 13.9 -> 13.3 (2048 of 1024, 128),
+  //     but 12.0 -> 12.4 (128 of 1024, 128), 12.7 -> 13.0 (400 of 1024, 512);
+  //   one reads: 22.5 -> 20.4 (17 280 of 512, 128: 270 workgroups), 48.8 -> 47.1 (55 168 of 512, 128: 862), 33.9 -> 31.9 (27 584 of 720, 128: 431), but 26.6 ->
+  //     27.4 (17 280 of 720, 128), 41.5 -> 44.2 (27 584 of 1024, 128);
+  //   two: 20.4 -> 17.6 (10 272 of 512, 192: 322), but 22.7 -> 24.4 (10 272 of 720, 192), 25.2 -> 27.2 (17 280 of 512, 192: 540), 70.7 -> 93.4 (55 168 of 720, 256);
+  //   four: 27.2 -> 31.7 (10 272 of 720, 512).
+  const long long wgs = vd_ceil_div(d, 128) * ((M + 63) / 64);
   const bool one_launch = dtype == VARDROP_BF16 && !embed_fused(L, dtype) && !dn.dev && aligned &&
-                          (d <= 256 || vd_ceil_div(d, 128) * ((M + 63) / 64) <= ctx->num_cus);
+                          (wgs <= ctx->num_cus ? pitch <= 960 || M > 1000
+                                                : d <= 128 ? pitch <= 512 || (pitch <= 896 && 2 * wgs >= 3 * ctx->num_cus)
+                                                         : d <= 256 && pitch <= 512 && 2 * wgs <= 3 * ctx->num_cus);
   if (embed_fused(L, dtype) || one_launch) {
     if (!aligned) return VARDROP_EINVAL;
     EmbedFused a = {};

@@ -114,6 +114,20 @@ def test_long_windows_in_one_launch_equal_two(vd, ctx, L):
     assert torch.equal(kept, full[:, at]) and torch.equal(rows(saved, 37), rows(saved_full, 1030)[:, at])
 
 
+@pytest.mark.parametrize("B,N,L,d,n_sel", [(8, 130, 1024, 136, 120), (32, 862, 896, 128, 540), (32, 540, 512, 192, 321)])
+def test_long_windows_around_the_rule_of_one_launch(vd, ctx, B, N, L, d, n_sel):
+    """All variates and the kept ones lie on either side of the rule by rows and samples, columns and rounds of the chip: the same bits."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(L)
+    x = torch.randn((B, N, L), generator=g, device="cuda") + 2.0
+    We = torch.randn((L, d), generator=g, device="cuda").to(torch.bfloat16)
+    be = torch.randn(d, generator=g, device="cuda").to(torch.bfloat16)
+    sel = torch.randperm(N, generator=g, device="cuda")[:n_sel].sort().values
+    full, _ = vd.vardrop_embed_fwd(ctx, x, torch.arange(N, dtype=torch.int32, device="cuda"), N, We, be)
+    kept, _ = vd.vardrop_embed_fwd(ctx, x, sel.to(torch.int32), n_sel, We, be)
+    assert torch.equal(kept, full[:, sel])
+
+
 def test_kept_only_equals_gather_of_the_full_embedding(vd, ctx):
     """Rows of the kept-only embedding are bit-identical to the same rows of the all-variate embedding."""
     rng = np.random.default_rng(3)
