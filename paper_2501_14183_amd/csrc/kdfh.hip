@@ -222,13 +222,14 @@ __device__ inline int wave_reduce(int v) {
 }
 
 // Ranked top-k of up to 64 mean amplitudes: lane b holds bin b and counts the bins that beat it (a larger amplitude, or an equal one of
-// a lower bin); the lanes of rank 0 .. k-1 are the result.  Up to 32 bins either half of the wavefront counts over half of them, eight
-// LDS reads in flight; more come one by one from the lanes that hold them (from LDS, eight at a time: 22.2 -> 28.1 us at 1 x 321 x 136, 8.1 ->
-// 8.9 at 16 x 321 x 136; from the lanes four at a time: 26.0 and 8.6).  Returns the hash.
+// a lower bin); the lanes of rank 0 .. k-1 are the result.  The bins come one by one from the lanes that hold them (from LDS, eight at
+// a time: 22.2 -> 28.1 us at 1 x 321 x 136, 8.1 -> 8.9 at 16 x 321 x 136; from the lanes four at a time: 26.0 and 8.6).  HALVES (up to 32
+// bins): either half of the wavefront counts over half of them, eight LDS reads in flight (32 x 862 x 96 9.2 -> 8.9).  Returns the hash.
+template <bool HALVES>
 __device__ __forceinline__ unsigned long long rank_few(const KdfhArgs& a, const float* amp, int n, int lane) {
   const int F = a.F;
   int rank = 0;
-  if (F <= 32) {
+  if constexpr (HALVES) {
     const int b = lane & 31, cnt = (F + 1) >> 1, j0 = (lane >> 5) * cnt, j1 = min(j0 + cnt, F);
     const float mine = b < F ? amp[b] : -2.f;
     for (int u0 = 0; u0 < cnt; u0 += 8) {
@@ -1003,8 +1004,10 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE)))
     const int n = n0 + v;
     if (n >= a.N) break;
     unsigned long long h = 0;
-    if (F <= 64) {
-      h = rank_few(a, asum + v * F, n, lane);
+    if (G == 4 && Vb <= 8) {                       // (more of them in sequence: its LDS reads cost more than the loop)
+      h = rank_few<true>(a, asum + v * F, n, lane);
+    } else if (G > 1 || F <= 64) {
+      h = rank_few<false>(a, asum + v * F, n, lane);
     } else {
       float vals[kMaxBinsPerLane];
 #pragma unroll
@@ -1264,6 +1267,7 @@ __device__ __forceinline__ void pipe_produce(RawRows<IW, R2>& w, const KdfhArgs&
 
 // ranked top-k and hash (Alg. 1 steps 4-5) of the variates v = cw, cw + 4, ... of a group, from its batch sums;
 // (the stray bins' row amplitudes of the group's last block have been added by the caller)
+template <bool HALVES = false>
 __device__ __forceinline__ void pipe_rank(const KdfhArgs& a, float* asum, int n0, int cw, int lane) {
   const int F = a.F, Vb = 32 >> a.log2_rpv;
   const unsigned long long R = (unsigned long long)(a.L / 2 + 1);
@@ -1271,8 +1275,10 @@ __device__ __forceinline__ void pipe_rank(const KdfhArgs& a, float* asum, int n0
     const int n = n0 + v;
     if (n < a.N) {
       unsigned long long h = 0;
-      if (F <= 64) {
-        h = rank_few(a, asum + v * F, n, lane);
+      if (HALVES && F <= 32) {
+        h = rank_few<true>(a, asum + v * F, n, lane);
+      } else if (F <= 64) {
+        h = rank_few<false>(a, asum + v * F, n, lane);
       } else {
         const int nslot = (F + 63) >> 6;           // bin lane + 64 j lives in slot j: only these slots hold bins
         float vals[kMaxBinsPerLane];
@@ -1359,7 +1365,7 @@ __global__ __launch_bounds__(256) void kdfh_rank_kernel(KdfhArgs a) {
     }
   }
   a.log2_rpv = 3;                                        // four variates a workgroup, one a wavefront
-  pipe_rank(a, asum, blockIdx.x * 4, wave, lane);
+  pipe_rank<true>(a, asum, blockIdx.x * 4, wave, lane);
 }
 
 // Workgroup barrier that orders LDS accesses only: outstanding global loads (the next block's rows, the table
