@@ -559,7 +559,10 @@ constexpr int gemm_async_lds() {
 }
 template <bool SPLIT, int BM, int BK, int NS, bool SUMS = false>
 constexpr int gemm_async_lds_v = gemm_async_lds<SPLIT, BM, BK, NS, SUMS>();
-// The product's dimensions, with a device-side token count (GemmBf16::n_dev) resolved; false: nothing to do.
+// The product's dimensions, with a device-side token count (GemmBf16::n_dev) resolved; false: nothing to do.  EMBED: K slices by the
+// embedding's rule (n_role 2), else by the attention's.  (Both in one kernel: code that the gradient launch never runs, and with
+// some versions of it that launch takes 2-4 % longer: 55.5 -> 57.9 us of a backward pass of 3584 rows of 576.)
+template <bool EMBED>
 __device__ __forceinline__ bool gemm_resolve(const GemmBf16& g, GemmDims& dm) {
   dm.M = g.M; dm.K = g.K; dm.splitk = g.splitk; dm.kchunk = g.kchunk; dm.rs_n = g.rs_n;
   if (!g.n_dev) return true;
@@ -571,8 +574,8 @@ __device__ __forceinline__ bool gemm_resolve(const GemmBf16& g, GemmDims& dm) {
   } else {
     dm.K = g.n_mul * n;
     int kchunk = 64;
-    dm.splitk = g.n_role == 2 ? vd_embed_splitk(g.M, g.N, (long long)dm.K, &kchunk)
-                              : vd_attn_bf16_splitk(g.M, (long long)dm.K, g.many != 0, &kchunk);
+    if constexpr (EMBED) dm.splitk = vd_embed_splitk(g.M, g.N, (long long)dm.K, &kchunk);
+    else dm.splitk = vd_attn_bf16_splitk(g.M, (long long)dm.K, g.many != 0, &kchunk);
     dm.kchunk = kchunk;
   }
   // (no tokens: an input gradient has no rows to write; a weight gradient is all zeros, which its tiles write
@@ -590,7 +593,7 @@ template <bool AKC, bool BKC, bool SPLIT, int BM, int BK, int NS, bool SUMS = fa
 // (wavefronts a SIMD: two or three workgroups share a compute unit)
 __global__ __launch_bounds__(kGemmThreads, BM == 128 || NS > 2 ? 4 : 6) void gemm_async_kernel(GemmBf16 g, int nz) {
   GemmDims dm;
-  if (!gemm_resolve(g, dm)) return;
+  if (!gemm_resolve<SPLIT>(g, dm)) return;
   // tiles in the order n fastest, then m, then batch entry: a die's range shares its rows of A
   const int gx = (g.N + 127) >> 7, gy = (dm.M + BM - 1) / BM;
   const int total = gx * gy * nz * (SPLIT ? dm.splitk : 1);
@@ -631,8 +634,8 @@ __global__ __launch_bounds__(kGemmThreads, CFG::KHW ? 2 : 4) void gemm_bwd_pair_
   //     d = 704 55.0 -> 56.7 at 3200, d = 768 57.4 -> 58.9 at 3200, 59.7 -> 62.2 at 3520 (264 and 288 weight-gradient tiles on 256 places),
   //     81.8 -> 80.8 at 4224.
   GemmDims dx, dw;
-  const bool has_x = gemm_resolve(gx, dx);
-  if (!gemm_resolve(gw, dw)) return;          // (an invalid count; with no tokens only the weight-gradient tiles run)
+  const bool has_x = gemm_resolve<false>(gx, dx);
+  if (!gemm_resolve<false>(gw, dw)) return;          // (an invalid count; with no tokens only the weight-gradient tiles run)
   if (!has_x) dx.M = 0;
   constexpr int BMX = CFG::BMX, BMW = CFG::BMW;
   const int gxn = (gx.N + 127) >> 7, gwn = (gw.N + 127) >> 7, gwm = (dw.M + BMW - 1) / BMW;
