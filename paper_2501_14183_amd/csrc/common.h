@@ -172,12 +172,15 @@ static inline bool vd_attn_bf16_many_tokens(int d, long long M) {
 //   d = 64 25.7 -> 25.4 at 1536 rows, 24.4 -> 25.1 at 1792, 34.6 -> 42.0 at 4096; d = 128 23.8 -> 23.0 at 1536, 26.9 -> 27.5 at 2048, 37.6 ->
 //   43.2 at 4096; d = 192 27.0 -> 26.6 at 1792, 28.2 -> 28.7 at 2048; d = 256 31.8 -> 30.9 at 2048, 36.8 -> 38.5 at 3072; d = 384 35.3 -> 34.6 at
 //   2304, 45.0 -> 46.2 at 3072; d = 512 27.1 -> 20.6 at 256, 39.5 -> 38.8 at 2560, 48.2 -> 50.2 at 3584;
-//   several slices: d = 64 40.0 -> 44.8 at 8192 (two of 4096), d = 256 45.9 -> 43.9 at 5120 (two of 2560), 50.9 -> 54.1 at 8192;
+//   several slices, whose sum runs anyway: two of 2560 d = 64 33.4 -> 33.7, d = 128 36.7 -> 34.5, d = 256 45.9 -> 43.9; two of 3072 d = 128 38.2 ->
+//   39.0, d = 256 46.8 -> 47.6; two of 4096 d = 64 40.0 -> 44.8, d = 256 50.9 -> 54.1;
 //   more tiles than places: d = 512 61.5 -> 65.0 at 4608 (272 tiles), d = 192 57.5 -> 59.8 at 12 288 (264), d = 384 58.1 -> 56.4 at 6144 (288),
 //   d = 320 1.08x at 12 288 (468), d = 448 1.08x at 8192 (480), from d = 576 on 1.1-1.25x at every count.  Many tokens: 1.01-1.14x.
 static inline bool vd_attn_bf16_sums_inside(int d, long long M, bool many, int splitk, int kchunk, int num_cus) {
   const long long tiles = (long long)vd_ceil_div(d, 128) * ((M + 127) / 128) + (long long)vd_attn_bf16_weight_tiles(d) * splitk;
-  return many || kchunk <= (d < 384 ? 1024 + 4 * d : 2560) || 10 * tiles >= 11ll * num_cus;
+  int rows = d < 384 ? 1024 + 4 * d : 2560;
+  if (splitk > 1) rows = rows + 1000 < 3000 ? rows + 1000 : 3000;
+  return many || kchunk <= rows || 10 * tiles >= 11ll * num_cus;
 }
 // Most slices of any count of up to M rows.  The few-token side has more than kManySlices only while one column of tiles
 // (d <= 128) keeps it going past 36864 rows: 15 at its end, 511 tiles.  Grows with M.
