@@ -97,7 +97,7 @@ enum {
   VARDROP_K_GEMM_EMBED,      /* xs = z We + be                                              */
   VARDROP_K_GEMM_DWE,        /* dWe = z^T dxs (K slices)                                    */
   VARDROP_K_SDPA_BWD_DQKV,   /* bf16, n > 128, few workgroups: dQ, dK, dV in one launch (GEMM_DO then forms rowsum(dO * O)) */
-  VARDROP_K_EMBED_FUSED,     /* kept windows gathered, standardised and embedded in one launch (bf16, short windows) */
+  VARDROP_K_EMBED_FUSED,     /* kept windows gathered, standardised and embedded in one launch (bf16: short windows always, longer ones by size) */
   VARDROP_K_COUNT
 };
 int vardrop_profile_select(vardrop_ctx* ctx, int kernel_id);
@@ -127,7 +127,8 @@ const char* vardrop_kernel_name(int kernel_id);
  *
  *   x      fp32 [B][N][L] with element strides sb, sn >= 0 and st >= 1.  Read as it is with time-contiguous
  *          rows (st = 1) and as a time-major batch [B][L][N] (sn = 1, for instance sb = L N, st = N; the sums
- *          of a part of the windows then go through the workspace `ws`); any other layout is first copied into
+ *          of a part of the windows then go through the workspace `ws`); any other layout, and a time-major batch
+ *          of few variates and windows, is first copied into
  *          time-contiguous rows in `ws`.  With st != 1 `ws` must hold vardrop_hash_strided_workspace_bytes(B, N, L) bytes, 16-byte aligned
  *          (EWORKSPACE otherwise; B <= 65535 on this path); with st = 1 no workspace is used
  *   topk   int32 [N][k]   bin indices, rank 1 first

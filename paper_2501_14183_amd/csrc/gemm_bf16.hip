@@ -287,7 +287,7 @@ __device__ __forceinline__ void gemm_async_tile(const GemmBf16& g, const GemmDim
       Bp = copy_source(fseg == 1 ? B1 : B2);                                                       \
     }                                                                                              \
   }
-  // Column sums of B, by the copy wavefronts (they wait for most of a slice; a launch of their own that reads B again took 11.5 + 5.0 us
+  // Column sums of B, by the copy wavefronts (which sizes: vd_attn_bf16_sums_inside; a launch of their own that reads B again took 11.5 + 5.0 us
   // for the four of 10 272 x 512, 5.7 + 2.3 for one of 3008 x 512; here dense training at 10 272 rows 196 -> 183 us a step, the
   // embedding of 3008 windows of 720 samples 35.0 -> 32.1).  Lane c + 16 j of copy wavefront w4 takes the eight columns of 16-byte chunk c in k-rows
   // BK / 4 w4 + j + {0, 4, ..} of every slice, adds those of a slice up first and the slices in order.
@@ -734,7 +734,7 @@ int vd_gemm_bf16_bwd_pair(vardrop_ctx* ctx, const GemmBf16& gx, const GemmBf16& 
 
 int vd_gemm_bf16_wgrad_split(vardrop_ctx* ctx, int kid, const GemmBf16& g, hipStream_t s) {
   if (g.M == 0 || g.N == 0) return VARDROP_OK;
-  if (g.M % 8 != 0 || g.N % 8 != 0 || g.splitk < 1 || g.kchunk % 64 != 0 ||
+  if (g.M % 8 != 0 || g.N % 8 != 0 || g.splitk < 1 || g.kchunk % 64 != 0 || (g.n_dev && g.n_role != 2) ||
       (long long)g.K * g.lda >= (1ll << 31) || (long long)g.K * g.ldb >= (1ll << 31))
     return VARDROP_EUNSUPPORTED;
   // (three stages: with two 20.9 -> 15.0 us and their sum at 27 584 rows of 96 x 512, 26.6 -> 25.5 at 10 272 of 720 x 512)

@@ -31,13 +31,15 @@
 // (Alg. 1 step 2).  Amplitudes are summed over the batch in a fixed order in fp32 (step 3), the
 // ranked top-k (step 4) lets the lower bin win ties, and the hash is the tuple in radix R (step 5).
 //
-// Data flow.  Every thread reads 8 consecutive samples of a row and the 8 mirrored ones straight
-// from global memory, folds them, and writes the four half-precision operand pieces (sum hi / lo,
-// difference hi / lo) to LDS in the layout the matrix instruction reads (row-major, 16 bytes per
-// lane).  The cosine / sine pieces come from a table in global memory that is laid out in
-// matrix-fragment order (it stays in L2) and is rebuilt when L or the candidate bins change.  A
-// wavefront owns a tile of 32 bins at a time and runs the whole contraction for it, real and
-// imaginary part together, so nothing is exchanged between wavefronts until the batch sums.
+// Data flow.  Every thread takes 8 consecutive samples of a row and the 8 mirrored ones, folds them, and writes the four
+// half-precision operand pieces (sum hi / lo, difference hi / lo) to LDS in the layout the matrix instruction reads (row-major, 16
+// bytes per lane).  The samples come straight from global memory, or from LDS, where asynchronous copies have put the rows (larger
+// grids and rows that are no aligned float4) or the windows of a time-major batch, whose blocks of windows leave their sums in the
+// workspace for a second kernel that adds them up and ranks.  The cosine / sine pieces come from a table in global memory that is
+// laid out in matrix-fragment order (it stays in L2) and is rebuilt when L or the candidate bins change.  A wavefront owns a tile
+// of 32 bins at a time and runs the whole contraction for it, real and imaginary part together, so nothing is exchanged between
+// wavefronts until the batch sums; short windows of one or two tiles are the exception: the wavefronts share a tile's contraction
+// and exchange partial sums through LDS.
 #include <algorithm>
 #include "common.h"
 
@@ -332,8 +334,8 @@ __device__ __forceinline__ void staged_item(int i, int KG, int& r, int& g) {
 // flight (2 for the short-window instance, which has to stay inside 128 registers).
 // WPE: wavefronts per SIMD the register budget is set for.  The short-window instances (ITEMS = 1) take four: at
 // 862 variates of 32 windows the grid is 3448 wavefronts, which only then are all resident at once (3 per SIMD
-// leave 376 of them waiting for a second round: 14.9 us instead of 11.7).  (Three for ITEMS = 2, which the LDS
-// would hold at L = 336, costs spills and was slower.)
+// leave 376 of them waiting for a second round: 14.9 us instead of 11.7).  ITEMS = 2 takes two with its samples in registers and three
+// with the rows staged in LDS (three with the samples in registers spills and was slower).
 // STRAY: the instance that also contracts stray bins (R2 only).
 // G (short windows, ITEMS = 1, of one or two bin tiles): 4 or 2 wavefronts share the four contraction steps of a tile.  A
 // wavefront with a tile of its own leaves the others idle over 24 dependent matrix instructions and 16 square roots a lane:
@@ -343,7 +345,8 @@ __device__ __forceinline__ void staged_item(int i, int KG, int& r, int& g) {
 // kTimeMajor (TM): the variate index is contiguous instead of time.  A workgroup owns one block of 1 << log2_rpv windows of Vb variates,
 // stages their samples in LDS by asynchronous copies (where the operand pieces go later), goes on as with rows in memory and
 // leaves the sums of its windows in `part`; kdfh_rank_kernel adds those up and ranks.  Bound by the same chain of phases as
-// with rows in memory; three workgroups a compute unit at up to 384 folded items (the samples wait in LDS, not in registers).
+// with rows in memory; three workgroups a compute unit at up to 352 samples with the radix-2 step (the samples wait in LDS, not in
+// registers; from 353 on the staged windows take a third of the LDS and more).
 template <int ITEMS, int RING, bool VEC, bool R2, bool STRAY = false, int WPE = (ITEMS == 1 ? 4 : (ITEMS <= 4 ? 2 : 1)), int LOAD = kDirect,
           int G = 1>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(WPE))) void kdfh_kernel(KdfhArgs a) {
@@ -1766,10 +1769,12 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
   const size_t lds = (size_t)units * 16 + stat_bytes + sizeof(float) * Vb * F;
   // Windows with the variate index contiguous are read as they are: a workgroup takes 32 rows, four windows of eight variates or two
   // of 16, 32 or 64 contiguous bytes of every point in time, and leaves their sums in the workspace.  Four windows leave half as
-  // many sums to add up, two fetch half as many lines a byte, which counts where batch and windows do not stay in the caches: us with
+  // many sums to add up, two fetch half as many lines a byte, which counts in large batches of long windows: us with
   // four / two windows 15.3 / 16.9 (32 x 862 x 96), 24.4 / 25.1 (8 x 8192 x 96), 32.1 / 33.7 (32 x 862 x 336), 67.8 / 74.7
   // (64 x 300 x 720), 34.2 / 33.9 (16 x 2048 x 336), 85.5 / 83.6 (32 x 2048 x 512), 49.7 / 44.3 (8 x 4096 x 512), 88.0 / 78.4 (8 x 8192 x 512).
-  // (With a copy into time-contiguous rows in front: 19.6, 30.1, 45.8, 94.7, 49.7, 133, 67.8, 124.)
+  // (With a copy into time-contiguous rows in front: 19.6, 30.1, 45.8, 94.7, 49.7, 133, 67.8, 124.)  Back to back, from caches that hold the
+  // batch, two are within 2 % of four up to 256 samples at 300 to 8192 variates; from 300 on they gain 0-4 % from 1200 variates on
+  // (31.2 / 30.4 at 16 x 1200 x 512, 27.7 / 26.9 at 16 x 1600 x 336) and -5 to 4 % below (17.4 / 17.8 at 8 x 862 x 512).
   const int tm_log2_rpv = B <= 1 ? 0 : (B == 2 || (N >= 2048 && L >= 256) ? 1 : 2);
   const int tm_tlog = 3 + tm_log2_rpv;                    // log2 of the points in time a copy of 1 KB holds
   const size_t tm_staged = ((size_t)vd_ceil_div(L, 1 << tm_tlog) * kStagePitch + 16) * sizeof(float) << tm_log2_rpv;
@@ -1884,7 +1889,7 @@ extern "C" int vardrop_hash(vardrop_ctx* ctx, const float* x, int B, int N, int 
   }
   // Rows staged in LDS by asynchronous copies leave registers for a third workgroup a compute unit at up to 512 items of eight folded
   // samples; that pays once the registers' two do not hold the grid and the LDS holds three (384 samples with the radix-2 step):
-  // us direct -> staged 28.7 -> 25.5 (16 x 2048 x 336), 59.0 -> 49.7 (16 x 4000 x 272), 25.2 -> 23.5 (32 x 862 x 336), 41.6 -> 34.7
+  // us direct -> staged 28.7 -> 25.5 (16 x 2048 x 336; inside a step 27.6 -> 26.5), 59.0 -> 49.7 (16 x 4000 x 272), 25.2 -> 23.5 (32 x 862 x 336), 41.6 -> 34.7
   // (16 x 4000 x 180), 36.6 -> 30.5 (16 x 3000 x 167), each back to back; but 12.6 -> 13.0 (32 x 321 x 336), 10.8 -> 12.0 (32 x 100 x 167), and where
   // the LDS holds two 25.6 -> 27.6 (32 x 862 x 400), 25.2 -> 27.3 (448), 33.0 -> 35.4 (512), 25.4 -> 29.5 (16 x 1300 x 512).
   // Longer rows that are no aligned float4 are staged always: their samples
