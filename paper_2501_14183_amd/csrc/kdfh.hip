@@ -246,7 +246,8 @@ __device__ __forceinline__ unsigned long long rank_few(const KdfhArgs& a, const 
     }
     rank += __shfl_xor(rank, 32, 64);
   } else {
-    const float mine = lane < F ? amp[lane] : -2.f;
+    float mine = lane < F ? amp[lane] : -2.f;
+    asm volatile("" : "+v"(mine));               // (waits for the read here, not in every turn of the loop)
     for (int j = 0; j < F; ++j) {
       const float other = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(mine), j));
       rank += other > mine || (other == mine && j < lane) ? 1 : 0;
